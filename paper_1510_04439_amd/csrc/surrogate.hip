@@ -157,78 +157,235 @@ __device__ inline float gelu_grad(float z) {
   return Phi + z * phi;
 }
 
-// One workgroup (NH threads) per sample. x is standardized on the fly:
-// (feat - mu) / sd. Saves z1, z2 (pre-activations) for the backward pass.
-__global__ __launch_bounds__(NH) void k_mlp_fwd(int B, const float *__restrict__ feat, const float *__restrict__ fmu,
-                                                 const float *__restrict__ fsd, const float *__restrict__ prm,
-                                                 float *__restrict__ out, float *__restrict__ z1s,
-                                                 float *__restrict__ z2s) {
-  __shared__ float x[NF], h1[NH], red[2];
-  const int b = blockIdx.x, j = threadIdx.x;
-  if (j < NF) x[j] = (feat[int64_t(b) * NF + j] - fmu[j]) / fsd[j];
-  __syncthreads();
-  float z = prm[OFF_B1 + j];
-  for (int i = 0; i < NF; ++i) z = fmaf(prm[OFF_W1 + j * NF + i], x[i], z);
-  if (z1s) z1s[int64_t(b) * NH + j] = z;
-  h1[j] = gelu(z);
-  __syncthreads();
-  float z2 = prm[OFF_B2 + j];
-  for (int i = 0; i < NH; ++i) z2 = fmaf(prm[OFF_W2 + j * NH + i], h1[i], z2);
-  if (z2s) z2s[int64_t(b) * NH + j] = z2;
-  float o = prm[OFF_W3 + j] * gelu(z2);
-  for (int s = 32; s > 0; s >>= 1) o += __shfl_xor(o, s);
-  if ((j & 63) == 0) red[j >> 6] = o;
-  __syncthreads();
-  if (j == 0) out[b] = red[0] + red[1] + prm[OFF_B3];
-}
+// The three products of a training step (forward, back-propagated deltas,
+// gradient) run on FP32 MFMA (16x16x4): operands are exact FP32, sums FP32 as
+// in a thread's own loop. A lane of the instruction holds A[row = lane % 16][k]
+// and B[k][col = lane % 16] for the k of its group lane / 16, and the outputs
+// D[4 (lane / 16) + v][lane % 16], v = 0..3. Where both operands can be read
+// along k, group g of chunk c takes k = 16 c + 4 g .. + 3 as one 16-byte read
+// and step t uses element t of it: the same k on both sides, in another order.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int MS = 16;        // samples per workgroup of the forward and delta kernels
+constexpr int HP = NH + 4;    // padded LDS row of NH values
+constexpr int GW = 16;        // wavefronts per workgroup of the gradient kernel
 
-// Per sample: the loss terms and the back-propagated deltas
-//   dout = 2 (out - y) / B,  dz2 = W3 dout gelu'(z2),  dz1 = W2^T dz2 gelu'(z1).
-__global__ __launch_bounds__(NH) void k_mlp_delta(int B, const float *__restrict__ prm, const float *__restrict__ out,
-                                                   const float *__restrict__ target, const float *__restrict__ z1s,
-                                                   const float *__restrict__ z2s, float *__restrict__ dz1s,
-                                                   float *__restrict__ dz2s, float *__restrict__ dout_s) {
-  __shared__ float dz2[NH];
-  const int b = blockIdx.x, j = threadIdx.x;
-  const float dout = 2.0f * (out[b] - target[b]) / float(B);
-  if (j == 0) dout_s[b] = dout;
-  const float d2 = prm[OFF_W3 + j] * dout * gelu_grad(z2s[int64_t(b) * NH + j]);
-  dz2[j] = d2;
-  dz2s[int64_t(b) * NH + j] = d2;
-  __syncthreads();
-  float dh1 = 0.f;
-  for (int k = 0; k < NH; ++k) dh1 = fmaf(prm[OFF_W2 + k * NH + j], dz2[k], dh1);
-  dz1s[int64_t(b) * NH + j] = dh1 * gelu_grad(z1s[int64_t(b) * NH + j]);
-}
-
-// Thread per parameter: the gradient summed over the batch in a fixed order.
-__global__ __launch_bounds__(256) void k_mlp_grad(int B, const float *__restrict__ feat, const float *__restrict__ fmu,
-                                                   const float *__restrict__ fsd, const float *__restrict__ z1s,
-                                                   const float *__restrict__ z2s, const float *__restrict__ dz1s,
-                                                   const float *__restrict__ dz2s, const float *__restrict__ dout_s,
-                                                   float *__restrict__ grad) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= NPARAM) return;
-  float s = 0.f;
-  if (p < OFF_B1) {
-    const int j = p / NF, i = p % NF;
-    for (int b = 0; b < B; ++b) s += dz1s[int64_t(b) * NH + j] * ((feat[int64_t(b) * NF + i] - fmu[i]) / fsd[i]);
-  } else if (p < OFF_W2) {
-    const int j = p - OFF_B1;
-    for (int b = 0; b < B; ++b) s += dz1s[int64_t(b) * NH + j];
-  } else if (p < OFF_B2) {
-    const int j = (p - OFF_W2) / NH, i = (p - OFF_W2) % NH;
-    for (int b = 0; b < B; ++b) s += dz2s[int64_t(b) * NH + j] * gelu(z1s[int64_t(b) * NH + i]);
-  } else if (p < OFF_W3) {
-    const int j = p - OFF_B2;
-    for (int b = 0; b < B; ++b) s += dz2s[int64_t(b) * NH + j];
-  } else if (p < OFF_B3) {
-    const int j = p - OFF_W3;
-    for (int b = 0; b < B; ++b) s += dout_s[b] * gelu(z2s[int64_t(b) * NH + j]);
-  } else {
-    for (int b = 0; b < B; ++b) s += dout_s[b];
+// MS samples per workgroup, one wavefront per 16 hidden units. x is
+// standardized on the fly: (feat - mu) / sd. Saves z1, z2 (pre-activations) for
+// the backward pass. The second layer's weights are read from L2 once per 16
+// samples and requested before the first layer's results are needed: with one
+// workgroup per sample and one weight row per thread the call was bound by
+// its uncoalesced 4-byte weight reads (batch 2000: 22.5 us).
+__global__ __launch_bounds__(NH / 16 * 64) void k_mlp_fwd(int B, const float *__restrict__ feat,
+                                                          const float *__restrict__ fmu,
+                                                          const float *__restrict__ fsd,
+                                                          const float *__restrict__ prm, float *__restrict__ out,
+                                                          float *__restrict__ z1s, float *__restrict__ z2s) {
+  __shared__ __attribute__((aligned(16))) float x[MS][NF + 4];
+  __shared__ __attribute__((aligned(16))) float h1[MS][HP];
+  __shared__ float red[NH / 16][MS];
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 15, g = (tid & 63) >> 4;
+  const int b0 = blockIdx.x * MS, j = 16 * w + l;
+  static_assert(MS * NF == NH / 16 * 64, "one input value per thread");
+  {
+    const int r = tid / NF, i = tid % NF;
+    x[r][i] = b0 + r < B ? (feat[int64_t(b0 + r) * NF + i] - fmu[i]) / fsd[i] : 0.f;
   }
-  grad[p] = s;
+  f32x4 w1[NF / 16], w2[NH / 16];
+#pragma unroll
+  for (int c = 0; c < NF / 16; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w1[c][t] = prm[OFF_W1 + j * NF + 16 * c + 4 * g + t];
+#pragma unroll
+  for (int c = 0; c < NH / 16; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w2[c][t] = prm[OFF_W2 + j * NH + 16 * c + 4 * g + t];
+  __syncthreads();
+  const float bias1 = prm[OFF_B1 + j], bias2 = prm[OFF_B2 + j], w3 = prm[OFF_W3 + j];
+  f32x4 z = {bias1, bias1, bias1, bias1};
+#pragma unroll
+  for (int c = 0; c < NF / 16; ++c) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(&x[l][16 * c + 4 * g]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) z = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], w1[c][t], z, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int r = 4 * g + v;
+    if (z1s && b0 + r < B) z1s[int64_t(b0 + r) * NH + j] = z[v];
+    h1[r][j] = gelu(z[v]);
+  }
+  __syncthreads();
+  f32x4 y = {bias2, bias2, bias2, bias2};
+#pragma unroll
+  for (int c = 0; c < NH / 16; ++c) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(&h1[l][16 * c + 4 * g]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) y = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], w2[c][t], y, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int r = 4 * g + v;
+    if (z2s && b0 + r < B) z2s[int64_t(b0 + r) * NH + j] = y[v];
+    float o = w3 * gelu(y[v]);
+    for (int s = 8; s > 0; s >>= 1) o += __shfl_xor(o, s);
+    if (l == 0) red[w][r] = o;
+  }
+  __syncthreads();
+  if (tid < MS && b0 + tid < B) {
+    float o = 0.f;
+#pragma unroll
+    for (int q = 0; q < NH / 16; ++q) o += red[q][tid];
+    out[b0 + tid] = o + prm[OFF_B3];
+  }
+}
+
+// The loss terms and the back-propagated deltas of MS samples,
+//   dout = 2 (out - y) / B,  dz2 = W3 dout gelu'(z2),  dz1 = W2^T dz2 gelu'(z1),
+// one wavefront per 16 hidden units (batch 2000: 9.3 us with one workgroup per sample).
+__global__ __launch_bounds__(NH / 16 * 64) void k_mlp_delta(int B, const float *__restrict__ prm,
+                                                            const float *__restrict__ out,
+                                                            const float *__restrict__ target,
+                                                            const float *__restrict__ z1s,
+                                                            const float *__restrict__ z2s,
+                                                            float *__restrict__ dz1s, float *__restrict__ dz2s,
+                                                            float *__restrict__ dout_s) {
+  __shared__ __attribute__((aligned(16))) float dz2[MS][HP];
+  constexpr int NT = NH / 16 * 64;
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 15, g = (tid & 63) >> 4;
+  const int b0 = blockIdx.x * MS, j = 16 * w + l;
+  float w2[NH / 16][4];
+#pragma unroll
+  for (int c = 0; c < NH / 16; ++c)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) w2[c][t] = prm[OFF_W2 + (16 * c + 4 * g + t) * NH + j];
+#pragma unroll
+  for (int u = 0; u < MS * NH / NT; ++u) {
+    const int e = tid + u * NT, r = e / NH, k = e % NH, b = b0 + r;
+    float d2 = 0.f;
+    if (b < B) {
+      const float dout = 2.0f * (out[b] - target[b]) / float(B);
+      if (k == 0) dout_s[b] = dout;
+      d2 = prm[OFF_W3 + k] * dout * gelu_grad(z2s[int64_t(b) * NH + k]);
+      dz2s[int64_t(b) * NH + k] = d2;
+    }
+    dz2[r][k] = d2;
+  }
+  __syncthreads();
+  f32x4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < NH / 16; ++c) {
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(&dz2[l][16 * c + 4 * g]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a[t], w2[c][t], d, 0, 0, 0);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int b = b0 + 4 * g + v;
+    if (b < B) dz1s[int64_t(b) * NH + j] = d[v] * gelu_grad(z1s[int64_t(b) * NH + j]);
+  }
+}
+
+// The gradient summed over the batch in a fixed order. Workgroups
+// 0 .. 63 own a 16 x 16 tile of W2's gradient (dz2^T gelu(z1)), 64 .. 79 one of
+// W1's (dz1^T x), the last 8 sixteen entries of W3's; the tiles of the first
+// column of each matrix also add its bias. Each of the GW wavefronts takes a
+// contiguous share of the samples and the shares are added in order. One
+// thread per parameter, walking the batch alone, took 669 us at batch 2000 (a
+// serial chain of dependent sums with an erf in it); 88 workgroups leave most
+// of the chip idle but need no second pass over partial sums.
+constexpr int G_W2 = (NH / 16) * (NH / 16), G_W1 = (NH / 16) * (NF / 16), G_W3 = NH / 16;
+__global__ __launch_bounds__(GW * 64) void k_mlp_grad(int B, const float *__restrict__ feat,
+                                                      const float *__restrict__ fmu, const float *__restrict__ fsd,
+                                                      const float *__restrict__ z1s, const float *__restrict__ z2s,
+                                                      const float *__restrict__ dz1s,
+                                                      const float *__restrict__ dz2s,
+                                                      const float *__restrict__ dout_s, float *__restrict__ grad) {
+  __shared__ float tile[GW][16][17];
+  __shared__ float vec[GW][16];
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 15, g = (tid & 63) >> 4;
+  const int steps = ((B + 3) / 4 + GW - 1) / GW;  // steps of four samples per wavefront
+  const int s0 = w * steps;
+  int id = blockIdx.x;
+  if (id < G_W2 + G_W1) {
+    const bool two = id < G_W2;
+    if (!two) id -= G_W2;
+    const int nc = two ? NH / 16 : NF / 16;
+    const int j0 = 16 * (id / nc), i0 = 16 * (id % nc);
+    const float *__restrict__ dz = two ? dz2s : dz1s;
+    const float mu = two ? 0.f : fmu[i0 + l], sd = two ? 1.f : fsd[i0 + l];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float bsum = 0.f;
+    for (int s = 0; s < steps; s += 4) {  // the loads of four steps in flight
+      float a[4], c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int b = 4 * (s0 + s + u) + g, bc = min(b, B - 1);
+        const bool ok = b < B && s + u < steps;
+        a[u] = dz[int64_t(bc) * NH + j0 + l];
+        c[u] = two ? z1s[int64_t(bc) * NH + i0 + l] : feat[int64_t(bc) * NF + i0 + l];
+        if (!ok) a[u] = c[u] = 0.f;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        // a step past the end adds 0 * 0
+        const float v = two ? gelu(c[u]) : (c[u] - mu) / sd;
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], s + u < steps && 4 * (s0 + s + u) + g < B ? v : 0.f, acc, 0,
+                                                   0, 0);
+        bsum += a[u];
+      }
+    }
+    bsum += __shfl_xor(bsum, 16);
+    bsum += __shfl_xor(bsum, 32);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) tile[w][4 * g + v][l] = acc[v];
+    if (g == 0) vec[w][l] = bsum;
+    __syncthreads();
+    if (tid < 256) {
+      const int r = tid >> 4, c = tid & 15;
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < GW; ++q) s += tile[q][r][c];
+      grad[two ? OFF_W2 + (j0 + r) * NH + i0 + c : OFF_W1 + (j0 + r) * NF + i0 + c] = s;
+    }
+    if (i0 == 0 && tid < 16) {
+      float s = 0.f;
+#pragma unroll
+      for (int q = 0; q < GW; ++q) s += vec[q][tid];
+      grad[(two ? OFF_B2 : OFF_B1) + j0 + tid] = s;
+    }
+    return;
+  }
+  const int j0 = 16 * (id - G_W2 - G_W1);
+  float s3 = 0.f, sb = 0.f;
+#pragma unroll 4
+  for (int s = 0; s < steps; ++s) {
+    const int b = 4 * (s0 + s) + g;
+    if (b < B) {
+      const float d = dout_s[b];
+      s3 += d * gelu(z2s[int64_t(b) * NH + j0 + l]);
+      sb += d;
+    }
+  }
+  s3 += __shfl_xor(s3, 16);
+  s3 += __shfl_xor(s3, 32);
+  sb += __shfl_xor(sb, 16);
+  sb += __shfl_xor(sb, 32);
+  if (g == 0) {
+    vec[w][l] = s3;
+    tile[w][0][l] = sb;
+  }
+  __syncthreads();
+  if (tid < 16) {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < GW; ++q) s += vec[q][tid];
+    grad[OFF_W3 + j0 + tid] = s;
+  } else if (tid == 16 && j0 == 0) {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < GW; ++q) s += tile[q][0][0];
+    grad[OFF_B3] = s;
+  }
 }
 
 // Adam (Kingma & Ba 2015) with decoupled weight decay.
@@ -282,7 +439,7 @@ int fpca_bw_mlp_forward(fpca_handle ctx, int batch, const float *feat, const flo
     return set_error(FPCA_ERR_INVALID_ARG, "batch >= 1 and feat, feat_mean, feat_sd, params, out are required");
   if ((z1 == nullptr) != (z2 == nullptr)) return set_error(FPCA_ERR_INVALID_ARG, "z1 and z2 go together");
   if (int rc = set_device(ctx)) return rc;
-  hipLaunchKernelGGL(k_mlp_fwd, dim3(unsigned(batch)), dim3(NH), 0, ctx->stream, batch, feat, feat_mean, feat_sd,
+  hipLaunchKernelGGL(k_mlp_fwd, dim3(unsigned((batch + MS - 1) / MS)), dim3(NH / 16 * 64), 0, ctx->stream, batch, feat, feat_mean, feat_sd,
                      params, out, z1, z2);
   FPCA_LAUNCH_CHECK("mlp_fwd");
   return FPCA_OK;
@@ -296,10 +453,10 @@ int fpca_bw_mlp_backward(fpca_handle ctx, int batch, const float *feat, const fl
     return set_error(FPCA_ERR_INVALID_ARG, "all arguments are required");
   if (int rc = set_device(ctx)) return rc;
   float *dz1 = work, *dz2 = work + int64_t(batch) * NH, *dout = work + 2 * int64_t(batch) * NH;
-  hipLaunchKernelGGL(k_mlp_delta, dim3(unsigned(batch)), dim3(NH), 0, ctx->stream, batch, params, out, target, z1, z2,
+  hipLaunchKernelGGL(k_mlp_delta, dim3(unsigned((batch + MS - 1) / MS)), dim3(NH / 16 * 64), 0, ctx->stream, batch, params, out, target, z1, z2,
                      dz1, dz2, dout);
   FPCA_LAUNCH_CHECK("mlp_delta");
-  hipLaunchKernelGGL(k_mlp_grad, dim3((NPARAM + 255) / 256), dim3(256), 0, ctx->stream, batch, feat, feat_mean, feat_sd,
+  hipLaunchKernelGGL(k_mlp_grad, dim3(G_W2 + G_W1 + G_W3), dim3(GW * 64), 0, ctx->stream, batch, feat, feat_mean, feat_sd,
                      z1, z2, dz1, dz2, dout, grad);
   FPCA_LAUNCH_CHECK("mlp_grad");
   return FPCA_OK;

@@ -1,0 +1,106 @@
+"""Kernels at the sizes where their tiling can go wrong (edges of tiles,
+remainders, the smallest and largest of a range), against the FP64 oracle.
+Bars as in the modules that cover the same calls at ordinary sizes."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import mlp as ref_mlp
+from tests._util import normwise_rel
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as T
+    assert T.cuda.is_available(), "GPU tests need a GPU"
+    return T
+
+
+@pytest.fixture(scope="module")
+def F(torch):
+    import paper_1510_04439_amd as F
+    F.load_library()
+    return F
+
+
+@pytest.fixture(scope="module")
+def h(F):
+    hh = F.Handle(0)
+    yield hh
+    hh.close()
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 64, 65, 300])
+def test_mlp_batches(torch, F, h, B):
+    """16 samples per workgroup, 4 per MFMA step, 16 shares of the batch."""
+    _say(f"mlp batch {B}")
+    rng = np.random.default_rng(40 + B)
+    theta = (rng.standard_normal(ref_mlp.NPARAM) * 0.1).astype(np.float32)
+    feat = rng.standard_normal((B, 32)).astype(np.float32) * 2 - 1
+    fmu = rng.standard_normal(32).astype(np.float32)
+    fsd = (rng.random(32) + 0.5).astype(np.float32)
+    target = rng.standard_normal(B).astype(np.float32)
+    X = (feat.astype(np.float64) - fmu) / fsd
+    out_ref, _ = ref_mlp.forward(theta.astype(np.float64), X)
+    _, g_ref = ref_mlp.loss_and_grad(theta.astype(np.float64), X, target.astype(np.float64))
+    T = lambda a: dev(torch, a)
+    prm, ft, mu_t, sd_t, tg = T(theta), T(feat), T(fmu), T(fsd), T(target)
+    z = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda:0")
+    out, z1, z2, work, grad = z(B), z(B, 128), z(B, 128), z(B * 257), z(ref_mlp.NPARAM)
+    F.fpca_bw_mlp_forward(h, B, ft, mu_t, sd_t, prm, out, z1, z2)
+    F.fpca_bw_mlp_backward(h, B, ft, mu_t, sd_t, prm, out, tg, z1, z2, work, grad)
+    h.sync()
+    assert np.abs(out.cpu().numpy() - out_ref).max() <= 1e-5 * max(1.0, np.abs(out_ref).max())
+    assert normwise_rel(grad.cpu().numpy(), g_ref) < 1e-4
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("M,R", [((259, 326), (13, 14)), ((326, 257), (15, 16)), ((304, 264), (17, 18)),
+                                 ((5001,), (403,)), ((61, 47, 66), (3, 5, 6))])
+def test_smooth_mean_strips(torch, F, h, dt, M, R):
+    """Strips of eight outputs: lines that end inside a strip, windows that
+    leave one to seven taps after the blocks of eight, a line that fills a
+    workgroup's LDS. A NaN sum reaches the windows that hold its node, and no
+    others."""
+    _say(f"strips M={M} R={R} {dt}")
+    npdt = np.float64 if dt == "f64" else np.float32
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    rng = np.random.default_rng(60 + sum(M))
+    P = int(np.prod(M))
+    w = (rng.integers(0, 6, P) * (rng.random(P) < 0.7)).astype(npdt)
+    g = (w * (1.0 + 0.3 * rng.standard_normal(P))).astype(npdt)
+    hb = [(r + 0.4) / (m - 1) for r, m in zip(R, M)]
+    bad = int(np.ravel_multi_index([m // 2 for m in M], M))
+    gn = g.copy()
+    gn[bad] = np.nan
+    code = F.FPCA_F64 if dt == "f64" else F.FPCA_F32
+    res = []
+    for sums in (g, gn):
+        mu = torch.empty(P, dtype=tdt, device="cuda:0")
+        st = torch.empty(P, dtype=torch.int8, device="cuda:0")
+        F.fpca_smooth_mean(h, F.Grid(M), code, dev(torch, w), dev(torch, sums), F.FPCA_K_EPANECHNIKOV, hb, mu, st)
+        h.sync()
+        res.append((mu.cpu().numpy().astype(np.float64), st.cpu().numpy()))
+    edge = [np.unique(np.clip([0, 1, 7, 8, m // 2, m - 9, m - 8, m - 2, m - 1], 0, m - 1)) for m in M]
+    nodes = np.ravel_multi_index([a.reshape(-1) for a in np.meshgrid(*edge, indexing="ij")], M)
+    nodes = np.unique(np.concatenate([nodes, rng.integers(0, P, 200)]))
+    want, st_ref = oracle.smooth(M, hb, w.astype(np.float64), g.astype(np.float64), nodes)
+    assert np.array_equal(res[0][1][nodes], st_ref)
+    ok = st_ref == oracle.ST_OK
+    assert normwise_rel(res[0][0][nodes], want, ok) < (1e-10 if dt == "f64" else 1e-5)
+    x = np.stack(np.unravel_index(np.arange(P), M), 1) - np.array(np.unravel_index(bad, M))
+    inside = np.all(np.abs(x) <= np.array(R), axis=1)
+    assert np.array_equal(np.isnan(res[1][0]), inside | np.isnan(res[0][0]))
