@@ -88,6 +88,155 @@ __global__ __launch_bounds__(256) void k_pass(int64_t total, int64_t stride, int
   if (nj > 2) pb.out[a][2][e] = a2;
 }
 
+// The same pass for longer windows, S consecutive outputs of a line per thread:
+// an input value is read once for S outputs (k_pass reads it once per tap), and
+// the taps, whose index is then the same for every lane, come through scalar
+// loads. Position q = 0 .. 2R + S - 1 of the strip's inputs (coordinate
+// x0 - R + q) enters output o with tap q - o where 0 <= q - o <= 2R: the first S
+// and the last S - 1 positions reach a triangle of outputs known at compile
+// time, those between reach all S. The sums run in tap order, so the results
+// are those of k_pass bit for bit. FP64-bound: 1000 x 1000 nodes, 199 taps, the
+// two passes take 165 us (33 TFLOP/s; k_pass 1702 us). S = 16 needs
+// twice the registers and half the threads (223 us).
+constexpr int S = 8;
+typedef const __attribute__((address_space(4))) double CTap;
+
+// ld(q0, v): the S values at positions q0 .. q0 + S - 1 of the strip's inputs, 0 outside the line
+template <int NJ, typename LD>
+__device__ inline void strip_sums(LD ld, CTap *taps, int R, double (&acc)[3][S]) {
+  const int W = 2 * R + 1;
+  double v[S];
+  ld(0, v);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+#pragma unroll
+      for (int o = 0; o <= u; ++o) acc[j][o] = fma(taps[j * W + u - o], v[u], acc[j][o]);
+  int q = S;
+  for (; q + S - 1 <= 2 * R; q += S) {
+    ld(q, v);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      double t[2 * S - 1];
+#pragma unroll
+      for (int i = 0; i < 2 * S - 1; ++i) t[i] = taps[j * W + q - (S - 1) + i];
+#pragma unroll
+      for (int u = 0; u < S; ++u)
+#pragma unroll
+        for (int o = 0; o < S; ++o) acc[j][o] = fma(t[S - 1 + u - o], v[u], acc[j][o]);
+    }
+  }
+  // the last positions: output o still lacks its positions up to q + o - 1
+  // (taps below q), then, diagonal by diagonal, the taps q .. 2R (fewer than S)
+  double v2[S];
+  ld(q, v);
+  ld(q + S, v2);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int u = 0; u < S; ++u)
+#pragma unroll
+      for (int o = u + 1; o < S; ++o) acc[j][o] = fma(taps[j * W + q + u - o], v[u], acc[j][o]);
+#pragma unroll
+  for (int d = 0; d < S - 1; ++d)
+    if (q + d <= 2 * R) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const double t = taps[j * W + q + d];
+#pragma unroll
+        for (int o = 0; o < S; ++o) acc[j][o] = fma(t, d + o < S ? v[(d + o) % S] : v2[(d + o) % S], acc[j][o]);
+      }
+    }
+}
+
+template <typename LD>
+__device__ inline void strip_pass(LD ld, CTap *taps, int R, int nj, double *__restrict__ o0, double *__restrict__ o1,
+                                  double *__restrict__ o2, int64_t base, int64_t stride, int x0, int Mk) {
+  double acc[3][S];
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+#pragma unroll
+    for (int o = 0; o < S; ++o) acc[j][o] = 0.0;
+  if (nj == 1)
+    strip_sums<1>(ld, taps, R, acc);
+  else if (nj == 2)
+    strip_sums<2>(ld, taps, R, acc);
+  else
+    strip_sums<3>(ld, taps, R, acc);
+#pragma unroll
+  for (int o = 0; o < S; ++o) {
+    if (x0 + o >= Mk) break;
+    const int64_t e = base + int64_t(x0 + o) * stride;
+    o0[e] = acc[0][o];
+    if (nj > 1) o1[e] = acc[1][o];
+    if (nj > 2) o2[e] = acc[2][o];
+  }
+}
+
+// Passes along a strided coordinate: neighbouring lanes take neighbouring
+// lines, which are neighbours in memory there, and the wavefronts of a
+// workgroup neighbouring strips of them, whose inputs overlap in the CU's cache.
+// The coordinate, and whether it lies on the line, is the same for every lane.
+constexpr int SW = 8;  // strips per workgroup
+template <typename TS>
+__global__ __launch_bounds__(64 * SW) void k_pass_strip(int64_t nlines, int64_t stride, int Mk, PassBatch<TS> pb,
+                                                    const double *__restrict__ taps, int R) {
+  const int64_t line = int64_t(blockIdx.x) * 64 + (threadIdx.x & 63);
+  const int a = blockIdx.y;
+  const int x0 = __builtin_amdgcn_readfirstlane((int(blockIdx.z) * SW + int(threadIdx.x >> 6)) * S);
+  if (line >= nlines || x0 >= Mk) return;
+  const int64_t base = (line / stride) * (stride * Mk) + line % stride;
+  const TS *__restrict__ src = pb.src[a];
+  auto ld = [&](int q, double (&v)[S]) {
+    const int x = x0 - R + q;
+    if (x >= 0 && x + S <= Mk) {
+#pragma unroll
+      for (int u = 0; u < S; ++u) v[u] = double((src + int64_t(x + u) * stride)[base]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < S; ++u) v[u] = x + u >= 0 && x + u < Mk ? double((src + int64_t(x + u) * stride)[base]) : 0.0;
+    }
+  };
+  strip_pass(ld, (CTap *)taps, R, pb.nj[a], pb.out[a][0], pb.out[a][1], pb.out[a][2], base, stride, x0, Mk);
+}
+
+// Passes along the contiguous coordinate: nl whole lines per workgroup in LDS
+// between R zeros before and R + 2S after, one padding value per S: lanes S
+// values apart then meet different banks, and a strip's reads are one lane
+// address plus offsets that are the same for every lane.
+inline int strip_row(int Mk, int R) { return (Mk + 2 * R + 3 * S) / S * (S + 1); }
+
+template <typename TS>
+__global__ __launch_bounds__(256) void k_pass_row(int64_t nlines, int Mk, int nl, int ld_row, PassBatch<TS> pb,
+                                                  const double *__restrict__ taps, int R) {
+  extern __shared__ double rows[];
+  const int a = blockIdx.y;
+  const int64_t line0 = int64_t(blockIdx.x) * nl;
+  const int have = int(min(int64_t(nl), nlines - line0));
+  const TS *__restrict__ src = pb.src[a] + line0 * Mk;
+  const int span = ld_row / (S + 1) * S;  // values of a padded row
+  for (int l = 0; l < have; ++l)
+    for (int p = threadIdx.x; p < span; p += blockDim.x) {
+      const int x = p - R;
+      rows[l * ld_row + p + p / S] = x >= 0 && x < Mk ? double(src[int64_t(l) * Mk + x]) : 0.0;
+    }
+  __syncthreads();
+  const int ns = (Mk + S - 1) / S;
+  for (int it = threadIdx.x; it < have * ns; it += blockDim.x) {
+    const int l = it / ns, sg = it - l * ns;
+    const double *row = rows + l * ld_row + sg * (S + 1);
+    // q is a multiple of S: position x0 + q of the padded row
+    auto ld = [&](int q, double (&v)[S]) {
+      const double *p = row + q / S * (S + 1);
+#pragma unroll
+      for (int u = 0; u < S; ++u) v[u] = p[u];
+    };
+    strip_pass(ld, (CTap *)taps, R, pb.nj[a], pb.out[a][0], pb.out[a][1], pb.out[a][2], (line0 + l) * Mk, 1, sg * S,
+               Mk);
+  }
+}
+
 struct MomPtrs {
   const double *p[MAXMOM];
 };
@@ -428,7 +577,39 @@ int smooth_generic(fpca_context *ctx, int D, const int *dims, const double *h, c
       ++logL;
     }
     const bool fft_ok = L <= FFT_LMAX && total / dims[k] <= 0x7fffffffLL;
+    // Strips need windows of at least S taps, and enough of them that an eighth
+    // of the threads still fills the chip: 100^2 nodes x 19 taps 19 us by k_pass
+    // and 23 by strips, 200^2 x 39 36 and 37, 300^2 x 29 44 and 29, 500^2 x 99 236
+    // and 58 (the whole call). Lines longer than a workgroup's LDS stay with k_pass.
+    const int64_t lines = total / dims[k];
+    const size_t row = size_t(strip_row(dims[k], R[k])) * sizeof(double);
+    const bool strips = 2 * R[k] + 1 >= S && total * (2 * R[k] + 1) >= (int64_t(1) << 21) &&
+                        (stride[k] == 1 ? row <= 64 * 1024 : (dims[k] + S - 1) / S <= 65535);
+    auto run_strips = [&]() -> int {
+      const int ns = (dims[k] + S - 1) / S;
+      if (stride[k] == 1) {
+        const int nl = int(std::max<int64_t>(1, std::min<int64_t>(256 / ns, int64_t(32 * 1024 / row))));
+        const dim3 grid(unsigned((lines + nl - 1) / nl), unsigned(na));
+        if (s == 0)
+          hipLaunchKernelGGL(k_pass_row<T>, grid, dim3(256), row * nl, ctx->stream, lines, dims[k], nl,
+                             strip_row(dims[k], R[k]), b0, taps + tap_off[k], R[k]);
+        else
+          hipLaunchKernelGGL(k_pass_row<double>, grid, dim3(256), row * nl, ctx->stream, lines, dims[k], nl,
+                             strip_row(dims[k], R[k]), b1, taps + tap_off[k], R[k]);
+      } else {
+        const dim3 grid(unsigned((lines + 63) / 64), unsigned(na), unsigned((ns + SW - 1) / SW));
+        if (s == 0)
+          hipLaunchKernelGGL(k_pass_strip<T>, grid, dim3(64 * SW), 0, ctx->stream, lines, stride[k], dims[k], b0,
+                             taps + tap_off[k], R[k]);
+        else
+          hipLaunchKernelGGL(k_pass_strip<double>, grid, dim3(64 * SW), 0, ctx->stream, lines, stride[k], dims[k], b1,
+                             taps + tap_off[k], R[k]);
+      }
+      FPCA_LAUNCH_CHECK("moment pass strips");
+      return FPCA_OK;
+    };
     auto run_direct = [&]() -> int {
+      if (strips) return run_strips();
       if (s == 0)
         hipLaunchKernelGGL(k_pass<T>, dim3(nblk(total), unsigned(na)), dim3(256), 0, ctx->stream, total, stride[k],
                            dims[k], b0, taps + tap_off[k], R[k]);
