@@ -29,15 +29,22 @@
 // product (tile by tile, nothing of the covariance kept) or formed once and
 // kept in tile blocks (the band only). Everything is FP64.
 //
-// Band tiles are boxes of 64 nodes (64; 8 x 8; 4 x 4 x 4). One workgroup per
-// s-tile visits the t-tiles within reach of the band; per tile pair:
-//   1. the 2d+1 response moments of the full pair sums as products over the
-//      curves, in chunks of 16 curves staged in LDS;
-//   2. the diagonal correction by mode products of the Y2 box with the 1-D
-//      factors of each coordinate (separable sums over the shared nodes);
-//   3. the weight moments from 1-D tables, the FP64 solve and Delta;
-//   4. Delta times the t-tile's rows of X added to the s-tile's outputs (or
-//      the block stored).
+// d = 1 (k_band): band tiles of 64 nodes; one workgroup per s-tile visits the
+// t-tiles within reach of the band. d = 2 and 3 (k_band_mfma): one workgroup per
+// 32 s-nodes (4 x 8 of the last two coordinates), t-blocks of 4 x 4 nodes; per
+// pair of blocks of 16 nodes:
+//   1. the 2d+1 response moments of the full pair sums as FP64 matrix
+//      products over the curves;
+//   2. the diagonal correction, coordinate by coordinate: summed over p_0 once
+//      per operator (k_hsum), over p_1 per workgroup and t-tile, over p_2 per
+//      lane;
+//   3. Delta from the first row of the inverse of the weight-moment matrix.
+//      That row depends on the two nodes' positions only, and coordinate by
+//      coordinate on t_k - s_k alone where both lie R_k or more from the border:
+//      the operator tabulates it for every combination of the coordinates' pair
+//      classes (k_wtab);
+//   4. Delta times the t-rows of X added to the s-rows' outputs (or the block
+//      stored).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -69,6 +76,16 @@ struct CovGeo {
   const double *E[3];  // E[(x*(4R+1) + delta + 2R)*6 + ab], ab: 00 10 01 20 11 02
   int tb[3], nt[3], span[3];
   int nslot;
+  double H[3];  // h_k (M_k - 1)
+  // d >= 2: pair classes of every coordinate (cls[(x * (4R + 1) + delta + 2R)]:
+  // 2 * class + 1 if the class is met mirrored), their numbers, the table of
+  // first rows of the inverse weight-moment matrices (8 doubles per combination
+  // of classes, the last coordinate's fastest), and per node of a coordinate
+  // 1 / W_0, a^2 / v and a / v
+  const int *cls[3];
+  int ncls[3];
+  const double *rows;
+  const double *nd[3];
 };
 
 template <int d>
@@ -338,6 +355,8 @@ struct BandArgs {
   int r;
   double *out;
   double *band;  // stored blocks
+  const double *Hs;  // d >= 2: Y2 summed over p_0 (k_hsum); Y2 itself for d = 2
+  int c0, nc;        // d >= 2: columns of X of this launch
 };
 
 // Local node li of a tile (coordinate d-1 fastest) and its grid coordinates.
@@ -358,162 +377,63 @@ __device__ inline void tile_node(int li, const int *lo, const CovGeo &g, int *x,
   *p = q;
 }
 
+// The per-coordinate products of window sums and the shared-node sums of the
+// pair (s, t) of coordinate k.
+__device__ inline void pair_factors(const CovGeo &g, int k, int xs, int xt, double (&P)[6], double (&E)[6]) {
+  const int R2 = 2 * g.R[k];
+  const double *Wk = g.W[k];
+  const double ws0 = Wk[xs * 3], ws1 = Wk[xs * 3 + 1], ws2 = Wk[xs * 3 + 2];
+  const double wt0 = Wk[xt * 3], wt1 = Wk[xt * 3 + 1], wt2 = Wk[xt * 3 + 2];
+  P[0] = ws0 * wt0;
+  P[1] = ws1 * wt0;
+  P[2] = ws0 * wt1;
+  P[3] = ws2 * wt0;
+  P[4] = ws1 * wt1;
+  P[5] = ws0 * wt2;
+  const int dc = min(max(xt - xs, -R2), R2);
+  const double *Er = &g.E[k][(int64_t(xs) * (2 * R2 + 1) + dc + R2) * 6];
+#pragma unroll
+  for (int j = 0; j < 6; ++j) E[j] = Er[j];
+}
+
 constexpr int ZH = 34;  // padded row of the 32 t-nodes of a half tile
 
-template <int d>
-constexpr int band_union_doubles() {
-  constexpr int zc = (d + 1) * NC * (ZP + ZH);
-  constexpr int dx = 64 * 33 + 32 * 64;
-  return zc > dx ? zc : dx;
-}
+// d = 1. Per s-tile: every t-tile within reach of the band, each in two halves
+// of 32 t-nodes (4 nodes per thread keep the FP64 solve within the registers).
+constexpr int B1_UN = 2 * NC * (ZP + ZH) > 64 * 33 + 32 * 64 ? 2 * NC * (ZP + ZH) : 64 * 33 + 32 * 64;
+constexpr int B1_LDS = B1_UN + 4096;  // curve chunks | Delta and X tiles, then the Y2 box
 
-template <int d>
-constexpr int band_lds_doubles() {
-  // union region (curve chunks | Delta and X tiles) + Y2 box + mode-product buffers
-  constexpr int extra = d == 3 ? (3 * 16 * 16 * 3 + 16 * 16 * 3 + 16 * 16 * 5) : (d == 2 ? 64 * 8 * 3 : 0);
-  return band_union_doubles<d>() + 4096 + extra;
-}
-
-// Per s-tile: every t-tile within reach of the band, each in two halves of 32
-// t-nodes (4 nodes per thread keep the FP64 solve within the registers).
-template <int d, bool STORE>
+template <bool STORE>
 __global__ __launch_bounds__(BT) void k_band(BandArgs A) {
-  constexpr int D = 2 * d;
-  constexpr int NT = 2 * d + 1;  // response moments
-  constexpr int NS = 1 + D + D * (D + 1) / 2;
-  constexpr int TB = tile_ext<d>();
-  constexpr int UN = band_union_doubles<d>();
+  constexpr int d = 1, NT = 3, NS = 6;
   extern __shared__ double sm[];
-  double *Zs = sm;                      // [d+1][NC][ZP]: the 64 s-nodes
-  double *Zt = sm + (d + 1) * NC * ZP;  // [d+1][NC][ZH]: the 32 t-nodes of the half
-  double *Dl = sm;                      // [64][33]
-  double *Xl = sm + 64 * 33;            // [32][64]
-  double *Yb = sm + UN;                 // Y2 box
-  double *Fb = Yb + 4096;               // d = 3: F[3][16][16][3]; d = 2: V[64][8][3]
-  double *V3 = Fb + 3 * 16 * 16 * 3;    // d = 3: [16][16][3]
-  double *V2 = V3 + 16 * 16 * 3;        // d = 3: [16][16][5]
-  __shared__ long long sidx[64], tidx[64];
-  __shared__ int sok[64], tok[64];
+  double *Zs = sm;                // [2][NC][ZP]: the 64 s-nodes
+  double *Zt = sm + 2 * NC * ZP;  // [2][NC][ZH]: the 32 t-nodes of the half
+  double *Dl = sm;                // [64][33]
+  double *Xl = sm + 64 * 33;      // [32][64]
+  double *Yb = sm + B1_UN;        // Y2 box
 
   const CovGeo &g = A.g;
-  const int n = g.n;
+  const int n = g.n, M = g.M[0], R = g.R[0];
   const int tid = threadIdx.x;
   const int a = tid >> 4, b = tid & 15;  // s-locals 2a, 2a+1; t-locals 32 hh + 2b, + 1
-  int sa[3] = {0, 0, 0}, s0[3] = {0, 0, 0};
-  {
-    int64_t rem = blockIdx.x;
-#pragma unroll
-    for (int k = d - 1; k >= 0; --k) {
-      sa[k] = int(rem % g.nt[k]);
-      rem /= g.nt[k];
-      s0[k] = sa[k] * TB;
-    }
-  }
-  if (tid < 64) {
-    int x[3];
-    bool ok;
-    int64_t p;
-    tile_node<d>(tid, s0, g, x, &ok, &p);
-    sok[tid] = ok;
-    sidx[tid] = ok ? p : 0;
-  }
-  int sl[2][3];
-#pragma unroll
-  for (int x = 0; x < 2; ++x) {
-    int rem = 2 * a + x;
-#pragma unroll
-    for (int k = d - 1; k >= 0; --k) {
-      sl[x][k] = rem % TB;
-      rem /= TB;
-    }
-  }
+  const int s0 = int(blockIdx.x) * 64;
   const int ro = tid >> 3, cg = tid & 7;  // fused product: s-row and column group
   double acco[8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) acco[j] = 0.0;
 
   for (int o = 0; o < g.nslot; ++o) {
-    int t0[3] = {0, 0, 0};
-    bool inside = true;
-    {
-      int rem = o;
-#pragma unroll
-      for (int k = d - 1; k >= 0; --k) {
-        const int w = 2 * g.span[k] + 1;
-        const int c = sa[k] + rem % w - g.span[k];
-        rem /= w;
-        inside = inside && c >= 0 && c < g.nt[k];
-        t0[k] = c * TB;
-      }
-    }
-    if (!inside) continue;  // uniform across the workgroup
-    __syncthreads();        // readers of the previous tile pair's tables are done
-    if (tid < 64) {
-      int x[3];
-      bool ok;
-      int64_t p;
-      tile_node<d>(tid, t0, g, x, &ok, &p);
-      tok[tid] = ok;
-      tidx[tid] = ok ? p : 0;
-    }
-    // Y2 over the nodes shared by some s- and t-window of the tile pair, and
-    // (d = 3) the 1-D factor tables F[k][q = sl*4 + tl][p][ab]
-    int plo[3], np[3];
-    bool any = true;
-#pragma unroll
-    for (int k = 0; k < d; ++k) {
-      const int shi = min(s0[k] + TB - 1, g.M[k] - 1), thi = min(t0[k] + TB - 1, g.M[k] - 1);
-      plo[k] = max(max(s0[k], t0[k]) - g.R[k], 0);
-      const int phi = min(min(shi, thi) + g.R[k], g.M[k] - 1);
-      np[k] = phi - plo[k] + 1;
-      any = any && np[k] > 0;
-    }
-    if (any) {
-      int nbx = 1;
-#pragma unroll
-      for (int k = 0; k < d; ++k) nbx *= np[k];
-      for (int e = tid; e < nbx; e += BT) {
-        int rem = e;
-        int64_t p = 0;
-#pragma unroll
-        for (int k = d - 1; k >= 0; --k) {
-          p += int64_t(plo[k] + rem % np[k]) * g.stride[k];
-          rem /= np[k];
-        }
-        Yb[e] = A.Y2[p];
-      }
-      if constexpr (d == 3) {
-        for (int e = tid; e < 3 * 16 * 16 * 3; e += BT) {
-          const int k = e / 768, rem = e - k * 768;
-          const int q = rem / 48, rem2 = rem - q * 48;
-          const int pi = rem2 / 3, ab = rem2 - pi * 3;
-          double f = 0.0;
-          if (pi < np[k]) {
-            const int R = g.R[k];
-            const int s = s0[k] + (q >> 2), t = t0[k] + (q & 3), p = plo[k] + pi;
-            const int ds = p - s, dt = p - t;
-            if (ds >= -R && ds <= R && dt >= -R && dt <= R) {
-              f = g.K[k][ds + R] * g.K[k][dt + R];
-              if (ab == 1) f *= g.U[k][ds + R];
-              if (ab == 2) f *= g.U[k][dt + R];
-            }
-          }
-          Fb[e] = f;
-        }
-      }
-    }
+    const int c = int(blockIdx.x) + o - g.span[0];
+    if (c < 0 || c >= g.nt[0]) continue;  // uniform across the workgroup
+    const int t0 = c * 64;
+    __syncthreads();  // readers of the previous tile pair's tables are done
+    // Y2 over the nodes shared by some s- and t-window of the tile pair
+    const int plo = max(max(s0, t0) - R, 0);
+    const int np = min(min(s0, t0) + 63 + R, M - 1) - plo + 1;
+    for (int e = tid; e < np; e += BT) Yb[e] = A.Y2[plo + e];
 
     for (int hh = 0; hh < 2; ++hh) {
-      int tl[2][3];
-#pragma unroll
-      for (int y = 0; y < 2; ++y) {
-        int rem = 32 * hh + 2 * b + y;
-#pragma unroll
-        for (int k = d - 1; k >= 0; --k) {
-          tl[y][k] = rem % TB;
-          rem /= TB;
-        }
-      }
       // ---- 1. response moments of the full pair sums
       double acc[2][2][NT];
 #pragma unroll
@@ -524,17 +444,15 @@ __global__ __launch_bounds__(BT) void k_band(BandArgs A) {
           for (int q = 0; q < NT; ++q) acc[x][y][q] = 0.0;
       for (int i0 = 0; i0 < n; i0 += NC) {
         __syncthreads();
-        constexpr int ps = (d + 1) * NC * 64, pt = (d + 1) * NC * 32;
+        constexpr int ps = 2 * NC * 64, pt = 2 * NC * 32;
         for (int e = tid; e < ps + pt; e += BT) {
           const bool side = e >= ps;
           const int rem = side ? e - ps : e;
-          const int node = rem / ((d + 1) * NC);
-          const int fi = rem - node * ((d + 1) * NC);
+          const int node = rem / (2 * NC);
+          const int fi = rem - node * (2 * NC);
           const int f = fi / NC, ii = fi - f * NC;
-          const int tn = 32 * hh + node;
-          const bool ok = (side ? tok[tn] : sok[node]) && i0 + ii < n;
-          const long long p = side ? tidx[tn] : sidx[node];
-          const double v = ok ? A.Zn[(p * (d + 1) + f) * n + i0 + ii] : 0.0;
+          const int x = side ? t0 + 32 * hh + node : s0 + node;
+          const double v = x < M && i0 + ii < n ? A.Zn[(int64_t(x) * 2 + f) * n + i0 + ii] : 0.0;
           if (side)
             Zt[(f * NC + ii) * ZH + node] = v;
           else
@@ -543,9 +461,9 @@ __global__ __launch_bounds__(BT) void k_band(BandArgs A) {
         __syncthreads();
 #pragma unroll 2
         for (int ii = 0; ii < NC; ++ii) {
-          double zs[2][d + 1], zt[2][d + 1];
+          double zs[2][2], zt[2][2];
 #pragma unroll
-          for (int f = 0; f <= d; ++f) {
+          for (int f = 0; f < 2; ++f) {
             const double2 s2 = *reinterpret_cast<const double2 *>(&Zs[(f * NC + ii) * ZP + 2 * a]);
             const double2 t2 = *reinterpret_cast<const double2 *>(&Zt[(f * NC + ii) * ZH + 2 * b]);
             zs[0][f] = s2.x;
@@ -558,216 +476,47 @@ __global__ __launch_bounds__(BT) void k_band(BandArgs A) {
 #pragma unroll
             for (int y = 0; y < 2; ++y) {
               acc[x][y][0] = fma(zs[x][0], zt[y][0], acc[x][y][0]);
-#pragma unroll
-              for (int k = 0; k < d; ++k) {
-                acc[x][y][1 + k] = fma(zs[x][k + 1], zt[y][0], acc[x][y][1 + k]);
-                acc[x][y][1 + d + k] = fma(zs[x][0], zt[y][k + 1], acc[x][y][1 + d + k]);
-              }
+              acc[x][y][1] = fma(zs[x][1], zt[y][0], acc[x][y][1]);
+              acc[x][y][2] = fma(zs[x][0], zt[y][1], acc[x][y][2]);
             }
         }
       }
 
-      // closed-form (tensor-product) intercept from the full moments
-      double low[2][2];
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-#pragma unroll
-        for (int y = 0; y < 2; ++y) {
-          double S = 1.0, fac = 1.0, lin = 0.0;
-#pragma unroll
-          for (int k = 0; k < d; ++k) {
-            const int xs = min(s0[k] + sl[x][k], g.M[k] - 1), xt = min(t0[k] + tl[y][k], g.M[k] - 1);
-            const double *Wk = g.W[k];
-            const double s0w = Wk[xs * 3], s1w = Wk[xs * 3 + 1], s2w = Wk[xs * 3 + 2];
-            const double t0w = Wk[xt * 3], t1w = Wk[xt * 3 + 1], t2w = Wk[xt * 3 + 2];
-            const double as = s1w / s0w, vs = s2w / s0w - as * as;
-            const double at = t1w / t0w, vt = t2w / t0w - at * at;
-            S *= s0w * t0w;
-            fac += as * as / vs + at * at / vt;
-            lin += (as / vs) * acc[x][y][1 + k] + (at / vt) * acc[x][y][1 + d + k];
-          }
-          low[x][y] = (acc[x][y][0] * fac - lin) * g.inv_n / S;
-        }
-
-      // ---- 2. diagonal correction: subtract sum_p f(p; s,t) Y2(p) from acc
-      if (any) {
-        if constexpr (d == 1) {
-          const int R = g.R[0];
-          const double *K0 = g.K[0], *U0 = g.U[0];
-#pragma unroll
-          for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int y = 0; y < 2; ++y) {
-              const int s = s0[0] + sl[x][0], t = t0[0] + tl[y][0];
-              const int lo = max(max(s, t) - R, 0), hi = min(min(s, t) + R, g.M[0] - 1);
-              double c0 = 0.0, c1 = 0.0, c2 = 0.0;
-              for (int p = lo; p <= hi; ++p) {
-                const double kk = K0[p - s + R] * K0[p - t + R] * Yb[p - plo[0]];
-                c0 += kk;
-                c1 = fma(kk, U0[p - s + R], c1);
-                c2 = fma(kk, U0[p - t + R], c2);
-              }
-              acc[x][y][0] -= c0;
-              acc[x][y][1] -= c1;
-              acc[x][y][2] -= c2;
-            }
-        } else if constexpr (d == 2) {
-          const int R0 = g.R[0], R1 = g.R[1];
-          const double *K0 = g.K[0], *U0 = g.U[0], *K1 = g.K[1], *U1 = g.U[1];
-          double *V = Fb;  // [np0][8][3]
-          for (int hs = 0; hs < 4; ++hs) {
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-              const int s1 = s0[1] + 2 * hs + x;
-              // V[p0][tl][ab] = sum_p1 f1(p1; s1, t1)^{ab} Y2(p0, p1)
-              for (int e = tid; e < np[0] * 8 * 3; e += BT) {
-                const int p0i = e / 24, rem = e - p0i * 24;
-                const int tlc = rem / 3, ab = rem - tlc * 3;
-                const int t1 = t0[1] + tlc;
-                double sacc = 0.0;
-                for (int p1i = 0; p1i < np[1]; ++p1i) {
-                  const int p1 = plo[1] + p1i;
-                  const int ds = p1 - s1, dt = p1 - t1;
-                  if (ds < -R1 || ds > R1 || dt < -R1 || dt > R1) continue;
-                  double f = K1[ds + R1] * K1[dt + R1];
-                  if (ab == 1) f *= U1[ds + R1];
-                  if (ab == 2) f *= U1[dt + R1];
-                  sacc = fma(f, Yb[p0i * np[1] + p1i], sacc);
-                }
-                V[e] = sacc;
-              }
-              __syncthreads();
-              if ((a & 3) == hs) {
-                const int s0c = s0[0] + sl[x][0];
-#pragma unroll
-                for (int y = 0; y < 2; ++y) {
-                  const int t0c = t0[0] + tl[y][0];
-                  const int tlc = tl[y][1];
-                  double c[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-                  for (int p0i = 0; p0i < np[0]; ++p0i) {
-                    const int p0 = plo[0] + p0i;
-                    const int ds = p0 - s0c, dt = p0 - t0c;
-                    if (ds < -R0 || ds > R0 || dt < -R0 || dt > R0) continue;
-                    const double f = K0[ds + R0] * K0[dt + R0];
-                    const double *v = &V[(p0i * 8 + tlc) * 3];
-                    c[0] = fma(f, v[0], c[0]);
-                    c[1] = fma(f * U0[ds + R0], v[0], c[1]);
-                    c[2] = fma(f * U0[dt + R0], v[0], c[2]);
-                    c[3] = fma(f, v[1], c[3]);
-                    c[4] = fma(f, v[2], c[4]);
-                  }
-                  // order of acc: T0, s0, s1, t0, t1
-                  acc[x][y][0] -= c[0];
-                  acc[x][y][1] -= c[1];
-                  acc[x][y][3] -= c[2];
-                  acc[x][y][2] -= c[3];
-                  acc[x][y][4] -= c[4];
-                }
-              }
-              __syncthreads();
-            }
-          }
-        } else {
-          // s-locals: s2 = 2 (a & 1) + x, s1 = (a >> 1) & 3, s0 = a >> 3;
-          // t-locals: t2 = 2 (b & 1) + y, t1 = (b >> 1) & 3, t0 = 2 hh + (b >> 3)
-          const int s1l = (a >> 1) & 3, s0l = a >> 3;
-          const int t1l = (b >> 1) & 3, t0l = 2 * hh + (b >> 3);
-          for (int hs = 0; hs < 2; ++hs)
-            for (int ht = 0; ht < 2; ++ht) {
-#pragma unroll
-              for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y) {
-                  const int q2 = (2 * hs + x) * 4 + 2 * ht + y;
-                  // (a) V3[p0][p1][ab] = sum_p2 F2[q2][p2][ab] Y2(p0,p1,p2)
-                  for (int e = tid; e < np[0] * np[1] * 3; e += BT) {
-                    const int p01 = e / 3, ab = e - p01 * 3;
-                    const double *Fr = &Fb[(2 * 256 + q2 * 16) * 3 + ab];
-                    const double *Yr = &Yb[p01 * np[2]];
-                    double sacc = 0.0;
-                    for (int p2 = 0; p2 < np[2]; ++p2) sacc = fma(Fr[p2 * 3], Yr[p2], sacc);
-                    V3[e] = sacc;
-                  }
-                  __syncthreads();
-                  // (b) V2[p0][q1][c5]; c5 = (ab1, ab2): 00 00, 10 00, 01 00, 00 10, 00 01
-                  for (int e = tid; e < np[0] * 16 * 5; e += BT) {
-                    const int p0 = e / 80, rem = e - p0 * 80;
-                    const int q1 = rem / 5, c5 = rem - q1 * 5;
-                    const int ab1 = c5 < 3 ? c5 : 0, ab2 = c5 < 3 ? 0 : c5 - 2;
-                    const double *Fr = &Fb[(256 + q1 * 16) * 3 + ab1];
-                    const double *Vr = &V3[(p0 * np[1]) * 3 + ab2];
-                    double sacc = 0.0;
-                    for (int p1 = 0; p1 < np[1]; ++p1) sacc = fma(Fr[p1 * 3], Vr[p1 * 3], sacc);
-                    V2[e] = sacc;
-                  }
-                  __syncthreads();
-                  // (c) the owners of (s2, t2): sum over p0
-                  if ((a & 1) == hs && (b & 1) == ht) {
-                    const int q0 = s0l * 4 + t0l, q1 = s1l * 4 + t1l;
-                    double c[7] = {0, 0, 0, 0, 0, 0, 0};
-                    for (int p0 = 0; p0 < np[0]; ++p0) {
-                      const double *Fr = &Fb[(q0 * 16 + p0) * 3];
-                      const double *Vr = &V2[(p0 * 16 + q1) * 5];
-                      c[0] = fma(Fr[0], Vr[0], c[0]);  // T0
-                      c[1] = fma(Fr[1], Vr[0], c[1]);  // s0
-                      c[2] = fma(Fr[2], Vr[0], c[2]);  // t0
-                      c[3] = fma(Fr[0], Vr[1], c[3]);  // s1
-                      c[4] = fma(Fr[0], Vr[2], c[4]);  // t1
-                      c[5] = fma(Fr[0], Vr[3], c[5]);  // s2
-                      c[6] = fma(Fr[0], Vr[4], c[6]);  // t2
-                    }
-                    // order of acc: T0, s0, s1, s2, t0, t1, t2
-                    acc[x][y][0] -= c[0];
-                    acc[x][y][1] -= c[1];
-                    acc[x][y][2] -= c[3];
-                    acc[x][y][3] -= c[5];
-                    acc[x][y][4] -= c[2];
-                    acc[x][y][5] -= c[4];
-                    acc[x][y][6] -= c[6];
-                  }
-                }
-            }
-        }
-      }
-
-      // ---- 3. weight moments, the solve and Delta
       double delta[2][2];
 #pragma unroll
       for (int x = 0; x < 2; ++x)
 #pragma unroll
         for (int y = 0; y < 2; ++y) {
-          const int si = 2 * a + x, ti = 32 * hh + 2 * b + y;
-          bool inb = sok[si] && tok[ti];
-          double Pk[3][6], Ek[3][6];
-#pragma unroll
-          for (int k = 0; k < d; ++k) {
-            const int xs = min(s0[k] + sl[x][k], g.M[k] - 1), xt = min(t0[k] + tl[y][k], g.M[k] - 1);
-            const int dl = xt - xs;
-            const int R2 = 2 * g.R[k];
-            inb = inb && dl >= -R2 && dl <= R2;
-            const double *Wk = g.W[k];
-            const double ws0 = Wk[xs * 3], ws1 = Wk[xs * 3 + 1], ws2 = Wk[xs * 3 + 2];
-            const double wt0 = Wk[xt * 3], wt1 = Wk[xt * 3 + 1], wt2 = Wk[xt * 3 + 2];
-            Pk[k][0] = ws0 * wt0;
-            Pk[k][1] = ws1 * wt0;
-            Pk[k][2] = ws0 * wt1;
-            Pk[k][3] = ws2 * wt0;
-            Pk[k][4] = ws1 * wt1;
-            Pk[k][5] = ws0 * wt2;
-            const int dc = min(max(dl, -R2), R2);
-            const double *Er = &g.E[k][(int64_t(xs) * (2 * R2 + 1) + dc + R2) * 6];
-#pragma unroll
-            for (int j = 0; j < 6; ++j) Ek[k][j] = Er[j];
+          const int s = s0 + 2 * a + x, t = t0 + 32 * hh + 2 * b + y;
+          const int xs = min(s, M - 1), xt = min(t, M - 1);
+          // closed-form (tensor-product) intercept from the full moments
+          const double *Wk = g.W[0];
+          const double as = Wk[xs * 3 + 1] / Wk[xs * 3], vs = Wk[xs * 3 + 2] / Wk[xs * 3] - as * as;
+          const double at = Wk[xt * 3 + 1] / Wk[xt * 3], vt = Wk[xt * 3 + 2] / Wk[xt * 3] - at * at;
+          const double fac = 1.0 + (as * as / vs + at * at / vt);
+          const double lin = (as / vs) * acc[x][y][1] + (at / vt) * acc[x][y][2];
+          const double low = (acc[x][y][0] * fac - lin) * g.inv_n / (Wk[xs * 3] * Wk[xt * 3]);
+          // ---- 2. diagonal correction: subtract sum_p f(p; s,t) Y2(p) from acc
+          const double *K0 = g.K[0], *U0 = g.U[0];
+          const int lo = max(max(s, t) - R, 0), hi = min(min(s, t) + R, M - 1);
+          double c0 = 0.0, c1 = 0.0, c2 = 0.0;
+          for (int p = lo; p <= hi; ++p) {
+            const double kk = K0[p - s + R] * K0[p - t + R] * Yb[p - plo];
+            c0 += kk;
+            c1 = fma(kk, U0[p - s + R], c1);
+            c2 = fma(kk, U0[p - t + R], c2);
           }
+          // ---- 3. weight moments, the solve and Delta
           double dv = 0.0;
-          if (inb) {
-            double m[NS + NT];
+          if (s < M && t < M && t - s >= -2 * R && t - s <= 2 * R) {
+            double Pk[3][6], Ek[3][6], m[NS + NT];
+            pair_factors(g, 0, xs, xt, Pk[0], Ek[0]);
             fill_weight_moments<d>(Pk, Ek, m, std::make_integer_sequence<int, NS>{});
-#pragma unroll
-            for (int q = 0; q < NT; ++q) m[NS + q] = acc[x][y][q] * g.inv_n;
+            m[NS] = (acc[x][y][0] - c0) * g.inv_n;
+            m[NS + 1] = (acc[x][y][1] - c1) * g.inv_n;
+            m[NS + 2] = (acc[x][y][2] - c2) * g.inv_n;
             int8_t st;
-            const double b0 = wls_b0<D>(m, &st);
-            dv = b0 - low[x][y];
+            dv = wls_b0<2>(m, &st) - low;
           }
           delta[x][y] = dv;
           // one element's solve at a time: no interleaving of their registers
@@ -788,9 +537,9 @@ __global__ __launch_bounds__(BT) void k_band(BandArgs A) {
 #pragma unroll
           for (int y = 0; y < 2; ++y) Dl[(2 * a + x) * 33 + 2 * b + y] = delta[x][y];
         for (int e = tid; e < 32 * 64; e += BT) {
-          const int t = e >> 6, c = e & 63;
-          const int tn = 32 * hh + t;
-          Xl[e] = (tok[tn] && c < A.r) ? A.X[tidx[tn] * A.r + c] : 0.0;
+          const int t = e >> 6, cc = e & 63;
+          const int tn = t0 + 32 * hh + t;
+          Xl[e] = (tn < M && cc < A.r) ? A.X[int64_t(tn) * A.r + cc] : 0.0;
         }
         __syncthreads();
         for (int t = 0; t < 32; ++t) {
@@ -802,14 +551,509 @@ __global__ __launch_bounds__(BT) void k_band(BandArgs A) {
     }
   }
   if constexpr (!STORE) {
-    if (sok[ro]) {
+    if (s0 + ro < M) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
-        const int c = cg + 8 * j;
-        if (c < A.r) A.out[sidx[ro] * A.r + c] += acco[j];
+        const int cc = cg + 8 * j;
+        if (cc < A.r) A.out[int64_t(s0 + ro) * A.r + cc] += acco[j];
       }
     }
   }
+}
+
+// ------------------------------------------------------------------ d = 2, 3
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// First row of the inverse of the (D+1) x (D+1) weight-moment matrix, with
+// wls_b0's factorization and status rule: b0 = sum_q w_q T_q. FALLBACK gives
+// (1/S0, 0, ..), EMPTY NaN.
+template <int D>
+__device__ inline void wls_weights(const double *m, double (&w)[D + 1]) {
+  constexpr int n = D + 1;
+  double A[n][n];
+  const double S0 = m[0];
+  A[0][0] = S0;
+  int q = 1 + D;
+#pragma unroll
+  for (int k = 0; k < D; ++k) A[1 + k][0] = m[1 + k];
+#pragma unroll
+  for (int k = 0; k < D; ++k)
+#pragma unroll
+    for (int l = k; l < D; ++l) A[1 + l][1 + k] = m[q++];
+  bool ok = true;
+#pragma unroll
+  for (int i = 1; i < n; ++i) ok = ok && (A[i][i] > 0.0);
+#pragma unroll
+  for (int j = 0; j < n; ++j) {
+    double dj = A[j][j];
+#pragma unroll
+    for (int k = 0; k < j; ++k) dj -= A[j][k] * (A[j][k] * A[k][k]);
+    ok = ok && (dj >= 1e-10 * A[j][j]);
+    const double inv = 1.0 / dj;
+#pragma unroll
+    for (int i = j + 1; i < n; ++i) {
+      double v = A[i][j];
+#pragma unroll
+      for (int k = 0; k < j; ++k) v -= A[i][k] * (A[j][k] * A[k][k]);
+      A[i][j] = v * inv;
+    }
+    A[j][j] = dj;
+  }
+  if (!(S0 > 0.0) || !ok) {
+    w[0] = S0 > 0.0 ? 1.0 / S0 : __builtin_nan("");
+#pragma unroll
+    for (int i = 1; i < n; ++i) w[i] = S0 > 0.0 ? 0.0 : __builtin_nan("");
+    return;
+  }
+  // L z = e_0, then L^T w = D^-1 z
+  w[0] = 1.0;
+#pragma unroll
+  for (int i = 1; i < n; ++i) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < i; ++k) v -= A[i][k] * w[k];
+    w[i] = v;
+  }
+#pragma unroll
+  for (int i = n - 1; i >= 0; --i) {
+    double v = w[i] / A[i][i];
+#pragma unroll
+    for (int k = i + 1; k < n; ++k) v -= A[k][i] * w[k];
+    w[i] = v;
+  }
+}
+
+template <int d>
+__device__ inline void pair_weights(const CovGeo &g, const int (&xs)[3], const int (&xt)[3], double (&w)[2 * d + 1]) {
+  constexpr int D = 2 * d, NS = 1 + D + D * (D + 1) / 2;
+  double Pk[3][6], Ek[3][6], m[NS];
+#pragma unroll
+  for (int k = 0; k < d; ++k) pair_factors(g, k, xs[k], xt[k], Pk[k], Ek[k]);
+  fill_weight_moments<d>(Pk, Ek, m, std::make_integer_sequence<int, NS>{});
+  wls_weights<D>(m, w);
+}
+
+// The table of rows: thread e takes the combination of classes e. rep[k][c]: the
+// class's own pair of nodes, as s * (4R + 1) + delta + 2R, or -1 where no pair of
+// the grid has that class (the row is not read then).
+template <int d>
+__global__ __launch_bounds__(64) void k_wtab(CovGeo g, int64_t count, const int *__restrict__ r0,
+                                             const int *__restrict__ r1, const int *__restrict__ r2,
+                                             double *__restrict__ tab) {
+  const int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (e >= count) return;
+  int xs[3] = {0, 0, 0}, xt[3] = {0, 0, 0};
+  int64_t rem = e;
+  bool have = true;
+#pragma unroll
+  for (int k = d - 1; k >= 0; --k) {
+    const int wd = 4 * g.R[k] + 1;
+    const int c = (k == 0 ? r0 : (k == 1 ? r1 : r2))[int(rem % g.ncls[k])];
+    rem /= g.ncls[k];
+    have = have && c >= 0;
+    xs[k] = max(c, 0) / wd;
+    xt[k] = xs[k] + max(c, 2 * g.R[k]) % wd - 2 * g.R[k];
+  }
+  if (!have) return;
+  double w[2 * d + 1];
+  pair_weights<d>(g, xs, xt, w);
+#pragma unroll
+  for (int q = 0; q < 2 * d + 1; ++q) tab[e * 8 + q] = w[q];
+}
+
+// d = 3: Y2 summed over p_0 with the factors of (s_0, t_0 = s_0 + delta):
+// H[(s_0 (4R_0 + 1) + delta + 2 R_0)][ab][p_1 p_2], ab: K K, K K u, K K v.
+__global__ __launch_bounds__(256) void k_hsum(CovGeo g, const double *__restrict__ Y2, double *__restrict__ H) {
+  const int64_t plane = int64_t(g.M[1]) * g.M[2];
+  const int64_t nb = (plane + 255) / 256, pair = blockIdx.x / nb;
+  const int64_t p = (blockIdx.x % nb) * 256 + threadIdx.x;
+  if (p >= plane) return;
+  const int R = g.R[0], wd = 4 * R + 1;
+  const int s = int(pair / wd), t = s + int(pair % wd) - 2 * R;
+  double h0 = 0.0, h1 = 0.0, h2 = 0.0;
+  if (t >= 0 && t < g.M[0])
+    for (int q = max(max(s, t) - R, 0); q <= min(min(s, t) + R, g.M[0] - 1); ++q) {
+      const double f = g.K[0][q - s + R] * g.K[0][q - t + R] * Y2[q * plane + p];
+      h0 += f;
+      h1 = fma(f, g.U[0][q - s + R], h1);
+      h2 = fma(f, g.U[0][q - t + R], h2);
+    }
+  double *o = H + pair * 3 * plane + p;
+  o[0] = h0;
+  o[plane] = h1;
+  o[2 * plane] = h2;
+}
+
+// Node-major curves [P][F][n] to blocks of 4 x 4 nodes of the last two
+// coordinates, [block][f][curve / 2][node][curve % 2] (missing nodes and the odd
+// curve 0): a wavefront's operands are then whole cache lines, where sixteen
+// nodes' rows are sixteen lines per quarter wavefront (64^3 nodes, n = 100, one
+// product: 282 -> 239 ms).
+__global__ __launch_bounds__(256) void k_retile(CovGeo g, const double *__restrict__ Zn, double *__restrict__ Zt) {
+  constexpr int KB = 128;
+  __shared__ double t[16][KB + 1];
+  const int d = g.d, F = d + 1, f = blockIdx.y, n = g.n, nk2 = (n + 1) / 2;
+  const int M1 = g.M[d - 2], M2 = g.M[d - 1], nT1 = (M1 + 3) / 4, nT2 = (M2 + 3) / 4;
+  const int64_t ti = blockIdx.x;
+  const int T2 = int(ti % nT2), T1 = int(ti / nT2 % nT1);
+  const int64_t x0 = ti / nT2 / nT1;
+  for (int k0 = 0; k0 < n; k0 += KB) {
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * KB; e += 256) {
+      const int k = e % KB, nd = e / KB, x1 = 4 * T1 + nd / 4, x2 = 4 * T2 + nd % 4;
+      const int64_t p = (x0 * M1 + x1) * M2 + x2;
+      t[nd][k] = x1 < M1 && x2 < M2 && k0 + k < n ? Zn[(p * F + f) * n + k0 + k] : 0.0;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < 16 * KB; e += 256) {
+      const int q = e >> 5, i = e & 31;
+      if (k0 / 2 + q < nk2) Zt[((ti * F + f) * nk2 + k0 / 2 + q) * 32 + i] = t[i >> 1][2 * q + (i & 1)];
+    }
+  }
+}
+
+constexpr int MT = 512;     // threads: 8 wavefronts
+constexpr int MKC = 104;    // curves per LDS chunk
+template <int d>
+constexpr int mfma_nv() { return 2 * d - 1; }  // H2 variants
+inline size_t band_mfma_lds(int d, int n, int R2, int ncb) {
+  const size_t kp = size_t(std::min(MKC, (n + 7) / 8 * 8));
+  const size_t z = size_t(d + 1) * kp * 32, red = size_t(8) * ncb * 256;
+  return (std::max(z, red) + 2 * size_t(8 + 2 * R2) * (2 * d - 1) * 16) * 8;
+}
+
+// One workgroup per s-set (s_0; 4 of s_1; 8 of s_2): two blocks of 16 s-nodes,
+// whose filtered curves stay in LDS. Steps over (t_0; 4 of t_1); each wavefront
+// takes 4 of t_2, so a block of 16 t-nodes, against one of the s-blocks (both at
+// once need twice the accumulators, which then spill: 334 against 282 ms at that
+// stage). The FP64 matrix products D[t][s] = Zt Zs^T run over the curves in steps
+// of eight (lane group g takes curves 2g and 2g + 1 of the eight, one 16-byte
+// read per t-node), Zt straight from memory, double buffered in registers. Lane
+// (g, l) of a result holds s-node l and the t-nodes (t_1 = v, t_2 = g), v = 0..3,
+// which is the operand layout of the product with X that follows: Delta never
+// leaves the registers. 64^3 nodes, R = 6, n = 100, r = 16: 230 ms, of which the
+// matrix instructions issue for 79 ms (7 of 64 cycles per 4 curves and 256 pairs);
+// the rest is the latency of two wavefronts per SIMD: the diagonal terms (about
+// 50 ms), the rows of weights (50 ms, a gather of 64 rows per instruction) and
+// curves missed in L2. With the responses on the vector units from LDS, the
+// diagonal terms by LDS passes with barriers and a solve per pair: 1166 ms.
+template <int d, int NCB, bool STORE>
+__global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
+  constexpr int F = d + 1, NT = 2 * d + 1, NV = mfma_nv<d>();
+  constexpr int k1 = d - 2, k2 = d - 1;
+  extern __shared__ double sm[];
+  const CovGeo &g = A.g;
+  const int n = g.n, R1 = g.R[k1], R2 = g.R[k2], M1 = g.M[k1], M2 = g.M[k2];
+  const int R0 = d == 3 ? g.R[0] : 0, M0 = d == 3 ? g.M[0] : 1;
+  const int kp = min(MKC, (n + 7) / 8 * 8);
+  const int nch = (n + MKC - 1) / MKC;
+  const int hw = 8 + 2 * R2;  // p_2 span of the s-set
+  double *Zs = sm;            // [F][kp][32], the halves of a row swapped where curve / 2 is odd
+  const int zsz = max(F * kp * 32, 8 * NCB * 256);
+  double *H2 = sm + zsz;      // [2][hw][NV][16 (s_1, t_1)]
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 15, gq = (tid & 63) >> 4;
+  // s-set of this workgroup; consecutive workgroups of an XCD are neighbours
+  int s0 = 0, s1a, s2a;
+  {
+    const int n1 = (M1 + 3) / 4, n2 = (M2 + 7) / 8;
+    const int nwg = int(gridDim.x), per = nwg / 8;
+    int id = int(blockIdx.x);
+    if (id < per * 8) id = (id % 8) * per + id / 8;
+    s2a = (id % n2) * 8;
+    id /= n2;
+    s1a = (id % n1) * 4;
+    s0 = id / n1;
+  }
+  const int64_t st0 = d == 3 ? g.stride[0] : 0, st1 = g.stride[k1];
+  auto node_of = [&](int x0, int x1, int x2) { return int64_t(x0) * st0 + int64_t(x1) * st1 + x2; };
+  // this wavefront's s-block and this lane's s-node
+  const int sb = wave & 1;
+  const int xs1 = s1a + (l >> 2), xs2 = s2a + 4 * sb + (l & 3);
+  const bool sok = xs1 < M1 && xs2 < M2;
+  const int xs1c = min(xs1, M1 - 1), xs2c = min(xs2, M2 - 1);
+  double sq[2 + d];
+  {
+    const double *n1 = g.nd[k1] + xs1c * 3, *n2 = g.nd[k2] + xs2c * 3;
+    sq[0] = n1[0] * n2[0];
+    sq[1] = n1[1] + n2[1];
+    sq[2 + k1] = n1[2];
+    sq[2 + k2] = n2[2];
+    if constexpr (d == 3) {
+      const double *n0 = g.nd[0] + s0 * 3;
+      sq[0] *= n0[0];
+      sq[1] += n0[1];
+      sq[2] = n0[2];
+    }
+  }
+  const int nT1 = (M1 + 3) / 4, nT2 = (M2 + 3) / 4, nk2 = (n + 1) / 2;
+  auto load_zs = [&](int ch) {
+    const int q0 = ch * (MKC / 2), kp2 = kp / 2;
+    const int64_t ti = (int64_t(s0) * nT1 + s1a / 4) * nT2 + s2a / 4;
+    for (int e = tid; e < 2 * F * kp2 * 32; e += MT) {
+      const int i = e & 31, r = e >> 5, q = r % kp2, fb = r / kp2, f = fb % F, b = fb / F;
+      const bool ok = s2a / 4 + b < nT2 && q0 + q < nk2;
+      const double v = ok ? A.Zn[(((ti + b) * F + f) * nk2 + q0 + q) * 32 + i] : 0.0;
+      Zs[(f * kp + 2 * q + (i & 1)) * 32 + ((16 * b + (i >> 1)) ^ (16 * (q & 1)))] = v;
+    }
+  };
+  if (nch == 1) load_zs(0);
+
+  f64x4 oacc[NCB];
+#pragma unroll
+  for (int c = 0; c < NCB; ++c) oacc[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+
+  const int t0lo = d == 3 ? max(0, s0 - 2 * R0) : 0, t0hi = d == 3 ? min(M0 - 1, s0 + 2 * R0) : 0;
+  // the t-tiles of coordinate 1 in an order by their number modulo the reach, so
+  // that the workgroups of an XCD, whose reaches overlap, take the same tile at
+  // about the same time and find its curves in their L2
+  const int T1h = (2 * R1 + 3) / 4, T1n = 2 * T1h + 1, T1lo = s1a / 4 - T1h;
+  const int T2lo = max(0, s2a - 2 * R2) / 4, T2hi = min(M2 - 1, s2a + 7 + 2 * R2) / 4;
+  const int p2lo = max(s2a - R2, 0), np2 = min(s2a + 7 + R2, M2 - 1) - p2lo + 1;
+  const int64_t plane = int64_t(M1) * M2;
+  const double iH1 = 1.0 / g.H[k1], iH2 = 1.0 / g.H[k2];
+  // this lane's place in the product over p_2: its value for lane (t_2; s_1, s_2) is in lane (s_1; t_2, s_2)
+  const int perm = (((tid >> 2) & 3) * 16 + ((tid >> 4) & 3) * 4 + (tid & 3)) * 4;
+  int buf = 0;
+  for (int t0 = t0lo; t0 <= t0hi; ++t0)
+    for (int k = 0; k < T1n; ++k) {
+      int T1 = k - (T1lo % T1n + T1n) % T1n;
+      T1 = T1lo + (T1 < 0 ? T1 + T1n : T1);
+      const int t1a = 4 * T1;
+      if (T1 < 0 || t1a >= M1) continue;
+      // ---- the diagonal terms summed over p_0 and p_1
+      double *Hb = H2 + buf * hw * NV * 16;
+      buf ^= 1;
+      const bool any = min(s1a, t1a) + 3 + R1 >= max(s1a, t1a) - R1;  // some shared p_1
+      if (any) {
+        const double *Hg = d == 3 ? A.Hs + int64_t(s0 * (4 * R0 + 1) + t0 - s0 + 2 * R0) * 3 * plane : A.Hs;
+        // rows s_1 + 4 t_1 (lane l of the first operand), columns p_2: one
+        // variant and 16 columns per task
+        const int ct = (np2 + 15) / 16;
+        const int lo = max(max(s1a, t1a) - R1, 0), hi = min(min(s1a, t1a) + 3 + R1, M1 - 1);
+        const int s1 = s1a + (l & 3), t1 = t1a + (l >> 2);
+        const int plo = max(s1, t1) - R1, phi = min(s1, t1) + R1;
+        for (int task = wave; task < NV * ct; task += 8) {
+          const int v = task % NV, col = 16 * (task / NV) + l;
+          const double *y = Hg + (v < 3 ? 0 : v - 2) * plane + p2lo + min(col, np2 - 1);
+          f64x4 h = {0.0, 0.0, 0.0, 0.0};
+          for (int p4 = lo; p4 <= hi; p4 += 4) {
+            const int p = p4 + gq;
+            const double us = double(p - s1) * iH1, vt = double(p - t1) * iH1;
+            const bool in = p <= hi && p >= plo && p <= phi;
+            double f = in ? fmax(1.0 - us * us, 0.0) * fmax(1.0 - vt * vt, 0.0) : 0.0;
+            if (v == 1) f *= us;
+            if (v == 2) f *= vt;
+            h = __builtin_amdgcn_mfma_f64_16x16x4f64(f, y[int64_t(min(p, hi)) * M2], h, 0, 0, 0);
+          }
+          if (col < np2) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) Hb[(col * NV + v) * 16 + gq + 4 * i] = h[i];
+          }
+        }
+      }
+      __syncthreads();
+      for (int T20 = T2lo; T20 <= T2hi; T20 += 4) {
+        const int T2 = T20 + (wave >> 1);
+        const int t2a = 4 * T2, s2b = s2a + 4 * sb;
+        const bool work = T2 <= T2hi && t2a - (s2b + 3) <= 2 * R2 && s2b - (t2a + 3) <= 2 * R2;
+        if (nch == 1 && !work) continue;
+        f64x4 acc[NT];
+#pragma unroll
+        for (int q = 0; q < NT; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+        // pair classes and the t-nodes' factors, requested ahead of the products
+        const int xt2 = t2a + gq, xt2c = min(xt2, M2 - 1);
+        int c1[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          c1[v] = g.cls[k1][xs1c * (4 * R1 + 1) + min(max(min(t1a + v, M1 - 1) - xs1c, -2 * R1), 2 * R1) + 2 * R1];
+        const int c2 = g.cls[k2][xs2c * (4 * R2 + 1) + min(max(xt2c - xs2c, -2 * R2), 2 * R2) + 2 * R2];
+        const double *n2 = g.nd[k2] + xt2c * 3;
+        const double tS2 = n2[0], tA2 = n2[1], tB2 = n2[2];
+        const int64_t tt = (int64_t(t0) * nT1 + T1) * nT2 + T2;
+        for (int ch = 0; ch < nch; ++ch) {
+          if (nch > 1) {
+            __syncthreads();
+            load_zs(ch);
+            __syncthreads();
+          }
+          if (!work) continue;
+          const int cn = min(MKC, n - ch * MKC);
+          const double2 *zt = reinterpret_cast<const double2 *>(A.Zn) + (tt * F * nk2 + ch * (MKC / 2) + gq) * 16 + l;
+          const int left = nk2 - ch * (MKC / 2) - gq;  // pairs of curves from this lane's first on
+          auto fetch = [&](int k, double2 (&v)[F]) {
+#pragma unroll
+            for (int f = 0; f < F; ++f)
+              v[f] = k / 2 < left ? zt[(int64_t(f) * nk2 + k / 2) * 16] : make_double2(0.0, 0.0);
+          };
+          const double *zs = Zs + 2 * gq * 32 + ((16 * sb + l) ^ (16 * (gq & 1)));
+          auto mult = [&](int k, const double2 (&v)[F]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              double z[F], a[F];
+#pragma unroll
+              for (int f = 0; f < F; ++f) {
+                z[f] = zs[(f * kp + k + u) * 32];
+                a[f] = u ? v[f].y : v[f].x;
+              }
+              acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], z[0], acc[0], 0, 0, 0);
+#pragma unroll
+              for (int q = 0; q < d; ++q) {
+                acc[1 + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], z[1 + q], acc[1 + q], 0, 0, 0);
+                acc[1 + d + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1 + q], z[0], acc[1 + d + q], 0, 0, 0);
+              }
+            }
+          };
+          double2 va[F], vb[F];
+          fetch(0, va);
+          for (int k = 0; k < cn; k += 16) {
+            fetch(k + 8, vb);
+            mult(k, va);
+            if (k + 8 >= cn) break;
+            fetch(k + 16, va);
+            mult(k + 8, vb);
+          }
+        }
+        if (!work) continue;
+        const int c0 = d == 3 ? g.cls[0][s0 * (4 * R0 + 1) + t0 - s0 + 2 * R0] : 0;
+        const double sg0 = c0 & 1 ? -1.0 : 1.0;
+        double low[4], w[4][NT];
+        bool inb[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int xt1 = t1a + v;
+          inb[v] = sok && xt1 < M1 && xt2 < M2 && abs(xt2 - xs2) <= 2 * R2 && abs(xt1 - xs1) <= 2 * R1;
+          // pairs outside the band or the grid read the row of some class; their Delta is 0
+          const int64_t e = (int64_t(d == 3 ? c0 >> 1 : 0) * g.ncls[k1] + (max(c1[v], 0) >> 1)) * g.ncls[k2] +
+                            (max(c2, 0) >> 1);
+          const double *row = g.rows + (inb[v] ? e : 0) * 8;
+#pragma unroll
+          for (int q = 0; q < NT; ++q) w[v][q] = row[q];
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double *n1 = g.nd[k1] + min(t1a + v, M1 - 1) * 3;
+          double tS = n1[0] * tS2, tA = n1[1] + tA2;
+          double x = sq[2 + k1] * acc[1 + k1][v] + n1[2] * acc[1 + d + k1][v] +
+                     sq[2 + k2] * acc[1 + k2][v] + tB2 * acc[1 + d + k2][v];
+          if constexpr (d == 3) {
+            const double *n0 = g.nd[0] + t0 * 3;
+            tS *= n0[0];
+            tA += n0[1];
+            x += sq[2] * acc[1][v] + n0[2] * acc[1 + d][v];
+          }
+          low[v] = (acc[0][v] * (1.0 + (sq[1] + tA)) - x) * g.inv_n * (sq[0] * tS);
+        }
+        // ---- 2. the diagonal terms summed over p_2, a matrix product of the
+        // sums over p_0 and p_1 (rows s_1 + 4 t_1) with the factors of
+        // coordinate 2 (columns s_2 + 4 t_2, here in lane l)
+        if (any) {
+          const int sc = s2b + (l & 3), tc = t2a + (l >> 2);
+          const int lo = max(max(s2b, t2a) - R2, 0), hi = min(min(s2b, t2a) + 3 + R2, M2 - 1);
+          const int plo = max(sc, tc) - R2, phi = min(sc, tc) + R2;
+          f64x4 cr[NT];
+#pragma unroll
+          for (int q = 0; q < NT; ++q) cr[q] = f64x4{0.0, 0.0, 0.0, 0.0};
+          for (int p4 = lo; p4 <= hi; p4 += 4) {
+            const int p = p4 + gq;
+            const double us = double(p - sc) * iH2, vt = double(p - tc) * iH2;
+            const bool in = p <= hi && p >= plo && p <= phi;
+            const double f = in ? fmax(1.0 - us * us, 0.0) * fmax(1.0 - vt * vt, 0.0) : 0.0;
+            const double *hp = Hb + (min(p, hi) - p2lo) * NV * 16 + l;
+            const double h0 = hp[0], h1 = hp[16], h2 = hp[32];
+            cr[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(h0, f, cr[0], 0, 0, 0);
+            cr[1 + k1] = __builtin_amdgcn_mfma_f64_16x16x4f64(h1, f, cr[1 + k1], 0, 0, 0);
+            cr[1 + d + k1] = __builtin_amdgcn_mfma_f64_16x16x4f64(h2, f, cr[1 + d + k1], 0, 0, 0);
+            cr[1 + k2] = __builtin_amdgcn_mfma_f64_16x16x4f64(h0, f * us, cr[1 + k2], 0, 0, 0);
+            cr[1 + d + k2] = __builtin_amdgcn_mfma_f64_16x16x4f64(h0, f * vt, cr[1 + d + k2], 0, 0, 0);
+            if constexpr (d == 3) {
+              cr[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(hp[48], f, cr[1], 0, 0, 0);
+              cr[1 + d] = __builtin_amdgcn_mfma_f64_16x16x4f64(hp[64], f, cr[1 + d], 0, 0, 0);
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < NT; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const double c = cr[q][v];
+              acc[q][v] -= __hiloint2double(__builtin_amdgcn_ds_bpermute(perm, __double2hiint(c)),
+                                               __builtin_amdgcn_ds_bpermute(perm, __double2loint(c)));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // ---- 3. Delta
+        double delta[4];
+        const double sg2 = c2 & 1 ? -1.0 : 1.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const double sg1 = c1[v] & 1 ? -1.0 : 1.0;
+          double dv = w[v][0] * acc[0][v];
+          dv = fma(sg1, w[v][1 + k1] * acc[1 + k1][v] + w[v][1 + d + k1] * acc[1 + d + k1][v], dv);
+          dv = fma(sg2, w[v][1 + k2] * acc[1 + k2][v] + w[v][1 + d + k2] * acc[1 + d + k2][v], dv);
+          if constexpr (d == 3) dv = fma(sg0, w[v][1] * acc[1][v] + w[v][1 + d] * acc[1 + d][v], dv);
+          delta[v] = inb[v] ? dv * g.inv_n - low[v] : 0.0;
+        }
+        // ---- 4. output
+        if constexpr (STORE) {
+          constexpr int TB = tile_ext<d>();
+          if (sok) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const int xt1 = t1a + v;
+              if (xt1 >= M1 || xt2 >= M2) continue;
+              const int a1 = xs1 / TB, a2 = xs2 / TB;
+              int64_t tile = int64_t(a1) * g.nt[k2] + a2;
+              int slot = (xt1 / TB - a1 + g.span[k1]) * (2 * g.span[k2] + 1) + (xt2 / TB - a2 + g.span[k2]);
+              int sl = (xs1 % TB) * TB + xs2 % TB, tl = (xt1 % TB) * TB + xt2 % TB;
+              if constexpr (d == 3) {
+                const int a0 = s0 / TB;
+                tile += int64_t(a0) * g.nt[1] * g.nt[2];
+                slot += (t0 / TB - a0 + g.span[0]) * (2 * g.span[1] + 1) * (2 * g.span[2] + 1);
+                sl += (s0 % TB) * TB * TB;
+                tl += (t0 % TB) * TB * TB;
+              }
+              A.band[((tile * g.nslot + slot) * 64 + sl) * 64 + tl] = delta[v];
+            }
+          }
+        } else {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int xt1 = t1a + v;
+            const bool tok = xt1 < M1 && xt2 < M2;
+            const int64_t q = node_of(t0, min(xt1, M1 - 1), min(xt2, M2 - 1));
+#pragma unroll
+            for (int c = 0; c < NCB; ++c) {
+              const int col = 16 * c + l;
+              const double xv = A.X[q * A.r + A.c0 + min(col, A.nc - 1)];
+              oacc[c] =
+                  __builtin_amdgcn_mfma_f64_16x16x4f64(tok && col < A.nc ? xv : 0.0, delta[v], oacc[c], 0, 0, 0);
+            }
+          }
+        }
+      }
+    }
+  if constexpr (!STORE) {
+    // the wavefronts' sums added in order: [wave / 2][s-block][c][row (column of X)][s]
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < NCB; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) sm[((wave * NCB + c) * 16 + gq + 4 * v) * 16 + l] = oacc[c][v];
+    __syncthreads();
+    for (int e = tid; e < 2 * NCB * 256; e += MT) {
+      const int col = e % (NCB * 16), sn = e / (NCB * 16);  // column of X, s-node 0..31
+      const int b = sn >> 4, c = col >> 4;
+      const int x1 = s1a + ((sn >> 2) & 3), x2 = s2a + 4 * b + (sn & 3);
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) v += sm[(((2 * w + b) * NCB + c) * 16 + (col & 15)) * 16 + (sn & 15)];
+      if (x1 < M1 && x2 < M2 && col < A.nc) A.out[node_of(s0, x1, x2) * A.r + A.c0 + col] += v;
+    }
+  }
+}
+
+__global__ void k_zero_f64(double *p, int64_t n) {
+  for (int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += int64_t(gridDim.x) * blockDim.x)
+    p[i] = 0.0;
 }
 
 // Product with the stored band blocks.
@@ -916,15 +1160,19 @@ CovGeo make_geo(const fpca_covop_s *op) {
     g.tb[k] = op->tb[k];
     g.nt[k] = op->nt[k];
     g.span[k] = op->span[k];
+    g.H[k] = op->H[k];
+    g.cls[k] = op->cls[k];
+    g.ncls[k] = op->ncls[k];
+    g.nd[k] = op->tab + op->tab_nd[k];
   }
+  g.rows = op->rows;
   g.nslot = op->nslot;
   return g;
 }
 
 unsigned nb256(int64_t n) { return unsigned((n + 255) / 256); }
 
-template <int d>
-int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *out) {
+BandArgs band_args(const fpca_covop_s *op, const double *X, int r, double *out) {
   BandArgs A{};
   A.g = make_geo(op);
   A.Zn = op->Zn;
@@ -933,17 +1181,47 @@ int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *ou
   A.r = r;
   A.out = out;
   A.band = op->band;
-  const size_t lds = size_t(band_lds_doubles<d>()) * 8;
-  if (store) {
-    FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band<d, true>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-    hipLaunchKernelGGL((k_band<d, true>), dim3(unsigned(op->n_stiles)), dim3(BT), lds, op->ctx->stream, A);
-  } else {
-    FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band<d, false>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-    hipLaunchKernelGGL((k_band<d, false>), dim3(unsigned(op->n_stiles)), dim3(BT), lds, op->ctx->stream, A);
-  }
+  A.Hs = op->d == 3 ? op->hsum : op->Y2;
+  return A;
+}
+
+template <bool STORE>
+int launch_band1(fpca_covop_s *op, const double *X, int r, double *out) {
+  const BandArgs A = band_args(op, X, r, out);
+  FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band<STORE>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, B1_LDS * 8));
+  hipLaunchKernelGGL((k_band<STORE>), dim3(unsigned(op->n_stiles)), dim3(BT), B1_LDS * 8, op->ctx->stream, A);
   FPCA_LAUNCH_CHECK("covop band");
+  return FPCA_OK;
+}
+
+template <int d, int NCB, bool STORE>
+int launch_band_mfma(fpca_covop_s *op, const BandArgs &A) {
+  const size_t lds = band_mfma_lds(d, int(op->n), op->R[d - 1], NCB);
+  const int64_t nwg = (d == 3 ? op->M[0] : 1) * int64_t((op->M[d - 2] + 3) / 4) * ((op->M[d - 1] + 7) / 8);
+  if (nwg > 0x7fffffffLL) return set_error(FPCA_ERR_UNSUPPORTED, "covariance operator: too many nodes");
+  FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+  hipLaunchKernelGGL((k_band_mfma<d, NCB, STORE>), dim3(unsigned(nwg)), dim3(MT), lds, op->ctx->stream, A);
+  FPCA_LAUNCH_CHECK("covop band");
+  return FPCA_OK;
+}
+
+// d >= 2: at most 32 columns of X per launch (their sums stay in registers).
+template <int d>
+int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *out) {
+  BandArgs A = band_args(op, X, r, out);
+  if (store) {
+    const int64_t n = op->n_stiles * op->nslot * 4096;
+    hipLaunchKernelGGL(k_zero_f64, dim3(unsigned(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0,
+                       op->ctx->stream, op->band, n);
+    FPCA_LAUNCH_CHECK("covop band zero");
+    return launch_band_mfma<d, 1, true>(op, A);
+  }
+  for (A.c0 = 0; A.c0 < r; A.c0 += 32) {
+    A.nc = std::min(32, r - A.c0);
+    if (int rc = A.nc <= 16 ? launch_band_mfma<d, 1, false>(op, A) : launch_band_mfma<d, 2, false>(op, A)) return rc;
+  }
   return FPCA_OK;
 }
 
@@ -965,7 +1243,7 @@ int launch_band_apply(fpca_covop_s *op, const double *X, int r, double *out) {
 
 int band_dispatch(fpca_covop_s *op, bool store, const double *X, int r, double *out) {
   switch (op->d) {
-    case 1: return launch_band<1>(op, store, X, r, out);
+    case 1: return store ? launch_band1<true>(op, X, r, out) : launch_band1<false>(op, X, r, out);
     case 2: return launch_band<2>(op, store, X, r, out);
     default: return launch_band<3>(op, store, X, r, out);
   }
@@ -1084,6 +1362,11 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
     htab.insert(htab.end(), W.begin(), W.end());
     op->tab_E[k] = int64_t(htab.size());
     htab.insert(htab.end(), E.begin(), E.end());
+    op->tab_nd[k] = int64_t(htab.size());
+    for (int x = 0; x < M; ++x) {
+      const double a = W[x * 3 + 1] / W[x * 3], v = W[x * 3 + 2] / W[x * 3] - a * a;
+      htab.insert(htab.end(), {1.0 / W[x * 3], a * a / v, a / v});
+    }
     const int TB = d == 1 ? 64 : (d == 2 ? 8 : 4);
     op->tb[k] = TB;
     op->nt[k] = (M + TB - 1) / TB;
@@ -1096,11 +1379,54 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
     op->nslot *= 2 * op->span[k] + 1;
   }
   op->lr_blocks = (P + 63) / 64;
+  // d >= 2: pair classes of every coordinate: one per offset for the pairs R
+  // or more from the border, then one per pair (s, t) near the left border;
+  // pairs near the right border alone are those mirrored (u and v change sign,
+  // and with them the entries of the row that go with them). 64^3, R = 6: 175
+  // classes, 343 MB of rows; at R = 28 on d = 2 up to 550 MB.
+  std::vector<int> itab;
+  int64_t cls_off[3] = {0, 0, 0}, rep_off[3] = {0, 0, 0}, nrows = 0;
+  if (d >= 2) {
+    nrows = 1;
+    for (int k = 0; k < d; ++k) {
+      const int M = op->M[k], R = op->R[k], wd = 4 * R + 1;
+      std::vector<int> rep(wd, -1), cls(size_t(M) * wd, 0);
+      for (int x = 0; x < M; ++x)
+        for (int j = 0; j < wd; ++j) {
+          const int t = x + j - 2 * R;
+          if (t < 0 || t >= M) continue;
+          if (std::min(x, t) >= R && std::max(x, t) <= M - 1 - R) {
+            rep[j] = x * wd + j;
+            cls[size_t(x) * wd + j] = 2 * j;
+          } else if (std::min(x, t) < R) {
+            cls[size_t(x) * wd + j] = 2 * int(rep.size());
+            rep.push_back(x * wd + j);
+          }
+        }
+      for (int x = 0; x < M; ++x)
+        for (int j = 0; j < wd; ++j) {
+          const int t = x + j - 2 * R;
+          if (t < 0 || t >= M || std::min(x, t) < R || std::max(x, t) <= M - 1 - R) continue;
+          cls[size_t(x) * wd + j] = cls[size_t(M - 1 - x) * wd + (4 * R - j)] + 1;
+        }
+      cls_off[k] = int64_t(itab.size());
+      itab.insert(itab.end(), cls.begin(), cls.end());
+      rep_off[k] = int64_t(itab.size());
+      itab.insert(itab.end(), rep.begin(), rep.end());
+      op->ncls[k] = int(rep.size());
+      nrows *= op->ncls[k];
+    }
+  }
+  const int64_t hs_n = d == 3 ? int64_t(op->M[0]) * (4 * op->R[0] + 1) * 3 * op->M[1] * op->M[2] : 0;
   const int F = d + 1;
-  const size_t bytes_main = carve_bytes(size_t(P) * F * n, 8) + 2 * carve_bytes(size_t(P) * n, 8) +
+  // filtered curves: node-major for d = 1, in blocks of 16 nodes above
+  const int64_t nblk16 = d == 1 ? 0 : (d == 3 ? op->M[0] : 1) * int64_t((op->M[d - 2] + 3) / 4) * ((op->M[d - 1] + 3) / 4);
+  const size_t zn_n = d == 1 ? size_t(P) * F * n : size_t(nblk16) * F * size_t((n + 1) / 2) * 32;
+  const size_t bytes_main = carve_bytes(zn_n, 8) + 2 * carve_bytes(size_t(P) * n, 8) +
                             2 * carve_bytes(P, 8) + carve_bytes(htab.size(), 8) +
                             carve_bytes(size_t(op->lr_blocks) * (2 * n + 1) * 64, 8) +
-                            carve_bytes(size_t(2 * n + 1) * 64, 8);
+                            carve_bytes(size_t(2 * n + 1) * 64, 8) + carve_bytes(itab.size(), 4) +
+                            carve_bytes(size_t(nrows) * 8, 8) + carve_bytes(size_t(hs_n), 8);
   const size_t bytes_band =
       mode == FPCA_COVOP_STORE_BAND ? carve_bytes(size_t(op->n_stiles) * op->nslot * 4096, 8) : 0;
   auto fail = [&](int rc) {
@@ -1113,7 +1439,7 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   {
     size_t free_b = 0, total_b = 0;
     FPCA_HIP(hipMemGetInfo(&free_b, &total_b));
-    const size_t temp = carve_bytes(size_t(P) * F * n, 8) + carve_bytes(size_t(P) * n, 8);
+    const size_t temp = carve_bytes(size_t(P) * F * n, 8) * (d == 1 ? 1 : 2) + carve_bytes(size_t(P) * n, 8);
     if (bytes_main + bytes_band + temp > free_b)
       return fail(set_error(FPCA_ERR_WORKSPACE, "covariance operator needs %zu bytes, %zu free",
                             bytes_main + bytes_band + temp, free_b));
@@ -1121,7 +1447,7 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   void *mem = nullptr;
   if (hipMalloc(&mem, bytes_main) != hipSuccess) return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
   Carver cv{static_cast<char *>(mem), 0, bytes_main};
-  op->Zn = cv.take<double>(size_t(P) * F * n);
+  op->Zn = cv.take<double>(zn_n);
   op->Ln = cv.take<double>(size_t(P) * n);
   op->Bn = cv.take<double>(size_t(P) * n);
   op->Y2 = cv.take<double>(P);
@@ -1129,18 +1455,33 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   op->tab = cv.take<double>(htab.size());
   op->lr_part = cv.take<double>(size_t(op->lr_blocks) * (2 * n + 1) * 64);
   op->lr_tot = cv.take<double>(size_t(2 * n + 1) * 64);
+  int *ditab = nullptr;
+  double *rows_tab = nullptr;
+  if (d >= 2) {
+    ditab = cv.take<int>(itab.size());
+    rows_tab = cv.take<double>(size_t(nrows) * 8);
+    for (int k = 0; k < d; ++k) op->cls[k] = ditab + cls_off[k];
+    op->rows = rows_tab;
+    if (hs_n) op->hsum = cv.take<double>(size_t(hs_n));
+  }
   if (bytes_band && hipMalloc(reinterpret_cast<void **>(&op->band), bytes_band) != hipSuccess)
     return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc of the band failed"));
   hipStream_t s = ctx->stream;
   if (hipMemcpyAsync(op->tab, htab.data(), htab.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
+      (ditab && hipMemcpyAsync(ditab, itab.data(), itab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) ||
       hipMemcpyAsync(op->mu, mu, size_t(P) * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
     return fail(set_error(FPCA_ERR_DEVICE, "copy failed"));
-  // temporaries: the transposed curves and a second family buffer
-  double *Yn = nullptr, *tmp = nullptr;
+  // temporaries: the transposed curves and the family buffers
+  double *Yn = nullptr, *tmp = nullptr, *last = op->Zn;
   if (hipMalloc(reinterpret_cast<void **>(&Yn), size_t(P) * n * 8) != hipSuccess)
     return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
   if (hipMalloc(reinterpret_cast<void **>(&tmp), size_t(P) * F * n * 8) != hipSuccess) {
     (void)hipFree(Yn);
+    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
+  }
+  if (d >= 2 && hipMalloc(reinterpret_cast<void **>(&last), size_t(P) * F * n * 8) != hipSuccess) {
+    (void)hipFree(Yn);
+    (void)hipFree(tmp);
     return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
   }
   const CovGeo g = make_geo(op);
@@ -1153,12 +1494,12 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
       break;
     }
     hipLaunchKernelGGL(k_sq, dim3(nb256(P)), dim3(256), 0, s, P, int(n), Yn, op->Y2);
-    // separable passes, last coordinate first; the last pass lands in Zn
+    // separable passes, last coordinate first; the last pass lands in `last`
     const double *in = Yn;
     int Fin = 1;
     for (int pass = 0; pass < d && rc == FPCA_OK; ++pass) {
       const int k = d - 1 - pass;
-      double *dst = ((d - 1 - pass) % 2 == 0) ? op->Zn : tmp;
+      double *dst = ((d - 1 - pass) % 2 == 0) ? last : tmp;
       FilterMap fm{};
       fm.nmap = 0;
       fm.fo[fm.nmap] = 0, fm.fi[fm.nmap] = 0, fm.e[fm.nmap] = 0, ++fm.nmap;
@@ -1170,10 +1511,26 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
       Fin = F;
     }
     if (rc != FPCA_OK) break;
-    hipLaunchKernelGGL(k_lr_prep, dim3(nb256(P * n)), dim3(256), 0, s, g, op->Zn, op->Ln, op->Bn);
+    hipLaunchKernelGGL(k_lr_prep, dim3(nb256(P * n)), dim3(256), 0, s, g, last, op->Ln, op->Bn);
+    if (d >= 2) hipLaunchKernelGGL(k_retile, dim3(unsigned(nblk16), unsigned(F)), dim3(256), 0, s, g, last, op->Zn);
     if (hipGetLastError() != hipSuccess) {
       rc = set_error(FPCA_ERR_DEVICE, "prep launch failed");
       break;
+    }
+    if (d >= 2) {
+      const int *rp[3] = {ditab + rep_off[0], ditab + rep_off[1], ditab + rep_off[2]};
+      if (hs_n)
+        hipLaunchKernelGGL(k_hsum, dim3(nb256(int64_t(op->M[1]) * op->M[2]) * unsigned(op->M[0] * (4 * op->R[0] + 1))),
+                           dim3(256), 0, s, g, op->Y2, op->hsum);
+      const dim3 wg(unsigned((nrows + 63) / 64));
+      if (d == 2)
+        hipLaunchKernelGGL(k_wtab<2>, wg, dim3(64), 0, s, g, nrows, rp[0], rp[1], rp[2], rows_tab);
+      else
+        hipLaunchKernelGGL(k_wtab<3>, wg, dim3(64), 0, s, g, nrows, rp[0], rp[1], rp[2], rows_tab);
+      if (hipGetLastError() != hipSuccess) {
+        rc = set_error(FPCA_ERR_DEVICE, "table launch failed");
+        break;
+      }
     }
     if (mode == FPCA_COVOP_STORE_BAND) rc = band_dispatch(op, true, nullptr, 0, nullptr);
   } while (false);
@@ -1181,6 +1538,7 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   const hipError_t e1 = hipStreamSynchronize(s);
   (void)hipFree(Yn);
   (void)hipFree(tmp);
+  if (last != op->Zn) (void)hipFree(last);
   if (rc != FPCA_OK) return fail(rc);
   if (e1 != hipSuccess) return fail(hip_fail(e1, "covariance operator set-up"));
   *op_out = op;

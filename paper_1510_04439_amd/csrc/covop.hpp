@@ -13,14 +13,22 @@ struct fpca_covop_s {
   int64_t n = 0;
   int mode = 0;
   // device data, all FP64, owned by the operator
-  double *Zn = nullptr;  // P x (d+1) x n: curves filtered by K, K u_0, .., K u_{d-1}
+  // curves filtered by K, K u_0, .., K u_{d-1}: P x (d+1) x n for d = 1, else in
+  // blocks of 16 nodes (k_retile)
+  double *Zn = nullptr;
   double *Ln = nullptr;  // P x n: local-linear smooth of each curve
   double *Bn = nullptr;  // P x n: the boundary part of Ln (zero in the interior)
   double *Y2 = nullptr;  // P: sum over curves of Y^2
   double *mu = nullptr;  // P: the mean
   double *tab = nullptr;  // per coordinate: taps K, u; window sums W; shared-node sums E
-  int64_t tab_K[3] = {0, 0, 0}, tab_U[3] = {0, 0, 0}, tab_W[3] = {0, 0, 0}, tab_E[3] = {0, 0, 0};
+  int64_t tab_K[3] = {0, 0, 0}, tab_U[3] = {0, 0, 0}, tab_W[3] = {0, 0, 0}, tab_E[3] = {0, 0, 0}, tab_nd[3] = {0, 0, 0};
   double *band = nullptr;  // stored band blocks (mode FPCA_COVOP_STORE_BAND)
+  // d >= 2 (see CovGeo): pair classes and rows of the inverse weight-moment
+  // matrices, and (d = 3) Y2 summed over p_0
+  const int *cls[3] = {nullptr, nullptr, nullptr};
+  int ncls[3] = {0, 0, 0};
+  const double *rows = nullptr;
+  double *hsum = nullptr;
   double *lr_part = nullptr;  // partial products of the low-rank apply
   double *lr_tot = nullptr;
   int64_t lr_blocks = 0;
@@ -29,7 +37,6 @@ struct fpca_covop_s {
   int span[3] = {0, 0, 0};  // band reach in tiles
   int64_t n_stiles = 0;
   int nslot = 1;
-  size_t band_lds = 0, apply_lds = 0;
 };
 
 namespace fpca {

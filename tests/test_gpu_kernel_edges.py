@@ -104,3 +104,39 @@ def test_smooth_mean_strips(torch, F, h, dt, M, R):
     x = np.stack(np.unravel_index(np.arange(P), M), 1) - np.array(np.unravel_index(bad, M))
     inside = np.all(np.abs(x) <= np.array(R), axis=1)
     assert np.array_equal(np.isnan(res[1][0]), inside | np.isnan(res[0][0]))
+
+
+@pytest.mark.parametrize("M,R,n,r", [((5, 9, 13), (2, 3, 2), 230, 40), ((7, 6, 21), (3, 2, 1), 3, 17),
+                                     ((13, 16, 14), (6, 1, 6), 104, 5), ((30, 33), (13, 14), 105, 33),
+                                     ((70, 12), (28, 3), 9, 16)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_covop_blocks(torch, F, h, M, R, n, r, mode):
+    """Blocks of 4 x 4 nodes cut by the grid, more curves than one LDS chunk and
+    odd counts, one to three launches of 32 columns, windows that leave no node
+    away from the border, the widest windows of d = 2 and 3: r columns of the
+    covariance, products of unit vectors."""
+    _say(f"covop blocks M={M} R={R} n={n} r={r} mode={mode}")
+    rng = np.random.default_rng(80 + n)
+    P = int(np.prod(M))
+    Y = 1.0 + rng.standard_normal((n, 3)) @ rng.standard_normal((3, P)) + 0.3 * rng.standard_normal((n, P))
+    mu = Y.mean(0)
+    hb = [(k + 0.45) / (m - 1) for k, m in zip(R, M)]
+    _, _, C, G = oracle.bin_common_grid(Y)
+    cols = np.sort(rng.choice(P, r, replace=False))
+    E = np.zeros((P, r))
+    E[cols, np.arange(r)] = 1.0
+    op = F.CovOp(h, F.Grid(M), dev(torch, Y), dev(torch, mu), hb, mode)
+    try:
+        out = torch.empty(P, r, dtype=torch.float64, device="cuda:0")
+        op.apply(dev(torch, E), out)
+        h.sync()
+        got = out.cpu().numpy()
+    finally:
+        op.close()
+    p = np.arange(P)
+    check = range(r) if len(M) == 2 else range(0, r, max(1, r // 5))
+    for j in check:
+        q = int(cols[j])
+        rb, _ = oracle.smooth_cov_raw(M, hb, C, G, np.concatenate([p * P + q, q * P + p]))
+        ref = 0.5 * (rb[:P] + rb[P:]) - mu * mu[q]
+        assert normwise_rel(got[:, j], ref) < 1e-10, j
