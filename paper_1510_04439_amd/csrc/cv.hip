@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "staged.hpp"
 #include "tiled.hpp"
 
 namespace fpca {
@@ -117,6 +118,30 @@ int cv_general(fpca_context *ctx, const fpca_cv_data &ds, int dtype, int n_folds
   return FPCA_OK;
 }
 
+// One dataset through the staged smoother, several jobs per launch; scores land
+// in scores_h[(hi * n_folds + f)].
+template <typename T>
+int cv_staged(fpca_context *ctx, const fpca_cv_data &ds, int n_folds, int n_h, const double *bw, double *scores_h) {
+  const int64_t PP = grid_P(ds.grid) * grid_P(ds.grid);
+  const T *C = static_cast<const T *>(ds.C);
+  const T *G = static_cast<const T *>(ds.G);
+  const T *Q = static_cast<const T *>(ds.Q);
+  std::vector<StagedJob> jobs;
+  jobs.reserve(size_t(n_h) * n_folds);
+  for (int hi = 0; hi < n_h; ++hi)
+    for (int f = 0; f < n_folds; ++f) {
+      const int64_t o = (int64_t(f) + 1) * PP;
+      jobs.push_back(StagedJob{C, C + o, G, G + o, Q + o, G + o, C + o, 0.0, bw + int64_t(hi) * ds.grid.d});
+    }
+  const size_t bytes = sizeof(double) * jobs.size();
+  if (int rc = ws3_reserve(ctx, bytes)) return rc;
+  double *sc = static_cast<double *>(ctx->ws3);
+  if (int rc = staged_scores<T>(ctx, &ds.grid, jobs, sc)) return rc;
+  FPCA_HIP(hipStreamSynchronize(ctx->stream));
+  FPCA_HIP(hipMemcpy(scores_h, sc, bytes, hipMemcpyDeviceToHost));
+  return FPCA_OK;
+}
+
 // Waits for the stream and turns a stalled queue wait into an error.
 int finish_and_check(fpca_context *ctx) {
   FPCA_HIP(hipMemcpyAsync(ctx->h_flags, ctx->d_flags, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
@@ -134,6 +159,13 @@ template <typename T>
 int cv_impl(fpca_context *ctx, int dtype, int n_data, const fpca_cv_data *data, int n_folds, int n_h,
             const double *bw, double *scores_h) {
   const int d = data[0].grid.d;
+  bool all_staged = ctx->engine == FPCA_ENGINE_AUTO;
+  for (int a = 0; a < n_data; ++a) all_staged = all_staged && staged_supported(&data[a].grid);
+  if (all_staged) {
+    for (int a = 0; a < n_data; ++a)
+      if (int rc = cv_staged<T>(ctx, data[a], n_folds, n_h, bw, scores_h + int64_t(a) * n_h * n_folds)) return rc;
+    return FPCA_OK;
+  }
   bool all_tiled = ctx->engine != FPCA_ENGINE_PASSES;
   for (int a = 0; a < n_data; ++a) all_tiled = all_tiled && tiled_supported(&data[a].grid);
   if (!all_tiled) {

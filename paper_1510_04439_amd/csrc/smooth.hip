@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "common.hpp"
+#include "staged.hpp"
 #include "tiled.hpp"
 #include "wls.hpp"
 
@@ -756,6 +757,15 @@ int smooth_cov_impl(fpca_context *ctx, const fpca_grid *grid, const T *C, double
   if constexpr (sizeof(T) == 4) {
     if (!C && smooth_cov_fused_d2_supported(grid, bw))
       return smooth_cov_fused_d2(ctx, grid, c_uniform, G, bw, mu, gamma, status);
+  }
+  if (ctx->engine == FPCA_ENGINE_AUTO && staged_supported(grid)) {
+    StagedJob j{};
+    j.Ca = C;
+    j.Ga = G;
+    j.c0 = c_uniform;
+    j.h = bw;
+    if (int rc = staged_smooth<T>(ctx, grid, j, gamma, status)) return rc;
+    return assemble<T>(ctx, P, gamma, mu, grid->mask);
   }
   if (use_queue_engine(ctx, grid)) {
     // the persistent-queue engine: FP64 moments kept on chip between passes

@@ -1,0 +1,631 @@
+// Covariance smoother for general pair weights (eq. 2.4 on the 2d-dimensional
+// grid, any C; d = 2 and 3) in three kernels, and its cross-validation scores.
+//
+// The moments of the local-linear fit factor over the 2d coordinates, so they
+// are formed by 1-D passes with the taps (1-u^2) u^e, e = 0..2, in FP64:
+//   k_stage_t   t_d .. t_1 of every s-row: X (9 arrays for d = 2, 14 for d = 3:
+//               C with t-degree <= 2, G with t-degree <= 1);
+//   k_stage_s   s_d .. s_2: Y (14 and 27 arrays);
+//   k_stage_w   s_1, the final moments of a block of nodes into LDS, then one
+//               lane per node solves its system (wls_b0).
+// In every pass a thread holds a whole line of at most N values in registers and
+// forms all its outputs from them: an input is read once, no index is computed
+// per tap and no tap is multiplied outside the window; taps have the same index
+// in every lane and come through scalar loads. Between passes of a stage a line
+// changes direction through LDS. N (16, 24, 32, 40) is the longest coordinate
+// rounded up.
+//
+// Bound: the FP64 arrays between the stages, 184 and 328 bytes written per node.
+// C and G are symmetric, so cross-validation needs the nodes s_1 <= t_1 only: the
+// stages skip the rows and columns that no such node reads.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+#include <type_traits>
+
+#include "common.hpp"
+#include "staged.hpp"
+#include "wls.hpp"
+
+namespace fpca {
+namespace {
+
+constexpr int SB_MAX = 8;    // jobs per launch (blockIdx.z)
+constexpr int SC_TILE = 32;  // score tile
+constexpr int SC_WG = 512;   // score workgroups per job, at most
+
+struct SJob {
+  const void *Ca, *Cb, *Ga, *Gb, *Qf, *Gf, *Cf;
+  double c0;
+  double h[3];
+  int R[3];
+  double *taps;  // [coordinate][e][TAPW], centred
+  double *X, *Y;
+  void *b0;  // P x P of T
+  double *part;
+};
+struct SBatch {
+  int M[3];
+  int P, PR;  // nodes, s-positions per s_1 index
+  int cv;
+  const uint8_t *mask;
+  int8_t *status;
+  SJob j[SB_MAX];
+};
+
+constexpr int NMAX = 40;  // longest coordinate
+constexpr int TAPW = 2 * NMAX + 1;
+typedef const __attribute__((address_space(4))) double CTap;
+__device__ inline CTap *taps_of(const SJob &jb, int k, int e) { return (CTap *)(jb.taps + (k * 3 + e) * TAPW + NMAX); }
+
+__global__ void k_staged_taps(SBatch b, int d) {
+  const SJob &jb = b.j[blockIdx.z];
+  const int k = blockIdx.y;
+  for (int i = threadIdx.x; i < 3 * TAPW; i += blockDim.x) {
+    const int e = i / TAPW, m = i % TAPW - NMAX;
+    const double u = double(m) / (jb.h[k] * double(b.M[k] - 1));
+    const double K = fabs(u) < 1.0 ? 1.0 - u * u : 0.0;
+    jb.taps[(k * 3 + e) * TAPW + m + NMAX] = K * (e == 0 ? 1.0 : (e == 1 ? u : u * u));
+  }
+}
+
+// Adds the taps k and -k, k = K .. R, to out[o] = sum over k of t[k] v[O0 + o + k]
+// (v zero outside 0 .. N - 1); k <= R holds for every lane or for none.
+template <int K, int N, int O0, int NO>
+__device__ inline void line_taps(const double (&v)[N], CTap *t, int R, double (&out)[NO]) {
+  if constexpr (K < N) {
+    if (K > R) return;
+    const double tp = t[K], tm = t[-K];
+#pragma unroll
+    for (int o = 0; o < NO; ++o) {
+      if (O0 + o + K < N) out[o] = fma(tp, v[O0 + o + K < N ? O0 + o + K : 0], out[o]);
+      if (O0 + o - K >= 0) out[o] = fma(tm, v[O0 + o - K >= 0 ? O0 + o - K : 0], out[o]);
+    }
+    line_taps<K + 1, N, O0, NO>(v, t, R, out);
+  }
+}
+
+// The outputs of a line, st(x, value) for x < n, in two halves for N > 16.
+template <int N, int O0 = 0, typename ST>
+__device__ inline void line_out(const double (&v)[N], CTap *t, int R, int n, ST st) {
+  constexpr int NO = N <= 16 ? N : N / 2;
+  const double c = t[0];
+  double out[NO];
+#pragma unroll
+  for (int o = 0; o < NO; ++o) out[o] = c * v[O0 + o];
+  line_taps<1, N, O0, NO>(v, t, R, out);
+#pragma unroll
+  for (int o = 0; o < NO; ++o)
+    if (O0 + o < n) st(O0 + o, out[o]);
+  if constexpr (O0 + NO < N) line_out<N, O0 + NO>(v, t, R, n, st);
+}
+
+template <int N, typename LD>
+__device__ inline void line_load(double (&v)[N], int n, LD ld) {
+#pragma unroll
+  for (int x = 0; x < N; ++x) v[x] = x < n ? ld(x) : 0.0;
+}
+
+// ------------------------------------------------------------------ stage T
+// d = 2: a workgroup takes RB s-rows; thread (row, i) passes the t_2 line of
+// t_1 = i, then the t_1 line of t_2 = i.
+template <typename T, int N>
+__global__ __launch_bounds__(128) void k_stage_t2(SBatch b, int RB, int L) {
+  extern __shared__ double lds[];
+  const SJob &jb = b.j[blockIdx.z];
+  const int M1 = b.M[0], M2 = b.M[1], P = b.P;
+  const int64_t PP = int64_t(P) * P;
+  const int r = threadIdx.x / L, i = threadIdx.x % L;
+  const int p = int(blockIdx.x) * RB + r;
+  const bool on = r < RB && p < P;
+  double *blk = lds + r * M1 * (M2 + 1);
+  int xi = 0;
+  for (int fam = 0; fam < 2; ++fam) {
+    const T *A = static_cast<const T *>(fam == 0 ? jb.Ca : jb.Ga), *B = static_cast<const T *>(fam == 0 ? jb.Cb : jb.Gb);
+    double v[N];
+    if (on && i < M1) {
+      const int64_t base = int64_t(p) * P + i * M2;
+      const int diag = p - i * M2;
+      if (!A)
+        line_load<N>(v, M2, [&](int x) { return x == diag ? 0.0 : jb.c0; });
+      else if (B)
+        line_load<N>(v, M2, [&](int x) { return double(A[base + x]) - double(B[base + x]); });
+      else
+        line_load<N>(v, M2, [&](int x) { return double(A[base + x]); });
+    }
+    const int md = 2 - fam;
+    for (int e2 = 0; e2 <= md; ++e2) {
+      if (on && i < M1) line_out<N>(v, taps_of(jb, 1, e2), jb.R[1], M2, [&](int x, double o) { blk[i * (M2 + 1) + x] = o; });
+      __syncthreads();
+      if (on && i < M2) {
+        double w[N];
+        line_load<N>(w, M1, [&](int x) { return blk[x * (M2 + 1) + i]; });
+        for (int e1 = 0; e1 <= md - e2; ++e1) {
+          double *X = jb.X + (xi + e1) * PP + int64_t(p) * P + i;
+          line_out<N>(w, taps_of(jb, 0, e1), jb.R[0], M1, [&](int x, double o) { X[x * M2] = o; });
+        }
+      }
+      xi += md - e2 + 1;
+      __syncthreads();
+    }
+  }
+}
+
+// d = 3: one s-row per workgroup, the t-block in LDS between passes; the threads
+// cover the lines of each pass (M_1 M_2, M_1 M_3, M_2 M_3 of them).
+template <typename T, int N>
+__global__ __launch_bounds__(256) void k_stage_t3(SBatch b) {
+  extern __shared__ double lds[];
+  const SJob &jb = b.j[blockIdx.z];
+  const int M1 = b.M[0], M2 = b.M[1], M3 = b.M[2], P = b.P, p = blockIdx.x;
+  const int64_t PP = int64_t(P) * P;
+  const int S3 = M3 | 1;  // odd row length: the t_3 lines of neighbouring threads meet different banks
+  double *B1 = lds, *B2 = lds + M1 * M2 * S3;
+  // cross-validation reads X at t_1 >= s_1 - R_1 only; those need t_1 >= s_1 - 2 R_1
+  const int x1 = b.cv ? max(0, p / b.PR - jb.R[0]) : 0, i1 = b.cv ? max(0, x1 - jb.R[0]) : 0;
+  int xi = 0;
+  for (int fam = 0; fam < 2; ++fam) {
+    const T *A = static_cast<const T *>(fam == 0 ? jb.Ca : jb.Ga), *B = static_cast<const T *>(fam == 0 ? jb.Cb : jb.Gb);
+    const int md = 2 - fam;
+    for (int e3 = 0; e3 <= md; ++e3) {
+      for (int l = threadIdx.x + i1 * M2; l < M1 * M2; l += 256) {
+        double v[N];
+        const int64_t base = int64_t(p) * P + l * M3;
+        const int diag = p - l * M3;
+        if (!A)
+          line_load<N>(v, M3, [&](int x) { return x == diag ? 0.0 : jb.c0; });
+        else if (B)
+          line_load<N>(v, M3, [&](int x) { return double(A[base + x]) - double(B[base + x]); });
+        else
+          line_load<N>(v, M3, [&](int x) { return double(A[base + x]); });
+        line_out<N>(v, taps_of(jb, 2, e3), jb.R[2], M3, [&](int x, double o) { B1[l * S3 + x] = o; });
+      }
+      __syncthreads();
+      for (int e2 = 0; e2 <= md - e3; ++e2) {
+        for (int l = threadIdx.x + i1 * M3; l < M1 * M3; l += 256) {
+          const int t1 = l / M3, t3 = l - t1 * M3;
+          double w[N];
+          line_load<N>(w, M2, [&](int x) { return B1[(t1 * M2 + x) * S3 + t3]; });
+          line_out<N>(w, taps_of(jb, 1, e2), jb.R[1], M2, [&](int x, double o) { B2[(t1 * M2 + x) * S3 + t3] = o; });
+        }
+        __syncthreads();
+        for (int l = threadIdx.x; l < M2 * M3; l += 256) {
+          const int t2 = l / M3, t3 = l - t2 * M3;
+          double w[N];
+          line_load<N>(w, M1, [&](int x) { return x >= i1 ? B2[(x * M2 + t2) * S3 + t3] : 0.0; });
+          for (int e1 = 0; e1 <= md - e3 - e2; ++e1) {
+            double *X = jb.X + (xi + e1) * PP + int64_t(p) * P + l;
+            line_out<N>(w, taps_of(jb, 0, e1), jb.R[0], M1, [&](int x, double o) {
+              if (x >= x1) X[int64_t(x) * M2 * M3] = o;
+            });
+          }
+        }
+        xi += md - e3 - e2 + 1;
+        __syncthreads();
+      }
+    }
+  }
+}
+
+// The stage-T array x: family, t-degree and the first of its stage-S arrays.
+template <int d>
+__device__ inline void x_array(int x, int &fam, int &deg, int &y0) {
+  int i = 0, y = 0;
+  fam = deg = y0 = 0;
+  for (int f = 0; f < 2; ++f) {
+    const int md = 2 - f;
+    for (int e3 = 0; e3 <= (d == 3 ? md : 0); ++e3)
+      for (int e2 = 0; e2 <= md - e3; ++e2)
+        for (int e1 = 0; e1 <= md - e3 - e2; ++e1) {
+          const int dg = e1 + e2 + e3, left = md - dg;
+          if (i == x) {
+            fam = f;
+            deg = dg;
+            y0 = y;
+          }
+          ++i;
+          y += d == 2 ? left + 1 : (left + 1) * (left + 2) / 2;
+        }
+  }
+}
+
+// ------------------------------------------------------------------ stage S
+// d = 2: thread = one s_2 line (s_1 = blockIdx.y * 4 + wave, one t column).
+template <int N>
+__global__ __launch_bounds__(256) void k_stage_s2(SBatch b, int nx) {
+  const SJob &jb = b.j[int(blockIdx.z) / nx];
+  const int x = int(blockIdx.z) % nx;
+  const int M1 = b.M[0], M2 = b.M[1], P = b.P;
+  const int64_t PP = int64_t(P) * P;
+  const int q = int(blockIdx.x) * 64 + (threadIdx.x & 63), a1 = int(blockIdx.y) * 4 + (threadIdx.x >> 6);
+  if (a1 >= M1 || q >= P) return;
+  // cross-validation: rows s_1 <= t_1 + R_1 of the columns
+  if (b.cv && a1 > (min(int(blockIdx.x) * 64 + 63, P - 1)) / b.PR + jb.R[0]) return;
+  int fam, deg, y0;
+  x_array<2>(x, fam, deg, y0);
+  const double *X = jb.X + x * PP + int64_t(a1) * M2 * P + q;
+  double v[N];
+  line_load<N>(v, M2, [&](int s) { return X[int64_t(s) * P]; });
+  for (int e = 0; e <= 2 - fam - deg; ++e) {
+    double *Y = jb.Y + (y0 + e) * PP + int64_t(a1) * M2 * P + q;
+    line_out<N>(v, taps_of(jb, 1, e), jb.R[1], M2, [&](int s, double o) { Y[int64_t(s) * P] = o; });
+  }
+}
+
+// d = 3: a workgroup takes an s_1 index, 16 t columns and one array: thread
+// (s_2, column) passes the s_3 line, then (s_3, column) the s_2 line.
+constexpr int QS = 16;
+template <int N>
+__global__ __launch_bounds__(256) void k_stage_s3(SBatch b, int nx) {
+  extern __shared__ double lds[];  // [s_2][s_3][QS]
+  const SJob &jb = b.j[int(blockIdx.z) / nx];
+  const int x = int(blockIdx.z) % nx;
+  const int M2 = b.M[1], M3 = b.M[2], P = b.P, a1 = blockIdx.y;
+  const int64_t PP = int64_t(P) * P;
+  const int q0 = int(blockIdx.x) * QS, c = threadIdx.x % QS, q = q0 + c;
+  if (b.cv && a1 > min(q0 + QS - 1, P - 1) / b.PR + jb.R[0]) return;
+  int fam, deg, y0;
+  x_array<3>(x, fam, deg, y0);
+  const int md = 2 - fam - deg;
+  const double *X = jb.X + x * PP + int64_t(a1) * b.PR * P + min(q, P - 1);
+  double *Y = jb.Y + int64_t(a1) * b.PR * P + q;
+  for (int e3 = 0; e3 <= md; ++e3) {
+    if (e3) __syncthreads();
+    for (int s2 = threadIdx.x / QS; s2 < M2; s2 += 256 / QS) {
+      double v[N];
+      line_load<N>(v, M3, [&](int s) { return X[int64_t(s2 * M3 + s) * P]; });
+      line_out<N>(v, taps_of(jb, 2, e3), jb.R[2], M3, [&](int s, double o) { lds[(s2 * M3 + s) * QS + c] = o; });
+    }
+    __syncthreads();
+    for (int s3 = threadIdx.x / QS; s3 < M3; s3 += 256 / QS) {
+      double w[N];
+      line_load<N>(w, M2, [&](int s) { return lds[(s * M3 + s3) * QS + c]; });
+      for (int e2 = 0; e2 <= md - e3; ++e2) {
+        double *Ye = Y + (y0 + e2) * PP;
+        if (q < P)
+          line_out<N>(w, taps_of(jb, 1, e2), jb.R[1], M2, [&](int s, double o) { Ye[int64_t(s * M3 + s3) * P] = o; });
+      }
+    }
+    y0 += md - e3 + 1;
+  }
+}
+
+// ------------------------------------------------------------------ stage W
+// Stage-S array y: family, degree left for s_1, and the final moments it gives.
+struct YInfo {
+  signed char nj[27];
+  signed char mom[27][3];
+};
+
+// Workgroup (position r of the s-coordinates other than s_1, QB t columns):
+// thread (y, column) passes the s_1 line of array y, its outputs land in LDS as
+// final moments, then one lane per node solves.
+template <typename T, int d, int N, int QB>
+__global__ __launch_bounds__(d == 2 ? 128 : 448) void k_stage_w(SBatch b, YInfo yi) {
+  constexpr int D = 2 * d, NM = 2 + 2 * D + D * (D + 1) / 2, NY = d == 2 ? 14 : 27;
+  constexpr int NTH = d == 2 ? 128 : 448;
+  static_assert(NY * QB <= NTH, "one line per thread");
+  extern __shared__ double F[];  // [NM][M1 * QB + pad]
+  const SJob &jb = b.j[blockIdx.z];
+  const int M1 = b.M[0], P = b.P, PR = b.PR;
+  const int64_t PP = int64_t(P) * P;
+  const int FS = M1 * QB + (d == 2 ? 8 : 16);
+  const int r = blockIdx.y, q0 = int(blockIdx.x) * QB;
+  // cross-validation: outputs s_1 <= the last t_1 of the columns, from rows below n_in
+  const int n_out = b.cv ? min(M1, min(q0 + QB - 1, P - 1) / PR + 1) : M1;
+  const int n_in = min(M1, n_out + jb.R[0]);
+  {
+    const int y = threadIdx.x / QB, c = threadIdx.x % QB;
+    if (y < NY) {
+      const double *Y = jb.Y + y * PP + int64_t(r) * P + min(q0 + c, P - 1);
+      double v[N];
+      line_load<N>(v, n_in, [&](int s) { return Y[int64_t(s) * PR * P]; });
+      for (int e = 0; e < 3; ++e) {
+        if (e >= yi.nj[y]) break;
+        double *f = F + yi.mom[y][e] * FS + c;
+        line_out<N>(v, taps_of(jb, 0, e), jb.R[0], n_out, [&](int s, double o) { f[s * QB] = o; });
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < n_out * QB; e += NTH) {
+    const int a1 = e / QB, c = e % QB;
+    if (q0 + c >= P) continue;
+    double m[NM];
+#pragma unroll
+    for (int i = 0; i < NM; ++i) m[i] = F[i * FS + e];
+    int8_t st;
+    const int64_t o = (int64_t(a1) * PR + r) * P + q0 + c;
+    static_cast<T *>(jb.b0)[o] = T(wls_b0<D>(m, &st));
+    if (!b.cv && b.status) b.status[o] = st;
+  }
+}
+
+// ------------------------------------------------------------------ score
+// sum Q_f - 2 G_f g + C_f g^2 over all nodes, g(p, q) = b0(min, max) (the fit at
+// (q, p) is the fit at (p, q) up to rounding), 0 outside the mask and where b0 is
+// NaN (an empty window). Tile pairs (I, J), I <= J; one FP64 partial per workgroup.
+template <typename T>
+__global__ __launch_bounds__(256) void k_staged_score(SBatch b, int npairs) {
+  __shared__ double A[SC_TILE][SC_TILE + 1];
+  __shared__ double red[4];
+  const SJob &jb = b.j[blockIdx.z];
+  const int P = b.P, nt = (P + SC_TILE - 1) / SC_TILE;
+  const T *Gh = static_cast<const T *>(jb.b0), *Q = static_cast<const T *>(jb.Qf);
+  const T *G = static_cast<const T *>(jb.Gf), *C = static_cast<const T *>(jb.Cf);
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  double s = 0.0;
+  for (int t = blockIdx.x; t < npairs; t += gridDim.x) {
+    int id = t, I = 0;
+    while (id >= nt - I) {
+      id -= nt - I;
+      ++I;
+    }
+    const int r0 = I * SC_TILE, c0 = (I + id) * SC_TILE;
+    double qv[8], gv[8], cv[8];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int rr = ty + 8 * u;
+      const bool ia = r0 + rr < P && c0 + tx < P, ib = id > 0 && c0 + rr < P && r0 + tx < P;
+      const int64_t o1 = ia ? int64_t(r0 + rr) * P + c0 + tx : 0, o2 = ib ? int64_t(c0 + rr) * P + r0 + tx : 0;
+      A[rr][tx] = ia ? double(Gh[o1]) : 0.0;
+      qv[u] = ia ? double(Q[o1]) : 0.0;
+      gv[u] = ia ? double(G[o1]) : 0.0;
+      cv[u] = ia ? double(C[o1]) : 0.0;
+      qv[4 + u] = ib ? double(Q[o2]) : 0.0;
+      gv[4 + u] = ib ? double(G[o2]) : 0.0;
+      cv[4 + u] = ib ? double(C[o2]) : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int rr = ty + 8 * u;
+      double g = id > 0 || rr <= tx ? A[rr][tx] : A[tx][rr];
+      if (b.mask && r0 + rr < P && c0 + tx < P && (!b.mask[r0 + rr] || !b.mask[c0 + tx])) g = 0.0;
+      if (g != g) g = 0.0;
+      s += qv[u] - 2.0 * gv[u] * g + cv[u] * g * g;
+      // (c0 + rr, r0 + tx): the node (r0 + tx, c0 + rr) of this tile
+      double g2 = A[tx][rr];
+      if (b.mask && c0 + rr < P && r0 + tx < P && (!b.mask[c0 + rr] || !b.mask[r0 + tx])) g2 = 0.0;
+      if (g2 != g2) g2 = 0.0;
+      s += qv[4 + u] - 2.0 * gv[4 + u] * g2 + cv[4 + u] * g2 * g2;
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) jb.part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+__global__ __launch_bounds__(64) void k_staged_finish(const double *__restrict__ part, int n,
+                                                      double *__restrict__ scores) {
+  double s = 0.0;
+  for (int i = threadIdx.x; i < n; i += 64) s += part[int64_t(blockIdx.x) * SC_WG + i];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+  if (threadIdx.x == 0) scores[blockIdx.x] = s;
+}
+
+// ------------------------------------------------------------------ host
+// Moment index in the order S0, S1[D], S2 (upper triangle by rows), T0, T1[D] of
+// the exponents e over (s_1 .. s_d, t_1 .. t_d).
+int moment_of(int D, int fam, const int *e) {
+  int c[2] = {-1, -1}, deg = 0;
+  for (int k = 0; k < D; ++k)
+    for (int r = 0; r < e[k]; ++r) c[deg++] = k;
+  const int NC = 1 + D + D * (D + 1) / 2;
+  if (fam == 1) return deg == 0 ? NC : NC + 1 + c[0];
+  if (deg == 0) return 0;
+  if (deg == 1) return 1 + c[0];
+  int idx = 1 + D;
+  for (int r = 0; r < c[0]; ++r) idx += D - r;
+  return idx + c[1] - c[0];
+}
+
+YInfo make_yinfo(int d) {
+  YInfo yi;
+  std::memset(&yi, 0, sizeof(yi));
+  int y = 0;
+  for (int f = 0; f < 2; ++f) {
+    const int md = 2 - f;
+    for (int t3 = 0; t3 <= (d == 3 ? md : 0); ++t3)
+      for (int t2 = 0; t2 <= md - t3; ++t2)
+        for (int t1 = 0; t1 <= md - t3 - t2; ++t1) {
+          const int left = md - t1 - t2 - t3;
+          for (int s3 = 0; s3 <= (d == 3 ? left : 0); ++s3)
+            for (int s2 = 0; s2 <= left - s3; ++s2) {
+              yi.nj[y] = (signed char)(left - s3 - s2 + 1);
+              for (int s1 = 0; s1 <= left - s3 - s2; ++s1) {
+                const int e2[4] = {s1, s2, t1, t2}, e3[6] = {s1, s2, s3, t1, t2, t3};
+                yi.mom[y][s1] = (signed char)moment_of(2 * d, f, d == 2 ? e2 : e3);
+              }
+              ++y;
+            }
+        }
+  }
+  return yi;
+}
+
+struct Shape {
+  int d, M[3], P, PR, N, nx, ny;
+};
+Shape shape_of(const fpca_grid *g) {
+  Shape s{};
+  s.d = g->d;
+  s.P = 1;
+  int mx = 1;
+  for (int k = 0; k < 3; ++k) {
+    s.M[k] = k < g->d ? g->M[k] : 1;
+    s.P *= s.M[k];
+    mx = std::max(mx, s.M[k]);
+  }
+  s.PR = s.P / s.M[0];
+  s.N = mx <= 16 ? 16 : (mx + 7) / 8 * 8;
+  s.nx = g->d == 2 ? 9 : 14;
+  s.ny = g->d == 2 ? 14 : 27;
+  return s;
+}
+
+size_t job_bytes(const Shape &s, size_t elem, bool cv) {
+  const size_t PP = size_t(s.P) * s.P;
+  return carve_bytes(size_t(s.nx) * PP, 8) + carve_bytes(size_t(s.ny) * PP, 8) + (cv ? carve_bytes(PP, elem) : 0) +
+         carve_bytes(9 * TAPW, 8);
+}
+
+template <typename K>
+int want_lds(K kernel, size_t lds) {
+  if (lds > 64 * 1024)
+    FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 int(lds)));
+  return FPCA_OK;
+}
+
+// The three stages of the batch's nb jobs.
+template <typename T, int N>
+int launch_stages(fpca_context *ctx, const Shape &s, const SBatch &b, int nb) {
+  hipStream_t st = ctx->stream;
+  hipLaunchKernelGGL(k_staged_taps, dim3(1, unsigned(s.d), unsigned(nb)), dim3(256), 0, st, b, s.d);
+  FPCA_LAUNCH_CHECK("staged taps");
+  const YInfo yi = make_yinfo(s.d);
+  if (s.d == 2) {
+    const int L = std::max(s.M[0], s.M[1]), RB = 128 / L;
+    const size_t lds = size_t(RB) * s.M[0] * (s.M[1] + 1) * 8;
+    if (int rc = want_lds(&k_stage_t2<T, N>, lds)) return rc;
+    hipLaunchKernelGGL((k_stage_t2<T, N>), dim3(unsigned((s.P + RB - 1) / RB), 1, unsigned(nb)), dim3(128), lds, st, b,
+                       RB, L);
+    FPCA_LAUNCH_CHECK("staged T");
+    hipLaunchKernelGGL((k_stage_s2<N>), dim3(unsigned((s.P + 63) / 64), unsigned((s.M[0] + 3) / 4), unsigned(nb * s.nx)),
+                       dim3(256), 0, st, b, s.nx);
+    FPCA_LAUNCH_CHECK("staged S");
+    constexpr int QB = 8;
+    const size_t ldw = size_t(20) * (s.M[0] * QB + 8) * 8;
+    if (int rc = want_lds(&k_stage_w<T, 2, N, QB>, ldw)) return rc;
+    hipLaunchKernelGGL((k_stage_w<T, 2, N, QB>), dim3(unsigned((s.P + QB - 1) / QB), unsigned(s.PR), unsigned(nb)),
+                       dim3(128), ldw, st, b, yi);
+    FPCA_LAUNCH_CHECK("staged W");
+    return FPCA_OK;
+  }
+  const size_t lds = size_t(2) * s.M[0] * s.M[1] * (s.M[2] | 1) * 8;
+  if (int rc = want_lds(&k_stage_t3<T, N>, lds)) return rc;
+  hipLaunchKernelGGL((k_stage_t3<T, N>), dim3(unsigned(s.P), 1, unsigned(nb)), dim3(256), lds, st, b);
+  FPCA_LAUNCH_CHECK("staged T");
+  const size_t lsd = size_t(s.M[1]) * s.M[2] * QS * 8;
+  if (int rc = want_lds(&k_stage_s3<N>, lsd)) return rc;
+  hipLaunchKernelGGL((k_stage_s3<N>), dim3(unsigned((s.P + QS - 1) / QS), unsigned(s.M[0]), unsigned(nb * s.nx)),
+                     dim3(256), lsd, st, b, s.nx);
+  FPCA_LAUNCH_CHECK("staged S");
+  auto run_w = [&](auto qb) -> int {
+    constexpr int QB = decltype(qb)::value;
+    const size_t ldw = size_t(35) * (s.M[0] * QB + 16) * 8;
+    if (int rc = want_lds(&k_stage_w<T, 3, N, QB>, ldw)) return rc;
+    hipLaunchKernelGGL((k_stage_w<T, 3, N, QB>), dim3(unsigned((s.P + QB - 1) / QB), unsigned(s.PR), unsigned(nb)),
+                       dim3(448), ldw, st, b, yi);
+    FPCA_LAUNCH_CHECK("staged W");
+    return FPCA_OK;
+  };
+  // the final moments of M_1 x QB nodes sit in LDS
+  if constexpr (N == 16) return run_w(std::integral_constant<int, 16>());
+  return run_w(std::integral_constant<int, 8>());
+}
+
+template <typename T>
+int launch_any(fpca_context *ctx, const Shape &s, const SBatch &b, int nb) {
+  if (s.N == 16) return launch_stages<T, 16>(ctx, s, b, nb);
+  if (s.N == 24) return launch_stages<T, 24>(ctx, s, b, nb);
+  if (s.N == 32) return launch_stages<T, 32>(ctx, s, b, nb);
+  return launch_stages<T, 40>(ctx, s, b, nb);
+}
+
+void fill_job(const Shape &s, const StagedJob &in, SJob *o) {
+  o->Ca = in.Ca;
+  o->Cb = in.Cb;
+  o->Ga = in.Ga;
+  o->Gb = in.Gb;
+  o->Qf = in.Qf;
+  o->Gf = in.Gf;
+  o->Cf = in.Cf;
+  o->c0 = in.c0;
+  for (int k = 0; k < 3; ++k) {
+    o->h[k] = k < s.d ? in.h[k] : 1.0;
+    o->R[k] = k < s.d ? int(std::min(std::floor(in.h[k] * double(s.M[k] - 1)), double(s.M[k] - 1))) : 0;
+  }
+}
+
+SBatch make_batch(const Shape &s, const fpca_grid *grid, bool cv) {
+  SBatch b;
+  std::memset(&b, 0, sizeof(b));
+  for (int k = 0; k < 3; ++k) b.M[k] = s.M[k];
+  b.P = s.P;
+  b.PR = s.PR;
+  b.cv = cv ? 1 : 0;
+  b.mask = grid->mask;
+  return b;
+}
+
+}  // namespace
+
+bool staged_supported(const fpca_grid *g) {
+  if (g->d != 2 && g->d != 3) return false;
+  int64_t P = 1;
+  for (int k = 0; k < g->d; ++k) {
+    if (g->M[k] > NMAX) return false;
+    P *= g->M[k];
+  }
+  // d = 3: stage S keeps M_2 M_3 x 16 values in LDS (stage T two t-blocks, at most 96 KB)
+  return P <= 4096 && (g->d == 2 || int64_t(g->M[1]) * g->M[2] * QS * 8 <= 160 * 1024);
+}
+
+template <typename T>
+int staged_smooth(fpca_context *ctx, const fpca_grid *grid, const StagedJob &job, T *out, int8_t *status) {
+  const Shape s = shape_of(grid);
+  const size_t PP = size_t(s.P) * s.P;
+  if (int rc = ws_reserve(ctx, job_bytes(s, sizeof(T), false))) return rc;
+  Carver cw{static_cast<char *>(ctx->ws), 0, ctx->ws_size};
+  SBatch b = make_batch(s, grid, false);
+  b.status = status;
+  fill_job(s, job, &b.j[0]);
+  b.j[0].X = cw.take<double>(size_t(s.nx) * PP);
+  b.j[0].Y = cw.take<double>(size_t(s.ny) * PP);
+  b.j[0].taps = cw.take<double>(9 * TAPW);
+  b.j[0].b0 = out;
+  return launch_any<T>(ctx, s, b, 1);
+}
+
+template <typename T>
+int staged_scores(fpca_context *ctx, const fpca_grid *grid, const std::vector<StagedJob> &jobs, double *scores) {
+  const Shape s = shape_of(grid);
+  const size_t PP = size_t(s.P) * s.P, per = job_bytes(s, sizeof(T), true), J = jobs.size();
+  const int nb_max = int(std::max<size_t>(1, std::min<size_t>({size_t(SB_MAX), J, (size_t(1) << 30) / per})));
+  const size_t bytes_part = carve_bytes(J * SC_WG, 8);
+  if (int rc = ws_reserve(ctx, bytes_part + nb_max * per)) return rc;
+  Carver cw{static_cast<char *>(ctx->ws), 0, ctx->ws_size};
+  double *part = cw.take<double>(J * SC_WG);
+  SBatch b = make_batch(s, grid, true);
+  for (int i = 0; i < nb_max; ++i) {
+    b.j[i].X = cw.take<double>(size_t(s.nx) * PP);
+    b.j[i].Y = cw.take<double>(size_t(s.ny) * PP);
+    b.j[i].b0 = cw.take<T>(PP);
+    b.j[i].taps = cw.take<double>(9 * TAPW);
+  }
+  const int nt = (s.P + SC_TILE - 1) / SC_TILE, npairs = nt * (nt + 1) / 2, nsc = std::min(npairs, SC_WG);
+  for (size_t j0 = 0; j0 < J; j0 += nb_max) {
+    const int nb = int(std::min<size_t>(nb_max, J - j0));
+    for (int i = 0; i < nb; ++i) {
+      fill_job(s, jobs[j0 + i], &b.j[i]);
+      b.j[i].part = part + (j0 + i) * SC_WG;
+    }
+    if (int rc = launch_any<T>(ctx, s, b, nb)) return rc;
+    hipLaunchKernelGGL(k_staged_score<T>, dim3(unsigned(nsc), 1, unsigned(nb)), dim3(256), 0, ctx->stream, b, npairs);
+    FPCA_LAUNCH_CHECK("staged score");
+  }
+  hipLaunchKernelGGL(k_staged_finish, dim3(unsigned(J)), dim3(64), 0, ctx->stream, part, nsc, scores);
+  FPCA_LAUNCH_CHECK("staged finish");
+  return FPCA_OK;
+}
+
+template int staged_smooth<float>(fpca_context *, const fpca_grid *, const StagedJob &, float *, int8_t *);
+template int staged_smooth<double>(fpca_context *, const fpca_grid *, const StagedJob &, double *, int8_t *);
+template int staged_scores<float>(fpca_context *, const fpca_grid *, const std::vector<StagedJob> &, double *);
+template int staged_scores<double>(fpca_context *, const fpca_grid *, const std::vector<StagedJob> &, double *);
+
+}  // namespace fpca

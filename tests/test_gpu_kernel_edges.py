@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 from oracle import mlp as ref_mlp
-from tests._util import normwise_rel
+from tests._util import normwise_rel, rand_irregular, status_agreement
 
 pytestmark = pytest.mark.gpu
 
@@ -140,3 +140,62 @@ def test_covop_blocks(torch, F, h, M, R, n, r, mode):
         rb, _ = oracle.smooth_cov_raw(M, hb, C, G, np.concatenate([p * P + q, q * P + p]))
         ref = 0.5 * (rb[:P] + rb[P:]) - mu * mu[q]
         assert normwise_rel(got[:, j], ref) < 1e-10, j
+
+
+@pytest.mark.parametrize("M,hb,dt", [((16, 17), 0.13, "f32"), ((24, 5), (0.1, 0.6), "f64"), ((25, 11), 0.12, "f32"),
+                                     ((33, 7), (0.07, 0.4), "f32"), ((2, 40), (1.5, 0.06), "f64"),
+                                     ((3, 16, 2), (0.6, 0.2, 1.2), "f32"), ((5, 2, 17), (0.5, 1.1, 0.14), "f64"),
+                                     ((6, 5, 4), 0.45, "f32")])
+def test_staged_smoother_and_cv(torch, F, h, M, hb, dt):
+    """Lines at and beside the lengths the staged smoother rounds to, windows from
+    one grid step to whole lines: the smoothed covariance with statuses, its
+    complete-grid form, and masked cross-validation scores."""
+    _say(f"staged M={M} h={hb} {dt}")
+    rng = np.random.default_rng(120 + sum(M))
+    d, P, nf = len(M), int(np.prod(M)), 3
+    npdt, tdt = (np.float64, torch.float64) if dt == "f64" else (np.float32, torch.float32)
+    code = F.FPCA_F64 if dt == "f64" else F.FPCA_F32
+    off, t, y = rand_irregular(rng, d, 40, 1, 30, npdt)
+    folds = np.arange(40, dtype=np.int32) % nf
+    slabs = [oracle.bin_cov_pairs(M, off, t.astype(np.float64), y.astype(np.float64), folds, f, want_Q=True)
+             for f in [-1] + list(range(nf))]
+    C, G, Q = (np.stack([s[i] for s in slabs]).astype(npdt) for i in range(3))
+    mask = (rng.random(P) < 0.8).astype(np.uint8)
+    D = lambda a: dev(torch, a)
+    tol = 1e-10 if dt == "f64" else 1e-5
+    # smoother
+    gam = torch.empty(P, P, dtype=tdt, device="cuda:0")
+    st = torch.empty(P, P, dtype=torch.int8, device="cuda:0")
+    F.fpca_smooth_cov(h, F.Grid(M), code, D(C[0]), 0.0, D(G[0]), None, F.FPCA_K_EPANECHNIKOV, hb, gam, st)
+    h.sync()
+    b, st_ref = oracle.smooth_cov_raw(M, hb, C[0].astype(np.float64), G[0].astype(np.float64))
+    g, s_got = gam.cpu().numpy().astype(np.float64), st.cpu().numpy().reshape(-1)
+    _, _, _, mp = oracle.smooth(M + M, np.tile(np.broadcast_to(hb, (d,)), 2), C[0].astype(np.float64),
+                                G[0].astype(np.float64), want_moments=True)
+    assert status_agreement(s_got, st_ref, mp)[0] == 0
+    ok = ((s_got == 0) & (st_ref == 0)).reshape(P, P)
+    ref = b.reshape(P, P)
+    both = ok & ok.T
+    assert normwise_rel(g, 0.5 * (ref + ref.T), both) < tol
+    # a complete grid: weights c0 off the diagonal
+    c0 = 0.01
+    F.fpca_smooth_cov(h, F.Grid(M), F.FPCA_F64, None, c0, D(G[0].astype(np.float64)), None, F.FPCA_K_EPANECHNIKOV, hb,
+                      g64 := torch.empty(P, P, dtype=torch.float64, device="cuda:0"), st)
+    h.sync()
+    W = np.full((P, P), c0)
+    np.fill_diagonal(W, 0.0)
+    b, st_ref = oracle.smooth_cov_raw(M, hb, W, G[0].astype(np.float64))
+    ref = b.reshape(P, P)
+    both = (st_ref == 0).reshape(P, P)
+    assert normwise_rel(g64.cpu().numpy(), 0.5 * (ref + ref.T), both & both.T) < 1e-10
+    # cross-validation, more jobs than one launch takes
+    hs = np.outer([1.0, 1.2, 1.45, 0.9], np.broadcast_to(hb, (d,)))
+    got = F.fpca_cv_batched(h, code, [(F.Grid(M, D(mask)), D(C), D(G), D(Q))], nf, hs)[0]
+    want = np.zeros_like(got)
+    for i, hv in enumerate(hs):
+        for f in range(nf):
+            bb, _ = oracle.smooth_cov_raw(M, hv, C[0].astype(np.float64) - C[f + 1], G[0].astype(np.float64) - G[f + 1])
+            Gh = oracle.assemble_cov(bb.reshape(P, P), np.zeros(P), mask)
+            want[i, f] = oracle.cv_score(Q[f + 1].astype(np.float64), G[f + 1].astype(np.float64),
+                                         C[f + 1].astype(np.float64), Gh)
+    np.testing.assert_allclose(got, want, rtol=1e-9 if dt == "f64" else 1e-5)
