@@ -627,11 +627,13 @@ int bin_impl(fpca_context *ctx, const fpca_grid *grid, int kind, int design, int
                        cntrow, ctx->d_flags);
     FPCA_LAUNCH_CHECK("bin_rows");
   }
+  auto products = [&](int64_t r0, int64_t rows, int64_t slab_no) {
+    const T *rws[3] = {Cr + r0 * P, Z + r0 * P, SQ ? Z2 + r0 * P : nullptr};
+    T *out[3] = {W + slab_no * slab, S + slab_no * slab, SQ ? SQ + slab_no * slab : nullptr};
+    return syrk_set(ctx, SQ ? 3 : 2, rws, rows, P, out, T(1), false, prec);
+  };
   if (nsl == 1) {
-    if (int rc = gram<T>(ctx, Cr, n, P, W, 1.0, false, prec)) return rc;
-    if (int rc = gram<T>(ctx, Z, n, P, S, 1.0, false, prec)) return rc;
-    if (SQ)
-      if (int rc = gram<T>(ctx, Z2, n, P, SQ, 1.0, false, prec)) return rc;
+    if (int rc = products(0, n, 0)) return rc;
   } else {
     // fold f occupies rows [fstart[f], fstart[f+1]); the boundaries are read
     // back once (n_folds+1 integers) to size each product.
@@ -650,10 +652,7 @@ int bin_impl(fpca_context *ctx, const fpca_grid *grid, int kind, int design, int
           if (int rc = fill_bytes_zero(ctx, SQ + (int64_t(f) + 1) * slab, slab * sizeof(T))) return rc;
         continue;
       }
-      if (int rc = gram<T>(ctx, Cr + r0 * P, kf, P, Wf, 1.0, false, prec)) return rc;
-      if (int rc = gram<T>(ctx, Z + r0 * P, kf, P, Sf, 1.0, false, prec)) return rc;
-      if (SQ)
-        if (int rc = gram<T>(ctx, Z2 + r0 * P, kf, P, SQ + (int64_t(f) + 1) * slab, 1.0, false, prec)) return rc;
+      if (int rc = products(r0, kf, int64_t(f) + 1)) return rc;
     }
     for (T *A : {W, S, SQ}) {
       if (!A) continue;

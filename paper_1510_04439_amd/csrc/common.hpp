@@ -147,5 +147,11 @@ int syrk_f32(fpca_context *ctx, const float *A, int64_t K, int64_t N, float *C, 
              float alpha, bool zero_diag, int prec, double *colsum = nullptr, double *colsq = nullptr);
 int syrk_f64(fpca_context *ctx, const double *A, int64_t K, int64_t N, double *C, int64_t ldc,
              double alpha, bool zero_diag);
+// The same for nm <= 3 matrices A[m] of one shape (ldc = N), in one launch
+// where the product is not large enough to fill the device by itself.
+int syrk_set(fpca_context *ctx, int nm, const float *const *A, int64_t K, int64_t N, float *const *C,
+             float alpha, bool zero_diag, int prec);
+int syrk_set(fpca_context *ctx, int nm, const double *const *A, int64_t K, int64_t N, double *const *C,
+             double alpha, bool zero_diag, int prec);
 
 }  // namespace fpca

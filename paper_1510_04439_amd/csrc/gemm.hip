@@ -57,7 +57,7 @@ __device__ inline bool tile_of(int id, int nb, int per, int *bi, int *bj) {
 }
 
 
-// FP32 operands on v_mfma_f32_16x16x4_f32.
+// FP32 operands on v_mfma_f32_16x16x4_f32, products of many tiles.
 template <bool VEC4>
 __global__ __launch_bounds__(256) void k_syrk_f32(const float *__restrict__ A, int64_t K, int64_t N,
                                                    float *__restrict__ C, int64_t ldc, float alpha,
@@ -530,31 +530,30 @@ __global__ __launch_bounds__(256) void k_syrk_fixup(const float *__restrict__ pa
   }
 }
 
-// 64x64 output tile, 256 threads with 4x4 outputs each, all tiles computed.
-template <typename Tin, typename Tacc, typename Tout>
-__global__ __launch_bounds__(256) void k_gram_valu(const Tin *__restrict__ A, int64_t K, int64_t N,
-                                                    Tout *__restrict__ C, int64_t ldc, Tacc alpha,
-                                                    int zero_diag) {
-  __shared__ Tin As[16][64];
-  __shared__ Tin Bs[16][64];
+// Exact integer product: 64x64 output tile, 256 threads with 4x4 outputs
+// each, all tiles computed.
+__global__ __launch_bounds__(256) void k_gram_i32(const int32_t *__restrict__ A, int64_t K, int64_t N,
+                                                   int64_t *__restrict__ C) {
+  __shared__ int32_t As[16][64];
+  __shared__ int32_t Bs[16][64];
   const int tid = threadIdx.x;
   const int64_t m0 = int64_t(blockIdx.y) * 64, n0 = int64_t(blockIdx.x) * 64;
   const int tr = (tid >> 4) * 4, tc = (tid & 15) * 4;
-  Tacc acc[4][4];
+  int64_t acc[4][4];
   for (int i = 0; i < 4; ++i)
-    for (int j = 0; j < 4; ++j) acc[i][j] = Tacc(0);
+    for (int j = 0; j < 4; ++j) acc[i][j] = 0;
   for (int64_t k0 = 0; k0 < K; k0 += 16) {
     for (int e = tid; e < 16 * 64; e += 256) {
       int r = e / 64, c = e % 64;
       int64_t kr = k0 + r;
-      As[r][c] = (kr < K && m0 + c < N) ? A[kr * N + m0 + c] : Tin(0);
-      Bs[r][c] = (kr < K && n0 + c < N) ? A[kr * N + n0 + c] : Tin(0);
+      As[r][c] = (kr < K && m0 + c < N) ? A[kr * N + m0 + c] : 0;
+      Bs[r][c] = (kr < K && n0 + c < N) ? A[kr * N + n0 + c] : 0;
     }
     __syncthreads();
     for (int kk = 0; kk < 16; ++kk) {
-      Tacc a[4], b[4];
-      for (int i = 0; i < 4; ++i) a[i] = Tacc(As[kk][tr + i]);
-      for (int j = 0; j < 4; ++j) b[j] = Tacc(Bs[kk][tc + j]);
+      int64_t a[4], b[4];
+      for (int i = 0; i < 4; ++i) a[i] = As[kk][tr + i];
+      for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tc + j];
       for (int i = 0; i < 4; ++i)
         for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
     }
@@ -563,12 +562,250 @@ __global__ __launch_bounds__(256) void k_gram_valu(const Tin *__restrict__ A, in
   for (int i = 0; i < 4; ++i)
     for (int j = 0; j < 4; ++j) {
       int64_t r = m0 + tr + i, c = n0 + tc + j;
-      if (r < N && c < N) {
-        Tacc v = alpha * acc[i][j];
-        if (zero_diag && r == c) v = Tacc(0);
-        C[r * ldc + c] = Tout(v);
-      }
+      if (r < N && c < N) C[r * N + c] = acc[i][j];
     }
+}
+
+// Products of few tiles, and all FP64 products: 64x64 output tiles (on or
+// above the diagonal) on FP32 / FP64 matrix instructions, the K rows of a
+// tile split over gridDim.y workgroups, up to GR_MAX matrices of one shape in
+// one launch (gridDim.z). Bound by the matrix rate of the CUs that get a
+// tile, so the split is there to give every CU some. 256 threads, wavefront
+// w the 32x32 quarter (w / 2, w % 2) as 2x2 fragments; gr_stage rows of both
+// column ranges are in LDS while the next ones are on their way in registers
+// (rows padded to 80 elements: the four K rows of a fragment then start 16
+// banks, for FP64 32, apart). Two FP32 products of 1000 rows and 1024 columns:
+// 262 us on 128x128 tiles (36 of them for 256 CUs), 35 + 7 us here (at 4096
+// columns and 5000 rows 86 TFLOP/s); two FP64 products of 200 rows and 51
+// columns: 69 us without matrix instructions and split, 7 + 4 us. With a split, the workgroups leave their sums
+// in fragment order at part[z][split][tile] and k_gram_sum adds them in that
+// order; without, they write C.
+constexpr int GT = 64;      // tile edge
+constexpr int GLD = GT + 16;  // LDS row
+constexpr int GR_MAX = 3;
+typedef double double4_t __attribute__((ext_vector_type(4)));
+typedef double double2_t __attribute__((ext_vector_type(2)));
+template <typename T>
+struct GramMats {
+  const T *A[GR_MAX];
+  T *C[GR_MAX];
+};
+template <typename T>
+struct Frag {
+  using vec = float4_t;
+  static constexpr int stage = 32;
+  static __device__ inline vec mfma(float a, float b, vec c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ inline int row(int lane, int v) { return 4 * (lane >> 4) + v; }
+};
+template <>
+struct Frag<double> {
+  using vec = double4_t;
+  static constexpr int stage = 16;
+  static __device__ inline vec mfma(double a, double b, vec c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ inline int row(int lane, int v) { return (lane >> 4) + 4 * v; }
+};
+
+// Columns c .. c + 3 of row kr, zero outside the matrix. The addresses are
+// clamped, not branched around, so that a stage's loads are in flight together.
+template <typename T, bool VEC>
+__device__ inline typename Frag<T>::vec gram_load4(const T *__restrict__ A, int64_t kr, int64_t K, int64_t N, int64_t c) {
+  typename Frag<T>::vec v;
+  const T *row = A + (kr < K ? kr : K - 1) * N;
+  if constexpr (VEC) {  // N a multiple of 4: a group of four is inside or outside
+    const T *src = row + (c < N ? c : N - 4);
+    if constexpr (sizeof(T) == 4) {
+      v = *reinterpret_cast<const float4_t *>(src);
+    } else {
+      const double2_t lo = reinterpret_cast<const double2_t *>(src)[0], hi = reinterpret_cast<const double2_t *>(src)[1];
+      v = double4_t{lo.x, lo.y, hi.x, hi.y};
+    }
+    const bool in = kr < K && c < N;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : T(0);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = row[c + e < N ? c + e : N - 1];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (kr < K && c + e < N) ? v[e] : T(0);
+  }
+  return v;
+}
+
+// Fragment of rows r0 .. r0 + 15 and columns c0 .. c0 + 15 to C and, mirrored,
+// below the diagonal; a diagonal tile keeps its upper triangle.
+template <typename T>
+__device__ inline void gram_store(T *__restrict__ C, int64_t ldc, int64_t N, T alpha, int zero_diag, bool diag_tile,
+                                  int64_t r0, int64_t c0, int lane, typename Frag<T>::vec acc) {
+  const int64_t c = c0 + (lane & 15);
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int64_t r = r0 + Frag<T>::row(lane, v);
+    if (r >= N || c >= N || (diag_tile && r > c)) continue;
+    const T val = (zero_diag && r == c) ? T(0) : alpha * acc[v];
+    C[r * ldc + c] = val;
+    if (r != c) C[c * ldc + r] = val;
+  }
+}
+
+template <typename T, bool VEC>
+__global__ __launch_bounds__(256) void k_gram_mfma(GramMats<T> ms, int64_t K, int64_t N, int64_t ldc, T alpha,
+                                                    int zero_diag, int nb, int per, int tiles, int64_t rows,
+                                                    T *__restrict__ part) {
+  using F = Frag<T>;
+  using vec = typename F::vec;
+  constexpr int ST = F::stage, PR = ST / 16;  // rows of a stage, groups of four per thread and operand
+  __shared__ __align__(32) T As[2][ST][GLD];
+  __shared__ __align__(32) T Bs[2][ST][GLD];
+  int bi, bj;
+  if (!tile_of(blockIdx.x, nb, per, &bi, &bj)) return;  // uniform per workgroup
+  const T *__restrict__ A = ms.A[blockIdx.z];
+  const bool diag_tile = bi == bj;
+  const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;
+  const int lr = tid >> 4, lc = (tid & 15) * 4;
+  const int64_t m0 = int64_t(bi) * GT, n0 = int64_t(bj) * GT;
+  const int64_t kb = int64_t(blockIdx.y) * rows, ke = kb + rows < K ? kb + rows : K;
+  vec acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = vec{0, 0, 0, 0};
+  vec ra[PR], rb[PR];
+  auto load = [&](int64_t k0) {
+#pragma unroll
+    for (int u = 0; u < PR; ++u) ra[u] = gram_load4<T, VEC>(A, k0 + u * 16 + lr, ke, N, m0 + lc);
+    if (!diag_tile) {
+#pragma unroll
+      for (int u = 0; u < PR; ++u) rb[u] = gram_load4<T, VEC>(A, k0 + u * 16 + lr, ke, N, n0 + lc);
+    }
+  };
+  auto put = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < PR; ++u) {
+      *reinterpret_cast<vec *>(&As[buf][u * 16 + lr][lc]) = ra[u];
+      if (!diag_tile) *reinterpret_cast<vec *>(&Bs[buf][u * 16 + lr][lc]) = rb[u];
+    }
+  };
+  int buf = 0;
+  if (kb < ke) {
+    load(kb);
+    put(0);
+  }
+  __syncthreads();
+  for (int64_t k0 = kb; k0 < ke; k0 += ST, buf ^= 1) {
+    if (k0 + ST < ke) load(k0 + ST);
+    const T(*pa)[GLD] = As[buf];
+    const T(*pb)[GLD] = diag_tile ? As[buf] : Bs[buf];
+#pragma unroll
+    for (int kk = 0; kk < ST; kk += 4) {
+      T a[2], b[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[i] = pa[kk + (lane >> 4)][wm * 32 + i * 16 + (lane & 15)];
+        b[i] = pb[kk + (lane >> 4)][wn * 32 + i * 16 + (lane & 15)];
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = F::mfma(a[i], b[j], acc[i][j]);
+    }
+    if (k0 + ST < ke) put(buf ^ 1);
+    __syncthreads();
+  }
+  const int id = (blockIdx.x % XCDS) * per + blockIdx.x / XCDS;
+  T *pt = part ? part + ((int64_t(blockIdx.z) * gridDim.y + blockIdx.y) * tiles + id) * (GT * GT) : nullptr;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      if (part)
+        *reinterpret_cast<vec *>(pt + ((i * 2 + j) * 256 + tid) * 4) = acc[i][j];
+      else
+        gram_store<T>(ms.C[blockIdx.z], ldc, N, alpha, zero_diag, diag_tile, m0 + wm * 32 + i * 16,
+                      n0 + wn * 32 + j * 16, lane, acc[i][j]);
+    }
+}
+
+// Fragments 2 i + j = blockIdx.x % 4 of tile blockIdx.x / 4: sums of the
+// splits, eight loads in flight, in FP64.
+template <typename T>
+__global__ __launch_bounds__(256) void k_gram_sum(GramMats<T> ms, int64_t N, int64_t ldc, T alpha, int zero_diag, int nb,
+                                                   int tiles, int splits, const T *__restrict__ part) {
+  using vec = typename Frag<T>::vec;
+  const int tile = blockIdx.x >> 2, ij = blockIdx.x & 3, tid = threadIdx.x;
+  int bi, bj;
+  if (!band_tile(tile, nb, &bi, &bj)) return;
+  const int64_t step = int64_t(tiles) * (GT * GT);
+  const T *p = part + int64_t(blockIdx.z) * splits * step + int64_t(tile) * (GT * GT) + (ij * 256 + tid) * 4;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int u0 = 0; u0 < splits; u0 += 8) {
+    vec v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const vec *>(p + (u0 + u < splits ? u0 + u : u0) * step);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] += u0 + u < splits ? double(v[u][e]) : 0.0;
+  }
+  const int wm = tid >> 7, wn = (tid >> 6) & 1;
+  gram_store<T>(ms.C[blockIdx.z], ldc, N, alpha, zero_diag, bi == bj, int64_t(bi) * GT + wm * 32 + (ij >> 1) * 16,
+                int64_t(bj) * GT + wn * 32 + (ij & 1) * 16, tid & 63,
+                vec{T(s[0]), T(s[1]), T(s[2]), T(s[3])});
+}
+
+// nm products of one shape. The K rows are split until about GR_WGS
+// workgroups per CU have work, in shares of at least two stages; without room
+// for the shares' sums (a scratch limit, a capture before the arena has grown)
+// the rows stay whole.
+constexpr int GR_WGS = 4;
+// FP32 products of this many 128x128 tiles per CU or more (P of about 5800 or
+// more) go to k_syrk_f32, which reads half the operand bytes per product: at
+// P = 8100 and 2000 rows it takes 1359 us, this kernel 1439 (P = 8190, rows
+// not aligned: 1744, 1958); at P = 4096 and 5000 rows 1107, this kernel 995.
+constexpr int F32_TILES_PER_CU = 4;
+template <typename T>
+int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64_t N, int64_t ldc, T alpha,
+              bool zero_diag) {
+  const int nb = int((N + GT - 1) / GT);
+  const int tiles = nb * (nb + 1) / 2;
+  const int per = (tiles + XCDS - 1) / XCDS;
+  constexpr int ST = Frag<T>::stage;
+  int64_t splits = std::max<int64_t>(1, int64_t(GR_WGS) * ctx->num_cus / (int64_t(tiles) * nm));
+  splits = std::max<int64_t>(1, std::min(splits, K / (2 * ST)));
+  const int64_t rows = ((K + splits - 1) / splits + ST - 1) / ST * ST;
+  splits = rows > 0 ? (K + rows - 1) / rows : 1;
+  T *part = nullptr;
+  if (splits > 1) {
+    const size_t need = carve_bytes(size_t(nm) * size_t(splits) * size_t(tiles) * GT * GT, sizeof(T));
+    bool room = need <= ctx->ws2_size;
+    if (!room && !(ctx->ws_limit && need > ctx->ws_limit)) {
+      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+      (void)hipStreamIsCapturing(ctx->stream, &cs);
+      room = cs == hipStreamCaptureStatusNone && ws2_reserve(ctx, need) == FPCA_OK;
+    }
+    if (room) part = static_cast<T *>(ctx->ws2);
+  }
+  const int64_t sp = part ? splits : 1;
+  bool vec = N % 4 == 0;
+  for (int m = 0; m < nm; ++m) vec = vec && (reinterpret_cast<uintptr_t>(ms.A[m]) & 15) == 0;
+  const dim3 grid(unsigned(per) * XCDS, unsigned(sp), unsigned(nm));
+  const int64_t share = part ? rows : K;
+  if (vec)
+    hipLaunchKernelGGL((k_gram_mfma<T, true>), grid, dim3(256), 0, ctx->stream, ms, K, N, ldc, alpha, int(zero_diag),
+                       nb, per, tiles, share, part);
+  else
+    hipLaunchKernelGGL((k_gram_mfma<T, false>), grid, dim3(256), 0, ctx->stream, ms, K, N, ldc, alpha, int(zero_diag),
+                       nb, per, tiles, share, part);
+  FPCA_LAUNCH_CHECK("gram_mfma");
+  if (part) {
+    hipLaunchKernelGGL(k_gram_sum<T>, dim3(unsigned(tiles) * 4, 1, unsigned(nm)), dim3(256), 0, ctx->stream, ms, N,
+                       ldc, alpha, int(zero_diag), nb, tiles, int(sp), part);
+    FPCA_LAUNCH_CHECK("gram_sum");
+  }
+  return FPCA_OK;
 }
 
 }  // namespace
@@ -580,7 +817,6 @@ int syrk_f32(fpca_context *ctx, const float *A, int64_t K, int64_t N, float *C, 
   const int tiles = nb * (nb + 1) / 2;
   const int per = (tiles + XCDS - 1) / XCDS;  // tiles per XCD
   const unsigned grid = unsigned(per) * XCDS;
-  bool vec = (N % 4 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
   if (prec == FPCA_PREC_BF16X3) {
     const int64_t Kp = ((K + 63) / 64) * 64;
     const int64_t nsteps = Kp / 64;
@@ -629,7 +865,10 @@ int syrk_f32(fpca_context *ctx, const float *A, int64_t K, int64_t N, float *C, 
                          alpha, int(zero_diag));
       FPCA_LAUNCH_CHECK("syrk_fixup");
     }
+  } else if (tiles < F32_TILES_PER_CU * ctx->num_cus) {
+    return gram_mfma<float>(ctx, 1, GramMats<float>{{A}, {C}}, K, N, ldc, alpha, zero_diag);
   } else {
+    const bool vec = (N % 4 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
     if (vec)
       hipLaunchKernelGGL((k_syrk_f32<true>), dim3(grid), dim3(256), 0, ctx->stream, A, K, N, C, ldc, alpha,
                          int(zero_diag), nb, per);
@@ -644,19 +883,35 @@ int syrk_f32(fpca_context *ctx, const float *A, int64_t K, int64_t N, float *C, 
 int syrk_f64(fpca_context *ctx, const double *A, int64_t K, int64_t N, double *C, int64_t ldc, double alpha,
              bool zero_diag) {
   if (N <= 0) return FPCA_OK;
-  dim3 grid(unsigned((N + 63) / 64), unsigned((N + 63) / 64));
-  hipLaunchKernelGGL((k_gram_valu<double, double, double>), grid, dim3(256), 0, ctx->stream, A, K, N, C, ldc,
-                     alpha, int(zero_diag));
-  FPCA_LAUNCH_CHECK("syrk_f64");
+  return gram_mfma<double>(ctx, 1, GramMats<double>{{A}, {C}}, K, N, ldc, alpha, zero_diag);
+}
+
+int syrk_set(fpca_context *ctx, int nm, const float *const *A, int64_t K, int64_t N, float *const *C, float alpha,
+             bool zero_diag, int prec) {
+  const int64_t nb = (N + TB - 1) / TB;
+  if (prec != FPCA_PREC_BF16X3 && N > 0 && nm <= GR_MAX && nb * (nb + 1) / 2 < F32_TILES_PER_CU * ctx->num_cus) {
+    GramMats<float> ms{};
+    for (int m = 0; m < nm; ++m) ms.A[m] = A[m], ms.C[m] = C[m];
+    return gram_mfma<float>(ctx, nm, ms, K, N, N, alpha, zero_diag);
+  }
+  for (int m = 0; m < nm; ++m)
+    if (int rc = syrk_f32(ctx, A[m], K, N, C[m], N, alpha, zero_diag, prec)) return rc;
   return FPCA_OK;
+}
+
+int syrk_set(fpca_context *ctx, int nm, const double *const *A, int64_t K, int64_t N, double *const *C, double alpha,
+             bool zero_diag, int) {
+  if (N <= 0) return FPCA_OK;
+  GramMats<double> ms{};
+  for (int m = 0; m < nm; ++m) ms.A[m] = A[m], ms.C[m] = C[m];
+  return gram_mfma<double>(ctx, nm, ms, K, N, N, alpha, zero_diag);
 }
 
 // Exact integer Gram product of per-curve count rows (int32) into int64.
 int gram_i32(fpca_context *ctx, const int32_t *A, int64_t K, int64_t N, int64_t *C) {
   if (N <= 0) return FPCA_OK;
   dim3 grid(unsigned((N + 63) / 64), unsigned((N + 63) / 64));
-  hipLaunchKernelGGL((k_gram_valu<int32_t, int64_t, int64_t>), grid, dim3(256), 0, ctx->stream, A, K, N, C, N,
-                     int64_t(1), 0);
+  hipLaunchKernelGGL(k_gram_i32, grid, dim3(256), 0, ctx->stream, A, K, N, C);
   FPCA_LAUNCH_CHECK("gram_i32");
   return FPCA_OK;
 }

@@ -199,3 +199,28 @@ def test_staged_smoother_and_cv(torch, F, h, M, hb, dt):
             want[i, f] = oracle.cv_score(Q[f + 1].astype(np.float64), G[f + 1].astype(np.float64),
                                          C[f + 1].astype(np.float64), Gh)
     np.testing.assert_allclose(got, want, rtol=1e-9 if dt == "f64" else 1e-5)
+
+
+@pytest.mark.parametrize("dtype,n,M", [("f32", 1, 3), ("f32", 33, 64), ("f32", 200, 65), ("f32", 1000, 130),
+                                       ("f32", 129, 260), ("f32", 17, 5764), ("f32", 16, 5761), ("f64", 1, 3),
+                                       ("f64", 17, 64), ("f64", 200, 101),
+                                       ("f64", 1000, 128), ("f64", 65, 258)])
+def test_gram_tiles(torch, F, h, dtype, n, M):
+    """64-column tiles, 16- or 32-row stages, shares of the rows, columns in groups of four or not, and the
+    128-column tiles of large FP32 products. The bar is
+    the rounding bound of an n-term sum, (n + 4) u |Y|^T |Y|, entry by entry; the product is exactly symmetric."""
+    _say(f"gram {dtype} n={n} M={M}")
+    rng = np.random.default_rng(n + M)
+    npt, tt, code, prec = ((np.float32, torch.float32, F.FPCA_F32, F.FPCA_PREC_F32) if dtype == "f32" else
+                           (np.float64, torch.float64, F.FPCA_F64, F.FPCA_PREC_F64))
+    y = (rng.standard_normal((n, M)) * 2 + 1).astype(npt)
+    w = 1.0 / (M * (M - 1))
+    S = torch.full((M, M), float("nan"), dtype=tt, device="cuda:0")
+    F.fpca_bin(h, F.Grid((M,)), F.FPCA_BIN_COV, F.FPCA_COMMON_GRID, code, prec, n, None, None, dev(torch, y), None, 0,
+               None, S)
+    got = S.cpu().numpy().astype(np.float64)
+    y64 = y.astype(np.float64)
+    ref, amp = w * (y64.T @ y64), w * (np.abs(y64).T @ np.abs(y64))
+    np.fill_diagonal(ref, 0.0)
+    assert np.array_equal(got, got.T)
+    assert np.all(np.abs(got - ref) <= (n + 4) * np.finfo(npt).eps * amp)
