@@ -3,7 +3,8 @@
 // A X is computed as W^1/2 (Gamma (W^1/2 X)).
 //
 //   test matrix  : counter-based normals (splitmix64 + Box-Muller), P x r
-//   products     : Gamma X on MFMA (FP32) with split K, FP64 reduction
+//   products     : Gamma X on MFMA (FP32, BF16x3 or FP64) with split K, FP64
+//                  reduction
 //   orthonormal  : CholeskyQR in FP64 between products, CholeskyQR2 before
 //                  the Rayleigh-Ritz step (columns that become numerically
 //                  dependent are dropped: their basis vector is set to 0);
@@ -12,6 +13,7 @@
 //   Rayleigh-Ritz: B = Q^T A Q in FP64, eigenpairs by a one-workgroup
 //                  parallel-ordered cyclic Jacobi method in FP64
 //   finalize     : psi = Q U, phi = psi / sqrt(w), sign rule, FVE.
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -315,17 +317,90 @@ __global__ __launch_bounds__(256) void k_panel_bf16x3(int64_t P, const float *__
   }
 }
 
-// FP64 product for FP64 storage (small grids): thread per (p, j); the Gamma
-// row stays in cache across the rp threads that share p.
-__global__ void k_panel_f64(int64_t P, int rp, const double *__restrict__ G, const double *__restrict__ X,
-                            double *__restrict__ Yraw) {
-  int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (e >= P * rp) return;
-  const int64_t p = e / rp;
-  const int j = int(e % rp);
-  double s = 0.0;
-  for (int64_t q = 0; q < P; ++q) s += G[p * P + q] * X[q * rp + j];
-  Yraw[e] = s;
+// The partial products for FP64 storage on FP64 MFMA 16x16x4: workgroup = (64
+// rows of Gamma, K chunk), four wavefronts x 16 rows. Bound by the reading of
+// Gamma where it is large (P = 4096: 134 MB), by latency where it is small.
+// Tiles of 32 (r > 32: 16) nodes q in two LDS buffers, the next one on its way in
+// registers; addresses past the edges are clamped and the values set to 0, so
+// that a tile's loads are in flight together (rows past P are not written).
+// One thread per entry over all q, without matrix instructions, took 13.7 us
+// at P = 51 (3.1 us here); whole decompositions in FP64 went from 2469 to
+// 303 us at P = 1600 and from 6297 to 479 us at P = 4096 (both r = 32).
+typedef double double4_t __attribute__((ext_vector_type(4)));
+template <int RB>
+__global__ __launch_bounds__(256) void k_panel_f64(int64_t P, const double *__restrict__ G,
+                                                    const double *__restrict__ X, int64_t kchunk,
+                                                    double *__restrict__ part) {
+  constexpr int RP = RB * 16;
+  constexpr int KT = RB <= 2 ? 32 : 16;
+  constexpr int NG = KT / 16, GR = 1024 / KT;  // rows of Gamma per thread, rows per pass
+  constexpr int NX = KT * RP / 256;  // basis entries per thread and tile
+  __shared__ double Gs[2][64][KT + 1];
+  __shared__ double Xs[2][KT][RP + 16];  // the two q rows of a half wavefront start 32 banks apart
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t c0 = int64_t(blockIdx.x) * 64;
+  const int64_t k0 = int64_t(blockIdx.y) * kchunk;
+  const int64_t k1 = min(P, k0 + kchunk);
+  double4_t acc[2][RB];  // two sets alternate over K steps: independent MFMA chains
+#pragma unroll
+  for (int b = 0; b < RB; ++b) acc[0][b] = acc[1][b] = double4_t{0.0, 0.0, 0.0, 0.0};
+  const int gp = tid / (KT / 4), gq = (tid % (KT / 4)) * 4;  // rows gp, gp + GR, .., nodes gq..gq+3
+  double rg[NG][4], rx[NX];
+  auto load = [&](int64_t kb) {
+#pragma unroll
+    for (int h = 0; h < NG; ++h) {
+      const double *row = G + min(c0 + gp + GR * h, P - 1) * P;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rg[h][e] = row[min(kb + gq + e, k1 - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < NX; ++u) rx[u] = X[min(kb * RP + tid + 256 * u, k1 * RP - 1)];
+#pragma unroll
+    for (int h = 0; h < NG; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) rg[h][e] = kb + gq + e < k1 ? rg[h][e] : 0.0;
+#pragma unroll
+    for (int u = 0; u < NX; ++u) rx[u] = kb * RP + tid + 256 * u < k1 * RP ? rx[u] : 0.0;
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int h = 0; h < NG; ++h)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Gs[buf][gp + GR * h][gq + e] = rg[h][e];
+#pragma unroll
+    for (int u = 0; u < NX; ++u) Xs[buf][(tid + 256 * u) / RP][(tid + 256 * u) % RP] = rx[u];
+  };
+  int buf = 0;
+  if (k0 < k1) {
+    load(k0);
+    store(0);
+  }
+  __syncthreads();
+  for (int64_t kb = k0; kb < k1; kb += KT) {
+    const bool more = kb + KT < k1;
+    if (more) load(kb + KT);
+#pragma unroll
+    for (int kk = 0; kk < KT; kk += 4) {
+      const int kr = kk + (lane >> 4);
+      const double b = Gs[buf][wave * 16 + (lane & 15)][kr];
+#pragma unroll
+      for (int mb = 0; mb < RB; ++mb)
+        acc[(kk >> 2) & 1][mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[buf][kr][mb * 16 + (lane & 15)], b,
+                                                                     acc[(kk >> 2) & 1][mb], 0, 0, 0);
+    }
+    if (more) store(buf ^ 1);
+    __syncthreads();
+    buf ^= 1;
+  }
+  // D[j][p]: row j = mb*16 + lane/16 + 4 v, column p = c0 + wave*16 + lane%16.
+  const int64_t p = c0 + wave * 16 + (lane & 15);
+  if (p < P) {
+    double *dst = part + (int64_t(blockIdx.y) * P + p) * RP;
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) dst[mb * 16 + (lane >> 4) + 4 * v] = acc[0][mb][v] + acc[1][mb][v];
+  }
 }
 
 constexpr int ROWS = 16;  // rows per workgroup of the row kernels
@@ -349,13 +424,13 @@ __device__ inline void rows_gram(const double *A, const double *B, double *__res
 }
 
 // Finishes a product, ROWS rows per workgroup: Y[p, j] = sqrt(w_p) * (sum of
-// the K-split partials in split order, or Yraw for FP64 storage), then the
-// rows' partial Gram matrix:
+// the K-split partials in split order; the covariance operator's product is
+// one such partial), then the rows' partial Gram matrix:
 //   MODE 1: part = Y_c^T Y_c;  MODE 2: part = Q_c^T Y_c  (Rayleigh-Ritz).
 // A thread loads sixteen splits of all its entries at once.
-template <int MODE, int RP>
-__global__ __launch_bounds__(RT) void k_rows_gram(int64_t P, int nsplit, const float *__restrict__ part32,
-                                                   const double *__restrict__ Yraw, const double *__restrict__ sw,
+template <int MODE, int RP, typename T>
+__global__ __launch_bounds__(RT) void k_rows_gram(int64_t P, int nsplit, const T *__restrict__ part,
+                                                   const double *__restrict__ sw,
                                                    const double *__restrict__ Q, double *__restrict__ Y,
                                                    double *__restrict__ gpart) {
   constexpr int LD = RP + 1;
@@ -369,27 +444,19 @@ __global__ __launch_bounds__(RT) void k_rows_gram(int64_t P, int nsplit, const f
   double acc[NE];
 #pragma unroll
   for (int u = 0; u < NE; ++u) acc[u] = 0.0;
-  if (part32) {
-    for (int c = 0; c < nsplit; c += 16) {
-      float v[16][NE];
+  for (int c = 0; c < nsplit; c += 16) {
+    T v[16][NE];
 #pragma unroll
-      for (int s = 0; s < 16; ++s)
+    for (int s = 0; s < 16; ++s)
 #pragma unroll
-        for (int u = 0; u < NE; ++u) {
-          const int64_t o = base + tid + RT * u;
-          v[s][u] = (c + s < nsplit && o < lim) ? part32[int64_t(c + s) * lim + o] : 0.f;
-        }
+      for (int u = 0; u < NE; ++u) {
+        const int64_t o = base + tid + RT * u;
+        v[s][u] = (c + s < nsplit && o < lim) ? part[int64_t(c + s) * lim + o] : T(0);
+      }
 #pragma unroll
-      for (int s = 0; s < 16; ++s)
+    for (int s = 0; s < 16; ++s)
 #pragma unroll
-        for (int u = 0; u < NE; ++u) acc[u] += double(v[s][u]);
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < NE; ++u) {
-      const int64_t o = base + tid + RT * u;
-      acc[u] = o < lim ? Yraw[o] : 0.0;
-    }
+      for (int u = 0; u < NE; ++u) acc[u] += double(v[s][u]);
   }
 #pragma unroll
   for (int u = 0; u < NE; ++u) {
@@ -472,16 +539,10 @@ __device__ inline double rcp_nr(double x) {
 // still read its old values. Rinv[c][r] = L^{-1}[r][c] (R = L^T) with the
 // columns of dropped vectors zeroed; act[j] = 1 for kept columns.
 template <int RP>
-__global__ __launch_bounds__(CT) void k_chol(const double *__restrict__ G, double *__restrict__ Rinv,
-                                             int *__restrict__ act) {
+__device__ inline void chol_wg(double *M, double (*Lodd)[RP], double *Dodd, double *diag, int *keep,
+                               const double *__restrict__ G, double *__restrict__ Rinv, int ldr, int tid) {
   static_assert(RP % 2 == 0, "steps go in pairs");
   constexpr int LD = 2 * RP + 1;
-  __shared__ double M[RP * LD];
-  __shared__ double Lodd[RP / 2][RP];  // I part of rows 1, 3, 5, ...
-  __shared__ double Dodd[RP / 2];      // pivots of rows 1, 3, 5, ...
-  __shared__ double diag[RP];
-  __shared__ int keep[RP];
-  const int tid = threadIdx.x;
   for (int e = tid; e < RP * RP; e += CT) {
     const int r = e / RP, c = e % RP;
     M[r * LD + c] = G[e];
@@ -528,9 +589,20 @@ __global__ __launch_bounds__(CT) void k_chol(const double *__restrict__ G, doubl
     const int c = e / RP, r = e % RP;
     const double pr = (r & 1) ? Dodd[r / 2] : M[r * LD + r];
     const double lv = (r & 1) ? Lodd[r / 2][c] : M[r * LD + RP + c];
-    Rinv[e] = keep[r] ? lv * rsqrt_nr(pr) : 0.0;
+    Rinv[c * ldr + r] = keep[r] ? lv * rsqrt_nr(pr) : 0.0;
   }
-  if (tid < RP) act[tid] = keep[tid];
+}
+
+template <int RP>
+__global__ __launch_bounds__(CT) void k_chol(const double *__restrict__ G, double *__restrict__ Rinv,
+                                             int *__restrict__ act) {
+  __shared__ double M[RP * (2 * RP + 1)];
+  __shared__ double Lodd[RP / 2][RP];  // I part of rows 1, 3, 5, ...
+  __shared__ double Dodd[RP / 2];      // pivots of rows 1, 3, 5, ...
+  __shared__ double diag[RP];
+  __shared__ int keep[RP];
+  chol_wg<RP>(M, Lodd, Dodd, diag, keep, G, Rinv, RP, threadIdx.x);
+  if (threadIdx.x < RP) act[threadIdx.x] = keep[threadIdx.x];
 }
 
 // Q = Y Rinv in FP64 for ROWS rows per workgroup. With GRAM the rows' partial
@@ -584,6 +656,179 @@ __global__ __launch_bounds__(RT) void k_rows_apply(int64_t P, const double *__re
   }
   __syncthreads();
   rows_gram<RP>(Ys, Ys, gpart + int64_t(blockIdx.x) * RP * RP, tid);
+}
+
+// The whole iteration on grids of SP_MAX nodes or fewer and r <= 32, in one
+// workgroup: setup, products, CholeskyQR, and at the end Q (in Q) and Q^T A Q
+// (in G). There every step takes a microsecond or two, and the general path's
+// five launches per step cost more than the step: with power_iters = 2 a
+// decomposition of 120 FP32 nodes with r = 12 takes 154 us with the 34
+// launches that come before k_jacobi, 116 us with this one (49 of them here
+// at P = 51; bound by the chain of the factorizations' steps and barriers).
+// Wavefront w keeps its 16 rows x K share of Gamma in registers as FP64 MFMA
+// operands for all the products; the basis, the product and the factorization
+// are in LDS. FP64 throughout, also for FP32 storage.
+constexpr int SP_MAX = 128;
+template <int RP>
+struct SmallLds {
+  static constexpr int LD = RP + 1;
+  static constexpr int GS = RP == 16 ? 8 : 4;  // shares of a Gram product's rows
+  double X[SP_MAX * LD], Y[SP_MAX * LD];
+  double sw[SP_MAX];
+  union {
+    double red[2 * SP_MAX * RP];  // shares of a product: [split][p][j]
+    struct {
+      double M[RP * (2 * RP + 1)], Lodd[RP / 2][RP], Dodd[RP / 2], diag[RP];
+      int keep[RP];
+      double gp[GS][RP * RP], G[RP * RP];
+      double Ri[RP * LD];
+    };
+  };
+};
+
+template <typename T, int RP>
+__global__ __launch_bounds__(CT) void k_subspace_small(uint64_t seed, int P, int r, int nprod,
+                                                        const T *__restrict__ gamma,
+                                                        const double *__restrict__ quad_w, double wv,
+                                                        const uint8_t *__restrict__ mask, double *__restrict__ w,
+                                                        double *__restrict__ Q, double *__restrict__ G,
+                                                        int *__restrict__ act) {
+  constexpr int LD = RP + 1, RB = RP / 16;
+  constexpr int NS = SP_MAX / 4 / 2;  // K steps of a wavefront: two shares at SP_MAX nodes, more on smaller grids
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  SmallLds<RP> &S = *reinterpret_cast<SmallLds<RP> *>(lds_raw);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int blocks = (P + 15) / 16, shares = min(16 / blocks, (P + 3) / 4);
+  const int steps = ((P + 3) / 4 + shares - 1) / shares;  // <= NS
+  const int blk = wave % blocks, share = wave / blocks;   // wavefronts past the last share: nothing to do
+  for (int e = tid; e < (SP_MAX - P) * LD; e += CT) S.X[P * LD + e] = S.Y[P * LD + e] = 0.0;  // rows past P stay 0
+  for (int e = tid; e < P * RP; e += CT) {
+    const int p = e / RP, j = e % RP;
+    const double wp = quad_w ? quad_w[p] : ((mask && !mask[p]) ? 0.0 : wv);
+    const double sq = sqrt(wp);
+    if (j == 0) {
+      w[p] = wp;
+      S.sw[p] = sq;
+    }
+    S.X[p * LD + j] = j < r ? sq * normal_at(seed, uint64_t(j) * uint64_t(P) + uint64_t(p)) : 0.0;
+  }
+  double g[NS];
+  {
+    const T *row = gamma + int64_t(min(blk * 16 + (lane & 15), P - 1)) * P;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      const int q = (share * steps + s) * 4 + (lane >> 4);
+      g[s] = double(row[min(q, P - 1)]);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s) g[s] = (share * steps + s) * 4 + (lane >> 4) < P && s < steps ? g[s] : 0.0;
+  }
+  __syncthreads();
+  // out = W^1/2 Gamma X
+  auto product = [&](double *out) {
+    if (share < shares) {
+      double4_t acc[RB];
+#pragma unroll
+      for (int b = 0; b < RB; ++b) acc[b] = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int s0 = 0; s0 < NS; s0 += 4) {
+        if (s0 < steps) {  // uniform; four steps' reads together, g = 0 past the share
+          double x[4][RB];
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+              x[s][b] = S.X[min((share * steps + s0 + s) * 4 + (lane >> 4), SP_MAX - 1) * LD + b * 16 + (lane & 15)];
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+              acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[s][b], g[s0 + s], acc[b], 0, 0, 0);
+        }
+      }
+      const int p = blk * 16 + (lane & 15);
+      if (p < P)
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) S.red[(share * P + p) * RP + b * 16 + (lane >> 4) + 4 * v] = acc[b][v];
+    }
+    __syncthreads();
+    for (int e = tid; e < P * RP; e += CT) {
+      double sum = 0.0;
+#pragma unroll 4
+      for (int u = 0; u < shares; ++u) sum += S.red[u * P * RP + e];
+      out[(e / RP) * LD + e % RP] = S.sw[e / RP] * sum;
+    }
+    __syncthreads();
+  };
+  // S.G = A^T B: wavefront = one 16x16 block and one of GS shares of the rows
+  constexpr int GS = SmallLds<RP>::GS;
+  auto gram = [&](const double *A, const double *B) {
+    if (wave < RB * RB * GS) {
+      const int ba = wave % (RB * RB) / RB * 16 + (lane & 15), bb = wave % RB * 16 + (lane & 15);
+      const int gsh = wave / (RB * RB);
+      double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 4
+      for (int p4 = gsh * 4; p4 < P; p4 += GS * 4) {
+        const int p = p4 + (lane >> 4);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(A[p * LD + ba], B[p * LD + bb], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) S.gp[gsh][((ba & ~15) + (lane >> 4) + 4 * v) * RP + bb] = acc[v];
+    }
+    __syncthreads();
+    for (int e = tid; e < RP * RP; e += CT) {
+      double sum = S.gp[0][e];
+#pragma unroll
+      for (int u = 1; u < GS; ++u) sum += S.gp[u][e];
+      S.G[e] = sum;
+    }
+    __syncthreads();
+  };
+  // out = A R^-1, times sqrt(w) if scale: wavefront = 16 rows x 16 columns
+  auto apply = [&](const double *A, double *out, bool scale) {
+    for (int c = wave; c < blocks * RB; c += CT / 64) {
+      const int p = c / RB * 16 + (lane & 15), j0 = c % RB * 16;
+      double4_t acc = double4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i4 = 0; i4 < RP; i4 += 4) {
+        const int i = i4 + (lane >> 4);
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(S.Ri[i * LD + j0 + (lane & 15)], A[p * LD + i], acc, 0, 0, 0);
+      }
+      if (p < P) {
+        const double f = scale ? S.sw[p] : 1.0;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) out[p * LD + j0 + (lane >> 4) + 4 * v] = f * acc[v];
+      }
+    }
+    __syncthreads();
+  };
+  for (int it = 0;; ++it) {
+    const bool basis = it + 1 == nprod, last = it == nprod;
+    product(last ? S.X : S.Y);
+    if (last) break;
+    // one CholeskyQR, for the basis of the Rayleigh-Ritz step two
+    for (int pass = 0; pass < (basis ? 2 : 1); ++pass) {
+      const double *A = pass ? S.X : S.Y;
+      gram(A, A);
+      chol_wg<RP>(S.M, S.Lodd, S.Dodd, S.diag, S.keep, S.G, S.Ri, LD, tid);
+      __syncthreads();
+      apply(A, pass ? S.Y : S.X, !basis);
+    }
+    if (basis) {
+      if (tid < RP) act[tid] = S.keep[tid];
+      for (int e = tid; e < P * RP; e += CT) {
+        const int p = e / RP, j = e % RP;
+        const double q = S.Y[p * LD + j];
+        Q[e] = q;
+        S.X[p * LD + j] = S.sw[p] * q;
+      }
+      __syncthreads();
+    }
+  }
+  gram(S.Y, S.X);
+  for (int e = tid; e < RP * RP; e += CT) G[e] = S.G[e];
 }
 
 // Jacobi rotation of the pair (p, q) from b_pp, b_qq, b_pq, without branches:
@@ -910,19 +1155,28 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
   const bool f32 = sizeof(T) == 4;
   // K split of the panel product: about two workgroups per compute unit
   // (fewer splits read fewer partials back; at P = 4096, 8 splits measured
-  // 29 us per product and Gram against 31 us with 16 and 37 us with 4)
+  // 29 us per product and Gram against 31 us with 16 and 37 us with 4), and at
+  // most the 16 that k_rows_gram loads at once: the whole decomposition at
+  // P = 1024, r = 16 takes 182 us with 16 splits, 215 with 32 (FP64 169, 184)
   const int64_t colblocks = (P + 63) / 64;
   int64_t nsplit = (2 * int64_t(ctx->num_cus) + colblocks - 1) / colblocks;
-  if (nsplit < 1) nsplit = 1;
+  nsplit = std::max<int64_t>(1, std::min<int64_t>(nsplit, 16));
   int64_t kchunk = ((P + nsplit - 1) / nsplit + 31) / 32 * 32;
   nsplit = (P + kchunk - 1) / kchunk;
   const int64_t ngram = (P + ROWS - 1) / ROWS;
   const int64_t nphi = (P + 255) / 256;
+  // r > 32 or more nodes: basis and product no longer fit one workgroup's LDS
+  const bool small = P <= SP_MAX && RP <= 32 && !op;
+  if (op || small) nsplit = 1;  // the operator writes the whole product; the small kernel has no partials
   size_t need = 2 * carve_bytes(P, 8) + carve_bytes(P * RP, sizeof(T)) + 3 * carve_bytes(P * RP, 8) +
                 carve_bytes(ngram * RP * RP, 8) + 2 * carve_bytes(RP * RP, 8) + carve_bytes(RP, 4) +
                 carve_bytes(RP * k, 8) +
                 carve_bytes(2 * k, 8) + carve_bytes(P * k, 8) + carve_bytes(nphi * k * 3, 8);
-  need += f32 ? carve_bytes(nsplit * P * RP, 4) : carve_bytes(P * RP, 8);
+  if (!f32 && ctx->ws_limit && need + carve_bytes(nsplit * P * RP, 8) > ctx->ws_limit) {
+    nsplit = 1;  // no room for the shares of a split
+    kchunk = P;
+  }
+  need += carve_bytes(nsplit * P * RP, sizeof(T));
   if (int rc = ws_reserve(ctx, need)) return rc;
   Carver cv{static_cast<char *>(ctx->ws), 0, ctx->ws_size};
   double *w = cv.take<double>(P);
@@ -940,12 +1194,22 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
   double *fve_d = ev_d + k;
   double *phi = cv.take<double>(P * k);
   double *red = cv.take<double>(nphi * k * 3);
-  float *part = f32 ? cv.take<float>(nsplit * P * RP) : nullptr;
-  double *Yraw = f32 ? nullptr : cv.take<double>(P * RP);
+  T *part = cv.take<T>(nsplit * P * RP);
 
-  {
-    double wv = 1.0;
-    for (int q = 0; q < grid->d; ++q) wv /= double(grid->M[q] - 1);
+  double wv = 1.0;
+  for (int q = 0; q < grid->d; ++q) wv /= double(grid->M[q] - 1);
+  const int nprod = 1 + 2 * power_iters;
+  if constexpr (RP <= 32) {
+    if (small) {
+      constexpr int lds = int(sizeof(SmallLds<RP>));
+      FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_subspace_small<T, RP>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+      hipLaunchKernelGGL((k_subspace_small<T, RP>), dim3(1), dim3(CT), lds, ctx->stream, seed, int(P), r, nprod, gamma,
+                         quad_w, wv, grid->mask, w, Q, G, act);
+      FPCA_LAUNCH_CHECK("subspace_small");
+    }
+  }
+  if (!small) {
     hipLaunchKernelGGL(k_setup<T>, dim3(nb(P * RP)), dim3(256), 0, ctx->stream, seed, P, r, RP, quad_w, wv,
                        grid->mask, w, sw, X);
     FPCA_LAUNCH_CHECK("setup");
@@ -977,19 +1241,19 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
     } else {
       if (op) {
         // the covariance operator: Gamma X without Gamma
-        if (int rc = covop_apply_internal(op, RP, (const double *)X, Yraw)) return rc;
+        if (int rc = covop_apply_internal(op, RP, (const double *)X, (double *)part)) return rc;
       } else {
-        hipLaunchKernelGGL(k_panel_f64, dim3(nb(P * RP)), dim3(256), 0, ctx->stream, P, RP, (const double *)gamma,
-                           (const double *)X, Yraw);
+        hipLaunchKernelGGL(k_panel_f64<RP / 16>, dim3((unsigned)colblocks, (unsigned)nsplit), dim3(256), 0, ctx->stream,
+                           P, (const double *)gamma, (const double *)X, kchunk, part);
         FPCA_LAUNCH_CHECK("panel_f64");
       }
     }
     if (mode == 2)
-      hipLaunchKernelGGL((k_rows_gram<2, RP>), dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit), part,
-                         Yraw, sw, Q, out, gpart);
+      hipLaunchKernelGGL((k_rows_gram<2, RP, T>), dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit),
+                         part, sw, Q, out, gpart);
     else
-      hipLaunchKernelGGL((k_rows_gram<1, RP>), dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit), part,
-                         Yraw, sw, Q, out, gpart);
+      hipLaunchKernelGGL((k_rows_gram<1, RP, T>), dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit),
+                         part, sw, Q, out, gpart);
     FPCA_LAUNCH_CHECK("rows_gram");
     return FPCA_OK;
   };
@@ -1027,15 +1291,16 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
 
   // orthonormalizations: single CholeskyQR between products, CholeskyQR2 for
   // the basis of the Rayleigh-Ritz step
-  const int nprod = 1 + 2 * power_iters;
-  for (int it = 0; it < nprod; ++it) {
-    if (int rc = product(Y, 1)) return rc;
-    if (int rc = (it + 1 < nprod) ? cholqr1() : cholqr2()) return rc;
+  if (!small) {
+    for (int it = 0; it < nprod; ++it) {
+      if (int rc = product(Y, 1)) return rc;
+      if (int rc = (it + 1 < nprod) ? cholqr1() : cholqr2()) return rc;
+    }
+    if (int rc = product(Z, 2)) return rc;  // Z = A Q and the partials of Q^T Z
+    hipLaunchKernelGGL(k_sum_gram<RP>, dim3(unsigned((RP * RP + 256 / SG - 1) / (256 / SG))), dim3(256), 0,
+                       ctx->stream, int(ngram), gpart, G);
+    FPCA_LAUNCH_CHECK("sum_gram");
   }
-  if (int rc = product(Z, 2)) return rc;  // Z = A Q and the partials of Q^T Z
-  hipLaunchKernelGGL(k_sum_gram<RP>, dim3(unsigned((RP * RP + 256 / SG - 1) / (256 / SG))), dim3(256), 0, ctx->stream,
-                     int(ngram), gpart, G);
-  FPCA_LAUNCH_CHECK("sum_gram");
   hipLaunchKernelGGL(k_jacobi<RP>, dim3(1), dim3((RP / 2) * (RP / 2)), 0, ctx->stream, G, act, k, ev_d, fve_d, Uk);
   FPCA_LAUNCH_CHECK("jacobi");
   hipLaunchKernelGGL(k_phi<RP>, dim3(unsigned(nphi), unsigned(k)), dim3(256), 0, ctx->stream, P, k, Q, Uk, w, phi,

@@ -224,3 +224,33 @@ def test_gram_tiles(torch, F, h, dtype, n, M):
     np.fill_diagonal(ref, 0.0)
     assert np.array_equal(got, got.T)
     assert np.all(np.abs(got - ref) <= (n + 4) * np.finfo(npt).eps * amp)
+
+
+@pytest.mark.parametrize("P,k,p,q", [(9, 3, 5, 2), (16, 4, 8, 0), (17, 4, 8, 2), (51, 3, 10, 2), (65, 20, 10, 2),
+                                     (113, 4, 12, 1), (127, 20, 10, 2), (128, 5, 11, 2), (129, 5, 11, 2),
+                                     (190, 20, 12, 1)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_eig_small_grids(torch, F, h, P, k, p, q, dt):
+    """Up to 128 nodes and 32 basis columns the iteration runs in one workgroup: 1 to 8 blocks of 16 rows, the
+    nodes in 2 to 16 shares; past that the split products, the last chunk of 129 nodes one node wide. Bars of the
+    decompositions at ordinary sizes."""
+    _say(f"eig small P={P} k={k} p={p} q={q} {dt}")
+    rng = np.random.default_rng(P + k)
+    V = np.linalg.qr(rng.standard_normal((P, P)))[0]
+    npdt, tdt, code, prec = ((np.float64, torch.float64, F.FPCA_F64, F.FPCA_PREC_F64) if dt == "f64" else
+                             (np.float32, torch.float32, F.FPCA_F32, F.FPCA_PREC_F32))
+    Gam = (V * 1.5 ** -np.arange(P)) @ V.T
+    Gam = ((Gam + Gam.T) / 2).astype(npdt)
+    om = oracle.quad_weights((P,), rule="trapezoid")
+    ef = torch.empty(k, P, dtype=tdt, device="cuda:0")
+    ev, fve = F.fpca_eig_randomized(h, code, prec, F.Grid((P,)), dev(torch, Gam), dev(torch, om), k, p, q, 11, ef)
+    rev, rphi, rfve = oracle.eig_randomized(Gam.astype(np.float64), om, k, p, q, 11)
+    tol = 1e-10 if dt == "f64" else 1e-5
+    assert np.abs(ev - rev).max() <= tol * np.abs(rev).max()
+    assert np.abs(fve - rfve).max() <= tol
+    phi = ef.cpu().numpy().astype(np.float64).T
+    for j in range(k):
+        gap = min(abs(rev[j] - rev[j - 1]) if j else np.inf, abs(rev[j] - rev[j + 1]) if j + 1 < k else np.inf)
+        scale = max(1.0, 0.1 * rev[0] / gap) if np.isfinite(gap) else 1.0
+        err = min(np.abs(phi[:, j] - rphi[:, j]).max(), np.abs(phi[:, j] + rphi[:, j]).max())
+        assert err <= 100 * tol * scale * np.abs(rphi[:, j]).max(), (j, err)
