@@ -9,6 +9,7 @@
 // (b_ij the binning-weight vector of t_ij): per-curve rows scaled by sqrt(w_i),
 // one symmetric Gram product on MFMA, then the j = l terms subtracted.
 // Covariance, common grid: G = Y^T Y / (P(P-1)) with the diagonal removed.
+#include <algorithm>
 #include <cmath>
 
 #include "binrule.hpp"
@@ -68,14 +69,15 @@ __global__ __launch_bounds__(256) void k_bin_mean(GridDims g, int64_t n, const i
 // from all workgroups queue on the same addresses.
 constexpr int MB_PMAX = 2048;
 constexpr int MB_WGS = 256;  // workgroups of the scatter
-template <typename T>
+template <typename T, int D>
 __global__ __launch_bounds__(256) void k_bin_mean_lds(GridDims g, int64_t n, const int64_t *__restrict__ off,
                                                        const T *__restrict__ t, const T *__restrict__ y, int narr,
                                                        double *__restrict__ part, int32_t *idx,
                                                        unsigned long long *cnt, int *flags) {
   __shared__ double acc[3][MB_PMAX];
   const int P = int(g.P);
-  for (int e = threadIdx.x; e < narr * P; e += blockDim.x) acc[e / P][e % P] = 0.0;
+  for (int r = 0; r < narr; ++r)
+    for (int e = threadIdx.x; e < P; e += blockDim.x) acc[r][e] = 0.0;
   __syncthreads();
   for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
     const int64_t a = off[i], b = off[i + 1];
@@ -84,18 +86,20 @@ __global__ __launch_bounds__(256) void k_bin_mean_lds(GridDims g, int64_t n, con
     for (int64_t j = a + threadIdx.x; j < b; j += blockDim.x) {
       int k[3];
       double rho[3];
-      if (!locate(t + j * g.d, g, k, rho)) {
+      if (!locate<D>(t + j * D, g, k, rho)) {
         atomicOr(flags, 1);
         if (idx) idx[j] = -1;
         continue;
       }
       const double yv = double(y[j]);
       int64_t lower = 0;
-      for (int q = 0; q < g.d; ++q) lower += int64_t(k[q]) * g.stride[q];
-      for (int cc = 0; cc < (1 << g.d); ++cc) {
+#pragma unroll
+      for (int q = 0; q < D; ++q) lower += int64_t(k[q]) * g.stride[q];
+#pragma unroll
+      for (int cc = 0; cc < (1 << D); ++cc) {
         int64_t p;
         double W;
-        corner(g, k, rho, cc, &p, &W);
+        corner<D>(g, k, rho, cc, &p, &W);
         const double ww = w * W;
         atomicAdd(&acc[0][p], ww);
         atomicAdd(&acc[1][p], ww * yv);
@@ -106,8 +110,8 @@ __global__ __launch_bounds__(256) void k_bin_mean_lds(GridDims g, int64_t n, con
     }
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < narr * P; e += blockDim.x)
-    part[int64_t(blockIdx.x) * narr * P + e] = acc[e / P][e % P];
+  for (int r = 0; r < narr; ++r)
+    for (int e = threadIdx.x; e < P; e += blockDim.x) part[(int64_t(blockIdx.x) * narr + r) * P + e] = acc[r][e];
 }
 
 // Sum over the nwg workgroups' partials of element e: 16 lanes per element,
@@ -288,7 +292,8 @@ __global__ __launch_bounds__(1024) void k_fold_rows(int64_t n, int n_folds, cons
 // Per-curve rows of the Gram identity, scaled by sqrt(w_i), w_i = 1/(N_i(N_i-1)):
 //   Z[r,p] = sqrt(w_i) sum_j W_p(t_ij) Y_ij,  Cr[r,p] = sqrt(w_i) sum_j W_p(t_ij),
 //   Z2[r,p] = sqrt(w_i) sum_j W_p(t_ij) Y_ij^2, cntrow[r,p] = #obs with lower corner p,
-// where r is the curve's row (grouped by fold). Rows must be zeroed first.
+// where r is the curve's row (grouped by fold). Rows must be zeroed first. For
+// rows too long for LDS.
 template <typename T>
 __global__ __launch_bounds__(256) void k_bin_rows(GridDims g, int64_t n, const int64_t *__restrict__ off,
                                                    const T *__restrict__ t, const T *__restrict__ y,
@@ -325,6 +330,64 @@ __global__ __launch_bounds__(256) void k_bin_rows(GridDims g, int64_t n, const i
         atomicAdd(&cntrow[r * g.P + lower], 1);
       }
     }
+  }
+}
+
+// The same rows summed in LDS, a workgroup per curve: the row is written
+// once, whole (no zero fill before, no atomics on global memory), also for
+// curves of fewer than two observations (zeros). 1000 curves of 100 to 300
+// observations, P = 1024, FP32: 70 us with two fills and global atomics,
+// 15 us here, bound by the LDS unit, which takes about 250 cycles for the 64
+// floating-point additions of one wavefront instruction.
+constexpr size_t BR_LDS_MAX = 64 * 1024;  // two workgroups per CU; longer rows: k_bin_rows
+template <typename T, int D>
+__global__ __launch_bounds__(256) void k_bin_rows_lds(GridDims g, int64_t n, const int64_t *__restrict__ off,
+                                                       const T *__restrict__ t, const T *__restrict__ y,
+                                                       const int64_t *__restrict__ pos, T *__restrict__ Z,
+                                                       T *__restrict__ Cr, T *__restrict__ Z2, int32_t *cntrow,
+                                                       int *flags) {
+  extern __shared__ __align__(16) unsigned char row_raw[];
+  T *row = reinterpret_cast<T *>(row_raw);  // [Z, Cr, Z2][P]
+  const int P = int(g.P), narr = Z2 ? 3 : 2;
+  for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+    const int64_t a = off[i], b = off[i + 1];
+    const int64_t Ni = b - a;
+    const int64_t r = pos ? pos[i] : i;
+    if (r < 0) continue;  // uniform per workgroup
+    for (int e = threadIdx.x; e < narr * P; e += 256) row[e] = T(0);
+    __syncthreads();
+    const double sw = Ni < 2 ? 0.0 : sqrt(1.0 / (double(Ni) * double(Ni - 1)));
+    for (int64_t j = Ni < 2 ? b : a + threadIdx.x; j < b; j += 256) {
+      int k[3];
+      double rho[3];
+      if (!locate<D>(t + j * D, g, k, rho)) {
+        atomicOr(flags, 1);
+        continue;
+      }
+      const double yv = double(y[j]);
+#pragma unroll
+      for (int cc = 0; cc < (1 << D); ++cc) {
+        int64_t p;
+        double W;
+        corner<D>(g, k, rho, cc, &p, &W);
+        atomicAdd(&row[P + p], T(sw * W));
+        atomicAdd(&row[p], T(sw * W * yv));
+        if (narr > 2) atomicAdd(&row[2 * P + p], T(sw * W * yv * yv));
+      }
+      if (cntrow) {
+        int64_t lower = 0;
+#pragma unroll
+        for (int q = 0; q < D; ++q) lower += int64_t(k[q]) * g.stride[q];
+        atomicAdd(&cntrow[r * g.P + lower], 1);
+      }
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < P; e += 256) {
+      Z[r * P + e] = row[e];
+      Cr[r * P + e] = row[P + e];
+      if (narr > 2) Z2[r * P + e] = row[2 * P + e];
+    }
+    __syncthreads();  // the next curve's zeros
   }
 }
 
@@ -377,60 +440,75 @@ __global__ __launch_bounds__(256) void k_pair_diag(GridDims g, int64_t n, const 
 
 // The same j = l terms on small grids without folds: every such pair (u, v)
 // joins two corners of one cell, so it is node u and one of the 3^d
-// neighbours u + sum_q dq stride_q (dq in {-1, 0, 1}). Each workgroup
-// (grid-stride over the curves) adds the terms into FP32 sums per (node,
-// neighbour) in LDS (in the storage type T: FP32 sums for FP32 data, FP64
-// for FP64) and writes them to part[blockIdx][a][node][neighbour];
-// k_pair_diag_finish adds the workgroups' sums in workgroup order (FP64) and
-// subtracts them from C, G and Q.
+// neighbours u + sum_q dq stride_q (dq in {-1, 0, 1}), and (v, u) has the same
+// term: the node itself and the half of the neighbours after it suffice, hb =
+// (3^d + 1) / 2 slots per node. Each workgroup (four curves at a time,
+// grid-stride) adds the terms into sums per (node, slot) in LDS (in the
+// storage type T: FP32 sums for FP32 data, FP64 for FP64) and writes them to
+// part[blockIdx][a][node][slot]; k_pair_diag_finish adds the workgroups' sums
+// in workgroup order (FP64) and subtracts them from C, G and Q. 1000 curves of
+// 100 to 300 observations, P = 1024, FP32: 59 + 16 us with all 3^d neighbours
+// and one curve of 256 threads at a time, 32 + 10 us here: bound by the LDS
+// unit (20 additions per observation, about 250 cycles per wavefront
+// instruction; with the dimension known at run time only, 36 us), the finish by
+// reading the workgroups' sums.
 constexpr size_t PD_LDS_MAX = 128 * 1024;  // bytes of LDS for the sums
 constexpr int PD_WGS = 256;                // workgroups of the scatter
-template <typename T>
-__global__ __launch_bounds__(256) void k_pair_diag_lds(GridDims g, int64_t n, const int64_t *__restrict__ off,
-                                                        const T *__restrict__ t, const T *__restrict__ y, int narr,
-                                                        T *__restrict__ part, unsigned long long *cnt) {
-  extern __shared__ __align__(8) unsigned char pacc_raw[];
-  T *pacc = reinterpret_cast<T *>(pacc_raw);  // [narr][P][nb]
-  const int P = int(g.P);
-  int nb = 1;
-  for (int q = 0; q < g.d; ++q) nb *= 3;
-  const int tot = narr * P * nb;
+constexpr int PD_GROUPS = 4;               // curves at a time
+__host__ __device__ inline int pair_slots(int d) { return d == 1 ? 2 : (d == 2 ? 5 : 14); }
+template <typename T, int D>
+__global__ __launch_bounds__(256 * PD_GROUPS) void k_pair_diag_lds(GridDims g, int64_t n,
+                                                                    const int64_t *__restrict__ off,
+                                                                    const T *__restrict__ t, const T *__restrict__ y,
+                                                                    int narr, T *__restrict__ part,
+                                                                    unsigned long long *cnt) {
+  extern __shared__ __align__(16) unsigned char pacc_raw[];
+  T *pacc = reinterpret_cast<T *>(pacc_raw);  // [narr][P][hb]
+  const int P = int(g.P), hb = pair_slots(D), mid = hb - 1;  // mid: the node itself among the 3^d neighbours
+  const int tot = narr * P * hb;
   for (int e = threadIdx.x; e < tot; e += blockDim.x) pacc[e] = T(0);
   __syncthreads();
-  for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+  const int grp = threadIdx.x >> 8, tg = threadIdx.x & 255;
+  for (int64_t i = int64_t(blockIdx.x) * PD_GROUPS + grp; i < n; i += int64_t(gridDim.x) * PD_GROUPS) {
     const int64_t a = off[i], b = off[i + 1];
     const int64_t Ni = b - a;
     if (Ni < 2) continue;
     const double w = 1.0 / (double(Ni) * double(Ni - 1));
-    for (int64_t j = a + threadIdx.x; j < b; j += blockDim.x) {
+    for (int64_t j = a + tg; j < b; j += 256) {
       int k[3];
       double rho[3];
-      if (!locate(t + j * g.d, g, k, rho)) continue;
+      if (!locate<D>(t + j * D, g, k, rho)) continue;
       const double yv = double(y[j]);
       const double y2 = yv * yv;
-      const int nc = 1 << g.d;
-      int64_t pu[8];
-      double Wu[8];
-      for (int cc = 0; cc < nc; ++cc) corner(g, k, rho, cc, &pu[cc], &Wu[cc]);
+      constexpr int nc = 1 << D;
+      int64_t pu[nc];
+      double Wu[nc];
+#pragma unroll
+      for (int cc = 0; cc < nc; ++cc) corner<D>(g, k, rho, cc, &pu[cc], &Wu[cc]);
+#pragma unroll
       for (int u = 0; u < nc; ++u)
+#pragma unroll
         for (int v = 0; v < nc; ++v) {
-          const double ww = w * Wu[u] * Wu[v];
-          if (ww == 0.0) continue;
           // digit q of bi: the step of coordinate q from corner u to corner v
           // (corner() takes coordinate q from bit d-1-q of the corner index)
           int bi = 0, m = 1;
-          for (int q = 0; q < g.d; ++q, m *= 3) {
-            const int sh = g.d - 1 - q;
+#pragma unroll
+          for (int q = 0; q < D; ++q, m *= 3) {
+            const int sh = D - 1 - q;
             bi += (((v >> sh) & 1) - ((u >> sh) & 1) + 1) * m;
           }
-          T *ac = pacc + int64_t(pu[u]) * nb + bi;
+          if (bi < mid) continue;  // (v, u)
+          const double ww = w * Wu[u] * Wu[v];
+          if (ww == 0.0) continue;
+          T *ac = pacc + int64_t(pu[u]) * hb + (bi - mid);
           atomicAdd(ac, T(ww));
-          atomicAdd(ac + int64_t(P) * nb, T(ww * y2));
-          if (narr > 2) atomicAdd(ac + 2 * int64_t(P) * nb, T(ww * y2 * y2));
+          atomicAdd(ac + int64_t(P) * hb, T(ww * y2));
+          if (narr > 2) atomicAdd(ac + 2 * int64_t(P) * hb, T(ww * y2 * y2));
         }
       if (cnt) {
         int64_t lower = 0;
-        for (int q = 0; q < g.d; ++q) lower += int64_t(k[q]) * g.stride[q];
+#pragma unroll
+        for (int q = 0; q < D; ++q) lower += int64_t(k[q]) * g.stride[q];
         atomicAdd(&cnt[lower * g.P + lower], (unsigned long long)(-1ll));
       }
     }
@@ -444,15 +522,14 @@ __global__ __launch_bounds__(256) void k_pair_diag_finish(GridDims g, int narr, 
                                                            const T *__restrict__ part, T *C, T *G, T *Q) {
   __shared__ double red[WS_LANES][256 / WS_LANES];
   const int P = int(g.P);
-  int nb = 1;
-  for (int q = 0; q < g.d; ++q) nb *= 3;
-  // element (node, neighbour) of this lane group
+  const int hb = pair_slots(g.d);
+  // element (node, slot) of this lane group
   const int64_t e = int64_t(blockIdx.x) * (256 / WS_LANES) + threadIdx.x % (256 / WS_LANES);
-  const bool in = e < int64_t(P) * nb;
-  const int p = in ? int(e / nb) : 0, bi = in ? int(e % nb) : 0;
+  const bool in = e < int64_t(P) * hb;
+  const int p = in ? int(e / hb) : 0, slot = in ? int(e % hb) : 0;
   // the neighbour's node, if it exists
   int64_t qn = p;
-  int m = bi;
+  int m = slot + hb - 1;
   bool ok = in;
   for (int q = 0; q < g.d; ++q) {
     const int dq = m % 3 - 1;
@@ -461,15 +538,17 @@ __global__ __launch_bounds__(256) void k_pair_diag_finish(GridDims g, int narr, 
     if (kq + dq < 0 || kq + dq >= g.M[q]) ok = false;
     qn += int64_t(dq) * g.stride[q];
   }
-  const int64_t tot = int64_t(narr) * P * nb;
-  for (int a = 0; a < narr; ++a) {
-    const double sum = sum_over_wgs(part + int64_t(a) * P * nb, tot, nwg, e, ok, red);
-    if (ok && threadIdx.x < 256 / WS_LANES && sum != 0.0) {
-      T *A = a == 0 ? C : (a == 1 ? G : Q);
-      const int64_t o = int64_t(p) * P + qn;
-      A[o] = T(double(A[o]) - sum);
+  const int64_t tot = int64_t(narr) * P * hb;
+  const int a = blockIdx.y;
+  const double sum = sum_over_wgs(part + int64_t(a) * P * hb, tot, nwg, e, ok, red);
+  if (ok && threadIdx.x < 256 / WS_LANES && sum != 0.0) {
+    T *A = a == 0 ? C : (a == 1 ? G : Q);
+    const int64_t o = int64_t(p) * P + qn;
+    A[o] = T(double(A[o]) - sum);
+    if (slot) {
+      const int64_t om = qn * P + p;
+      A[om] = T(double(A[om]) - sum);
     }
-    __syncthreads();  // red is reused for the next array
   }
 }
 
@@ -535,8 +614,9 @@ int bin_impl(fpca_context *ctx, const fpca_grid *grid, int kind, int design, int
         const int nwg = int(n < MB_WGS ? n : MB_WGS);
         if (int rc = ws_reserve(ctx, carve_bytes(size_t(nwg) * narr * P, 8))) return rc;
         double *part = static_cast<double *>(ctx->ws);
-        hipLaunchKernelGGL(k_bin_mean_lds<T>, dim3(unsigned(nwg)), dim3(256), 0, ctx->stream, g, n, offsets, t, y,
-                           narr, part, bin_index, reinterpret_cast<unsigned long long *>(cell_count), ctx->d_flags);
+        auto *kern = g.d == 1 ? k_bin_mean_lds<T, 1> : (g.d == 2 ? k_bin_mean_lds<T, 2> : k_bin_mean_lds<T, 3>);
+        hipLaunchKernelGGL(kern, dim3(unsigned(nwg)), dim3(256), 0, ctx->stream, g, n, offsets, t, y, narr, part,
+                           bin_index, reinterpret_cast<unsigned long long *>(cell_count), ctx->d_flags);
         FPCA_LAUNCH_CHECK("bin_mean_lds");
         hipLaunchKernelGGL(k_bin_mean_finish<T>, dim3(unsigned((narr * P + 15) / 16)), dim3(256), 0, ctx->stream, P,
                            narr, nwg, part, W, S, SQ);
@@ -610,10 +690,14 @@ int bin_impl(fpca_context *ctx, const fpca_grid *grid, int kind, int design, int
     fstart = cv.take<int64_t>(n_folds + 1);
   }
   const int64_t rowbytes = nrows * P * int64_t(sizeof(T));
-  if (int rc = fill_bytes_zero(ctx, Z, rowbytes)) return rc;
-  if (int rc = fill_bytes_zero(ctx, Cr, rowbytes)) return rc;
-  if (Z2)
-    if (int rc = fill_bytes_zero(ctx, Z2, rowbytes)) return rc;
+  const size_t row_lds = size_t(SQ ? 3 : 2) * size_t(P) * sizeof(T);
+  const bool rows_lds = row_lds <= BR_LDS_MAX;
+  if (!rows_lds) {
+    if (int rc = fill_bytes_zero(ctx, Z, rowbytes)) return rc;
+    if (int rc = fill_bytes_zero(ctx, Cr, rowbytes)) return rc;
+    if (Z2)
+      if (int rc = fill_bytes_zero(ctx, Z2, rowbytes)) return rc;
+  }
   if (cntrow)
     if (int rc = fill_bytes_zero(ctx, cntrow, nrows * P * 4)) return rc;
   if (nsl > 1 && n > 0) {
@@ -622,7 +706,12 @@ int bin_impl(fpca_context *ctx, const fpca_grid *grid, int kind, int design, int
     FPCA_LAUNCH_CHECK("fold_rows");
   }
   unsigned blocks = unsigned(n < 16384 ? (n > 0 ? n : 1) : 16384);
-  if (n > 0) {
+  if (n > 0 && rows_lds) {
+    auto *kern = g.d == 1 ? k_bin_rows_lds<T, 1> : (g.d == 2 ? k_bin_rows_lds<T, 2> : k_bin_rows_lds<T, 3>);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), row_lds, ctx->stream, g, n, offsets, t, y, pos, Z,
+                       Cr, Z2, cntrow, ctx->d_flags);
+    FPCA_LAUNCH_CHECK("bin_rows_lds");
+  } else if (n > 0) {
     hipLaunchKernelGGL(k_bin_rows<T>, dim3(blocks), dim3(256), 0, ctx->stream, g, n, offsets, t, y, pos, Z, Cr, Z2,
                        cntrow, ctx->d_flags);
     FPCA_LAUNCH_CHECK("bin_rows");
@@ -664,24 +753,20 @@ int bin_impl(fpca_context *ctx, const fpca_grid *grid, int kind, int design, int
     if (int rc = gram_i32(ctx, cntrow, n, P, cell_count)) return rc;
   }
   if (n > 0) {
-    int nb = 1;
-    for (int q = 0; q < g.d; ++q) nb *= 3;
     const int narr = SQ ? 3 : 2;
-    const size_t lds = size_t(narr) * size_t(P) * nb * sizeof(T);
-    if (nsl == 1 && lds <= PD_LDS_MAX) {
-      static size_t lds_set = 0;  // the attribute is set once per size (not inside a captured stream)
-      if (lds > lds_set) {
-        FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_pair_diag_lds<T>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(PD_LDS_MAX)));
-        lds_set = PD_LDS_MAX;
-      }
-      const int nwg = int(n < PD_WGS ? n : PD_WGS);
-      if (int rc = ws_reserve(ctx, carve_bytes(size_t(nwg) * narr * P * nb, sizeof(T)))) return rc;
+    const size_t sums = size_t(narr) * size_t(P) * pair_slots(g.d);
+    const size_t lds = sums * sizeof(T);
+    const int nwg = int(std::min<int64_t>((n + PD_GROUPS - 1) / PD_GROUPS, PD_WGS));
+    if (nsl == 1 && lds <= PD_LDS_MAX && ws_room(ctx, carve_bytes(size_t(nwg) * sums, sizeof(T)))) {
+      auto *kern = g.d == 1 ? k_pair_diag_lds<T, 1> : (g.d == 2 ? k_pair_diag_lds<T, 2> : k_pair_diag_lds<T, 3>);
+      FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   int(PD_LDS_MAX)));
       T *part = static_cast<T *>(ctx->ws);
-      hipLaunchKernelGGL(k_pair_diag_lds<T>, dim3(unsigned(nwg)), dim3(256), lds, ctx->stream, g, n, offsets, t, y,
-                         narr, part, reinterpret_cast<unsigned long long *>(cell_count));
+      hipLaunchKernelGGL(kern, dim3(unsigned(nwg)), dim3(256 * PD_GROUPS), lds, ctx->stream, g, n, offsets, t, y, narr,
+                         part, reinterpret_cast<unsigned long long *>(cell_count));
       FPCA_LAUNCH_CHECK("pair_diag_lds");
-      hipLaunchKernelGGL(k_pair_diag_finish<T>, dim3(unsigned((int64_t(P) * nb + 15) / 16)), dim3(256), 0,
+      hipLaunchKernelGGL(k_pair_diag_finish<T>, dim3(unsigned((int64_t(P) * pair_slots(g.d) + 15) / 16), unsigned(narr)),
+                         dim3(256), 0,
                          ctx->stream, g, narr, nwg, part, W, S, SQ);
       FPCA_LAUNCH_CHECK("pair_diag_finish");
       return FPCA_OK;

@@ -87,6 +87,11 @@ int hip_fail(hipError_t e, const char *what);
 // Scratch arenas: ensure at least `bytes`; returns FPCA_OK or an error.
 int ws_reserve(fpca_context *ctx, size_t bytes);
 int ws2_reserve(fpca_context *ctx, size_t bytes);
+// Whether an arena holds `bytes` or has been grown to: false, with no error
+// set, past the scratch limit, while the stream is capturing and when the
+// allocation fails. For paths that have another way without the memory.
+bool ws_room(fpca_context *ctx, size_t bytes);
+bool ws2_room(fpca_context *ctx, size_t bytes);
 int ws3_reserve(fpca_context *ctx, size_t bytes);
 // Pinned host staging of at least `bytes` for table uploads; waits for the
 // previous upload from it first.

@@ -132,6 +132,18 @@ int tables_stage(fpca_context *ctx, size_t bytes, char **out) {
 int ws2_reserve(fpca_context *ctx, size_t bytes) { return arena_reserve(ctx, &ctx->ws2, &ctx->ws2_size, bytes); }
 int ws3_reserve(fpca_context *ctx, size_t bytes) { return arena_reserve(ctx, &ctx->ws3, &ctx->ws3_size, bytes); }
 
+static bool may_grow(fpca_context *ctx, size_t bytes) {
+  if (ctx->ws_limit && bytes > ctx->ws_limit) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(ctx->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+}
+bool ws_room(fpca_context *ctx, size_t bytes) {
+  return bytes <= ctx->ws_size || (may_grow(ctx, bytes) && ws_reserve(ctx, bytes) == FPCA_OK);
+}
+bool ws2_room(fpca_context *ctx, size_t bytes) {
+  return bytes <= ctx->ws2_size || (may_grow(ctx, bytes) && ws2_reserve(ctx, bytes) == FPCA_OK);
+}
+
 template <typename T>
 __global__ void k_fill(T *__restrict__ p, T v, int64_t n) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;

@@ -780,13 +780,7 @@ int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64
   T *part = nullptr;
   if (splits > 1) {
     const size_t need = carve_bytes(size_t(nm) * size_t(splits) * size_t(tiles) * GT * GT, sizeof(T));
-    bool room = need <= ctx->ws2_size;
-    if (!room && !(ctx->ws_limit && need > ctx->ws_limit)) {
-      hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-      (void)hipStreamIsCapturing(ctx->stream, &cs);
-      room = cs == hipStreamCaptureStatusNone && ws2_reserve(ctx, need) == FPCA_OK;
-    }
-    if (room) part = static_cast<T *>(ctx->ws2);
+    if (ws2_room(ctx, need)) part = static_cast<T *>(ctx->ws2);
   }
   const int64_t sp = part ? splits : 1;
   bool vec = N % 4 == 0;

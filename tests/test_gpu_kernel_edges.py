@@ -254,3 +254,29 @@ def test_eig_small_grids(torch, F, h, P, k, p, q, dt):
         scale = max(1.0, 0.1 * rev[0] / gap) if np.isfinite(gap) else 1.0
         err = min(np.abs(phi[:, j] - rphi[:, j]).max(), np.abs(phi[:, j] + rphi[:, j]).max())
         assert err <= 100 * tol * scale * np.abs(rphi[:, j]).max(), (j, err)
+
+
+@pytest.mark.parametrize("M,dt,q,Ns", [((3,), "f32", False, [2]), ((40, 41), "f32", True, [0, 300, 1, 2, 256, 257]),
+                                       ((57, 57), "f32", False, [257, 3, 0, 90, 40]),
+                                       ((58, 57), "f32", False, [2, 300]), ((74, 74), "f32", True, [300, 1, 7]),
+                                       ((10, 10, 11), "f32", False, [60, 2, 100]),
+                                       ((11, 11, 10), "f32", False, [60, 2, 100]), ((101,), "f64", True, [50] * 9),
+                                       ((53, 52), "f64", False, [120, 30]), ((64, 43), "f64", True, [80, 11])])
+def test_bin_cov_rows(torch, F, h, M, dt, q, Ns):
+    """Rows of curves and the j = l terms in LDS: grids on both sides of what LDS holds of either, curves of no,
+    one, two and more than one workgroup's observations, last groups of four curves not full. Bars as for the
+    binning at ordinary sizes."""
+    _say(f"bin cov rows M={M} {dt} Q={q}")
+    rng = np.random.default_rng(len(Ns) + M[0])
+    npdt, tdt, code, prec = ((np.float64, torch.float64, F.FPCA_F64, F.FPCA_PREC_F64) if dt == "f64" else
+                             (np.float32, torch.float32, F.FPCA_F32, F.FPCA_PREC_F32))
+    off = np.concatenate([[0], np.cumsum(Ns)]).astype(np.int64)
+    t = rng.random((int(off[-1]), len(M))).astype(npdt)
+    y = rng.standard_normal(int(off[-1])).astype(npdt)
+    P = int(np.prod(M))
+    out = [torch.full((P, P), float("nan"), dtype=tdt, device="cuda:0") for _ in range(3 if q else 2)]
+    F.fpca_bin(h, F.Grid(M), F.FPCA_BIN_COV, F.FPCA_IRREGULAR, code, prec, len(Ns), dev(torch, off), dev(torch, t),
+               dev(torch, y), None, 0, out[0], out[1], out[2] if q else None)
+    ref = oracle.bin_cov_pairs(M, off, t.astype(np.float64), y.astype(np.float64), want_Q=q)
+    for a, r in zip(out, ref):
+        assert normwise_rel(a.cpu().numpy().astype(np.float64), r) < (1e-12 if dt == "f64" else 1e-5)
