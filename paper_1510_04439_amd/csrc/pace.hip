@@ -19,47 +19,12 @@ namespace fpca {
 namespace {
 
 constexpr int PACE_KMAX = 32;
-constexpr int PACE_CH = 64;  // observations staged in LDS per chunk
 constexpr int PACE_THREADS = 256;
-constexpr int PACE_TRI = PACE_KMAX * (PACE_KMAX + 1) / 2;
-constexpr int PACE_ACC = (PACE_TRI + PACE_KMAX + PACE_THREADS - 1) / PACE_THREADS;
 
 // sigma^2 / lambda_l for the kept components, -1 for the others
 struct PaceDiag {
   double v[PACE_KMAX];
 };
-
-// A = L L^T in place (lower triangle of A, k x k, row stride PACE_KMAX + 1);
-// false if a pivot is not positive.
-__device__ inline bool chol_inplace(double (*A)[PACE_KMAX + 1], int k) {
-  for (int c = 0; c < k; ++c) {
-    double d = A[c][c];
-    for (int p = 0; p < c; ++p) d -= A[c][p] * A[c][p];
-    if (!(d > 0.0)) return false;
-    const double lc = sqrt(d);
-    A[c][c] = lc;
-    for (int r = c + 1; r < k; ++r) {
-      double s = A[r][c];
-      for (int p = 0; p < c; ++p) s -= A[r][p] * A[c][p];
-      A[r][c] = s / lc;
-    }
-  }
-  return true;
-}
-
-// x = (L L^T)^{-1} x with L from chol_inplace.
-__device__ inline void chol_solve(const double (*L)[PACE_KMAX + 1], double *x, int k) {
-  for (int r = 0; r < k; ++r) {
-    double s = x[r];
-    for (int p = 0; p < r; ++p) s -= L[r][p] * x[p];
-    x[r] = s / L[r][r];
-  }
-  for (int r = k - 1; r >= 0; --r) {
-    double s = x[r];
-    for (int p = r + 1; p < k; ++p) s -= L[p][r] * x[p];
-    x[r] = s / L[r][r];
-  }
-}
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
@@ -73,6 +38,12 @@ __device__ inline void load4(const double *p, double *o) {
   const double2 a = reinterpret_cast<const double2 *>(p)[0], b = reinterpret_cast<const double2 *>(p)[1];
   o[0] = a.x, o[1] = a.y, o[2] = b.x, o[3] = b.y;
 }
+// As load4, unconverted.
+__device__ inline void copy4(const float *p, float *o) {
+  const float4 v = *reinterpret_cast<const float4 *>(p);
+  o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
+}
+__device__ inline void copy4(const double *p, double *o) { load4(p, o); }
 constexpr int MB = 8;             // MFMA steps (4 nodes each) whose operands are loaded together
 
 // Common grid: one wavefront's part of Phi^T Phi, the shared matrix of the
@@ -236,10 +207,10 @@ __device__ void cg_inverse(int k, const PaceDiag &dg, const double *__restrict__
 // (rows = curves, columns = components, K = nodes). Each of the eight
 // wavefronts streams an eighth of the nodes straight from memory into the
 // operands (lane l: Y[curve l % 16][node + l / 16] minus mu, and the basis at
-// the same node for components l % 16 and 16 + l % 16), MB steps loaded
-// before they are used; the wavefronts' tiles are summed in a fixed order. A
-// curve with a missing value
-// gets a NaN first score: k_pace solves it on its own. The scores are the
+// the same node for components l % 16 and 16 + l % 16), MB steps at a time,
+// the next ones on their way; the wavefronts' tiles are summed in a fixed
+// order. A curve with a missing value gets a NaN first score: k_pace solves it
+// on its own. The scores are the
 // shared inverse times the right-hand sides. Workgroups 1..CG_NGW form
 // partial sums of the shared matrix (cg_gram_part) and count themselves on
 // ready[1]; workgroup 0 adds them, inverts the matrix (cg_inverse) and
@@ -325,42 +296,64 @@ __global__ __launch_bounds__(RH_THREADS) void k_pace_cg_rhs(int64_t n, int64_t P
   const int64_t n0 = wave * per, n1 = min(P, n0 + per);
   v4d d0 = {0, 0, 0, 0}, d1 = d0;
   bool bad = false;
-  for (int64_t q = n0; q < n1; q += 4 * MB) {
-    double a[MB], b0[MB], b1[MB];
-    if (VEC && q + 4 * MB <= n1) {
-      // step 4b + j takes node q + 16 b + 4 kk + j: each lane's four nodes of
-      // a 16-node block in one vector load per array
-      double ml[MB];
+  int64_t q = n0;
+  if constexpr (VEC) {
+    // MB whole steps at a time, the next ones loaded while these are used
+    // (the last ones once more at the end: no branch between a load and its
+    // use). Step 4b + j takes node q + 16 b + 4 kk + j: each lane's four nodes
+    // of a 16-node block in one vector load per array.
+    struct Raw {
+      T y[MB], m[MB], f0[MB], f1[MB];
+    };
+    const int64_t whole = n1 > n0 ? (n1 - n0) / (4 * MB) : 0;
+    auto load = [&](int64_t it, Raw &v) {
+      const int64_t p0 = n0 + min(it, whole - 1) * (4 * MB) + 4 * kk;
 #pragma unroll
       for (int bl = 0; bl < MB / 4; ++bl) {
-        const int64_t p = q + 16 * bl + 4 * kk;
-        load4(yr + p, a + 4 * bl);
-        load4(mu + p, ml + 4 * bl);
-        load4(f0p + p, b0 + 4 * bl);
-        load4(f1p + p, b1 + 4 * bl);
+        const int64_t p = p0 + 16 * bl;
+        copy4(yr + p, v.y + 4 * bl);
+        copy4(mu + p, v.m + 4 * bl);
+        copy4(f0p + p, v.f0 + 4 * bl);
+        copy4(f1p + p, v.f1 + 4 * bl);
       }
+    };
+    auto use = [&](const Raw &v) {
 #pragma unroll
       for (int s = 0; s < MB; ++s) {
-        const double yv = cin ? a[s] : 0.0;
+        const double yv = cin ? double(v.y[s]) : 0.0;
         bad |= !isfinite(yv);
-        a[s] = cin ? yv - ml[s] : 0.0;
-        b0[s] = r0 ? b0[s] : 0.0;
-        b1[s] = r1 ? b1[s] : 0.0;
+        const double a = cin ? yv - double(v.m[s]) : 0.0;
+        d0 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, r0 ? double(v.f0[s]) : 0.0, d0, 0, 0, 0);
+        if (nt > 1) d1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, r1 ? double(v.f1[s]) : 0.0, d1, 0, 0, 0);
       }
-    } else {
-      // every load is issued (addresses clamped into the range), then masked
+    };
+    if (whole > 0) {
+      Raw u0, u1;
+      load(0, u0);
+      for (int64_t it = 0; it < whole; it += 2) {
+        load(it + 1, u1);
+        use(u0);
+        if (it + 1 >= whole) break;
+        load(it + 2, u0);
+        use(u1);
+      }
+      q += whole * (4 * MB);
+    }
+  }
+  for (; q < n1; q += 4 * MB) {
+    double a[MB], b0[MB], b1[MB];
+    // every load is issued (addresses clamped into the range), then masked
 #pragma unroll
-      for (int s = 0; s < MB; ++s) {
-        const int64_t p = q + 16 * (s >> 2) + 4 * kk + (s & 3);
-        const int64_t pc = min(p, n1 - 1);
-        const double yl = double(yr[pc]), ml = double(mu[pc]), v0 = double(f0p[pc]), v1 = double(f1p[pc]);
-        const bool in = p < n1 && cin;
-        const double yv = in ? yl : 0.0;
-        bad |= !isfinite(yv);
-        a[s] = in ? yv - ml : 0.0;
-        b0[s] = (p < n1 && r0) ? v0 : 0.0;
-        b1[s] = (p < n1 && r1) ? v1 : 0.0;
-      }
+    for (int s = 0; s < MB; ++s) {
+      const int64_t p = q + 16 * (s >> 2) + 4 * kk + (s & 3);
+      const int64_t pc = min(p, n1 - 1);
+      const double yl = double(yr[pc]), ml = double(mu[pc]), v0 = double(f0p[pc]), v1 = double(f1p[pc]);
+      const bool in = p < n1 && cin;
+      const double yv = in ? yl : 0.0;
+      bad |= !isfinite(yv);
+      a[s] = in ? yv - ml : 0.0;
+      b0[s] = (p < n1 && r0) ? v0 : 0.0;
+      b1[s] = (p < n1 && r1) ? v1 : 0.0;
     }
 #pragma unroll
     for (int s = 0; s < MB; ++s) {
@@ -431,143 +424,177 @@ __global__ __launch_bounds__(RH_THREADS) void k_pace_cg_rhs(int64_t n, int64_t P
   }
 }
 
-// One workgroup per curve (grid-stride). Chunks of observations: each thread
-// of the first PACE_CH interpolates one observation (every component and the
-// mean), then thread e accumulates entries e, e + 256, ... of the upper
-// triangle of Phi^T Phi (row by row) followed by the k entries of
-// Phi^T (Y - mu), in observation order.
-// Thread 0 solves the k x k system by Cholesky in FP64. On the common grid a
-// curve with no missing value takes the factor shared by all such curves.
-template <typename T>
-__global__ __launch_bounds__(PACE_THREADS) void k_pace(GridDims g, int64_t n, int design,
-                                                       const int64_t *__restrict__ off, const T *__restrict__ t,
-                                                       const T *__restrict__ y, const T *__restrict__ mu,
-                                                       const T *__restrict__ efuns, int k, PaceDiag dg,
-                                                       const double *__restrict__ Lcg, const int *__restrict__ cg_ok,
+// LDS written by a wavefront is read by its other lanes
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One workgroup per curve (grid-stride), D = 0: the nodes of the common grid,
+// else scattered observations in d = D coordinates. Each of the four
+// wavefronts takes every fourth run of PaceWg::OB observations, by itself: its
+// lanes interpolate the components and the residual Y - mu, which goes behind
+// them as column k, into LDS, and the Gram matrix of the k + 1 columns is
+// taken with FP64 MFMA 16x16x4, CT column tiles wide (its last column is the
+// right-hand side). The wavefronts' tiles are added in order, and the
+// workgroup solves the k x k system by Gauss-Jordan elimination (pivots as in
+// LDL^T; one that is not positive gives NaN scores). On the common grid
+// k_pace_cg_rhs has solved the curves with no missing value.
+// Bound by the latency of a curve's loads and of the elimination. 1000 curves
+// of 100 to 300 observations, k = 10: 84 us with 64 observations per barrier,
+// dot products in LDS and the solve in one thread, 19 us here; 2000 rows of
+// 2304 nodes with missing values, k = 12: 377 us, 59 here (with the image).
+template <int D, int CT>
+struct PaceWg {
+  // observations per wavefront and step: 32 (two lanes each) leave LDS for
+  // more workgroups; the long rows of the common grid take 64 where they fit
+  static constexpr int OB = D == 0 && CT == 1 ? 64 : 32;
+  static constexpr int LD = 16 * CT + 1;
+  static constexpr int NT = CT == 1 ? 1 : (CT == 2 ? 3 : 5);  // tiles (0,0) (0,1) (1,1) (0,2) (1,2)
+  union {
+    double ph[4][OB][LD];
+    double red[4][NT * 256];
+  };
+  double M[PACE_KMAX][PACE_KMAX + 1];  // [A | rhs]
+};
+
+template <typename T, int D, int CT>
+__global__ __launch_bounds__(PACE_THREADS) void k_pace(GridDims g, int64_t n, const int64_t *__restrict__ off,
+                                                       const T *__restrict__ t, const T *__restrict__ y,
+                                                       const T *__restrict__ mu, const T *__restrict__ efuns, int k,
+                                                       PaceDiag dg, const int *__restrict__ cg_ok,
                                                        T *__restrict__ scores, int *__restrict__ ready) {
+  using W = PaceWg<D, CT>;
+  constexpr int OB = W::OB, LPO = 64 / OB, NC = 1 << D;
   // k_pace_cg_rhs has finished: its two flags return to zero for the next call
   if (ready && blockIdx.x == 0 && threadIdx.x < 2) ready[threadIdx.x] = 0;
-  __shared__ double ph[PACE_CH][PACE_KMAX + 1];
-  __shared__ double yc[PACE_CH];
-  __shared__ double A[PACE_KMAX][PACE_KMAX + 1];
-  __shared__ double rhs[PACE_KMAX];
-  __shared__ unsigned char tri_r[PACE_TRI], tri_c[PACE_TRI];
-  const int tid = threadIdx.x;
+  __shared__ W S;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int ob = lane % OB, part = lane / OB;  // an observation's lanes take every LPO-th component
   const int64_t P = g.P;
-  const int nmat = k * (k + 1) / 2, nacc = nmat + k;
-  const bool fast = design == FPCA_COMMON_GRID && Lcg && cg_ok && cg_ok[0] == 1;
-  bool built = false;  // the triangle's index tables, formed at the first curve this workgroup solves
+  const bool fast = D == 0 && cg_ok && cg_ok[0] == 1;
+  const int rw = k <= 8 ? 8 : (k <= 16 ? 16 : 32);  // rows of the elimination
+  const int er = tid & (rw - 1), ej = tid / rw, en = PACE_THREADS / rw;
   for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
-    int64_t a, b;
-    if (design == FPCA_IRREGULAR) {
-      a = off[i];
-      b = off[i + 1];
-    } else {
-      a = i * P;
-      b = a + P;
-    }
+    const int64_t a = D ? off[i] : i * P, b = D ? off[i + 1] : a + P;
     // with the shared factor, k_pace_cg_rhs has solved every complete curve
     // and marked the others with a NaN first score
     if (fast) {
       const double s0 = double(scores[i * k]);
       if (s0 == s0) continue;  // uniform: every thread reads the same value
     }
-    if (!built) {
-      if (tid == 0)
-        for (int r = 0, e = 0; r < k; ++r)
-          for (int c = r; c < k; ++c, ++e) {
-            tri_r[e] = (unsigned char)r;
-            tri_c[e] = (unsigned char)c;
-          }
-      __syncthreads();
-      built = true;
-    }
-    double acc[PACE_ACC];
+    __syncthreads();  // the previous curve's tiles and system have been read
+    for (int c = k + 1 + part; c < 16 * CT; c += LPO) S.ph[wave][ob][c] = 0.0;
+    v4d acc[W::NT];
 #pragma unroll
-    for (int q = 0; q < PACE_ACC; ++q) acc[q] = 0.0;
-    for (int64_t c0 = a; c0 < b; c0 += PACE_CH) {
-      const int m = int(min(int64_t(PACE_CH), b - c0));
-      __syncthreads();  // the previous chunk has been read
-      if (tid < m) {
-        const int64_t j = c0 + tid;
-        int64_t node[8];
-        double W[8];
-        int nc = 0;
-        bool ok = true;
-        if (design == FPCA_IRREGULAR) {
+    for (int q = 0; q < W::NT; ++q) acc[q] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int64_t c0 = a + wave * OB; c0 < b; c0 += 4 * OB) {
+      const int64_t j = c0 + ob;
+      int64_t node[NC];
+      double Wt[NC];
+      bool ok = j < b;
+      double yv = 0.0;
+      if (ok) {
+        yv = double(y[j]);
+        if constexpr (D > 0) {
           int kk[3];
           double rho[3];
-          ok = locate(t + j * g.d, g, kk, rho);
+          ok = locate<D>(t + j * D, g, kk, rho);
           if (ok) {
-            nc = 1 << g.d;
 #pragma unroll
-            for (int cc = 0; cc < 8; ++cc)
-              if (cc < nc) corner(g, kk, rho, cc, &node[cc], &W[cc]);
+            for (int cc = 0; cc < NC; ++cc) corner<D>(g, kk, rho, cc, &node[cc], &Wt[cc]);
           }
         } else {
-          nc = 1;
           node[0] = j - a;
-          W[0] = 1.0;
+          Wt[0] = 1.0;
         }
-        const double yv = double(y[j]);
         ok = ok && isfinite(yv);
+      }
+      if (!ok) {
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc) {
+          node[cc] = 0;
+          Wt[cc] = 0.0;
+        }
+      }
+      double *row = S.ph[wave][ob];
+      if (part == 0) {
         double mv = 0.0;
-        if (ok) {
 #pragma unroll
-          for (int cc = 0; cc < 8; ++cc)
-            if (cc < nc) mv += W[cc] * double(mu[node[cc]]);
-        }
-        yc[tid] = ok ? yv - mv : 0.0;
-        for (int l = 0; l < k; ++l) {
-          double v = 0.0;
-          if (ok) {
+        for (int cc = 0; cc < NC; ++cc) mv += Wt[cc] * double(mu[node[cc]]);
+        row[k] = ok ? yv - mv : 0.0;
+      }
+#pragma unroll 4
+      for (int l = part; l < k; l += LPO) {
+        double v = 0.0;
 #pragma unroll
-            for (int cc = 0; cc < 8; ++cc)
-              if (cc < nc) v += W[cc] * double(efuns[int64_t(l) * P + node[cc]]);
-          }
-          ph[tid][l] = v;
+        for (int cc = 0; cc < NC; ++cc) v += Wt[cc] * double(efuns[int64_t(l) * P + node[cc]]);
+        row[l] = ok ? v : 0.0;
+      }
+      wave_sync();
+#pragma unroll 4
+      for (int o = 0; o < OB; o += 4) {
+        const double *src = S.ph[wave][o + (lane >> 4)] + (lane & 15);
+        double f[CT];
+#pragma unroll
+        for (int q = 0; q < CT; ++q) f[q] = src[16 * q];
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[0], f[0], acc[0], 0, 0, 0);
+        if constexpr (CT > 1) {
+          acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[0], f[1], acc[1], 0, 0, 0);
+          acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[1], f[1], acc[2], 0, 0, 0);
         }
+        if constexpr (CT > 2) {
+          acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[0], f[2], acc[3], 0, 0, 0);
+          acc[4] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[1], f[2], acc[4], 0, 0, 0);
+        }
+      }
+      wave_sync();
+    }
+    __syncthreads();  // the tiles take the rows' place
+#pragma unroll
+    for (int q = 0; q < W::NT; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) S.red[wave][q * 256 + ((lane >> 4) + 4 * v) * 16 + (lane & 15)] = acc[q][v];
+    __syncthreads();
+    for (int e = tid; e < k * (k + 1); e += PACE_THREADS) {
+      const int r = e / (k + 1), c = e % (k + 1);
+      const int lo = r < c ? r : c, hi = r < c ? c : r;
+      const int tb = hi >> 4, q = tb == 0 ? 0 : (tb == 1 ? 1 : 3) + (lo >> 4);
+      const int o = q * 256 + (lo & 15) * 16 + (hi & 15);
+      const double sum = (S.red[0][o] + S.red[1][o]) + (S.red[2][o] + S.red[3][o]);
+      const bool kr = dg.v[r] >= 0.0, kc = c == k || dg.v[c] >= 0.0;
+      // dropped components: identity rows and columns, zero right-hand side
+      S.M[r][c] = (kr && kc) ? sum + (r == c ? dg.v[r] : 0.0) : (r == c ? 1.0 : 0.0);
+    }
+    __syncthreads();
+    // step c takes row c off every other row, columns past c only: neither row
+    // c nor column c changes while it is read
+    bool good = true;
+    for (int c = 0; c < k; ++c) {
+      const double piv = S.M[c][c];
+      good = good && piv > 0.0;
+      if (er < k && er != c) {
+        const double f = S.M[er][c] / piv;
+        for (int j = c + 1 + ej; j <= k; j += en) S.M[er][j] = fma(-f, S.M[c][j], S.M[er][j]);
       }
       __syncthreads();
-#pragma unroll
-      for (int q = 0; q < PACE_ACC; ++q) {
-        const int e = tid + PACE_THREADS * q;
-        if (e < nmat) {
-          const int r = tri_r[e], c = tri_c[e];
-          double s = 0.0;
-          for (int o = 0; o < m; ++o) s += ph[o][r] * ph[o][c];
-          acc[q] += s;
-        } else if (e < nacc) {
-          const int r = e - nmat;
-          double s = 0.0;
-          for (int o = 0; o < m; ++o) s += ph[o][r] * yc[o];
-          acc[q] += s;
-        }
-      }
     }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PACE_ACC; ++q) {
-      const int e = tid + PACE_THREADS * q;
-      if (e < nmat) {
-        const int r = tri_r[e], c = tri_c[e];
-        const bool kr = dg.v[r] >= 0.0, kc = dg.v[c] >= 0.0;
-        // dropped components: identity rows and columns, zero right-hand side
-        const double v = (kr && kc) ? acc[q] + (r == c ? dg.v[r] : 0.0) : (r == c ? 1.0 : 0.0);
-        A[r][c] = v;
-        A[c][r] = v;
-      } else if (e < nacc) {
-        const int r = e - nmat;
-        rhs[r] = dg.v[r] >= 0.0 ? acc[q] : 0.0;
-      }
-    }
-    __syncthreads();
-    if (tid == 0) {
-      const bool good = chol_inplace(A, k);
-      if (good) chol_solve(A, rhs, k);
-      for (int l = 0; l < k; ++l) scores[i * k + l] = T(good ? rhs[l] : __builtin_nan(""));
-    }
+    if (tid < k) scores[i * k + tid] = T(good ? S.M[tid][k] / S.M[tid][tid] : __builtin_nan(""));
   }
+}
+
+template <typename T, int D>
+int pace_launch(fpca_context *ctx, const GridDims &g, int64_t n, const int64_t *offsets, const T *t, const T *y,
+                const T *mu, const T *efuns, int k, const PaceDiag &dg, const int *cg_ok, T *scores, int *ready) {
+  // grid-stride over the curves; on the common grid most of them are done
+  // (k_pace_cg_rhs solved them) and a workgroup only checks their marker
+  const unsigned blocks = unsigned(n < 2048 ? n : 2048);
+  auto *kern = k + 1 <= 16 ? k_pace<T, D, 1> : (k + 1 <= 32 ? k_pace<T, D, 2> : k_pace<T, D, 3>);
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(PACE_THREADS), 0, ctx->stream, g, n, offsets, t, y, mu, efuns, k, dg,
+                     cg_ok, scores, ready);
+  FPCA_LAUNCH_CHECK("pace");
+  return FPCA_OK;
 }
 
 // Scratch of the common-grid design: the shared k x k inverse, its
@@ -592,7 +619,6 @@ int pace_impl(fpca_context *ctx, const fpca_grid *grid, int design, int64_t n, c
               const T *y, const T *mu, const T *efuns, int k, const PaceDiag &dg, T *scores, void *fixed) {
   if (n == 0) return FPCA_OK;
   const GridDims g = make_dims(grid);
-  const double *Lcg = nullptr;
   const int *cg_ok = nullptr;
   int *ready_out = nullptr;   // the flags k_pace clears (common grid)
   bool *clean_out = nullptr;  // set again once that k_pace is queued
@@ -617,7 +643,6 @@ int pace_impl(fpca_context *ctx, const fpca_grid *grid, int design, int64_t n, c
     *clean = false;
     ready_out = ready;
     clean_out = clean;
-    Lcg = L;
     cg_ok = okf;
     // workgroup 0 inverts the shared matrix, the next CG_NGW form its partial
     // sums, the others take 16 curves each
@@ -630,48 +655,78 @@ int pace_impl(fpca_context *ctx, const fpca_grid *grid, int design, int64_t n, c
                          dg, gpart, L, okf, ready, scores);
     FPCA_LAUNCH_CHECK("pace_cg_rhs");
   }
-  // grid-stride over the curves; on the common grid most of them are done
-  // (k_pace_cg_rhs solved them) and a workgroup only checks their marker
-  const unsigned blocks = unsigned(n < 2048 ? n : 2048);
-  hipLaunchKernelGGL(k_pace<T>, dim3(blocks), dim3(PACE_THREADS), 0, ctx->stream, g, n, design, offsets, t, y, mu,
-                     efuns, k, dg, Lcg, cg_ok, scores, ready_out);
-  FPCA_LAUNCH_CHECK("pace");
+  const auto launch = design == FPCA_COMMON_GRID ? pace_launch<T, 0>
+                      : g.d == 1                 ? pace_launch<T, 1>
+                      : g.d == 2                 ? pace_launch<T, 2>
+                                                 : pace_launch<T, 3>;
+  if (int rc = launch(ctx, g, n, offsets, t, y, mu, efuns, k, dg, cg_ok, scores, ready_out)) return rc;
   if (clean_out) *clean_out = true;
   return FPCA_OK;
 }
 
 // Reconstruction on the grid (the display after eq. 2.7):
-//   xhat[i][p] = mu[p] + sum_l xi[i][l] phi_l[p].
-// Thread per node p of a 256-node block with its k basis values in registers
-// (KB of them: k rounded up to a multiple of 8, the rest zero), the block's
-// RC_CURVES score rows in LDS (zero past k); writes are contiguous along p.
-// 64 curves per block: each block reads its nodes' basis values once per 64
-// output rows.
-constexpr int RC_CURVES = 64;
+//   xhat[i][p] = mu[p] + sum_l xi[i][l] phi_l[p]
+// on FP64 MFMA 16x16x4 (rows = curves, columns = nodes, K = components in KS
+// steps of 4, zero past k). A wavefront keeps the basis of its RC_NODES nodes
+// in registers and walks the workgroup's curves 16 at a time, the next 16
+// scores on their way. Bound by the writing of xhat. 5000 curves, P = 4096,
+// k = 20: 44 us with a thread per node and the scores read from LDS for every
+// multiplication, 28 us here (2.9 TB/s).
+constexpr int RC_CURVES = 64;  // curves per workgroup, at most
+constexpr int RC_NODES = 32;   // nodes per wavefront (64 need twice the registers: 31 us)
 
-template <typename T, int KB>
-__global__ __launch_bounds__(256) void k_reconstruct(int64_t P, int64_t n, int k, const T *__restrict__ mu,
+template <typename T, int KS>
+__global__ __launch_bounds__(256) void k_reconstruct(int64_t P, int64_t n, int k, int curves, const T *__restrict__ mu,
                                                      const T *__restrict__ efuns, const T *__restrict__ xi,
                                                      T *__restrict__ xhat) {
-  __shared__ double xs[RC_CURVES][KB];
-  const int64_t i0 = int64_t(blockIdx.y) * RC_CURVES;
-  const int nc = int(min(int64_t(RC_CURVES), n - i0));
-  for (int e = threadIdx.x; e < nc * KB; e += blockDim.x) {
-    const int c = e / KB, l = e % KB;
-    xs[c][l] = l < k ? double(xi[(i0 + c) * k + l]) : 0.0;
+  constexpr int NB = RC_NODES / 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kk = lane >> 4, col = lane & 15;
+  const int64_t p0 = int64_t(blockIdx.x) * (4 * RC_NODES) + wave * RC_NODES;
+  if (p0 >= P) return;
+  const int64_t i0 = int64_t(blockIdx.y) * curves, i1 = min(n, i0 + curves);
+  double ph[KS][NB], m[NB];
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    const int64_t p = min(p0 + 16 * q + col, P - 1);
+    m[q] = double(mu[p]);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) ph[s][q] = double(efuns[int64_t(min(4 * s + kk, k - 1)) * P + p]);
   }
-  __syncthreads();
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= P) return;
-  double ph[KB];
 #pragma unroll
-  for (int l = 0; l < KB; ++l) ph[l] = l < k ? double(efuns[int64_t(l) * P + p]) : 0.0;
-  const double m = double(mu[p]);
-  for (int c = 0; c < nc; ++c) {
-    double v = m;
+  for (int q = 0; q < NB; ++q)
 #pragma unroll
-    for (int l = 0; l < KB; ++l) v = fma(xs[c][l], ph[l], v);
-    xhat[(i0 + c) * P + p] = T(v);
+    for (int s = 0; s < KS; ++s) ph[s][q] = 4 * s + kk < k ? ph[s][q] : 0.0;
+  // scores of curve i + col, components 4 s + kk (clamped; zeroed where used)
+  T x[KS];
+  auto load = [&](int64_t i) {
+    const T *src = xi + min(i + col, n - 1) * k;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) x[s] = src[min(4 * s + kk, k - 1)];
+  };
+  load(i0);
+  for (int64_t i = i0; i < i1; i += 16) {
+    double a[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) a[s] = 4 * s + kk < k ? double(x[s]) : 0.0;
+    if (i + 16 < i1) load(i + 16);
+    v4d acc[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) acc[q] = v4d{m[q], m[q], m[q], m[q]};
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int q = 0; q < NB; ++q) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[s], ph[s][q], acc[q], 0, 0, 0);
+    // D[i][p]: row kk + 4 v, column col
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int64_t r = i + kk + 4 * v;
+      if (r >= i1) continue;
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        const int64_t p = p0 + 16 * q + col;
+        if (p < P) xhat[r * P + p] = T(acc[q][v]);
+      }
+    }
   }
 }
 
@@ -679,24 +734,24 @@ template <typename T>
 int reconstruct_impl(fpca_context *ctx, int64_t P, int64_t n, int k, const T *mu, const T *efuns, const T *xi,
                      T *xhat) {
   if (n == 0 || P == 0) return FPCA_OK;
-  const int64_t gy = (n + RC_CURVES - 1) / RC_CURVES;
-  if (gy > 65535) return set_error(FPCA_ERR_UNSUPPORTED, "n = %lld curves exceeds %d", (long long)n, 65535 * RC_CURVES);
-  const dim3 grid(unsigned((P + 255) / 256), unsigned(gy));
-  switch ((k + 7) / 8) {
-    case 1:
-      hipLaunchKernelGGL((k_reconstruct<T, 8>), grid, dim3(256), 0, ctx->stream, P, n, k, mu, efuns, xi, xhat);
-      break;
-    case 2:
-      hipLaunchKernelGGL((k_reconstruct<T, 16>), grid, dim3(256), 0, ctx->stream, P, n, k, mu, efuns, xi, xhat);
-      break;
-    case 3:
-      hipLaunchKernelGGL((k_reconstruct<T, 24>), grid, dim3(256), 0, ctx->stream, P, n, k, mu, efuns, xi, xhat);
-      break;
-    default:
-      hipLaunchKernelGGL((k_reconstruct<T, PACE_KMAX>), grid, dim3(256), 0, ctx->stream, P, n, k, mu, efuns, xi,
-                         xhat);
-      break;
+  if ((n + RC_CURVES - 1) / RC_CURVES > 65535)
+    return set_error(FPCA_ERR_UNSUPPORTED, "n = %lld curves exceeds %d", (long long)n, 65535 * RC_CURVES);
+  const int64_t gx = (P + 4 * RC_NODES - 1) / (4 * RC_NODES);
+  int curves = RC_CURVES;  // fewer while the workgroups would leave CUs idle
+  while (curves > 16 && gx * ((n + curves - 1) / curves) < 4 * ctx->num_cus) curves /= 2;
+  const dim3 grid(unsigned(gx), unsigned((n + curves - 1) / curves));
+  auto *kern = k_reconstruct<T, PACE_KMAX / 4>;
+  switch ((k + 3) / 4) {
+    case 1: kern = k_reconstruct<T, 1>; break;
+    case 2: kern = k_reconstruct<T, 2>; break;
+    case 3: kern = k_reconstruct<T, 3>; break;
+    case 4: kern = k_reconstruct<T, 4>; break;
+    case 5: kern = k_reconstruct<T, 5>; break;
+    case 6: kern = k_reconstruct<T, 6>; break;
+    case 7: kern = k_reconstruct<T, 7>; break;
+    default: break;
   }
+  hipLaunchKernelGGL(kern, grid, dim3(256), 0, ctx->stream, P, n, k, curves, mu, efuns, xi, xhat);
   FPCA_LAUNCH_CHECK("reconstruct");
   return FPCA_OK;
 }

@@ -280,3 +280,40 @@ def test_bin_cov_rows(torch, F, h, M, dt, q, Ns):
     ref = oracle.bin_cov_pairs(M, off, t.astype(np.float64), y.astype(np.float64), want_Q=q)
     for a, r in zip(out, ref):
         assert normwise_rel(a.cpu().numpy().astype(np.float64), r) < (1e-12 if dt == "f64" else 1e-5)
+
+
+@pytest.mark.parametrize("M,k", [((7,), 1), ((30,), 15), ((9, 8), 4), ((9, 8), 8), ((9, 8), 16), ((20, 11), 31),
+                                 ((12, 10), 32), ((5, 4, 6), 9), ((6, 5, 4), 17), ((6, 6, 4), 32)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("common", [False, True])
+def test_pace_runs_and_column_tiles(torch, F, h, M, k, dt, common):
+    """1, 2 or 3 tiles of 16 columns (k components and the residual); curves of no, one, a run's and one more
+    than a run's or a round's observations, or rows of the common grid with missing values. Bars of the scores at
+    ordinary sizes."""
+    _say(f"pace tiles M={M} k={k} {dt} common={common}")
+    rng = np.random.default_rng(k + len(M))
+    npdt, tdt, code = ((np.float64, torch.float64, F.FPCA_F64) if dt == "f64" else
+                       (np.float32, torch.float32, F.FPCA_F32))
+    P, d = int(np.prod(M)), len(M)
+    mu = rng.standard_normal(P).astype(npdt)
+    ef = (rng.standard_normal((k, P)) / np.sqrt(P)).astype(npdt)
+    lam = np.linspace(2.0, 0.05, k)
+    if common:
+        n, off, t, design = 5, None, None, F.FPCA_COMMON_GRID
+        y = rng.standard_normal((n, P)).astype(npdt)
+        y[rng.random((n, P)) < 0.2] = np.nan
+        y[2] = np.nan
+    else:
+        Ns = np.array([0, 1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300])
+        n, design = len(Ns), F.FPCA_IRREGULAR
+        off = np.concatenate([[0], np.cumsum(Ns)]).astype(np.int64)
+        t = rng.random((int(off[-1]), d)).astype(npdt)
+        t[40, 0] = -0.5  # outside the domain: left out
+        y = rng.standard_normal(int(off[-1])).astype(npdt)
+    out = torch.full((n, k), float("nan"), dtype=tdt, device="cuda:0")
+    D = lambda a: None if a is None else dev(torch, a)
+    F.fpca_pace_scores(h, F.Grid(M), design, code, n, D(off), D(t), D(y), D(mu), D(ef), k, lam, 0.05, out)
+    ref = oracle.pace_scores(M, off, None if t is None else t.astype(np.float64), y.astype(np.float64),
+                             mu.astype(np.float64), ef.T.astype(np.float64), lam, 0.05)
+    got = out.cpu().numpy().astype(np.float64)
+    assert np.abs(got - ref).max() <= (1e-10 if dt == "f64" else 1e-5) * np.abs(ref).max()
