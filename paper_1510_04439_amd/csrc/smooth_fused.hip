@@ -130,7 +130,9 @@ __global__ void k_tables(int M0, int M1, double H0, double H1, int R0, int R1, i
 
 // ---------------------------------------------------------------- stage T
 // U layout: 3 arrays of P x P (row s, column t): G00, G10, G01 (exponents of
-// u in (t1, t2)).
+// u in (t1, t2)); columns with t1 < s1 - R are not written (stage S only uses
+// such values for nodes p > q, which it does not compute). Bound by memory: 64
+// x 64 nodes, R = 6: whole planes 88 us, these 62 (170 MB).
 template <int R>
 __global__ __launch_bounds__(512) void k_stage_t(int M1, int M2, int64_t P, const float *__restrict__ G, Taps tp,
                                                   float *__restrict__ U) {
@@ -143,15 +145,18 @@ __global__ __launch_bounds__(512) void k_stage_t(int M1, int M2, int64_t P, cons
   float *A = lds + plane;  // t2-pass planes GK, GU
   const int64_t s = blockIdx.x;
   const int tid = threadIdx.x;
-  for (int64_t e = tid; e < P; e += blockDim.x) {
+  // stage S takes the moments of row s at (t1, t2) only for s1 <= t1 + R:
+  // outputs from tlo on, from lines l0 on
+  const int s1 = int(s / M2), tlo = max(0, s1 - R), l0 = max(0, s1 - 2 * R), nl = M1 - l0;
+  for (int64_t e = int64_t(l0) * M2 + tid; e < P; e += blockDim.x) {
     const int t1 = int(e / M2), t2 = int(e % M2);
     rowG[t1 * LD + t2] = G[s * P + e];
   }
   __syncthreads();
   // t2 pass: thread -> (strip of NB outputs along t2, line t1), t1 fastest
   const int nst2 = (M2 + NB - 1) / NB;
-  for (int sidx = tid; sidx < nst2 * M1; sidx += blockDim.x) {
-    const int t1 = sidx % M1, t20 = (sidx / M1) * NB;
+  for (int sidx = tid; sidx < nst2 * nl; sidx += blockDim.x) {
+    const int t1 = l0 + sidx % nl, t20 = (sidx / nl) * NB;
     float wg[WIN];
 #pragma unroll
     for (int i = 0; i < WIN; ++i) {
@@ -176,9 +181,9 @@ __global__ __launch_bounds__(512) void k_stage_t(int M1, int M2, int64_t P, cons
   __syncthreads();
   // t1 pass: thread -> (t2, strip of NB outputs along t1), t2 fastest; results to HBM row s
   const int64_t PP = P * P;
-  const int nst1 = (M1 + NB - 1) / NB;
+  const int nst1 = (M1 - tlo + NB - 1) / NB;
   for (int sidx = tid; sidx < nst1 * M2; sidx += blockDim.x) {
-    const int t2 = sidx % M2, t10 = (sidx / M2) * NB;
+    const int t2 = sidx % M2, t10 = tlo + (sidx / M2) * NB;
     float out[3][NB];
 #pragma unroll
     for (int q = 0; q < 3; ++q)
