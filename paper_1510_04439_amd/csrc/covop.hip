@@ -357,6 +357,7 @@ struct BandArgs {
   double *band;  // stored blocks
   const double *Hs;  // d >= 2: Y2 summed over p_0 (k_hsum); Y2 itself for d = 2
   int c0, nc;        // d >= 2: columns of X of this launch
+  double *Tsum;      // half of the pairs formed: P x nc sums of the other half
 };
 
 // Local node li of a tile (coordinate d-1 fastest) and its grid coordinates.
@@ -712,14 +713,23 @@ __global__ __launch_bounds__(256) void k_retile(CovGeo g, const double *__restri
   }
 }
 
+// LDS written by a wavefront is read by its other lanes
+__device__ inline void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 constexpr int MT = 512;     // threads: 8 wavefronts
 constexpr int MKC = 104;    // curves per LDS chunk
 template <int d>
 constexpr int mfma_nv() { return 2 * d - 1; }  // H2 variants
-inline size_t band_mfma_lds(int d, int n, int R2, int ncb) {
+constexpr int TR_LD = 17;  // LDS row of a wavefront's transposed Delta
+inline size_t band_mfma_lds(int d, int n, int R2, int ncb, bool half) {
   const size_t kp = size_t(std::min(MKC, (n + 7) / 8 * 8));
   const size_t z = size_t(d + 1) * kp * 32, red = size_t(8) * ncb * 256;
-  return (std::max(z, red) + 2 * size_t(8 + 2 * R2) * (2 * d - 1) * 16) * 8;
+  const size_t tr = half ? size_t(8 * 16 * TR_LD + 2 * 16 * 16 * ncb) : 0;
+  return (std::max(z, red) + 2 * size_t(8 + 2 * R2) * (2 * d - 1) * 16 + tr) * 8;
 }
 
 // One workgroup per s-set (s_0; 4 of s_1; 8 of s_2): two blocks of 16 s-nodes,
@@ -737,7 +747,15 @@ inline size_t band_mfma_lds(int d, int n, int R2, int ncb) {
 // 50 ms), the rows of weights (50 ms, a gather of 64 rows per instruction) and
 // curves missed in L2. With the responses on the vector units from LDS, the
 // diagonal terms by LDS passes with barriers and a solve per pair: 1166 ms.
-template <int d, int NCB, bool STORE>
+// HALF (where there is scratch for it): Delta is symmetric, so of the blocks with
+// s_0 != t_0 (at s_0 = t_0: with other tiles of coordinate 1) only one of (s, t)
+// and (t, s) is formed, by the parity of the two numbers' sum the one with the
+// larger or with the smaller s (every s-set then has as many t). Its transpose,
+// through LDS, times X at the s-nodes is added to Tsum at the t-nodes with FP64
+// atomics: 4 matrix instructions and 256 additions per block beside the 200
+// instructions that form it. All pairs 230 ms (above),
+// these 129; d = 2, 100^2 nodes, R = 6, n = 100, r = 20: 518 and 381 us.
+template <int d, int NCB, bool STORE, bool HALF = false>
 __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   constexpr int F = d + 1, NT = 2 * d + 1, NV = mfma_nv<d>();
   constexpr int k1 = d - 2, k2 = d - 1;
@@ -751,6 +769,8 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   double *Zs = sm;            // [F][kp][32], the halves of a row swapped where curve / 2 is odd
   const int zsz = max(F * kp * 32, 8 * NCB * 256);
   double *H2 = sm + zsz;      // [2][hw][NV][16 (s_1, t_1)]
+  double *tr = H2 + 2 * hw * NV * 16;  // HALF: [wave][16 s][TR_LD t]
+  double *Xs = tr + 8 * 16 * TR_LD;    // HALF: [s-block][16 s][16 NCB columns of X]
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 15, gq = (tid & 63) >> 4;
   // s-set of this workgroup; consecutive workgroups of an XCD are neighbours
   int s0 = 0, s1a, s2a;
@@ -797,6 +817,15 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
     }
   };
   if (nch == 1) load_zs(0);
+  if constexpr (HALF) {
+    for (int e = tid; e < 2 * 16 * 16 * NCB; e += MT) {
+      const int col = e % (16 * NCB), i = e / (16 * NCB) & 15, b = e / (256 * NCB);
+      const int x1 = s1a + (i >> 2), x2 = s2a + 4 * b + (i & 3);
+      Xs[e] = x1 < M1 && x2 < M2 && col < A.nc ? A.X[node_of(s0, x1, x2) * A.r + A.c0 + col] : 0.0;
+    }
+    tr += wave * 16 * TR_LD;
+    Xs += sb * 256 * NCB;
+  }
 
   f64x4 oacc[NCB];
 #pragma unroll
@@ -814,12 +843,15 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   // this lane's place in the product over p_2: its value for lane (t_2; s_1, s_2) is in lane (s_1; t_2, s_2)
   const int perm = (((tid >> 2) & 3) * 16 + ((tid >> 4) & 3) * 4 + (tid & 3)) * 4;
   int buf = 0;
-  for (int t0 = t0lo; t0 <= t0hi; ++t0)
+  for (int t0 = t0lo; t0 <= t0hi; ++t0) {
+    if (HALF && t0 != s0 && (((s0 + t0) & 1) == 0) != (t0 > s0)) continue;  // formed as (t, s)
     for (int k = 0; k < T1n; ++k) {
       int T1 = k - (T1lo % T1n + T1n) % T1n;
       T1 = T1lo + (T1 < 0 ? T1 + T1n : T1);
       const int t1a = 4 * T1;
       if (T1 < 0 || t1a >= M1) continue;
+      if (HALF && t0 == s0 && t1a != s1a && (((t1a + s1a) & 4) == 0) != (t1a > s1a)) continue;
+      const bool mirror = HALF && (t0 != s0 || t1a != s1a);
       // ---- the diagonal terms summed over p_0 and p_1
       double *Hb = H2 + buf * hw * NV * 16;
       buf ^= 1;
@@ -1028,9 +1060,37 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
                   __builtin_amdgcn_mfma_f64_16x16x4f64(tok && col < A.nc ? xv : 0.0, delta[v], oacc[c], 0, 0, 0);
             }
           }
+          if (mirror) {
+            // lane l holds s-node l and t-nodes 4 gq + v (t_2 = gq, t_1 = v); as
+            // the second operand lane l has t-node l, step j the s-nodes 4 j + gq
+#pragma unroll
+            for (int v = 0; v < 4; ++v) tr[l * TR_LD + 4 * gq + v] = delta[v];
+            wave_sync();
+            f64x4 ta[NCB];
+#pragma unroll
+            for (int c = 0; c < NCB; ++c) ta[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const double dt = tr[(4 * j + gq) * TR_LD + l];
+#pragma unroll
+              for (int c = 0; c < NCB; ++c)
+                ta[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[(4 * j + gq) * 16 * NCB + 16 * c + l], dt, ta[c], 0, 0, 0);
+            }
+            wave_sync();
+            const int y1 = t1a + (l & 3), y2 = t2a + (l >> 2);
+            if (y1 < M1 && y2 < M2) {
+              double *dst = A.Tsum + node_of(t0, y1, y2) * A.nc;
+#pragma unroll
+              for (int c = 0; c < NCB; ++c)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                  if (16 * c + gq + 4 * v < A.nc) atomicAdd(dst + 16 * c + gq + 4 * v, ta[c][v]);
+            }
+          }
         }
       }
     }
+  }
   if constexpr (!STORE) {
     // the wavefronts' sums added in order: [wave / 2][s-block][c][row (column of X)][s]
     __syncthreads();
@@ -1195,14 +1255,20 @@ int launch_band1(fpca_covop_s *op, const double *X, int r, double *out) {
   return FPCA_OK;
 }
 
-template <int d, int NCB, bool STORE>
+// out[p][c0 + c] += Tsum[p][c]
+__global__ void k_add_cols(int64_t count, int nc, int r, int c0, const double *__restrict__ Tsum, double *out) {
+  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < count; e += int64_t(gridDim.x) * blockDim.x)
+    out[e / nc * r + c0 + e % nc] += Tsum[e];
+}
+
+template <int d, int NCB, bool STORE, bool HALF = false>
 int launch_band_mfma(fpca_covop_s *op, const BandArgs &A) {
-  const size_t lds = band_mfma_lds(d, int(op->n), op->R[d - 1], NCB);
+  const size_t lds = band_mfma_lds(d, int(op->n), op->R[d - 1], NCB, HALF);
   const int64_t nwg = (d == 3 ? op->M[0] : 1) * int64_t((op->M[d - 2] + 3) / 4) * ((op->M[d - 1] + 7) / 8);
   if (nwg > 0x7fffffffLL) return set_error(FPCA_ERR_UNSUPPORTED, "covariance operator: too many nodes");
-  FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE>),
+  FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE, HALF>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  hipLaunchKernelGGL((k_band_mfma<d, NCB, STORE>), dim3(unsigned(nwg)), dim3(MT), lds, op->ctx->stream, A);
+  hipLaunchKernelGGL((k_band_mfma<d, NCB, STORE, HALF>), dim3(unsigned(nwg)), dim3(MT), lds, op->ctx->stream, A);
   FPCA_LAUNCH_CHECK("covop band");
   return FPCA_OK;
 }
@@ -1220,6 +1286,19 @@ int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *ou
   }
   for (A.c0 = 0; A.c0 < r; A.c0 += 32) {
     A.nc = std::min(32, r - A.c0);
+    // half of the pairs, where there is room for the sums of the other half
+    const int64_t count = op->P * A.nc;
+    if (ws2_room(op->ctx, carve_bytes(size_t(count), 8))) {
+      A.Tsum = static_cast<double *>(op->ctx->ws2);
+      const unsigned blocks = unsigned(std::min<int64_t>((count + 255) / 256, 65536));
+      hipLaunchKernelGGL(k_zero_f64, dim3(blocks), dim3(256), 0, op->ctx->stream, A.Tsum, count);
+      FPCA_LAUNCH_CHECK("covop band zero");
+      if (int rc = A.nc <= 16 ? launch_band_mfma<d, 1, false, true>(op, A) : launch_band_mfma<d, 2, false, true>(op, A))
+        return rc;
+      hipLaunchKernelGGL(k_add_cols, dim3(blocks), dim3(256), 0, op->ctx->stream, count, A.nc, r, A.c0, A.Tsum, out);
+      FPCA_LAUNCH_CHECK("covop band add");
+      continue;
+    }
     if (int rc = A.nc <= 16 ? launch_band_mfma<d, 1, false>(op, A) : launch_band_mfma<d, 2, false>(op, A)) return rc;
   }
   return FPCA_OK;

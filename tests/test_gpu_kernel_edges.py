@@ -317,3 +317,46 @@ def test_pace_runs_and_column_tiles(torch, F, h, M, k, dt, common):
                              mu.astype(np.float64), ef.T.astype(np.float64), lam, 0.05)
     got = out.cpu().numpy().astype(np.float64)
     assert np.abs(got - ref).max() <= (1e-10 if dt == "f64" else 1e-5) * np.abs(ref).max()
+
+
+def test_paths_without_scratch(torch, F, h, monkeypatch):
+    """A handle whose scratch limit leaves no room for split sums, for the mirrored half of the operator's band and
+    for the sums of the j = l terms takes the ways without them, to the same results."""
+    _say("no scratch")
+    rng = np.random.default_rng(3)
+    M, n, r = (9, 8, 7), 11, 17
+    P = int(np.prod(M))
+    Y, X = rng.standard_normal((n, P)), rng.standard_normal((P, r))
+    Yc = rng.standard_normal((300, 65))
+    Ns, M2 = [40, 7, 12], (50, 52)
+    off = np.concatenate([[0], np.cumsum(Ns)]).astype(np.int64)
+    t, y = rng.random((int(off[-1]), 2)).astype(np.float32), rng.standard_normal(int(off[-1])).astype(np.float32)
+
+    def run(hh):
+        out = []
+        op = F.CovOp(hh, F.Grid(M), dev(torch, Y), dev(torch, Y.mean(0)), [0.3, 0.3, 0.4], F.FPCA_COVOP_RECOMPUTE)
+        o = torch.empty(P, r, dtype=torch.float64, device="cuda:0")
+        op.apply(dev(torch, X), o)
+        out.append(o.cpu().numpy())
+        op.close()
+        for tt, code, prec in ((torch.float32, F.FPCA_F32, F.FPCA_PREC_F32), (torch.float64, F.FPCA_F64, F.FPCA_PREC_F64)):
+            S = torch.empty(65, 65, dtype=tt, device="cuda:0")
+            F.fpca_bin(hh, F.Grid((65,)), F.FPCA_BIN_COV, F.FPCA_COMMON_GRID, code, prec, 300, None, None,
+                       dev(torch, Yc).to(tt), None, 0, None, S)
+            out.append(S.cpu().numpy().astype(np.float64))
+        C, G = (torch.empty(2600, 2600, dtype=torch.float32, device="cuda:0") for _ in range(2))
+        F.fpca_bin(hh, F.Grid(M2), F.FPCA_BIN_COV, F.FPCA_IRREGULAR, F.FPCA_F32, F.FPCA_PREC_F32, len(Ns),
+                   dev(torch, off), dev(torch, t), dev(torch, y), None, 0, C, G)
+        out += [C.cpu().numpy().astype(np.float64), G.cpu().numpy().astype(np.float64)]
+        return out
+
+    full = run(h)
+    # rows of the three curves (2 x 31 KB) fit, their j = l sums (104 KB) and everything larger do not
+    monkeypatch.setenv("FPCA_DEBUG_WS_LIMIT", str(66 * 1024))
+    lim = F.Handle(0)
+    try:
+        small = run(lim)
+    finally:
+        lim.close()
+    for a, b, tol in zip(full, small, (1e-12, 1e-5, 1e-12, 1e-5, 1e-5)):
+        assert normwise_rel(b, a) < tol
