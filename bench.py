@@ -254,7 +254,7 @@ def f2_timing(h, torch, F):
     finally:
         op.close()
     flops = band_pairs * 2.0 * 7 * ds.n
-    res["roofline"] = {"bound": "fp64", "kernel": "k_band<3> (one product, r=16)",
+    res["roofline"] = {"bound": "fp64", "kernel": "k_band_mfma<3> (one product, r=16)",
                        "alg_flops_per_band_pair": 2 * 7 * ds.n, "achieved": flops / (t_apply * 1e-3) / 1e12,
                        "peak": 78.6, "unit": "TFLOP/s", "frac": flops / (t_apply * 1e-3) / 1e12 / 78.6}
     free, _ = torch.cuda.mem_get_info()

@@ -213,10 +213,12 @@ int fpca_set_conv(fpca_handle handle, int mode);
  * moments kept on chip between passes; grids of P <= 4096 with M <= 64 for
  * d = 1, 32 x 64 for d = 2, 16^3 for d = 3); FPCA_ENGINE_PASSES the 1-D pass
  * engine (FP64 moment arrays in device memory between passes, any grid);
- * FPCA_ENGINE_AUTO (default) takes the queue kernel when the pass engine's
- * arrays would not fit in the 256 MB Infinity Cache, and batched CV also
- * times the job-by-job pass engine against the queue kernel's tile shapes.
- * Both engines compute the same sums in FP64 (results agree to rounding).
+ * FPCA_ENGINE_AUTO (default) takes the staged kernels for d = 2 and 3 with
+ * M <= 40 per coordinate and P <= 4096 (whole lines in registers, three
+ * stages); elsewhere the queue kernel when the pass engine's arrays would not
+ * fit in the 256 MB Infinity Cache, and batched CV times the job-by-job pass
+ * engine against the queue kernel's tile shapes. All engines compute the same
+ * sums in FP64 (results agree to rounding).
  */
 #define FPCA_ENGINE_AUTO 0
 #define FPCA_ENGINE_QUEUE 1
@@ -303,7 +305,8 @@ int fpca_eig_randomized(fpca_handle handle, int dtype, int prec, const fpca_grid
  *     grid steps (R_max = 2016, 28, 6 for d = 1, 2, 3) and be non-degenerate
  *     at every node, else FPCA_ERR_UNSUPPORTED.
  *   mode: FPCA_COVOP_RECOMPUTE (the band is recomputed tile by tile in every
- *     product; the operator holds O(n P) memory) or FPCA_COVOP_STORE_BAND (the
+ *     product; the operator holds O(n P) memory, a product for d >= 2 takes
+ *     P x min(r, 32) doubles of the handle's scratch where they fit) or FPCA_COVOP_STORE_BAND (the
  *     band is formed once and kept in 64 x 64 FP64 blocks, about
  *     P x 64 x prod_k (2 ceil(2R_k / b_k) + 1) doubles with tile extents
  *     b = 64 / 8 / 4 for d = 1 / 2 / 3; products then stream it).
@@ -420,13 +423,15 @@ int fpca_reconstruct(fpca_handle handle, int dtype, int64_t P, int64_t n, int k,
  *     with folds and sq_sums (slab 0 all curves, slab f+1 fold f).
  *   bandwidths: host, n_h x d, shared by the datasets. scores: host,
  *     n_data x n_h x n_folds.
- * All jobs run in one persistent launch on the handle's stream (moments and
- * solves in FP64); the tile shape is chosen by timing on the first call with a
- * shape, the second call captures the launch into a HIP graph and later calls
- * replay it. Grids with more than 4096 nodes, or a first coordinate longer
- * than the launch's LDS allows (d = 1: 64, d = 2: 32, d = 3: 16), run job by
- * job instead. Synchronizes; FPCA_ERR_DEVICE if a task of the launch waited
- * past its spin limit.
+ * Moments and solves are in FP64. On grids that the staged kernels take (see
+ * fpca_set_engine) the jobs run through them in batches, a launch per stage.
+ * Elsewhere all jobs run in one persistent launch on the handle's stream: the
+ * tile shape is chosen by timing on the first call with a shape, the second
+ * call captures the launch into a HIP graph and later calls replay it; grids
+ * with more than 4096 nodes, or a first coordinate longer than the launch's
+ * LDS allows (d = 1: 64, d = 2: 32, d = 3: 16), run job by job instead.
+ * Synchronizes; FPCA_ERR_DEVICE if a task of the persistent launch waited past
+ * its spin limit.
  */
 typedef struct {
   fpca_grid grid;

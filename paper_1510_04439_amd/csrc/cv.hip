@@ -9,8 +9,10 @@
 // i.e. sum over held-out pairs of w (Y_ij Y_il - Ghat(bin))^2 spread over the
 // pair's bins by the binning weights (Ghat = 0 where the window is empty).
 //
-// Every (dataset, bandwidth, fold) job of a call runs in one persistent launch
-// of the task-queue smoother (smooth_tiled.hip). Its tile shape (t-columns per
+// On grids that the staged smoother takes (smooth_staged.hip; d = 2, 3) the
+// jobs run through it in batches, a launch per stage. Elsewhere, and where the
+// engine is set, every (dataset, bandwidth, fold) job of a call runs in one
+// persistent launch of the task-queue smoother (smooth_tiled.hip). Its tile shape (t-columns per
 // task) and the number of persistent workgroups per compute unit are chosen
 // per shape by timing the candidates that fit in LDS on the first call (with
 // the job-by-job general pass engine as one more candidate); the

@@ -647,8 +647,9 @@ template <typename T>
 int staged_scores(fpca_context *ctx, const fpca_grid *grid, const std::vector<StagedJob> &jobs, double *scores) {
   const Shape s = shape_of(grid);
   const size_t PP = size_t(s.P) * s.P, per = job_bytes(s, sizeof(T), true), J = jobs.size();
-  const int nb_max = int(std::max<size_t>(1, std::min<size_t>({size_t(SB_MAX), J, (size_t(1) << 30) / per})));
   const size_t bytes_part = carve_bytes(J * SC_WG, 8);
+  int nb_max = int(std::max<size_t>(1, std::min<size_t>({size_t(SB_MAX), J, (size_t(1) << 30) / per})));
+  while (nb_max > 1 && !ws_room(ctx, bytes_part + nb_max * per)) --nb_max;  // a scratch limit: fewer jobs at a time
   if (int rc = ws_reserve(ctx, bytes_part + nb_max * per)) return rc;
   Carver cw{static_cast<char *>(ctx->ws), 0, ctx->ws_size};
   double *part = cw.take<double>(J * SC_WG);

@@ -319,6 +319,27 @@ def test_pace_runs_and_column_tiles(torch, F, h, M, k, dt, common):
     assert np.abs(got - ref).max() <= (1e-10 if dt == "f64" else 1e-5) * np.abs(ref).max()
 
 
+def test_cv_batches_under_a_scratch_limit(torch, F, h, monkeypatch):
+    """A scratch limit with room for some jobs of a staged batch takes fewer at a time, to the same scores."""
+    _say("cv under a limit")
+    rng = np.random.default_rng(5)
+    M, P, nf = (8, 9), 72, 3
+    off, t, y = rand_irregular(rng, 2, 40, 2, 12, np.float64)
+    folds = (np.arange(40) % nf).astype(np.int32)
+    slabs = [oracle.bin_cov_pairs(M, off, t, y, folds, f, want_Q=True) for f in [-1] + list(range(nf))]
+    C, G, Q = (dev(torch, np.stack([s[i] for s in slabs])) for i in range(3))
+    run = lambda hh: F.fpca_cv_batched(hh, F.FPCA_F64, [(F.Grid(M), C, G, Q)], nf, [0.3, 0.5])[0]
+    full = run(h)
+    # a job takes 14 P^2 doubles of moments and P^2 of fits, about 0.63 MB, the six jobs' partial sums less
+    monkeypatch.setenv("FPCA_DEBUG_WS_LIMIT", str(2 << 20))
+    lim = F.Handle(0)
+    try:
+        got = run(lim)
+    finally:
+        lim.close()
+    np.testing.assert_allclose(got, full, rtol=1e-12)
+
+
 def test_paths_without_scratch(torch, F, h, monkeypatch):
     """A handle whose scratch limit leaves no room for split sums, for the mirrored half of the operator's band and
     for the sums of the j = l terms takes the ways without them, to the same results."""
