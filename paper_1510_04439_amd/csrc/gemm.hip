@@ -609,13 +609,17 @@ struct Frag<double> {
   static __device__ inline int row(int lane, int v) { return (lane >> 4) + 4 * v; }
 };
 
-// Columns c .. c + 3 of row kr, zero outside the matrix. The addresses are
-// clamped, not branched around, so that a stage's loads are in flight together.
+// Four values of row kr, zero outside the matrix: columns c0 + 4 l .. + 3 for
+// thread l of 16, or without alignment c0 + l + 16 e (whole segments of a row
+// per load). The addresses are clamped, not branched around, so that a stage's
+// loads are in flight together.
 template <typename T, bool VEC>
-__device__ inline typename Frag<T>::vec gram_load4(const T *__restrict__ A, int64_t kr, int64_t K, int64_t N, int64_t c) {
+__device__ inline typename Frag<T>::vec gram_load4(const T *__restrict__ A, int64_t kr, int64_t K, int64_t N,
+                                                   int64_t c0, int l) {
   typename Frag<T>::vec v;
   const T *row = A + (kr < K ? kr : K - 1) * N;
   if constexpr (VEC) {  // N a multiple of 4: a group of four is inside or outside
+    const int64_t c = c0 + 4 * l;
     const T *src = row + (c < N ? c : N - 4);
     if constexpr (sizeof(T) == 4) {
       v = *reinterpret_cast<const float4_t *>(src);
@@ -627,10 +631,11 @@ __device__ inline typename Frag<T>::vec gram_load4(const T *__restrict__ A, int6
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = in ? v[e] : T(0);
   } else {
+    const int64_t c = c0 + l;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = row[c + e < N ? c + e : N - 1];
+    for (int e = 0; e < 4; ++e) v[e] = row[c + 16 * e < N ? c + 16 * e : N - 1];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (kr < K && c + e < N) ? v[e] : T(0);
+    for (int e = 0; e < 4; ++e) v[e] = (kr < K && c + 16 * e < N) ? v[e] : T(0);
   }
   return v;
 }
@@ -665,7 +670,7 @@ __global__ __launch_bounds__(256) void k_gram_mfma(GramMats<T> ms, int64_t K, in
   const T *__restrict__ A = ms.A[blockIdx.z];
   const bool diag_tile = bi == bj;
   const int tid = threadIdx.x, lane = tid & 63, wm = tid >> 7, wn = (tid >> 6) & 1;
-  const int lr = tid >> 4, lc = (tid & 15) * 4;
+  const int lr = tid >> 4, ll = tid & 15;
   const int64_t m0 = int64_t(bi) * GT, n0 = int64_t(bj) * GT;
   const int64_t kb = int64_t(blockIdx.y) * rows, ke = kb + rows < K ? kb + rows : K;
   vec acc[2][2];
@@ -676,17 +681,25 @@ __global__ __launch_bounds__(256) void k_gram_mfma(GramMats<T> ms, int64_t K, in
   vec ra[PR], rb[PR];
   auto load = [&](int64_t k0) {
 #pragma unroll
-    for (int u = 0; u < PR; ++u) ra[u] = gram_load4<T, VEC>(A, k0 + u * 16 + lr, ke, N, m0 + lc);
+    for (int u = 0; u < PR; ++u) ra[u] = gram_load4<T, VEC>(A, k0 + u * 16 + lr, ke, N, m0, ll);
     if (!diag_tile) {
 #pragma unroll
-      for (int u = 0; u < PR; ++u) rb[u] = gram_load4<T, VEC>(A, k0 + u * 16 + lr, ke, N, n0 + lc);
+      for (int u = 0; u < PR; ++u) rb[u] = gram_load4<T, VEC>(A, k0 + u * 16 + lr, ke, N, n0, ll);
     }
   };
   auto put = [&](int buf) {
 #pragma unroll
     for (int u = 0; u < PR; ++u) {
-      *reinterpret_cast<vec *>(&As[buf][u * 16 + lr][lc]) = ra[u];
-      if (!diag_tile) *reinterpret_cast<vec *>(&Bs[buf][u * 16 + lr][lc]) = rb[u];
+      if constexpr (VEC) {
+        *reinterpret_cast<vec *>(&As[buf][u * 16 + lr][4 * ll]) = ra[u];
+        if (!diag_tile) *reinterpret_cast<vec *>(&Bs[buf][u * 16 + lr][4 * ll]) = rb[u];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          As[buf][u * 16 + lr][ll + 16 * e] = ra[u][e];
+          if (!diag_tile) Bs[buf][u * 16 + lr][ll + 16 * e] = rb[u][e];
+        }
+      }
     }
   };
   int buf = 0;
@@ -756,11 +769,10 @@ __global__ __launch_bounds__(256) void k_gram_sum(GramMats<T> ms, int64_t N, int
                 vec{T(s[0]), T(s[1]), T(s[2]), T(s[3])});
 }
 
-// nm products of one shape. The K rows are split until about GR_WGS
-// workgroups per CU have work, in shares of at least two stages; without room
-// for the shares' sums (a scratch limit, a capture before the arena has grown)
-// the rows stay whole.
-constexpr int GR_WGS = 4;
+// nm products of one shape, the K rows in the number of shares that the rules
+// below give, at least two stages each; without room for the
+// shares' sums (a scratch limit, a capture before the arena has grown) the rows
+// stay whole.
 // FP32 products of this many 128x128 tiles per CU or more (P of about 5800 or
 // more) go to k_syrk_f32, which reads half the operand bytes per product: at
 // P = 8100 and 2000 rows it takes 1359 us, this kernel 1439 (P = 8190, rows
@@ -773,8 +785,28 @@ int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64
   const int tiles = nb * (nb + 1) / 2;
   const int per = (tiles + XCDS - 1) / XCDS;
   constexpr int ST = Frag<T>::stage;
-  int64_t splits = std::max<int64_t>(1, int64_t(GR_WGS) * ctx->num_cus / (int64_t(tiles) * nm));
-  splits = std::max<int64_t>(1, std::min(splits, K / (2 * ST)));
+  const int64_t all = int64_t(tiles) * nm;
+  int64_t splits = 1;
+  if constexpr (sizeof(T) == 8) {
+    // until about four workgroups per CU have work (2000 rows, 1600 columns, 325
+    // tiles on 256 CUs: 242 us whole, 144 in 3 shares, 154 in 4, 147 in 6)
+    splits = std::max<int64_t>(1, std::min(4 * ctx->num_cus / all, K / (2 * ST)));
+  } else {
+    // In units of one tile's time over all K: a CU works through ceil(workgroups
+    // / CUs) shares, half a share more for the loads before its first and the
+    // sums after its last, and each share's sums are written and read (bytes at
+    // 5 TB/s against the matrix rate of a CU: 0.46 tiles / K). 3000 rows, 2025
+    // columns, 528 tiles: 313 us whole, 280 in 2 shares, 251 in 3, 240 in 5.
+    double best = 1e300;
+    for (int64_t s = 1; s <= 16 && (s == 1 || s * 2 * ST <= K); ++s) {
+      const double share = double((all * s + ctx->num_cus - 1) / ctx->num_cus) + 0.5;
+      const double cost = share / double(s) + (s > 1 ? 0.46 * double(all) * double(s) / double(K) : 0.0);
+      if (cost < best) {
+        best = cost;
+        splits = s;
+      }
+    }
+  }
   const int64_t rows = ((K + splits - 1) / splits + ST - 1) / ST * ST;
   splits = rows > 0 ? (K + rows - 1) / rows : 1;
   T *part = nullptr;
