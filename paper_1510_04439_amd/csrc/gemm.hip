@@ -57,8 +57,8 @@ __device__ inline bool tile_of(int id, int nb, int per, int *bi, int *bj) {
 }
 
 
-// FP32 operands on v_mfma_f32_16x16x4_f32, products of many tiles.
-template <bool VEC4>
+// FP32 operands on v_mfma_f32_16x16x4_f32: products of many tiles and rows, N a
+// multiple of 4 and A 16-byte aligned.
 __global__ __launch_bounds__(256) void k_syrk_f32(const float *__restrict__ A, int64_t K, int64_t N,
                                                    float *__restrict__ C, int64_t ldc, float alpha,
                                                    int zero_diag, int nb, int per) {
@@ -87,30 +87,14 @@ __global__ __launch_bounds__(256) void k_syrk_f32(const float *__restrict__ A, i
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       const int c = half * 64 + lc;
-      float va[4], vb[4];
-      if (VEC4) {
-        if (kr < K && m0 + c + 3 < N) {
-          float4 v = *reinterpret_cast<const float4 *>(A + kr * N + m0 + c);
-          va[0] = v.x; va[1] = v.y; va[2] = v.z; va[3] = v.w;
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) va[e] = (kr < K && m0 + c + e < N) ? A[kr * N + m0 + c + e] : 0.f;
-        }
-        if (!diag_tile) {
-          if (kr < K && n0 + c + 3 < N) {
-            float4 v = *reinterpret_cast<const float4 *>(A + kr * N + n0 + c);
-            vb[0] = v.x; vb[1] = v.y; vb[2] = v.z; vb[3] = v.w;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) vb[e] = (kr < K && n0 + c + e < N) ? A[kr * N + n0 + c + e] : 0.f;
-          }
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          va[e] = (kr < K && m0 + c + e < N) ? A[kr * N + m0 + c + e] : 0.f;
-          if (!diag_tile) vb[e] = (kr < K && n0 + c + e < N) ? A[kr * N + n0 + c + e] : 0.f;
-        }
+      float va[4] = {0.f, 0.f, 0.f, 0.f}, vb[4] = {0.f, 0.f, 0.f, 0.f};
+      if (kr < K && m0 + c < N) {
+        const float4 v = *reinterpret_cast<const float4 *>(A + kr * N + m0 + c);
+        va[0] = v.x; va[1] = v.y; va[2] = v.z; va[3] = v.w;
+      }
+      if (!diag_tile && kr < K && n0 + c < N) {
+        const float4 v = *reinterpret_cast<const float4 *>(A + kr * N + n0 + c);
+        vb[0] = v.x; vb[1] = v.y; vb[2] = v.z; vb[3] = v.w;
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -566,7 +550,7 @@ __global__ __launch_bounds__(256) void k_gram_i32(const int32_t *__restrict__ A,
     }
 }
 
-// Products of few tiles, and all FP64 products: 64x64 output tiles (on or
+// FP64 products and all but the largest FP32 ones: 64x64 output tiles (on or
 // above the diagonal) on FP32 / FP64 matrix instructions, the K rows of a
 // tile split over gridDim.y workgroups, up to GR_MAX matrices of one shape in
 // one launch (gridDim.z). Bound by the matrix rate of the CUs that get a
@@ -773,11 +757,6 @@ __global__ __launch_bounds__(256) void k_gram_sum(GramMats<T> ms, int64_t N, int
 // below give, at least two stages each; without room for the
 // shares' sums (a scratch limit, a capture before the arena has grown) the rows
 // stay whole.
-// FP32 products of this many 128x128 tiles per CU or more (P of about 5800 or
-// more) go to k_syrk_f32, which reads half the operand bytes per product: at
-// P = 8100 and 2000 rows it takes 1359 us, this kernel 1439 (P = 8190, rows
-// not aligned: 1744, 1958); at P = 4096 and 5000 rows 1107, this kernel 995.
-constexpr int F32_TILES_PER_CU = 4;
 template <typename T>
 int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64_t N, int64_t ldc, T alpha,
               bool zero_diag) {
@@ -832,6 +811,17 @@ int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64
     FPCA_LAUNCH_CHECK("gram_sum");
   }
   return FPCA_OK;
+}
+
+// FP32 products of 1024 or more 128x128 tiles (P of about 5800 or more) and 1000
+// or more rows, with aligned rows, go to k_syrk_f32, which reads half the operand
+// bytes per product: P = 8100, 2000 rows 1306 us there, 1344 on the 64x64 tiles
+// (200 rows: 209, 197; P = 5820, 2000 rows: 777, 772; P = 8190, not aligned, which
+// k_syrk_f32 took element by element: 1729, 1547).
+bool large_tiles(const fpca_context *ctx, const float *A, int64_t K, int64_t N) {
+  const int64_t nb = (N + TB - 1) / TB;
+  return nb * (nb + 1) / 2 >= 4 * ctx->num_cus && K >= 1000 && N % 4 == 0 &&
+         (reinterpret_cast<uintptr_t>(A) & 15) == 0;
 }
 
 }  // namespace
@@ -891,16 +881,11 @@ int syrk_f32(fpca_context *ctx, const float *A, int64_t K, int64_t N, float *C, 
                          alpha, int(zero_diag));
       FPCA_LAUNCH_CHECK("syrk_fixup");
     }
-  } else if (tiles < F32_TILES_PER_CU * ctx->num_cus) {
+  } else if (!large_tiles(ctx, A, K, N)) {
     return gram_mfma<float>(ctx, 1, GramMats<float>{{A}, {C}}, K, N, ldc, alpha, zero_diag);
   } else {
-    const bool vec = (N % 4 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
-    if (vec)
-      hipLaunchKernelGGL((k_syrk_f32<true>), dim3(grid), dim3(256), 0, ctx->stream, A, K, N, C, ldc, alpha,
-                         int(zero_diag), nb, per);
-    else
-      hipLaunchKernelGGL((k_syrk_f32<false>), dim3(grid), dim3(256), 0, ctx->stream, A, K, N, C, ldc, alpha,
-                         int(zero_diag), nb, per);
+    hipLaunchKernelGGL(k_syrk_f32, dim3(grid), dim3(256), 0, ctx->stream, A, K, N, C, ldc, alpha, int(zero_diag), nb,
+                       per);
   }
   FPCA_LAUNCH_CHECK("syrk_f32");
   return FPCA_OK;
@@ -914,8 +899,9 @@ int syrk_f64(fpca_context *ctx, const double *A, int64_t K, int64_t N, double *C
 
 int syrk_set(fpca_context *ctx, int nm, const float *const *A, int64_t K, int64_t N, float *const *C, float alpha,
              bool zero_diag, int prec) {
-  const int64_t nb = (N + TB - 1) / TB;
-  if (prec != FPCA_PREC_BF16X3 && N > 0 && nm <= GR_MAX && nb * (nb + 1) / 2 < F32_TILES_PER_CU * ctx->num_cus) {
+  bool small = prec != FPCA_PREC_BF16X3 && N > 0 && nm <= GR_MAX;
+  for (int m = 0; m < nm; ++m) small = small && !large_tiles(ctx, A[m], K, N);
+  if (small) {
     GramMats<float> ms{};
     for (int m = 0; m < nm; ++m) ms.A[m] = A[m], ms.C[m] = C[m];
     return gram_mfma<float>(ctx, nm, ms, K, N, N, alpha, zero_diag);

@@ -202,7 +202,8 @@ def test_staged_smoother_and_cv(torch, F, h, M, hb, dt):
 
 
 @pytest.mark.parametrize("dtype,n,M", [("f32", 1, 3), ("f32", 33, 64), ("f32", 200, 65), ("f32", 1000, 130),
-                                       ("f32", 129, 260), ("f32", 17, 5764), ("f32", 16, 5761), ("f64", 1, 3),
+                                       ("f32", 129, 260), ("f32", 17, 5764), ("f32", 16, 5761), ("f32", 1003, 5764),
+                                       ("f64", 1, 3),
                                        ("f64", 17, 64), ("f64", 200, 101),
                                        ("f64", 1000, 128), ("f64", 65, 258)])
 def test_gram_tiles(torch, F, h, dtype, n, M):
