@@ -437,7 +437,10 @@ __global__ __launch_bounds__(256) void k_staged_score(SBatch b, int npairs) {
       if (b.mask && r0 + rr < P && c0 + tx < P && (!b.mask[r0 + rr] || !b.mask[c0 + tx])) g = 0.0;
       if (g != g) g = 0.0;
       s += qv[u] - 2.0 * gv[u] * g + cv[u] * g * g;
-      // (c0 + rr, r0 + tx): the node (r0 + tx, c0 + rr) of this tile
+      // (c0 + rr, r0 + tx): the node (r0 + tx, c0 + rr) of this tile. Not on a
+      // diagonal tile, where half of those nodes are never written: weights of
+      // zero do not make up for an infinity in them
+      if (id == 0) continue;
       double g2 = A[tx][rr];
       if (b.mask && c0 + rr < P && r0 + tx < P && (!b.mask[c0 + rr] || !b.mask[r0 + tx])) g2 = 0.0;
       if (g2 != g2) g2 = 0.0;

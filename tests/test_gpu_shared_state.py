@@ -1,0 +1,81 @@
+"""What one call leaves on a handle (values in scratch memory, modes, limits)
+must not show in the next one."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+from tests._util import normwise_rel, rand_irregular
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as T
+    assert T.cuda.is_available(), "GPU tests need a GPU"
+    return T
+
+
+@pytest.fixture(scope="module")
+def F(torch):
+    import paper_1510_04439_amd as F
+    F.load_library()
+    return F
+
+
+@pytest.fixture()
+def h(F):
+    hh = F.Handle(0)
+    yield hh
+    hh.close()
+
+
+def dev(torch, a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def cv_slabs(M, npdt, seed, nf=3, n=40):
+    rng = np.random.default_rng(seed)
+    off, t, y = rand_irregular(rng, len(M), n, 2, 12, npdt)
+    folds = (np.arange(n) % nf).astype(np.int32)
+    slabs = [oracle.bin_cov_pairs(M, off, t.astype(np.float64), y.astype(np.float64), folds, f, want_Q=True)
+             for f in [-1] + list(range(nf))]
+    return [np.stack([s[i] for s in slabs]).astype(npdt) for i in range(3)]
+
+
+@pytest.mark.parametrize("M", [(9, 7), (12, 5), (5, 4, 3)])
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_cv_scores_after_other_data(torch, F, h, M, dt):
+    """Cross-validation fits the nodes s_1 <= t_1 and leaves the rest of its scratch as it was. Scratch that holds
+    infinities (the rows of a binning of infinite observations) must give the scores of a fresh handle, bit for bit."""
+    _say(f"cv after other data M={M} {dt}")
+    npdt, tdt, code, prec = ((np.float64, torch.float64, F.FPCA_F64, F.FPCA_PREC_F64) if dt == "f64" else
+                             (np.float32, torch.float32, F.FPCA_F32, F.FPCA_PREC_F32))
+    C, G, Q = (dev(torch, a) for a in cv_slabs(M, npdt, 5))
+    run = lambda hh: F.fpca_cv_batched(hh, code, [(F.Grid(M), C, G, Q)], 3, [0.4])[0]
+    fresh = F.Handle(0)
+    try:
+        want = run(fresh)
+    finally:
+        fresh.close()
+    assert np.all(np.isfinite(want))
+    # every curve meets every node: its row of sums is infinite throughout
+    rng = np.random.default_rng(8)
+    n, Ni, P = 8000, 300, int(np.prod(M))
+    off = np.arange(n + 1, dtype=np.int64) * Ni
+    t = (rng.random((n * Ni, len(M))) * 0.999 + 0.0005).astype(npdt)
+    y = torch.full((n * Ni,), float("inf"), dtype=tdt, device="cuda:0")
+    folds = dev(torch, np.zeros(n, np.int32))
+    out = [torch.empty(2, P, P, dtype=tdt, device="cuda:0") for _ in range(2)]
+    F.fpca_bin(h, F.Grid(M), F.FPCA_BIN_COV, F.FPCA_IRREGULAR, code, prec, n, dev(torch, off), dev(torch, t), y, folds,
+               1, *out)
+    h.sync()
+    got = run(h)
+    assert np.array_equal(got, want)
