@@ -187,9 +187,9 @@ int fpca_smooth_mean(fpca_handle handle, const fpca_grid *grid, int dtype, const
                      int8_t *status);
 
 /*
- * fpca_set_conv -- how the general smoother (fpca_smooth_mean, and
- * fpca_smooth_cov on grids the task-queue smoother does not take) forms its
- * 1-D moment passes: FPCA_CONV_DIRECT sums the 2R+1 taps per output
+ * fpca_set_conv -- how the pass engine (fpca_smooth_mean, and fpca_smooth_cov
+ * and fpca_cv_batched where fpca_set_engine chooses it) forms its 1-D moment
+ * passes: FPCA_CONV_DIRECT sums the 2R+1 taps per output
  * (default); FPCA_CONV_FFT uses the FFT strategy of Section 3.2 on binned data
  * (per line of the pass, the zero-padded line and the taps are transformed
  * with L >= M + R points, L a power of two up to 4096, multiplied and
@@ -215,7 +215,7 @@ int fpca_set_conv(fpca_handle handle, int mode);
  * engine (FP64 moment arrays in device memory between passes, any grid);
  * FPCA_ENGINE_AUTO (default) takes the staged kernels for d = 2 and 3 with
  * M <= 40 per coordinate and P <= 4096 (whole lines in registers, three
- * stages); elsewhere the queue kernel when the pass engine's arrays would not
+ * stages) while fpca_set_conv is FPCA_CONV_DIRECT; elsewhere the queue kernel when the pass engine's arrays would not
  * fit in the 256 MB Infinity Cache, and batched CV times the job-by-job pass
  * engine against the queue kernel's tile shapes. All engines compute the same
  * sums in FP64 (results agree to rounding).

@@ -161,8 +161,8 @@ template <typename T>
 int cv_impl(fpca_context *ctx, int dtype, int n_data, const fpca_cv_data *data, int n_folds, int n_h,
             const double *bw, double *scores_h) {
   const int d = data[0].grid.d;
-  bool all_staged = ctx->engine == FPCA_ENGINE_AUTO;
-  for (int a = 0; a < n_data; ++a) all_staged = all_staged && staged_supported(&data[a].grid);
+  bool all_staged = true;
+  for (int a = 0; a < n_data; ++a) all_staged = all_staged && takes_staged(ctx, &data[a].grid);
   if (all_staged) {
     for (int a = 0; a < n_data; ++a)
       if (int rc = cv_staged<T>(ctx, data[a], n_folds, n_h, bw, scores_h + int64_t(a) * n_h * n_folds)) return rc;

@@ -758,7 +758,7 @@ int smooth_cov_impl(fpca_context *ctx, const fpca_grid *grid, const T *C, double
     if (!C && smooth_cov_fused_d2_supported(grid, bw))
       return smooth_cov_fused_d2(ctx, grid, c_uniform, G, bw, mu, gamma, status);
   }
-  if (ctx->engine == FPCA_ENGINE_AUTO && staged_supported(grid)) {
+  if (takes_staged(ctx, grid)) {
     StagedJob j{};
     j.Ca = C;
     j.Ga = G;

@@ -19,6 +19,12 @@ struct StagedJob {
 
 // d = 2 and 3, P <= 4096 and at most 40 nodes per coordinate.
 bool staged_supported(const fpca_grid *grid);
+// Whether the handle's covariance fits on this grid are staged ones: the default
+// engine, and direct moment sums (the other convolution modes ask for the pass
+// engine's FFT, which the staged kernels have no place for).
+inline bool takes_staged(const fpca_context *ctx, const fpca_grid *grid) {
+  return ctx->engine == FPCA_ENGINE_AUTO && ctx->conv_mode == FPCA_CONV_DIRECT && staged_supported(grid);
+}
 // b0 of one fit at every node (and its status, optional).
 template <typename T>
 int staged_smooth(fpca_context *ctx, const fpca_grid *grid, const StagedJob &job, T *out, int8_t *status);

@@ -79,3 +79,33 @@ def test_cv_scores_after_other_data(torch, F, h, M, dt):
     h.sync()
     got = run(h)
     assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("M", [(12, 10), (33, 7), (4, 17, 3)])
+def test_conv_mode_reaches_the_covariance(torch, F, h, M):
+    """With FFT passes asked for, the default engine's covariance and cross-validation are those of the pass engine
+    with FFT passes, bit for bit (grids that the queue kernel does not take, and one below the pass engine's limit)."""
+    _say(f"conv mode M={M}")
+    rng = np.random.default_rng(3)
+    P = int(np.prod(M))
+    C = rng.random((P, P)) + 0.01
+    C = (C + C.T) * 0.5
+    G = C * rng.standard_normal((P, P))
+    G = (G + G.T) * 0.5
+    hb = [0.4] * len(M)
+    slabs = [dev(torch, a) for a in cv_slabs(M, np.float64, 6)]
+    F.fpca_set_conv(h, F.FPCA_CONV_FFT)
+    res = {}
+    for engine in (F.FPCA_ENGINE_PASSES, F.FPCA_ENGINE_AUTO):
+        F.fpca_set_engine(h, engine)
+        gam = torch.empty(P, P, dtype=torch.float64, device="cuda:0")
+        st = torch.empty(P, P, dtype=torch.int8, device="cuda:0")
+        F.fpca_smooth_cov(h, F.Grid(M), F.FPCA_F64, dev(torch, C), 0.0, dev(torch, G), None, F.FPCA_K_EPANECHNIKOV, hb,
+                          gam, st)
+        h.sync()
+        sc = F.fpca_cv_batched(h, F.FPCA_F64, [(F.Grid(M), *slabs)], 3, [0.4])[0] if M != (12, 10) else None
+        res[engine] = (gam.cpu().numpy(), st.cpu().numpy(), sc)
+    a, b = res[F.FPCA_ENGINE_PASSES], res[F.FPCA_ENGINE_AUTO]
+    assert np.array_equal(a[0], b[0], equal_nan=True)
+    assert np.array_equal(a[1], b[1])
+    assert a[2] is None or np.array_equal(a[2], b[2])
