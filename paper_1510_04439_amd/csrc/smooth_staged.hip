@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void k_staged_score(SBatch b, int npairs) {
 __global__ __launch_bounds__(64) void k_staged_finish(const double *__restrict__ part, int n,
                                                       double *__restrict__ scores) {
   double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 64) s += part[int64_t(blockIdx.x) * SC_WG + i];
+  for (int i = threadIdx.x; i < n; i += 64) s += part[int64_t(blockIdx.x) * n + i];
   for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
   if (threadIdx.x == 0) scores[blockIdx.x] = s;
 }
@@ -650,12 +650,14 @@ template <typename T>
 int staged_scores(fpca_context *ctx, const fpca_grid *grid, const std::vector<StagedJob> &jobs, double *scores) {
   const Shape s = shape_of(grid);
   const size_t PP = size_t(s.P) * s.P, per = job_bytes(s, sizeof(T), true), J = jobs.size();
-  const size_t bytes_part = carve_bytes(J * SC_WG, 8);
+  // score workgroups per job, by the grid: many jobs on a small one need little
+  const int nt = (s.P + SC_TILE - 1) / SC_TILE, npairs = nt * (nt + 1) / 2, nsc = std::min(npairs, SC_WG);
+  const size_t bytes_part = carve_bytes(J * nsc, 8);
   int nb_max = int(std::max<size_t>(1, std::min<size_t>({size_t(SB_MAX), J, (size_t(1) << 30) / per})));
   while (nb_max > 1 && !ws_room(ctx, bytes_part + nb_max * per)) --nb_max;  // a scratch limit: fewer jobs at a time
   if (int rc = ws_reserve(ctx, bytes_part + nb_max * per)) return rc;
   Carver cw{static_cast<char *>(ctx->ws), 0, ctx->ws_size};
-  double *part = cw.take<double>(J * SC_WG);
+  double *part = cw.take<double>(J * nsc);
   SBatch b = make_batch(s, grid, true);
   for (int i = 0; i < nb_max; ++i) {
     b.j[i].X = cw.take<double>(size_t(s.nx) * PP);
@@ -663,12 +665,11 @@ int staged_scores(fpca_context *ctx, const fpca_grid *grid, const std::vector<St
     b.j[i].b0 = cw.take<T>(PP);
     b.j[i].taps = cw.take<double>(9 * TAPW);
   }
-  const int nt = (s.P + SC_TILE - 1) / SC_TILE, npairs = nt * (nt + 1) / 2, nsc = std::min(npairs, SC_WG);
   for (size_t j0 = 0; j0 < J; j0 += nb_max) {
     const int nb = int(std::min<size_t>(nb_max, J - j0));
     for (int i = 0; i < nb; ++i) {
       fill_job(s, jobs[j0 + i], &b.j[i]);
-      b.j[i].part = part + (j0 + i) * SC_WG;
+      b.j[i].part = part + (j0 + i) * nsc;
     }
     if (int rc = launch_any<T>(ctx, s, b, nb)) return rc;
     hipLaunchKernelGGL(k_staged_score<T>, dim3(unsigned(nsc), 1, unsigned(nb)), dim3(256), 0, ctx->stream, b, npairs);

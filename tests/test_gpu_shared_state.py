@@ -109,3 +109,22 @@ def test_conv_mode_reaches_the_covariance(torch, F, h, M):
     assert np.array_equal(a[0], b[0], equal_nan=True)
     assert np.array_equal(a[1], b[1])
     assert a[2] is None or np.array_equal(a[2], b[2])
+
+
+def test_many_cv_jobs_under_a_scratch_limit(torch, F, h, monkeypatch):
+    """600 jobs on a small grid: their scores' partial sums are sized by the grid, so that a limit with room for one
+    job's moments takes them all, to the same scores."""
+    _say("many cv jobs under a limit")
+    M = (8, 8)
+    C, G, Q = (dev(torch, a) for a in cv_slabs(M, np.float64, 7))
+    hs = np.geomspace(0.2, 0.6, 200)
+    run = lambda hh: F.fpca_cv_batched(hh, F.FPCA_F64, [(F.Grid(M), C, G, Q)], 3, hs)[0]
+    full = run(h)
+    # one job: 14 P^2 doubles of moments and P^2 of fits, 0.5 MB
+    monkeypatch.setenv("FPCA_DEBUG_WS_LIMIT", str(3 << 19))
+    lim = F.Handle(0)
+    try:
+        got = run(lim)
+    finally:
+        lim.close()
+    assert np.array_equal(got, full)
