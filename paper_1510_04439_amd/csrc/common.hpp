@@ -17,6 +17,7 @@ struct fpca_context {
   void *ws = nullptr;
   size_t ws_size = 0;
   size_t ws_limit = 0;  // 0 = unlimited
+  size_t alloc_limit = 0;  // one scratch allocation larger than this fails as without memory (0 = none does)
   // Second arena for the split bf16 operands of the Gram product (its inputs
   // may live in the first arena).
   void *ws2 = nullptr;
@@ -88,8 +89,9 @@ int hip_fail(hipError_t e, const char *what);
 int ws_reserve(fpca_context *ctx, size_t bytes);
 int ws2_reserve(fpca_context *ctx, size_t bytes);
 // Whether an arena holds `bytes` or has been grown to: false, with no error
-// set, past the scratch limit, while the stream is capturing and when the
-// allocation fails. For paths that have another way without the memory.
+// set and the arena as it was, past the scratch limit, while the stream is
+// capturing and when the allocation fails. For paths that have another way
+// without the memory.
 bool ws_room(fpca_context *ctx, size_t bytes);
 bool ws2_room(fpca_context *ctx, size_t bytes);
 int ws3_reserve(fpca_context *ctx, size_t bytes);

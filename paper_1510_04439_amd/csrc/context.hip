@@ -65,49 +65,69 @@ GridDims make_dims(const fpca_grid *g) {
   return gd;
 }
 
-int ws_reserve(fpca_context *ctx, size_t bytes) {
-  if (bytes <= ctx->ws_size) return FPCA_OK;
-  if (ctx->ws_limit && bytes > ctx->ws_limit)
-    return set_error(FPCA_ERR_WORKSPACE, "scratch request %zu bytes exceeds the limit %zu", bytes,
-                     ctx->ws_limit);
-  if (ctx->ws) {
-    // Earlier queued work may still read the old arena.
-    FPCA_HIP(hipStreamSynchronize(ctx->stream));
-    FPCA_HIP(hipFree(ctx->ws));
-    ctx->ws = nullptr;
-    ctx->ws_size = 0;
-  }
-  size_t want = bytes + bytes / 8;
-  hipError_t e = hipMalloc(&ctx->ws, want);
+// hipMalloc for a scratch block, within the handle's debugging limit on one
+// allocation; a failure leaves no error behind in the runtime.
+static hipError_t scratch_malloc(fpca_context *ctx, void **p, size_t bytes) {
+  hipError_t e = hipErrorOutOfMemory;
+  if (!ctx->alloc_limit || bytes <= ctx->alloc_limit) e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
-    ctx->ws = nullptr;
+    *p = nullptr;
     (void)hipGetLastError();
-    return set_error(FPCA_ERR_WORKSPACE, "hipMalloc of %zu scratch bytes failed: %s", want,
-                     hipGetErrorString(e));
   }
-  ctx->ws_size = want;
-  return FPCA_OK;
+  return e;
 }
 
-static int arena_reserve(fpca_context *ctx, void **arena, size_t *size, size_t bytes) {
+// An arena's block is replaced by one of `want` >= bytes when it is too small.
+static int arena_reserve(fpca_context *ctx, void **arena, size_t *size, size_t bytes, size_t want) {
   if (bytes <= *size) return FPCA_OK;
   if (ctx->ws_limit && bytes > ctx->ws_limit)
     return set_error(FPCA_ERR_WORKSPACE, "scratch request %zu bytes exceeds the limit %zu", bytes, ctx->ws_limit);
   if (*arena) {
+    // Earlier queued work may still read the old block.
     FPCA_HIP(hipStreamSynchronize(ctx->stream));
     FPCA_HIP(hipFree(*arena));
     *arena = nullptr;
     *size = 0;
   }
-  hipError_t e = hipMalloc(arena, bytes);
-  if (e != hipSuccess) {
-    *arena = nullptr;
-    (void)hipGetLastError();
-    return set_error(FPCA_ERR_WORKSPACE, "hipMalloc of %zu scratch bytes failed: %s", bytes, hipGetErrorString(e));
-  }
-  *size = bytes;
+  const hipError_t e = scratch_malloc(ctx, arena, want);
+  if (e != hipSuccess)
+    return set_error(FPCA_ERR_WORKSPACE, "hipMalloc of %zu scratch bytes failed: %s", want, hipGetErrorString(e));
+  *size = want;
   return FPCA_OK;
 }
+
+// The same for work that has another way: false where the block cannot grow
+// (the scratch limit, a capture, no memory), and then the old block stays and
+// no error is set. The new block is there before the old one goes.
+static bool arena_room(fpca_context *ctx, void **arena, size_t *size, size_t bytes, size_t want) {
+  if (bytes <= *size) return true;
+  if (ctx->ws_limit && bytes > ctx->ws_limit) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
+  void *p = nullptr;
+  if (scratch_malloc(ctx, &p, want) != hipSuccess) return false;
+  if (*arena && (hipStreamSynchronize(ctx->stream) != hipSuccess || hipFree(*arena) != hipSuccess)) {
+    (void)hipFree(p);
+    return false;
+  }
+  *arena = p;
+  *size = want;
+  return true;
+}
+
+int ws_reserve(fpca_context *ctx, size_t bytes) {
+  return arena_reserve(ctx, &ctx->ws, &ctx->ws_size, bytes, bytes + bytes / 8);
+}
+int ws2_reserve(fpca_context *ctx, size_t bytes) {
+  return arena_reserve(ctx, &ctx->ws2, &ctx->ws2_size, bytes, bytes);
+}
+int ws3_reserve(fpca_context *ctx, size_t bytes) {
+  return arena_reserve(ctx, &ctx->ws3, &ctx->ws3_size, bytes, bytes);
+}
+bool ws_room(fpca_context *ctx, size_t bytes) {
+  return arena_room(ctx, &ctx->ws, &ctx->ws_size, bytes, bytes + bytes / 8);
+}
+bool ws2_room(fpca_context *ctx, size_t bytes) { return arena_room(ctx, &ctx->ws2, &ctx->ws2_size, bytes, bytes); }
 
 int tables_stage(fpca_context *ctx, size_t bytes, char **out) {
   if (!ctx->ev_tables) FPCA_HIP(hipEventCreateWithFlags(&ctx->ev_tables, hipEventDisableTiming));
@@ -127,21 +147,6 @@ int tables_stage(fpca_context *ctx, size_t bytes, char **out) {
   }
   *out = static_cast<char *>(ctx->h_tables);
   return FPCA_OK;
-}
-
-int ws2_reserve(fpca_context *ctx, size_t bytes) { return arena_reserve(ctx, &ctx->ws2, &ctx->ws2_size, bytes); }
-int ws3_reserve(fpca_context *ctx, size_t bytes) { return arena_reserve(ctx, &ctx->ws3, &ctx->ws3_size, bytes); }
-
-static bool may_grow(fpca_context *ctx, size_t bytes) {
-  if (ctx->ws_limit && bytes > ctx->ws_limit) return false;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(ctx->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
-}
-bool ws_room(fpca_context *ctx, size_t bytes) {
-  return bytes <= ctx->ws_size || (may_grow(ctx, bytes) && ws_reserve(ctx, bytes) == FPCA_OK);
-}
-bool ws2_room(fpca_context *ctx, size_t bytes) {
-  return bytes <= ctx->ws2_size || (may_grow(ctx, bytes) && ws2_reserve(ctx, bytes) == FPCA_OK);
 }
 
 template <typename T>
@@ -195,6 +200,7 @@ int fpca_create(fpca_handle *handle, int device) {
   ctx->device = device;
   ctx->num_cus = prop.multiProcessorCount;
   if (const char *lim = std::getenv("FPCA_DEBUG_WS_LIMIT")) ctx->ws_limit = std::strtoull(lim, nullptr, 10);
+  if (const char *lim = std::getenv("FPCA_DEBUG_ALLOC_LIMIT")) ctx->alloc_limit = std::strtoull(lim, nullptr, 10);
   if (hipMalloc(&ctx->d_flags, 256) != hipSuccess || hipHostMalloc(&ctx->h_flags, 256) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void **>(&ctx->h_stage), fpca_context::kStageBytes) != hipSuccess) {
     if (ctx->d_flags) (void)hipFree(ctx->d_flags);

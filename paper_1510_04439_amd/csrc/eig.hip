@@ -1172,7 +1172,7 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
                 carve_bytes(ngram * RP * RP, 8) + 2 * carve_bytes(RP * RP, 8) + carve_bytes(RP, 4) +
                 carve_bytes(RP * k, 8) +
                 carve_bytes(2 * k, 8) + carve_bytes(P * k, 8) + carve_bytes(nphi * k * 3, 8);
-  if (!f32 && ctx->ws_limit && need + carve_bytes(nsplit * P * RP, 8) > ctx->ws_limit) {
+  if (!f32 && nsplit > 1 && !ws_room(ctx, need + carve_bytes(nsplit * P * RP, 8))) {
     nsplit = 1;  // no room for the shares of a split
     kchunk = P;
   }

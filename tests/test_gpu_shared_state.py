@@ -128,3 +128,56 @@ def test_many_cv_jobs_under_a_scratch_limit(torch, F, h, monkeypatch):
     finally:
         lim.close()
     assert np.array_equal(got, full)
+
+
+def test_optional_scratch_that_does_not_fit(torch, F, monkeypatch):
+    """Scratch that a call can do without and cannot have (the allocation fails) costs the handle neither the block it
+    holds nor the message of its last error, and the results are those of a handle that got it."""
+    _say("optional scratch")
+    rng = np.random.default_rng(9)
+    M, n = (40, 40), 1024
+    P = M[0] * M[1]
+    off = np.arange(n + 1, dtype=np.int64) * 5
+    t, y = rng.random((5 * n, 2)), rng.standard_normal(5 * n)
+    D = lambda a: dev(torch, a)
+    d_off, d_t, d_y, folds = D(off), D(t), D(y), D(np.zeros(n, np.int32))
+    Gam = rng.standard_normal((200, 200))
+    Gam, om = D(Gam @ Gam.T), D(np.full(200, 1.0 / 200))
+    z = lambda *s: torch.empty(*s, dtype=torch.float64, device="cuda:0")
+    two, out, ef = [z(2, P, P) for _ in range(2)], [z(P, P) for _ in range(2)], z(4, 200)
+    # 26 MB of rows (29.5 with the arena's margin), 32.8 MB of sums of the j = l terms
+    monkeypatch.setenv("FPCA_DEBUG_ALLOC_LIMIT", str(31 << 20))
+    lim = F.Handle(0)
+    monkeypatch.delenv("FPCA_DEBUG_ALLOC_LIMIT")
+    free = F.Handle(0)
+    try:
+        args = (F.Grid(M), F.FPCA_BIN_COV, F.FPCA_IRREGULAR, F.FPCA_F64, F.FPCA_PREC_F64, n, d_off, d_t, d_y)
+        F.fpca_bin(lim, *args, folds, 1, *two)  # takes the rows' block
+        lim.sync()
+        with pytest.raises(F.FpcaError):
+            F.fpca_set_conv(lim, 7)
+        last = F.load_library().fpca_last_error()
+        held = torch.cuda.mem_get_info()[0]
+        res = []
+        for hh in (lim, free):
+            F.fpca_bin(hh, *args, None, 0, *out)
+            hh.sync()
+            if hh is lim:
+                assert torch.cuda.mem_get_info()[0] == held
+                assert F.load_library().fpca_last_error() == last
+            res.append([o.cpu().numpy() for o in out])
+        for a, b in zip(*res):
+            assert normwise_rel(a, b) < 1e-13
+    finally:
+        lim.close()
+        free.close()
+    # the decomposition: 170 KB that it cannot do without, 324 KB with the shares of a split
+    ev = []
+    for cap in ("", str(300 << 10)):
+        monkeypatch.setenv("FPCA_DEBUG_ALLOC_LIMIT", cap) if cap else None
+        hh = F.Handle(0)
+        try:
+            ev.append(F.fpca_eig_randomized(hh, F.FPCA_F64, F.FPCA_PREC_F64, F.Grid((200,)), Gam, om, 4, 8, 2, 3, ef)[0])
+        finally:
+            hh.close()
+    np.testing.assert_allclose(ev[0], ev[1], rtol=1e-12)
