@@ -129,6 +129,44 @@ bool ws_room(fpca_context *ctx, size_t bytes) {
 }
 bool ws2_room(fpca_context *ctx, size_t bytes) { return arena_room(ctx, &ctx->ws2, &ctx->ws2_size, bytes, bytes); }
 
+// The block belongs to the stream that used it last. When the handle goes on to
+// another one, fpca_set_stream marks the end of that stream's work with an event
+// (gram_ev), which the next stream waits for here; where it could not be marked
+// (the stream is gone or being captured), the whole device is waited for.
+void *gram_scratch(fpca_context *ctx, size_t bytes) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
+  if (ctx->gram_wait) {
+    hipError_t e = ctx->gram_wait == 1 ? hipStreamWaitEvent(ctx->stream, ctx->gram_ev, 0) : hipErrorUnknown;
+    if (e != hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    ctx->gram_wait = 0;
+  }
+  if (!arena_room(ctx, &ctx->gram_ws, &ctx->gram_ws_size, bytes, bytes)) return nullptr;
+  ctx->gram_used = true;
+  ctx->gram_stream = ctx->stream;
+  return ctx->gram_ws;
+}
+
+// Before the handle's stream becomes `next`: see gram_scratch. A stream that is
+// being captured gets no block, so nothing is marked for it.
+static void gram_leave_stream(fpca_context *ctx, hipStream_t next) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  hipError_t e = hipStreamIsCapturing(next, &cs);
+  if (e == hipSuccess && cs != hipStreamCaptureStatusNone) return;
+  e = hipSetDevice(ctx->device);
+  if (e == hipSuccess) e = hipStreamIsCapturing(ctx->gram_stream, &cs);
+  if (e == hipSuccess && cs != hipStreamCaptureStatusNone) e = hipErrorStreamCaptureUnsupported;
+  if (e == hipSuccess && !ctx->gram_ev) e = hipEventCreateWithFlags(&ctx->gram_ev, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventRecord(ctx->gram_ev, ctx->gram_stream);
+  if (e != hipSuccess) (void)hipGetLastError();
+  ctx->gram_wait = e == hipSuccess ? 1 : 2;
+  ctx->gram_used = false;
+}
+
 int tables_stage(fpca_context *ctx, size_t bytes, char **out) {
   if (!ctx->ev_tables) FPCA_HIP(hipEventCreateWithFlags(&ctx->ev_tables, hipEventDisableTiming));
   else FPCA_HIP(hipEventSynchronize(ctx->ev_tables));
@@ -221,6 +259,8 @@ int fpca_destroy(fpca_handle ctx) {
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->ws2) (void)hipFree(ctx->ws2);
   if (ctx->ws3) (void)hipFree(ctx->ws3);
+  if (ctx->gram_ws) (void)hipFree(ctx->gram_ws);
+  if (ctx->gram_ev) (void)hipEventDestroy(ctx->gram_ev);
   if (ctx->cv_exec) (void)hipGraphExecDestroy(ctx->cv_exec);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->ev_a) (void)hipEventDestroy(ctx->ev_a);
@@ -236,7 +276,9 @@ int fpca_destroy(fpca_handle ctx) {
 
 int fpca_set_stream(fpca_handle ctx, void *stream) {
   if (int rc = check_handle(ctx)) return rc;
-  ctx->stream = reinterpret_cast<hipStream_t>(stream);
+  const hipStream_t next = reinterpret_cast<hipStream_t>(stream);
+  if (ctx->gram_used && next != ctx->gram_stream) gram_leave_stream(ctx, next);
+  ctx->stream = next;
   return FPCA_OK;
 }
 

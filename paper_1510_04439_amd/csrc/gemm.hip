@@ -754,9 +754,8 @@ __global__ __launch_bounds__(256) void k_gram_sum(GramMats<T> ms, int64_t N, int
 }
 
 // nm products of one shape, the K rows in the number of shares that the rules
-// below give, at least two stages each; without room for the
-// shares' sums (a scratch limit, a capture before the arena has grown) the rows
-// stay whole.
+// below give, at least two stages each; without room for the shares' sums (a
+// scratch limit, a capture) the rows stay whole.
 template <typename T>
 int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64_t N, int64_t ldc, T alpha,
               bool zero_diag) {
@@ -791,7 +790,7 @@ int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64
   T *part = nullptr;
   if (splits > 1) {
     const size_t need = carve_bytes(size_t(nm) * size_t(splits) * size_t(tiles) * GT * GT, sizeof(T));
-    if (ws2_room(ctx, need)) part = static_cast<T *>(ctx->ws2);
+    part = static_cast<T *>(gram_scratch(ctx, need));
   }
   const int64_t sp = part ? splits : 1;
   bool vec = N % 4 == 0;

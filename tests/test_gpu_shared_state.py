@@ -181,3 +181,59 @@ def test_optional_scratch_that_does_not_fit(torch, F, monkeypatch):
         finally:
             hh.close()
     np.testing.assert_allclose(ev[0], ev[1], rtol=1e-12)
+
+
+def gram_case(torch, F, npdt, n, P, seed):
+    y = np.random.default_rng(seed).standard_normal((n, P)).astype(npdt)
+    ref = (y.astype(np.float64).T @ y.astype(np.float64)) / (P * (P - 1.0))
+    np.fill_diagonal(ref, 0.0)
+    code, prec = (F.FPCA_F64, F.FPCA_PREC_F64) if npdt == np.float64 else (F.FPCA_F32, F.FPCA_PREC_F32)
+    args = (F.Grid((P,)), F.FPCA_BIN_COV, F.FPCA_COMMON_GRID, code, prec, n, None, None, dev(torch, y), None, 0, None)
+    S = torch.full((P, P), float("nan"), dtype=torch.float64 if npdt == np.float64 else torch.float32, device="cuda:0")
+    return args, S, ref
+
+
+@pytest.mark.parametrize("npdt", [np.float64, np.float32])
+def test_captured_gram_after_the_scratch_moved(torch, F, h, npdt):
+    """A captured binning of complete curves holds no address of the handle's scratch: replays are right after larger
+    calls have replaced it."""
+    _say(f"captured gram {npdt.__name__}")
+    args, S, ref = gram_case(torch, F, npdt, 600, 96, 1)
+    big, S2, ref2 = gram_case(torch, F, npdt, 4000, 300, 2)
+    tol = 1e-13 if npdt == np.float64 else 1e-5
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        F.fpca_bin(h, *args, S)  # the handle has a block when the capture starts
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        F.fpca_bin(h, *args, S)
+    for _ in range(3):
+        F.fpca_bin(h, *big, S2)
+        F.fpca_bin(h, *args, S)
+        h.sync()
+        eager = S.cpu().numpy()
+        S.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert normwise_rel(S.cpu().numpy().astype(np.float64), ref) < tol
+        assert normwise_rel(eager.astype(np.float64), ref) < tol
+        assert normwise_rel(S2.cpu().numpy().astype(np.float64), ref2) < tol
+
+
+@pytest.mark.parametrize("npdt", [np.float64, np.float32])
+def test_gram_on_two_streams_in_turn(torch, F, h, npdt):
+    """One handle, products of complete curves queued on two streams in turn with nothing waited for between them."""
+    _say(f"gram on two streams {npdt.__name__}")
+    tol = 1e-13 if npdt == np.float64 else 1e-5
+    cases = [gram_case(torch, F, npdt, 3000 + 40 * i, 200 + 30 * (i % 3), 10 + i) for i in range(6)]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for i, (args, S, _) in enumerate(cases):
+            with torch.cuda.stream(streams[i % 2]):
+                F.fpca_bin(h, *args, S)
+    torch.cuda.synchronize()
+    for args, S, ref in cases:
+        assert normwise_rel(S.cpu().numpy().astype(np.float64), ref) < tol
