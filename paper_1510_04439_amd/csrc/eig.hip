@@ -68,14 +68,36 @@ __global__ void k_setup(uint64_t seed, int64_t P, int r, int rp, const double *_
   X[e] = T(j < r ? s * normal_at(seed, uint64_t(j) * uint64_t(P) + uint64_t(p)) : 0.0);
 }
 
+// What a panel kernel has summed so far beside its two accumulator sets:
+// nothing where the partial product is FP32, the finished tiles where it is FP64.
+template <int RB, typename PT>
+struct PanelSums {
+  __device__ void take(float4_t (&)[2][RB]) {}
+  __device__ float total(const float4_t (&acc)[2][RB], int mb, int v) const { return acc[0][mb][v] + acc[1][mb][v]; }
+};
+template <int RB>
+struct PanelSums<RB, double> {
+  double s[RB][4] = {};
+  __device__ void take(float4_t (&acc)[2][RB]) {
+#pragma unroll
+    for (int mb = 0; mb < RB; ++mb) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) s[mb][v] += double(acc[0][mb][v]) + double(acc[1][mb][v]);
+      acc[0][mb] = acc[1][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  __device__ double total(const float4_t (&)[2][RB], int mb, int v) const { return s[mb][v]; }
+};
+
 // Partial products of Y^T = X^T Gamma over one K chunk (Gamma symmetric):
 // workgroup = (64 nodes, K chunk); 4 wavefronts x 16 nodes; MFMA 16x16x4 FP32
 // with the basis as the A operand and Gamma rows as the B operand. Tiles of 32
 // Gamma rows are prefetched into registers while the previous tile is used.
-template <int RB, bool VEC>
+// PT = double: every tile's sums go to FP64 and so does the partial product.
+template <int RB, bool VEC, typename PT>
 __global__ __launch_bounds__(256) void k_panel_f32(int64_t P, const float *__restrict__ G,
                                                     const float *__restrict__ X, int64_t kchunk,
-                                                    float *__restrict__ part) {
+                                                    PT *__restrict__ part) {
   constexpr int RP = RB * 16;
   constexpr int KT = 32;
   __shared__ float As[2][KT][64 + 4];
@@ -87,6 +109,7 @@ __global__ __launch_bounds__(256) void k_panel_f32(int64_t P, const float *__res
   float4_t acc[2][RB];  // two sets alternate over K steps: independent MFMA chains
 #pragma unroll
   for (int b = 0; b < RB; ++b) acc[0][b] = acc[1][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+  PanelSums<RB, PT> sums;
   const int ar = tid >> 4, ac = (tid & 15) * 4;  // rows ar and ar+16, columns ac..ac+3
   float ra[2][4], rx[2][4];
   auto load = [&](int64_t kb) {
@@ -141,17 +164,18 @@ __global__ __launch_bounds__(256) void k_panel_f32(int64_t P, const float *__res
       }
     }
     if (more) store(buf ^ 1);
+    sums.take(acc);
     __syncthreads();
     buf ^= 1;
   }
   // D[j][p]: row j = mb*16 + 4*(lane/16) + v, column p = c0 + wave*16 + lane%16.
   const int64_t p = c0 + wave * 16 + (lane & 15);
   if (p < P) {
-    float *dst = part + (int64_t(blockIdx.y) * P + p) * RP;
+    PT *dst = part + (int64_t(blockIdx.y) * P + p) * RP;
 #pragma unroll
     for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dst[mb * 16 + 4 * (lane >> 4) + v] = acc[0][mb][v] + acc[1][mb][v];
+      for (int v = 0; v < 4; ++v) dst[mb * 16 + 4 * (lane >> 4) + v] = sums.total(acc, mb, v);
   }
 }
 
@@ -168,11 +192,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 // one 16-byte read per lane. Tiles of 64 nodes (two MFMA k-steps) in two LDS
 // buffers, loaded into registers two tiles ahead of their products. Rows
 // past P are read from row P - 1 and feed only outputs past P, which are not
-// written.
-template <int RB, bool VEC>
+// written. PT as in k_panel_f32.
+template <int RB, bool VEC, typename PT>
 __global__ __launch_bounds__(256) void k_panel_bf16x3(int64_t P, const float *__restrict__ G,
                                                        const float *__restrict__ X, int64_t kchunk,
-                                                       float *__restrict__ part) {
+                                                       PT *__restrict__ part) {
   constexpr int RP = RB * 16;
   constexpr int KT = 64;
   constexpr int LK = KT + 8;  // padded LDS row (144 bytes): the 16 rows of an operand read on distinct banks
@@ -186,6 +210,7 @@ __global__ __launch_bounds__(256) void k_panel_bf16x3(int64_t P, const float *__
   float4_t acc[2][RB];  // one set per k-step of a tile: independent MFMA chains
 #pragma unroll
   for (int b = 0; b < RB; ++b) acc[0][b] = acc[1][b] = float4_t{0.f, 0.f, 0.f, 0.f};
+  PanelSums<RB, PT> sums;
   const int gp = tid >> 2, gg = tid & 3;
   const float *grow = G + min(c0 + gp, P - 1) * P;
   // a tile's raw values in registers: g = this thread's two 8-node runs of
@@ -283,6 +308,7 @@ __global__ __launch_bounds__(256) void k_panel_bf16x3(int64_t P, const float *__
 #pragma unroll
       for (int mb = 0; mb < RB; ++mb)
         acc[s][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[s][mb], bh[s], acc[s][mb], 0, 0, 0);
+    sums.take(acc);
   };
   // Two register sets, two tiles ahead: while tile kb is multiplied from LDS
   // buffer 0, tile kb + KT waits in set B and tile kb + 2 KT is loading into
@@ -309,11 +335,11 @@ __global__ __launch_bounds__(256) void k_panel_bf16x3(int64_t P, const float *__
   // D[j][p]: row j = mb*16 + 4*(lane/16) + v, column p = c0 + wave*16 + lane%16.
   const int64_t p = c0 + wave * 16 + (lane & 15);
   if (p < P) {
-    float *dst = part + (int64_t(blockIdx.y) * P + p) * RP;
+    PT *dst = part + (int64_t(blockIdx.y) * P + p) * RP;
 #pragma unroll
     for (int mb = 0; mb < RB; ++mb)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) dst[mb * 16 + 4 * (lane >> 4) + v] = acc[0][mb][v] + acc[1][mb][v];
+      for (int v = 0; v < 4; ++v) dst[mb * 16 + 4 * (lane >> 4) + v] = sums.total(acc, mb, v);
   }
 }
 
@@ -424,7 +450,7 @@ __device__ inline void rows_gram(const double *A, const double *B, double *__res
 }
 
 // Finishes a product, ROWS rows per workgroup: Y[p, j] = sqrt(w_p) * (sum of
-// the K-split partials in split order; the covariance operator's product is
+// the K-split partials (FP32 or FP64) in split order; the operator's product is
 // one such partial), then the rows' partial Gram matrix:
 //   MODE 1: part = Y_c^T Y_c;  MODE 2: part = Q_c^T Y_c  (Rayleigh-Ritz).
 // A thread loads sixteen splits of all its entries at once.
@@ -1156,27 +1182,41 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
   // K split of the panel product: about two workgroups per compute unit
   // (fewer splits read fewer partials back; at P = 4096, 8 splits measured
   // 29 us per product and Gram against 31 us with 16 and 37 us with 4), and at
-  // most the 16 that k_rows_gram loads at once: the whole decomposition at
-  // P = 1024, r = 16 takes 182 us with 16 splits, 215 with 32 (FP64 169, 184)
+  // most the 16 that k_rows_gram loads at once: FP64 at P = 1024, r = 16 takes
+  // 169 us with 16 splits, 184 with 32. FP32 partial products that the 16 make
+  // longer are summed in FP64, tile by tile, so that no FP32 sum is (wide): the
+  // same decomposition on BF16x3 products takes 228 us in 32 FP32 products, 178
+  // in these.
   const int64_t colblocks = (P + 63) / 64;
-  int64_t nsplit = (2 * int64_t(ctx->num_cus) + colblocks - 1) / colblocks;
-  nsplit = std::max<int64_t>(1, std::min<int64_t>(nsplit, 16));
-  int64_t kchunk = ((P + nsplit - 1) / nsplit + 31) / 32 * 32;
-  nsplit = (P + kchunk - 1) / kchunk;
+  const int64_t two_each = std::max<int64_t>(1, (2 * int64_t(ctx->num_cus) + colblocks - 1) / colblocks);
+  auto chunk_of = [&](int64_t splits) { return ((P + splits - 1) / splits + 31) / 32 * 32; };
+  int64_t kchunk = chunk_of(two_each);
+  int64_t nsplit = (P + kchunk - 1) / kchunk;
+  bool wide = false;
+  const int64_t kchunk16 = chunk_of(std::min<int64_t>(two_each, 16)), nsplit16 = (P + kchunk16 - 1) / kchunk16;
   const int64_t ngram = (P + ROWS - 1) / ROWS;
   const int64_t nphi = (P + 255) / 256;
   // r > 32 or more nodes: basis and product no longer fit one workgroup's LDS
   const bool small = P <= SP_MAX && RP <= 32 && !op;
-  if (op || small) nsplit = 1;  // the operator writes the whole product; the small kernel has no partials
   size_t need = 2 * carve_bytes(P, 8) + carve_bytes(P * RP, sizeof(T)) + 3 * carve_bytes(P * RP, 8) +
                 carve_bytes(ngram * RP * RP, 8) + 2 * carve_bytes(RP * RP, 8) + carve_bytes(RP, 4) +
                 carve_bytes(RP * k, 8) +
                 carve_bytes(2 * k, 8) + carve_bytes(P * k, 8) + carve_bytes(nphi * k * 3, 8);
-  if (!f32 && nsplit > 1 && !ws_room(ctx, need + carve_bytes(nsplit * P * RP, 8))) {
-    nsplit = 1;  // no room for the shares of a split
-    kchunk = P;
+  if (op || small) {
+    nsplit = 1;  // the operator writes the whole product; the small kernel has no partials
+  } else if (!f32 || nsplit > 16) {
+    // without room for these shares: FP64 in one, FP32 in the short ones
+    if (nsplit16 > 1 && ws_room(ctx, need + carve_bytes(nsplit16 * P * RP, 8))) {
+      nsplit = nsplit16;
+      kchunk = kchunk16;
+      wide = f32;
+    } else if (!f32) {
+      nsplit = 1;
+      kchunk = P;
+    }
   }
-  need += carve_bytes(nsplit * P * RP, sizeof(T));
+  const size_t part_elem = wide ? sizeof(double) : sizeof(T);
+  need += carve_bytes(nsplit * P * RP, part_elem);
   if (int rc = ws_reserve(ctx, need)) return rc;
   Carver cv{static_cast<char *>(ctx->ws), 0, ctx->ws_size};
   double *w = cv.take<double>(P);
@@ -1194,7 +1234,7 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
   double *fve_d = ev_d + k;
   double *phi = cv.take<double>(P * k);
   double *red = cv.take<double>(nphi * k * 3);
-  T *part = cv.take<T>(nsplit * P * RP);
+  void *part = cv.take<char>(nsplit * P * RP * part_elem);
 
   double wv = 1.0;
   for (int q = 0; q < grid->d; ++q) wv /= double(grid->M[q] - 1);
@@ -1221,39 +1261,36 @@ int eig_run(fpca_context *ctx, const fpca_grid *grid, int64_t P, const T *gamma,
       dim3 grd((unsigned)colblocks, (unsigned)nsplit);
       const bool vec = (P % 4 == 0) && ((reinterpret_cast<uintptr_t>(gamma) & 15) == 0);
       constexpr int RB = RP / 16;
-      if (prec == FPCA_PREC_BF16X3) {
-        if (vec)
-          hipLaunchKernelGGL((k_panel_bf16x3<RB, true>), grd, dim3(256), 0, ctx->stream, P, (const float *)gamma,
-                             (const float *)X, kchunk, part);
-        else
-          hipLaunchKernelGGL((k_panel_bf16x3<RB, false>), grd, dim3(256), 0, ctx->stream, P, (const float *)gamma,
-                             (const float *)X, kchunk, part);
-        FPCA_LAUNCH_CHECK("panel_bf16x3");
-      } else {
-        if (vec)
-          hipLaunchKernelGGL((k_panel_f32<RB, true>), grd, dim3(256), 0, ctx->stream, P, (const float *)gamma,
-                             (const float *)X, kchunk, part);
-        else
-          hipLaunchKernelGGL((k_panel_f32<RB, false>), grd, dim3(256), 0, ctx->stream, P, (const float *)gamma,
-                             (const float *)X, kchunk, part);
-        FPCA_LAUNCH_CHECK("panel_f32");
-      }
+      const float *ga = (const float *)gamma, *x = (const float *)X;
+      auto launch = [&](auto *out_part, auto *kern, auto *kern_vec) {
+        hipLaunchKernelGGL(vec ? kern_vec : kern, grd, dim3(256), 0, ctx->stream, P, ga, x, kchunk, out_part);
+      };
+      if (prec == FPCA_PREC_BF16X3 && wide)
+        launch((double *)part, k_panel_bf16x3<RB, false, double>, k_panel_bf16x3<RB, true, double>);
+      else if (prec == FPCA_PREC_BF16X3)
+        launch((float *)part, k_panel_bf16x3<RB, false, float>, k_panel_bf16x3<RB, true, float>);
+      else if (wide)
+        launch((double *)part, k_panel_f32<RB, false, double>, k_panel_f32<RB, true, double>);
+      else
+        launch((float *)part, k_panel_f32<RB, false, float>, k_panel_f32<RB, true, float>);
+      FPCA_LAUNCH_CHECK("panel");
     } else {
       if (op) {
         // the covariance operator: Gamma X without Gamma
         if (int rc = covop_apply_internal(op, RP, (const double *)X, (double *)part)) return rc;
       } else {
         hipLaunchKernelGGL(k_panel_f64<RP / 16>, dim3((unsigned)colblocks, (unsigned)nsplit), dim3(256), 0, ctx->stream,
-                           P, (const double *)gamma, (const double *)X, kchunk, part);
+                           P, (const double *)gamma, (const double *)X, kchunk, (double *)part);
         FPCA_LAUNCH_CHECK("panel_f64");
       }
     }
-    if (mode == 2)
-      hipLaunchKernelGGL((k_rows_gram<2, RP, T>), dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit),
-                         part, sw, Q, out, gpart);
+    auto rows = [&](auto *kern, auto *sums) {
+      hipLaunchKernelGGL(kern, dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit), sums, sw, Q, out, gpart);
+    };
+    if (f32 && !wide)
+      rows(mode == 2 ? k_rows_gram<2, RP, float> : k_rows_gram<1, RP, float>, (const float *)part);
     else
-      hipLaunchKernelGGL((k_rows_gram<1, RP, T>), dim3(unsigned(ngram)), dim3(RT), 0, ctx->stream, P, int(nsplit),
-                         part, sw, Q, out, gpart);
+      rows(mode == 2 ? k_rows_gram<2, RP, double> : k_rows_gram<1, RP, double>, (const double *)part);
     FPCA_LAUNCH_CHECK("rows_gram");
     return FPCA_OK;
   };

@@ -237,3 +237,28 @@ def test_gram_on_two_streams_in_turn(torch, F, h, npdt):
     torch.cuda.synchronize()
     for args, S, ref in cases:
         assert normwise_rel(S.cpu().numpy().astype(np.float64), ref) < tol
+
+
+@pytest.mark.parametrize("M,bar", [(676, 3.4e-8), (1024, 3.2e-8), (1600, 3.7e-8)])
+def test_eig_fp32_sums_stay_short(torch, F, h, M, bar):
+    """FP32 products of a range where the nodes are split into many shares: the eigenfunctions' error against 64 bits,
+    over six covariances, is no larger than with a separate FP32 partial product for every 32 (1600 nodes: 96) nodes,
+    whose measured error and a tenth more is the bar (sums twice as long exceed it)."""
+    _say(f"eig fp32 sums P={M}")
+    err = []
+    for seed in range(6):
+        rng = np.random.default_rng(100 + seed)
+        V = np.linalg.qr(rng.standard_normal((M, 30)))[0]
+        Gam = ((V * 0.8 ** np.arange(30)) @ V.T).astype(np.float32)
+        Gam = (Gam + Gam.T) / 2
+        om = np.full(M, 1.0 / M)
+        ef = torch.empty(6, M, dtype=torch.float32, device="cuda:0")
+        F.fpca_eig_randomized(h, F.FPCA_F32, F.FPCA_PREC_F32, F.Grid((M,)), dev(torch, Gam), dev(torch, om), 6, 10, 2,
+                              seed, ef)
+        _, ref, _ = oracle.eig_randomized(Gam.astype(np.float64), om, 6, 10, 2, seed)
+        got = ef.cpu().numpy().astype(np.float64)
+        ref = ref.T * np.sign(np.sum(ref.T * got, axis=1, keepdims=True))
+        err.append(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    err = float(np.sqrt(np.mean(np.square(err))))
+    _say(f"error {err:.3e} bar {bar:.1e}")
+    assert err <= bar
