@@ -305,8 +305,9 @@ int fpca_eig_randomized(fpca_handle handle, int dtype, int prec, const fpca_grid
  *     grid steps (R_max = 2016, 28, 6 for d = 1, 2, 3) and be non-degenerate
  *     at every node, else FPCA_ERR_UNSUPPORTED.
  *   mode: FPCA_COVOP_RECOMPUTE (the band is recomputed tile by tile in every
- *     product; the operator holds O(n P) memory, a product for d >= 2 takes
- *     P x min(r, 32) doubles of the handle's scratch where they fit) or FPCA_COVOP_STORE_BAND (the
+ *     product; the operator holds O(n P) memory and, for d >= 2 where it fits,
+ *     up to 512 MB (d = 2: 1 GB) in which a product keeps band blocks between
+ *     launches) or FPCA_COVOP_STORE_BAND (the
  *     band is formed once and kept in 64 x 64 FP64 blocks, about
  *     P x 64 x prod_k (2 ceil(2R_k / b_k) + 1) doubles with tile extents
  *     b = 64 / 8 / 4 for d = 1 / 2 / 3; products then stream it).
@@ -314,7 +315,8 @@ int fpca_eig_randomized(fpca_handle handle, int dtype, int prec, const fpca_grid
  *   does not fit), keeps the handle, and uses the handle's stream at each
  *   call. Synchronizes the stream.
  * fpca_covop_apply -- out = Gamma_hat X; X, out: device, P x r row-major FP64
- *   (node-major), 1 <= r <= 64; asynchronous on the handle's stream.
+ *   (node-major), 1 <= r <= 64; asynchronous on the handle's stream. The same
+ *   product gives the same bits; it uses the operator's memory only.
  * fpca_covop_destroy -- waits for the handle's stream and frees the operator.
  * fpca_eig_covop -- fpca_eig_randomized (same algorithm, test matrix,
  *   orthonormalization, rescaling and sign rule, FP64) with every product

@@ -93,6 +93,8 @@ int hip_fail(hipError_t e, const char *what);
     if (e_ != hipSuccess) return fpca::hip_fail(e_, what);  \
   } while (0)
 
+// Scratch memory outside the arenas (context.hip).
+hipError_t scratch_malloc(fpca_context *ctx, void **p, size_t bytes);
 // Scratch arenas: ensure at least `bytes`; returns FPCA_OK or an error.
 int ws_reserve(fpca_context *ctx, size_t bytes);
 int ws2_reserve(fpca_context *ctx, size_t bytes);
@@ -101,7 +103,6 @@ int ws2_reserve(fpca_context *ctx, size_t bytes);
 // capturing and when the allocation fails. For paths that have another way
 // without the memory.
 bool ws_room(fpca_context *ctx, size_t bytes);
-bool ws2_room(fpca_context *ctx, size_t bytes);
 int ws3_reserve(fpca_context *ctx, size_t bytes);
 // A block for the shares' sums of a Gram product, or null where there is none
 // (the conditions of ws_room). These products had no scratch of their own, so

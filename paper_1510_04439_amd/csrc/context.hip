@@ -67,7 +67,7 @@ GridDims make_dims(const fpca_grid *g) {
 
 // hipMalloc for a scratch block, within the handle's debugging limit on one
 // allocation; a failure leaves no error behind in the runtime.
-static hipError_t scratch_malloc(fpca_context *ctx, void **p, size_t bytes) {
+hipError_t scratch_malloc(fpca_context *ctx, void **p, size_t bytes) {
   hipError_t e = hipErrorOutOfMemory;
   if (!ctx->alloc_limit || bytes <= ctx->alloc_limit) e = hipMalloc(p, bytes);
   if (e != hipSuccess) {
@@ -127,7 +127,6 @@ int ws3_reserve(fpca_context *ctx, size_t bytes) {
 bool ws_room(fpca_context *ctx, size_t bytes) {
   return arena_room(ctx, &ctx->ws, &ctx->ws_size, bytes, bytes + bytes / 8);
 }
-bool ws2_room(fpca_context *ctx, size_t bytes) { return arena_room(ctx, &ctx->ws2, &ctx->ws2_size, bytes, bytes); }
 
 // The block belongs to the stream that used it last. When the handle goes on to
 // another one, fpca_set_stream marks the end of that stream's work with an event

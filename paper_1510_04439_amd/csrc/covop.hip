@@ -357,7 +357,11 @@ struct BandArgs {
   double *band;  // stored blocks
   const double *Hs;  // d >= 2: Y2 summed over p_0 (k_hsum); Y2 itself for d = 2
   int c0, nc;        // d >= 2: columns of X of this launch
-  double *Tsum;      // half of the pairs formed: P x nc sums of the other half
+  // d >= 2: the units of s-nodes of this launch, lo .. lo + cnt - 1: s_0 for d = 3,
+  // tiles of four s_1 for d = 2. Half of the pairs formed: the distances of this
+  // launch, and the blocks of Delta formed (TurnedGeo).
+  int lo, cnt, i0, ni;
+  double *delta;
 };
 
 // Local node li of a tile (coordinate d-1 fastest) and its grid coordinates.
@@ -713,23 +717,53 @@ __global__ __launch_bounds__(256) void k_retile(CovGeo g, const double *__restri
   }
 }
 
-// LDS written by a wavefront is read by its other lanes
-__device__ inline void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int MT = 512;     // threads: 8 wavefronts
 constexpr int MKC = 104;    // curves per LDS chunk
 template <int d>
 constexpr int mfma_nv() { return 2 * d - 1; }  // H2 variants
-constexpr int TR_LD = 17;  // LDS row of a wavefront's transposed Delta
-inline size_t band_mfma_lds(int d, int n, int R2, int ncb, bool half) {
+inline size_t band_mfma_lds(int d, int n, int R2, int ncb) {
   const size_t kp = size_t(std::min(MKC, (n + 7) / 8 * 8));
   const size_t z = size_t(d + 1) * kp * 32, red = size_t(8) * ncb * 256;
-  const size_t tr = half ? size_t(8 * 16 * TR_LD + 2 * 16 * 16 * ncb) : 0;
-  return (std::max(z, red) + 2 * size_t(8 + 2 * R2) * (2 * d - 1) * 16 + tr) * 8;
+  return (std::max(z, red) + 2 * size_t(8 + 2 * R2) * (2 * d - 1) * 16) * 8;
+}
+
+// Half of the pairs. Delta is symmetric, so of the blocks (s, t) and (t, s) one is
+// formed where they lie apart in s_0, or in the tile of s_1: with an even distance
+// t - s the one with t > s, with an odd one that with t < s (every s has as many t
+// then). A launch takes the distances half_dt(i), i0 <= i < i0 + ni, of coordinate 0
+// (d = 2: 0) and leaves its blocks, 16 s x 16 t each, at [distance][s-unit][block of
+// s][tile distance in coordinate 1][in coordinate 2]; k_band_turned applies the
+// transposes.
+struct TurnedGeo {
+  int T1h, T2h, T2n;  // reach in tiles; distances in coordinate 2
+  int nk;             // distances in coordinate 1, at most
+  int nT1, nT2, nB2;  // tiles of the coordinates; blocks of s in coordinate 2 (pairs of them)
+};
+__host__ __device__ inline TurnedGeo turned_geo(const int *M, const int *R, int d) {
+  TurnedGeo t;
+  t.T1h = (2 * R[d - 2] + 3) / 4;
+  t.T2h = (2 * R[d - 1] + 3) / 4;
+  t.T2n = 2 * t.T2h + 1;
+  t.nk = d == 3 ? 2 * t.T1h + 1 : t.T1h;
+  t.nT1 = (M[d - 2] + 3) / 4;
+  t.nT2 = (M[d - 1] + 3) / 4;
+  t.nB2 = (M[d - 1] + 7) / 8 * 2;
+  return t;
+}
+__host__ __device__ inline int half_dt(int i) { return i % 2 == 0 ? i : -i; }
+// Tile distance in coordinate 1 to its place (T1h of them at dt = 0), and back.
+__device__ inline int turned_k(const TurnedGeo &t, int dt, int d1) {
+  return dt ? d1 + t.T1h : (d1 > 0 ? d1 / 2 - 1 : t.T1h / 2 + (-d1 - 1) / 2);
+}
+__device__ inline int turned_d1(const TurnedGeo &t, int dt, int k) {
+  return dt ? k - t.T1h : (k < t.T1h / 2 ? 2 * (k + 1) : -(2 * (k - t.T1h / 2) + 1));
+}
+// The block's place: u the s-unit within the launch (all of its distances count
+// on: (i - i0) cnt + unit), S1 (d = 3) and S2 the tiles of s.
+template <int d>
+__device__ inline int64_t turned_slot(const TurnedGeo &t, int u, int S1, int S2, int k, int d2) {
+  const int64_t blk = d == 3 ? (int64_t(u) * t.nT1 + S1) * t.nB2 + S2 : int64_t(u) * t.nB2 + S2;
+  return ((blk * t.nk + k) * t.T2n + d2 + t.T2h) * 256;
 }
 
 // One workgroup per s-set (s_0; 4 of s_1; 8 of s_2): two blocks of 16 s-nodes,
@@ -747,14 +781,8 @@ inline size_t band_mfma_lds(int d, int n, int R2, int ncb, bool half) {
 // 50 ms), the rows of weights (50 ms, a gather of 64 rows per instruction) and
 // curves missed in L2. With the responses on the vector units from LDS, the
 // diagonal terms by LDS passes with barriers and a solve per pair: 1166 ms.
-// HALF (where there is scratch for it): Delta is symmetric, so of the blocks with
-// s_0 != t_0 (at s_0 = t_0: with other tiles of coordinate 1) only one of (s, t)
-// and (t, s) is formed, by the parity of the two numbers' sum the one with the
-// larger or with the smaller s (every s-set then has as many t). Its transpose,
-// through LDS, times X at the s-nodes is added to Tsum at the t-nodes with FP64
-// atomics: 4 matrix instructions and 256 additions per block beside the 200
-// instructions that form it. All pairs 230 ms (above),
-// these 129; d = 2, 100^2 nodes, R = 6, n = 100, r = 20: 518 and 381 us.
+// HALF: half of the pairs (TurnedGeo), Delta's blocks also left in memory. All pairs 230 ms (above), half of them and k_band_turned 114;
+// d = 2, 100^2 nodes, R = 6, n = 100, r = 20: 486 and 343 us.
 template <int d, int NCB, bool STORE, bool HALF = false>
 __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   constexpr int F = d + 1, NT = 2 * d + 1, NV = mfma_nv<d>();
@@ -769,8 +797,6 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   double *Zs = sm;            // [F][kp][32], the halves of a row swapped where curve / 2 is odd
   const int zsz = max(F * kp * 32, 8 * NCB * 256);
   double *H2 = sm + zsz;      // [2][hw][NV][16 (s_1, t_1)]
-  double *tr = H2 + 2 * hw * NV * 16;  // HALF: [wave][16 s][TR_LD t]
-  double *Xs = tr + 8 * 16 * TR_LD;    // HALF: [s-block][16 s][16 NCB columns of X]
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 15, gq = (tid & 63) >> 4;
   // s-set of this workgroup; consecutive workgroups of an XCD are neighbours
   int s0 = 0, s1a, s2a;
@@ -781,8 +807,12 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
     if (id < per * 8) id = (id % 8) * per + id / 8;
     s2a = (id % n2) * 8;
     id /= n2;
-    s1a = (id % n1) * 4;
-    s0 = id / n1;
+    if constexpr (d == 3) {
+      s1a = (id % n1) * 4;
+      s0 = A.lo + id / n1;
+    } else {
+      s1a = (A.lo + id) * 4;
+    }
   }
   const int64_t st0 = d == 3 ? g.stride[0] : 0, st1 = g.stride[k1];
   auto node_of = [&](int x0, int x1, int x2) { return int64_t(x0) * st0 + int64_t(x1) * st1 + x2; };
@@ -817,21 +847,12 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
     }
   };
   if (nch == 1) load_zs(0);
-  if constexpr (HALF) {
-    for (int e = tid; e < 2 * 16 * 16 * NCB; e += MT) {
-      const int col = e % (16 * NCB), i = e / (16 * NCB) & 15, b = e / (256 * NCB);
-      const int x1 = s1a + (i >> 2), x2 = s2a + 4 * b + (i & 3);
-      Xs[e] = x1 < M1 && x2 < M2 && col < A.nc ? A.X[node_of(s0, x1, x2) * A.r + A.c0 + col] : 0.0;
-    }
-    tr += wave * 16 * TR_LD;
-    Xs += sb * 256 * NCB;
-  }
-
   f64x4 oacc[NCB];
 #pragma unroll
   for (int c = 0; c < NCB; ++c) oacc[c] = f64x4{0.0, 0.0, 0.0, 0.0};
 
   const int t0lo = d == 3 ? max(0, s0 - 2 * R0) : 0, t0hi = d == 3 ? min(M0 - 1, s0 + 2 * R0) : 0;
+  const TurnedGeo tg = turned_geo(g.M, g.R, d);
   // the t-tiles of coordinate 1 in an order by their number modulo the reach, so
   // that the workgroups of an XCD, whose reaches overlap, take the same tile at
   // about the same time and find its curves in their L2
@@ -843,15 +864,16 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   // this lane's place in the product over p_2: its value for lane (t_2; s_1, s_2) is in lane (s_1; t_2, s_2)
   const int perm = (((tid >> 2) & 3) * 16 + ((tid >> 4) & 3) * 4 + (tid & 3)) * 4;
   int buf = 0;
-  for (int t0 = t0lo; t0 <= t0hi; ++t0) {
-    if (HALF && t0 != s0 && (((s0 + t0) & 1) == 0) != (t0 > s0)) continue;  // formed as (t, s)
+  for (int i = HALF ? A.i0 : t0lo; i < (HALF ? A.i0 + A.ni : t0hi + 1); ++i) {
+    const int dt = HALF ? half_dt(i) : 0, t0 = HALF ? s0 + dt : i;
+    if (HALF && (t0 < 0 || t0 >= M0)) continue;
     for (int k = 0; k < T1n; ++k) {
       int T1 = k - (T1lo % T1n + T1n) % T1n;
       T1 = T1lo + (T1 < 0 ? T1 + T1n : T1);
       const int t1a = 4 * T1;
       if (T1 < 0 || t1a >= M1) continue;
-      if (HALF && t0 == s0 && t1a != s1a && (((t1a + s1a) & 4) == 0) != (t1a > s1a)) continue;
-      const bool mirror = HALF && (t0 != s0 || t1a != s1a);
+      if (HALF && dt == 0 && t1a != s1a && (((t1a + s1a) & 4) == 0) != (t1a > s1a)) continue;  // formed as (t, s)
+      const bool turned = HALF && (dt != 0 || t1a != s1a);
       // ---- the diagonal terms summed over p_0 and p_1
       double *Hb = H2 + buf * hw * NV * 16;
       buf ^= 1;
@@ -1060,33 +1082,11 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
                   __builtin_amdgcn_mfma_f64_16x16x4f64(tok && col < A.nc ? xv : 0.0, delta[v], oacc[c], 0, 0, 0);
             }
           }
-          if (mirror) {
-            // lane l holds s-node l and t-nodes 4 gq + v (t_2 = gq, t_1 = v); as
-            // the second operand lane l has t-node l, step j the s-nodes 4 j + gq
-#pragma unroll
-            for (int v = 0; v < 4; ++v) tr[l * TR_LD + 4 * gq + v] = delta[v];
-            wave_sync();
-            f64x4 ta[NCB];
-#pragma unroll
-            for (int c = 0; c < NCB; ++c) ta[c] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const double dt = tr[(4 * j + gq) * TR_LD + l];
-#pragma unroll
-              for (int c = 0; c < NCB; ++c)
-                ta[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(Xs[(4 * j + gq) * 16 * NCB + 16 * c + l], dt, ta[c], 0, 0, 0);
-            }
-            wave_sync();
-            const int y1 = t1a + (l & 3), y2 = t2a + (l >> 2);
-            if (y1 < M1 && y2 < M2) {
-              double *dst = A.Tsum + node_of(t0, y1, y2) * A.nc;
-#pragma unroll
-              for (int c = 0; c < NCB; ++c)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                  if (16 * c + gq + 4 * v < A.nc) atomicAdd(dst + 16 * c + gq + 4 * v, ta[c][v]);
-            }
-          }
+          if (turned)
+            *reinterpret_cast<f64x4 *>(A.delta +
+                                       turned_slot<d>(tg, (i - A.i0) * A.cnt + (d == 3 ? s0 : s1a / 4) - A.lo, s1a / 4,
+                                                      s2a / 4 + sb, turned_k(tg, dt, T1 - s1a / 4), T2 - s2a / 4 - sb) +
+                                       l * 16 + 4 * gq) = f64x4{delta[0], delta[1], delta[2], delta[3]};
         }
       }
     }
@@ -1108,6 +1108,69 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
       for (int w = 0; w < 4; ++w) v += sm[(((2 * w + b) * NCB + c) * 16 + (col & 15)) * 16 + (sn & 15)];
       if (x1 < M1 && x2 < M2 && col < A.nc) A.out[node_of(s0, x1, x2) * A.r + A.c0 + col] += v;
     }
+  }
+}
+
+// The transposes of the blocks of Delta that a launch of k_band_mfma has left,
+// times X at their s-nodes, added to the t-nodes' outputs. One workgroup per block
+// of 16 t-nodes; its four wavefronts take every fourth of the blocks that have it
+// for their t, and their sums are added in order: products repeat bit for bit
+// (added with FP64 atomics by k_band_mfma itself, one product at 64^3 took 130 ms,
+// now 114, and the order was the scheduler's). Bound by the reading of Delta, 2 KB per block.
+template <int d, int NCB>
+__global__ __launch_bounds__(256) void k_band_turned(BandArgs A, int tlo) {
+  __shared__ double red[4][16 * NCB][17];
+  const CovGeo &g = A.g;
+  const int M1 = g.M[d - 2], M2 = g.M[d - 1];
+  const int64_t st0 = d == 3 ? g.stride[0] : 0, st1 = g.stride[d - 2];
+  const TurnedGeo tg = turned_geo(g.M, g.R, d);
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 15, gq = (tid & 63) >> 4;
+  int id = int(blockIdx.x);
+  const int T2 = id % tg.nT2;
+  id /= tg.nT2;
+  const int T1 = d == 3 ? id % tg.nT1 : tlo + id, t0 = d == 3 ? tlo + id / tg.nT1 : 0;
+  f64x4 acc[NCB];
+#pragma unroll
+  for (int c = 0; c < NCB; ++c) acc[c] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int e = wave; e < A.ni * tg.nk * tg.T2n; e += 4) {
+    const int i = e / (tg.nk * tg.T2n), k = e / tg.T2n % tg.nk, d2 = e % tg.T2n - tg.T2h;
+    const int dist = half_dt(A.i0 + i), s0 = t0 - dist;
+    if (dist == 0 && k >= tg.T1h) continue;
+    const int S1 = T1 - turned_d1(tg, dist, k), S2 = T2 - d2, su = d == 3 ? s0 : S1;
+    if (S1 < 0 || S1 >= tg.nT1 || S2 < 0 || S2 >= tg.nT2 || su < A.lo || su >= A.lo + A.cnt) continue;
+    const double *dl = A.delta + turned_slot<d>(tg, i * A.cnt + su - A.lo, S1, S2, k, d2) + l;
+    double dt[4], x[4][NCB];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dt[j] = dl[(4 * j + gq) * 16];
+    // lane group gq of step j: s-node 4 j + gq, so (s_1 = j, s_2 = gq) of its block
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int x1 = 4 * S1 + j, x2 = 4 * S2 + gq;
+      const double *row = A.X + (int64_t(s0) * st0 + int64_t(min(x1, M1 - 1)) * st1 + min(x2, M2 - 1)) * A.r + A.c0;
+#pragma unroll
+      for (int c = 0; c < NCB; ++c) {
+        const int col = 16 * c + l;
+        const double v = row[min(col, A.nc - 1)];
+        x[j][c] = x1 < M1 && x2 < M2 && col < A.nc ? v : 0.0;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int c = 0; c < NCB; ++c) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[j][c], dt[j], acc[c], 0, 0, 0);
+  }
+#pragma unroll
+  for (int c = 0; c < NCB; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[wave][16 * c + gq + 4 * v][l] = acc[c][v];
+  __syncthreads();
+  // t-node i of a block: t_1 = i % 4, t_2 = i / 4
+  for (int e = tid; e < 256 * NCB; e += 256) {
+    const int col = e % (16 * NCB), i = e / (16 * NCB);
+    const int y1 = 4 * T1 + (i & 3), y2 = 4 * T2 + (i >> 2);
+    if (y1 >= M1 || y2 >= M2 || col >= A.nc) continue;
+    A.out[(int64_t(t0) * st0 + int64_t(y1) * st1 + y2) * A.r + A.c0 + col] +=
+        (red[0][col][i] + red[1][col][i]) + (red[2][col][i] + red[3][col][i]);
   }
 }
 
@@ -1255,16 +1318,10 @@ int launch_band1(fpca_covop_s *op, const double *X, int r, double *out) {
   return FPCA_OK;
 }
 
-// out[p][c0 + c] += Tsum[p][c]
-__global__ void k_add_cols(int64_t count, int nc, int r, int c0, const double *__restrict__ Tsum, double *out) {
-  for (int64_t e = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; e < count; e += int64_t(gridDim.x) * blockDim.x)
-    out[e / nc * r + c0 + e % nc] += Tsum[e];
-}
-
 template <int d, int NCB, bool STORE, bool HALF = false>
 int launch_band_mfma(fpca_covop_s *op, const BandArgs &A) {
-  const size_t lds = band_mfma_lds(d, int(op->n), op->R[d - 1], NCB, HALF);
-  const int64_t nwg = (d == 3 ? op->M[0] : 1) * int64_t((op->M[d - 2] + 3) / 4) * ((op->M[d - 1] + 7) / 8);
+  const size_t lds = band_mfma_lds(d, int(op->n), op->R[d - 1], NCB);
+  const int64_t nwg = A.cnt * (d == 3 ? int64_t((op->M[1] + 3) / 4) : 1) * ((op->M[d - 1] + 7) / 8);
   if (nwg > 0x7fffffffLL) return set_error(FPCA_ERR_UNSUPPORTED, "covariance operator: too many nodes");
   FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE, HALF>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
@@ -1273,10 +1330,66 @@ int launch_band_mfma(fpca_covop_s *op, const BandArgs &A) {
   return FPCA_OK;
 }
 
+// Units of s-nodes (see BandArgs) of the whole grid.
+template <int d>
+int band_units(const fpca_covop_s *op) {
+  return d == 3 ? op->M[0] : (op->M[0] + 3) / 4;
+}
+
+// Blocks of Delta per unit and distance, in bytes.
+template <int d>
+size_t turned_unit_bytes(const fpca_covop_s *op) {
+  const TurnedGeo t = turned_geo(op->M, op->R, d);
+  return size_t(d == 3 ? t.nT1 : 1) * t.nB2 * t.nk * t.T2n * 256 * 8;
+}
+// Workgroups of k_band_mfma per unit, and the distances of coordinate 0.
+template <int d>
+int64_t unit_wgs(const fpca_covop_s *op) {
+  return (d == 3 ? int64_t((op->M[1] + 3) / 4) : 1) * ((op->M[d - 1] + 7) / 8);
+}
+template <int d>
+int half_dists(const fpca_covop_s *op) {
+  return d == 3 ? std::min(2 * op->R[0], op->M[0] - 1) + 1 : 1;
+}
+
+// Half of the pairs and their transposes: all units and as many distances at a time
+// as there is memory for, or one distance and a share of its units.
+template <int d, int NCB>
+int launch_turned(fpca_covop_s *op, BandArgs A) {
+  const TurnedGeo tg = turned_geo(op->M, op->R, d);
+  const int units = band_units<d>(op), dists = half_dists<d>(op);
+  A.delta = op->delta;
+  auto launch = [&]() -> int {
+    if (int rc = launch_band_mfma<d, NCB, false, true>(op, A)) return rc;
+    // the units of t-nodes that the launch's s-nodes reach
+    const int dt = A.ni == 1 ? half_dt(A.i0) : 0;
+    const int tlo = d == 2 ? std::max(0, A.lo - tg.T1h) : A.lo + dt;
+    const int tcnt = d == 2 ? std::min(tg.nT1, A.lo + A.cnt + tg.T1h) - tlo : A.cnt;
+    const int64_t nwg = int64_t(tcnt) * (d == 3 ? tg.nT1 : 1) * tg.nT2;
+    hipLaunchKernelGGL((k_band_turned<d, NCB>), dim3(unsigned(nwg)), dim3(256), 0, op->ctx->stream, A, tlo);
+    FPCA_LAUNCH_CHECK("covop band turned");
+    return FPCA_OK;
+  };
+  for (A.i0 = 0; A.i0 < dists; A.i0 += A.ni) {
+    A.ni = std::min(op->delta_dists, dists - A.i0);
+    const int dt = half_dt(A.i0);
+    const int lo = A.ni == 1 ? std::max(0, -dt) : 0, hi = units - (A.ni == 1 ? std::max(0, dt) : 0);
+    const int parts = (hi - lo + op->delta_units - 1) / op->delta_units;
+    for (int u = 0; u < parts; ++u) {
+      A.lo = lo + int(int64_t(hi - lo) * u / parts);
+      A.cnt = lo + int(int64_t(hi - lo) * (u + 1) / parts) - A.lo;
+      if (int rc = launch()) return rc;
+    }
+  }
+  return FPCA_OK;
+}
+
 // d >= 2: at most 32 columns of X per launch (their sums stay in registers).
 template <int d>
 int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *out) {
   BandArgs A = band_args(op, X, r, out);
+  A.lo = 0;
+  A.cnt = band_units<d>(op);
   if (store) {
     const int64_t n = op->n_stiles * op->nslot * 4096;
     hipLaunchKernelGGL(k_zero_f64, dim3(unsigned(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0,
@@ -1286,22 +1399,44 @@ int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *ou
   }
   for (A.c0 = 0; A.c0 < r; A.c0 += 32) {
     A.nc = std::min(32, r - A.c0);
-    // half of the pairs, where there is room for the sums of the other half
-    const int64_t count = op->P * A.nc;
-    if (ws2_room(op->ctx, carve_bytes(size_t(count), 8))) {
-      A.Tsum = static_cast<double *>(op->ctx->ws2);
-      const unsigned blocks = unsigned(std::min<int64_t>((count + 255) / 256, 65536));
-      hipLaunchKernelGGL(k_zero_f64, dim3(blocks), dim3(256), 0, op->ctx->stream, A.Tsum, count);
-      FPCA_LAUNCH_CHECK("covop band zero");
-      if (int rc = A.nc <= 16 ? launch_band_mfma<d, 1, false, true>(op, A) : launch_band_mfma<d, 2, false, true>(op, A))
-        return rc;
-      hipLaunchKernelGGL(k_add_cols, dim3(blocks), dim3(256), 0, op->ctx->stream, count, A.nc, r, A.c0, A.Tsum, out);
-      FPCA_LAUNCH_CHECK("covop band add");
+    const bool one = A.nc <= 16;
+    if (!op->delta) {
+      if (int rc = one ? launch_band_mfma<d, 1, false>(op, A) : launch_band_mfma<d, 2, false>(op, A)) return rc;
       continue;
     }
-    if (int rc = A.nc <= 16 ? launch_band_mfma<d, 1, false>(op, A) : launch_band_mfma<d, 2, false>(op, A)) return rc;
+    if (int rc = one ? launch_turned<d, 1>(op, A) : launch_turned<d, 2>(op, A)) return rc;
   }
   return FPCA_OK;
+}
+
+// Memory for Delta's blocks, up to 512 MB for d = 3 (64^3 nodes, R = 6, one product:
+// 120 ms with 256, 114 with 512, 113 with 1024) and 1024 MB for d = 2 (100^2 nodes,
+// R = 28: 3.2 ms with 256, 2.3 with 512, 1.9 with 1024). Where all units' blocks fit, as many
+// distances as do go into a launch. Otherwise a launch takes one distance and so
+// many units that its workgroups, one per CU at a time, fill whole rounds of the
+// CUs. Without the memory, or where a launch would leave half of the CUs without
+// work (all pairs are formed in about the same time then), products form all pairs.
+template <int d>
+void reserve_delta(fpca_covop_s *op) {
+  const size_t unit = turned_unit_bytes<d>(op);
+  const int units = band_units<d>(op);
+  const int64_t wgs = unit_wgs<d>(op), cus = op->ctx->num_cus;
+  for (size_t budget = size_t(d == 3 ? 512 : 1024) << 20; budget >= unit; budget /= 2) {
+    int64_t u = std::min<int64_t>(units, int64_t(budget / unit)), dists = 1;
+    if (u == units)
+      dists = std::min<int64_t>(half_dists<d>(op), int64_t(budget / unit) / units);
+    else if (u * wgs >= cus)
+      u = u * wgs / cus * cus / wgs;
+    else if (2 * u * wgs < cus)
+      return;
+    void *p = nullptr;
+    if (scratch_malloc(op->ctx, &p, unit * size_t(u * dists)) == hipSuccess) {
+      op->delta = static_cast<double *>(p);
+      op->delta_units = int(u);
+      op->delta_dists = int(dists);
+      return;
+    }
+  }
 }
 
 template <int d>
@@ -1511,6 +1646,7 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   auto fail = [&](int rc) {
     if (op->Zn) (void)hipFree(op->Zn);
     if (op->band) (void)hipFree(op->band);
+    if (op->delta) (void)hipFree(op->delta);
     delete op;
     return rc;
   };
@@ -1620,6 +1756,8 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   if (last != op->Zn) (void)hipFree(last);
   if (rc != FPCA_OK) return fail(rc);
   if (e1 != hipSuccess) return fail(hip_fail(e1, "covariance operator set-up"));
+  if (mode == FPCA_COVOP_RECOMPUTE && d == 2) reserve_delta<2>(op);
+  if (mode == FPCA_COVOP_RECOMPUTE && d == 3) reserve_delta<3>(op);
   *op_out = op;
   return FPCA_OK;
 }
@@ -1639,6 +1777,7 @@ extern "C" int fpca_covop_destroy(fpca_covop op) {
   if (op->ctx && op->ctx->stream) (void)hipStreamSynchronize(op->ctx->stream);
   if (op->Zn) (void)hipFree(op->Zn);
   if (op->band) (void)hipFree(op->band);
+  if (op->delta) (void)hipFree(op->delta);
   delete op;
   return FPCA_OK;
 }

@@ -29,6 +29,8 @@ struct fpca_covop_s {
   int ncls[3] = {0, 0, 0};
   const double *rows = nullptr;
   double *hsum = nullptr;
+  double *delta = nullptr;  // blocks of Delta between a launch and their transposes (null: all pairs formed)
+  int delta_units = 0, delta_dists = 0;  // units of s-nodes and distances that it holds
   double *lr_part = nullptr;  // partial products of the low-rank apply
   double *lr_tot = nullptr;
   int64_t lr_blocks = 0;

@@ -262,3 +262,49 @@ def test_eig_fp32_sums_stay_short(torch, F, h, M, bar):
     err = float(np.sqrt(np.mean(np.square(err))))
     _say(f"error {err:.3e} bar {bar:.1e}")
     assert err <= bar
+
+
+@pytest.mark.parametrize("M,R,n,limit", [((9, 13, 11), (2, 3, 2), 20, 0), ((6, 60, 60), (2, 1, 1), 9, 10 << 20),
+                                         ((200, 90), (3, 3), 9, 13 << 20), ((30, 21), (4, 5), 20, 0)])
+def test_operator_products_repeat(torch, F, h, monkeypatch, M, R, n, limit):
+    """Products of an operator repeat bit for bit, also replayed from a graph between other work of the handle; half
+    of the pairs formed at once, in shares of the nodes (a limit on one allocation), and all pairs (a limit that leaves
+    no room for the other half's blocks) agree to rounding. 40 columns: a launch of 32 and one of 8."""
+    _say(f"operator products M={M} limit={limit}")
+    rng = np.random.default_rng(len(M) + n)
+    P, r = int(np.prod(M)), 40
+    Y, X = dev(torch, 1.0 + rng.standard_normal((n, P))), dev(torch, rng.standard_normal((P, r)))
+    mu = Y.mean(0)
+    hb = [(k + 0.45) / (m - 1) for k, m in zip(R, M)]
+    res = []
+    for cap in (limit, 1):
+        if cap:
+            monkeypatch.setenv("FPCA_DEBUG_ALLOC_LIMIT", str(cap))
+        hh = F.Handle(0)
+        monkeypatch.delenv("FPCA_DEBUG_ALLOC_LIMIT", raising=False)
+        op = F.CovOp(hh, F.Grid(M), Y, mu, hb, F.FPCA_COVOP_RECOMPUTE)
+        try:
+            outs = [torch.full((P, r), float("nan"), dtype=torch.float64, device="cuda:0") for _ in range(5)]
+            for o in outs:
+                op.apply(X, o)
+            torch.cuda.synchronize()
+            for o in outs[1:]:
+                assert torch.equal(o, outs[0])
+            s = torch.cuda.Stream()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=s):
+                op.apply(X, outs[1])
+            other = F.CovOp(hh, F.Grid(M), Y, mu, hb, F.FPCA_COVOP_RECOMPUTE)
+            for _ in range(3):
+                outs[1].fill_(float("nan"))
+                other.apply(X, outs[2])
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(outs[1], outs[0])
+            other.close()
+            res.append(outs[0].cpu().numpy())
+        finally:
+            op.close()
+            hh.close()
+    assert normwise_rel(res[0], res[1]) < 1e-13
