@@ -305,9 +305,11 @@ int fpca_eig_randomized(fpca_handle handle, int dtype, int prec, const fpca_grid
  *     grid steps (R_max = 2016, 28, 6 for d = 1, 2, 3) and be non-degenerate
  *     at every node, else FPCA_ERR_UNSUPPORTED.
  *   mode: FPCA_COVOP_RECOMPUTE (the band is recomputed tile by tile in every
- *     product; the operator holds O(n P) memory and, for d >= 2 where it fits,
- *     up to 512 MB (d = 2: 1 GB) in which a product keeps band blocks between
- *     launches) or FPCA_COVOP_STORE_BAND (the
+ *     product; the operator holds O(n P) memory and, for d >= 2 where they fit,
+ *     tables that depend on the windows, not on n: up to 343 MB for d = 3 and
+ *     687 MB for d = 2 at the widest windows, 3 (4 R + 1) P doubles for d = 3
+ *     (R: the first coordinate's window in grid steps), and up to 512 MB (d = 2: 1 GB) in which a product keeps band blocks
+ *     between launches; without them products take longer) or FPCA_COVOP_STORE_BAND (the
  *     band is formed once and kept in 64 x 64 FP64 blocks, about
  *     P x 64 x prod_k (2 ceil(2R_k / b_k) + 1) doubles with tile extents
  *     b = 64 / 8 / 4 for d = 1 / 2 / 3; products then stream it).

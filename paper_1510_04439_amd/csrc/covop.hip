@@ -355,7 +355,8 @@ struct BandArgs {
   int r;
   double *out;
   double *band;  // stored blocks
-  const double *Hs;  // d >= 2: Y2 summed over p_0 (k_hsum); Y2 itself for d = 2
+  const double *Hs;  // d >= 2: Y2 summed over p_0 (k_hsum) for s_0 from hs0 on; Y2 itself for d = 2
+  int hs0;
   int c0, nc;        // d >= 2: columns of X of this launch
   // d >= 2: the units of s-nodes of this launch, lo .. lo + cnt - 1: s_0 for d = 3,
   // tiles of four s_1 for d = 2. Half of the pairs formed: the distances of this
@@ -666,15 +667,15 @@ __global__ __launch_bounds__(64) void k_wtab(CovGeo g, int64_t count, const int 
   for (int q = 0; q < 2 * d + 1; ++q) tab[e * 8 + q] = w[q];
 }
 
-// d = 3: Y2 summed over p_0 with the factors of (s_0, t_0 = s_0 + delta):
-// H[(s_0 (4R_0 + 1) + delta + 2 R_0)][ab][p_1 p_2], ab: K K, K K u, K K v.
-__global__ __launch_bounds__(256) void k_hsum(CovGeo g, const double *__restrict__ Y2, double *__restrict__ H) {
+// d = 3: Y2 summed over p_0 with the factors of (s_0, t_0 = s_0 + delta), s_0 from
+// lo on: H[((s_0 - lo) (4R_0 + 1) + delta + 2 R_0)][ab][p_1 p_2], ab: K K, K K u, K K v.
+__global__ __launch_bounds__(256) void k_hsum(CovGeo g, int lo, const double *__restrict__ Y2, double *__restrict__ H) {
   const int64_t plane = int64_t(g.M[1]) * g.M[2];
   const int64_t nb = (plane + 255) / 256, pair = blockIdx.x / nb;
   const int64_t p = (blockIdx.x % nb) * 256 + threadIdx.x;
   if (p >= plane) return;
   const int R = g.R[0], wd = 4 * R + 1;
-  const int s = int(pair / wd), t = s + int(pair % wd) - 2 * R;
+  const int s = lo + int(pair / wd), t = s + int(pair % wd) - 2 * R;
   double h0 = 0.0, h1 = 0.0, h2 = 0.0;
   if (t >= 0 && t < g.M[0])
     for (int q = max(max(s, t) - R, 0); q <= min(min(s, t) + R, g.M[0] - 1); ++q) {
@@ -783,7 +784,10 @@ __device__ inline int64_t turned_slot(const TurnedGeo &t, int u, int S1, int S2,
 // diagonal terms by LDS passes with barriers and a solve per pair: 1166 ms.
 // HALF: half of the pairs (TurnedGeo), Delta's blocks also left in memory. All pairs 230 ms (above), half of them and k_band_turned 114;
 // d = 2, 100^2 nodes, R = 6, n = 100, r = 20: 486 and 343 us.
-template <int d, int NCB, bool STORE, bool HALF = false>
+// TAB: the rows of weights come from the operator's table; without the memory for
+// it each is solved where it is needed (a solve per pair, with spills: all pairs at
+// 64^3, k_hsum for one s_0 at a time, 589 ms; d = 2, 100^2 nodes, R = 28: 4.5 for 1.9).
+template <int d, int NCB, bool STORE, bool HALF, bool TAB>
 __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
   constexpr int F = d + 1, NT = 2 * d + 1, NV = mfma_nv<d>();
   constexpr int k1 = d - 2, k2 = d - 1;
@@ -879,7 +883,7 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
       buf ^= 1;
       const bool any = min(s1a, t1a) + 3 + R1 >= max(s1a, t1a) - R1;  // some shared p_1
       if (any) {
-        const double *Hg = d == 3 ? A.Hs + int64_t(s0 * (4 * R0 + 1) + t0 - s0 + 2 * R0) * 3 * plane : A.Hs;
+        const double *Hg = d == 3 ? A.Hs + int64_t((s0 - A.hs0) * (4 * R0 + 1) + t0 - s0 + 2 * R0) * 3 * plane : A.Hs;
         // rows s_1 + 4 t_1 (lane l of the first operand), columns p_2: one
         // variant and 16 columns per task
         const int ct = (np2 + 15) / 16;
@@ -916,11 +920,11 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
         for (int q = 0; q < NT; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
         // pair classes and the t-nodes' factors, requested ahead of the products
         const int xt2 = t2a + gq, xt2c = min(xt2, M2 - 1);
-        int c1[4];
+        int c1[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int v = 0; TAB && v < 4; ++v)
           c1[v] = g.cls[k1][xs1c * (4 * R1 + 1) + min(max(min(t1a + v, M1 - 1) - xs1c, -2 * R1), 2 * R1) + 2 * R1];
-        const int c2 = g.cls[k2][xs2c * (4 * R2 + 1) + min(max(xt2c - xs2c, -2 * R2), 2 * R2) + 2 * R2];
+        const int c2 = !TAB ? 0 : g.cls[k2][xs2c * (4 * R2 + 1) + min(max(xt2c - xs2c, -2 * R2), 2 * R2) + 2 * R2];
         const double *n2 = g.nd[k2] + xt2c * 3;
         const double tS2 = n2[0], tA2 = n2[1], tB2 = n2[2];
         const int64_t tt = (int64_t(t0) * nT1 + T1) * nT2 + T2;
@@ -968,7 +972,7 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
           }
         }
         if (!work) continue;
-        const int c0 = d == 3 ? g.cls[0][s0 * (4 * R0 + 1) + t0 - s0 + 2 * R0] : 0;
+        const int c0 = d == 3 && TAB ? g.cls[0][s0 * (4 * R0 + 1) + t0 - s0 + 2 * R0] : 0;
         const double sg0 = c0 & 1 ? -1.0 : 1.0;
         double low[4], w[4][NT];
         bool inb[4];
@@ -976,12 +980,23 @@ __global__ __launch_bounds__(MT) void k_band_mfma(BandArgs A) {
         for (int v = 0; v < 4; ++v) {
           const int xt1 = t1a + v;
           inb[v] = sok && xt1 < M1 && xt2 < M2 && abs(xt2 - xs2) <= 2 * R2 && abs(xt1 - xs1) <= 2 * R1;
-          // pairs outside the band or the grid read the row of some class; their Delta is 0
-          const int64_t e = (int64_t(d == 3 ? c0 >> 1 : 0) * g.ncls[k1] + (max(c1[v], 0) >> 1)) * g.ncls[k2] +
-                            (max(c2, 0) >> 1);
-          const double *row = g.rows + (inb[v] ? e : 0) * 8;
+          if constexpr (TAB) {
+            // pairs outside the band or the grid read the row of some class; their Delta is 0
+            const int64_t e = (int64_t(d == 3 ? c0 >> 1 : 0) * g.ncls[k1] + (max(c1[v], 0) >> 1)) * g.ncls[k2] +
+                              (max(c2, 0) >> 1);
+            const double *row = g.rows + (inb[v] ? e : 0) * 8;
 #pragma unroll
-          for (int q = 0; q < NT; ++q) w[v][q] = row[q];
+            for (int q = 0; q < NT; ++q) w[v][q] = row[q];
+          } else {
+            int xs[3] = {s0, xs1c, xs2c}, xt[3] = {t0, min(xt1, M1 - 1), xt2c};
+            if constexpr (d == 2) {
+              xs[0] = xs1c, xs[1] = xs2c;
+              xt[0] = min(xt1, M1 - 1), xt[1] = xt2c;
+            }
+            pair_weights<d>(g, xs, xt, w[v]);
+            // one solve at a time: no interleaving of their registers
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -1293,6 +1308,13 @@ CovGeo make_geo(const fpca_covop_s *op) {
   return g;
 }
 
+void free_op(fpca_covop_s *op) {
+  for (void *p : {static_cast<void *>(op->mem), static_cast<void *>(op->Zn), static_cast<void *>(op->tables),
+                  static_cast<void *>(op->hsum), static_cast<void *>(op->delta), static_cast<void *>(op->band)})
+    if (p) (void)hipFree(p);
+  delete op;
+}
+
 unsigned nb256(int64_t n) { return unsigned((n + 255) / 256); }
 
 BandArgs band_args(const fpca_covop_s *op, const double *X, int r, double *out) {
@@ -1305,6 +1327,7 @@ BandArgs band_args(const fpca_covop_s *op, const double *X, int r, double *out) 
   A.out = out;
   A.band = op->band;
   A.Hs = op->d == 3 ? op->hsum : op->Y2;
+  A.lo = A.hs0 = A.i0 = A.ni = 0;
   return A;
 }
 
@@ -1318,14 +1341,14 @@ int launch_band1(fpca_covop_s *op, const double *X, int r, double *out) {
   return FPCA_OK;
 }
 
-template <int d, int NCB, bool STORE, bool HALF = false>
+template <int d, int NCB, bool STORE, bool HALF, bool TAB>
 int launch_band_mfma(fpca_covop_s *op, const BandArgs &A) {
   const size_t lds = band_mfma_lds(d, int(op->n), op->R[d - 1], NCB);
   const int64_t nwg = A.cnt * (d == 3 ? int64_t((op->M[1] + 3) / 4) : 1) * ((op->M[d - 1] + 7) / 8);
   if (nwg > 0x7fffffffLL) return set_error(FPCA_ERR_UNSUPPORTED, "covariance operator: too many nodes");
-  FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE, HALF>),
+  FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE, HALF, TAB>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
-  hipLaunchKernelGGL((k_band_mfma<d, NCB, STORE, HALF>), dim3(unsigned(nwg)), dim3(MT), lds, op->ctx->stream, A);
+  hipLaunchKernelGGL((k_band_mfma<d, NCB, STORE, HALF, TAB>), dim3(unsigned(nwg)), dim3(MT), lds, op->ctx->stream, A);
   FPCA_LAUNCH_CHECK("covop band");
   return FPCA_OK;
 }
@@ -1352,19 +1375,32 @@ int half_dists(const fpca_covop_s *op) {
   return d == 3 ? std::min(2 * op->R[0], op->M[0] - 1) + 1 : 1;
 }
 
-// Half of the pairs and their transposes: all units and as many distances at a time
-// as there is memory for, or one distance and a share of its units.
+// All pairs of the launch's units.
+template <int d, int NCB, bool STORE>
+int launch_all(fpca_covop_s *op, const BandArgs &A) {
+  return op->rows ? launch_band_mfma<d, NCB, STORE, false, true>(op, A)
+                  : launch_band_mfma<d, NCB, STORE, false, false>(op, A);
+}
+
+// Half of the pairs with s in the units A.lo .. A.lo + A.cnt - 1, and their
+// transposes: all units and as many distances at a time as there is memory for, or
+// one distance and a share of the units.
 template <int d, int NCB>
 int launch_turned(fpca_covop_s *op, BandArgs A) {
   const TurnedGeo tg = turned_geo(op->M, op->R, d);
-  const int units = band_units<d>(op), dists = half_dists<d>(op);
+  const int units = band_units<d>(op), dists = half_dists<d>(op), ulo = A.lo, uhi = A.lo + A.cnt;
   A.delta = op->delta;
   auto launch = [&]() -> int {
-    if (int rc = launch_band_mfma<d, NCB, false, true>(op, A)) return rc;
+    if (int rc = launch_band_mfma<d, NCB, false, true, true>(op, A)) return rc;
     // the units of t-nodes that the launch's s-nodes reach
-    const int dt = A.ni == 1 ? half_dt(A.i0) : 0;
-    const int tlo = d == 2 ? std::max(0, A.lo - tg.T1h) : A.lo + dt;
-    const int tcnt = d == 2 ? std::min(tg.nT1, A.lo + A.cnt + tg.T1h) - tlo : A.cnt;
+    int tlo = 0, tcnt = units;
+    if (d == 2) {
+      tlo = std::max(0, A.lo - tg.T1h);
+      tcnt = std::min(tg.nT1, A.lo + A.cnt + tg.T1h) - tlo;
+    } else if (A.ni == 1) {
+      tlo = A.lo + half_dt(A.i0);
+      tcnt = A.cnt;
+    }
     const int64_t nwg = int64_t(tcnt) * (d == 3 ? tg.nT1 : 1) * tg.nT2;
     hipLaunchKernelGGL((k_band_turned<d, NCB>), dim3(unsigned(nwg)), dim3(256), 0, op->ctx->stream, A, tlo);
     FPCA_LAUNCH_CHECK("covop band turned");
@@ -1373,7 +1409,8 @@ int launch_turned(fpca_covop_s *op, BandArgs A) {
   for (A.i0 = 0; A.i0 < dists; A.i0 += A.ni) {
     A.ni = std::min(op->delta_dists, dists - A.i0);
     const int dt = half_dt(A.i0);
-    const int lo = A.ni == 1 ? std::max(0, -dt) : 0, hi = units - (A.ni == 1 ? std::max(0, dt) : 0);
+    const int lo = A.ni == 1 ? std::max(ulo, -dt) : ulo, hi = A.ni == 1 ? std::min(uhi, units - std::max(0, dt)) : uhi;
+    if (lo >= hi) continue;
     const int parts = (hi - lo + op->delta_units - 1) / op->delta_units;
     for (int u = 0; u < parts; ++u) {
       A.lo = lo + int(int64_t(hi - lo) * u / parts);
@@ -1384,27 +1421,43 @@ int launch_turned(fpca_covop_s *op, BandArgs A) {
   return FPCA_OK;
 }
 
-// d >= 2: at most 32 columns of X per launch (their sums stay in registers).
+// k_hsum for cnt s_0 from lo on.
+int launch_hsum(fpca_covop_s *op, const CovGeo &g, int lo, int cnt) {
+  const int64_t nwg = int64_t(nb256(int64_t(op->M[1]) * op->M[2])) * cnt * (4 * op->R[0] + 1);
+  if (nwg > 0x7fffffffLL) return set_error(FPCA_ERR_UNSUPPORTED, "covariance operator: too many nodes");
+  hipLaunchKernelGGL(k_hsum, dim3(unsigned(nwg)), dim3(256), 0, op->ctx->stream, g, lo, op->Y2, op->hsum);
+  FPCA_LAUNCH_CHECK("covop hsum");
+  return FPCA_OK;
+}
+
+// d >= 2: at most 32 columns of X per launch (their sums stay in registers). Where
+// the sums of k_hsum do not fit for all s_0, they are formed for hs_planes at a time.
 template <int d>
 int launch_band(fpca_covop_s *op, bool store, const double *X, int r, double *out) {
   BandArgs A = band_args(op, X, r, out);
-  A.lo = 0;
-  A.cnt = band_units<d>(op);
+  const int units = band_units<d>(op), step = d == 3 ? op->hs_planes : units;
   if (store) {
     const int64_t n = op->n_stiles * op->nslot * 4096;
     hipLaunchKernelGGL(k_zero_f64, dim3(unsigned(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0,
                        op->ctx->stream, op->band, n);
     FPCA_LAUNCH_CHECK("covop band zero");
-    return launch_band_mfma<d, 1, true>(op, A);
   }
-  for (A.c0 = 0; A.c0 < r; A.c0 += 32) {
-    A.nc = std::min(32, r - A.c0);
-    const bool one = A.nc <= 16;
-    if (!op->delta) {
-      if (int rc = one ? launch_band_mfma<d, 1, false>(op, A) : launch_band_mfma<d, 2, false>(op, A)) return rc;
+  for (int u = 0; u < units; u += step) {
+    A.lo = A.hs0 = u;
+    A.cnt = std::min(step, units - u);
+    if (step < units)
+      if (int rc = launch_hsum(op, A.g, A.lo, A.cnt)) return rc;
+    if (store) {
+      if (int rc = launch_all<d, 1, true>(op, A)) return rc;
       continue;
     }
-    if (int rc = one ? launch_turned<d, 1>(op, A) : launch_turned<d, 2>(op, A)) return rc;
+    for (A.c0 = 0; A.c0 < r; A.c0 += 32) {
+      A.nc = std::min(32, r - A.c0);
+      const bool one = A.nc <= 16;
+      if (int rc = op->delta ? (one ? launch_turned<d, 1>(op, A) : launch_turned<d, 2>(op, A))
+                             : (one ? launch_all<d, 1, false>(op, A) : launch_all<d, 2, false>(op, A)))
+        return rc;
+    }
   }
   return FPCA_OK;
 }
@@ -1421,6 +1474,7 @@ void reserve_delta(fpca_covop_s *op) {
   const size_t unit = turned_unit_bytes<d>(op);
   const int units = band_units<d>(op);
   const int64_t wgs = unit_wgs<d>(op), cus = op->ctx->num_cus;
+  if (!op->rows) return;
   for (size_t budget = size_t(d == 3 ? 512 : 1024) << 20; budget >= unit; budget /= 2) {
     int64_t u = std::min<int64_t>(units, int64_t(budget / unit)), dists = 1;
     if (u == units)
@@ -1596,8 +1650,9 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
   // d >= 2: pair classes of every coordinate: one per offset for the pairs R
   // or more from the border, then one per pair (s, t) near the left border;
   // pairs near the right border alone are those mirrored (u and v change sign,
-  // and with them the entries of the row that go with them). 64^3, R = 6: 175
-  // classes, 343 MB of rows; at R = 28 on d = 2 up to 550 MB.
+  // and with them the entries of the row that go with them). The rows' number
+  // depends on the windows, not on the curves: R = 6 on d = 3 up to 175 classes per
+  // coordinate, 343 MB; R = 28 on d = 2 up to 3277, 687 MB.
   std::vector<int> itab;
   int64_t cls_off[3] = {0, 0, 0}, rep_off[3] = {0, 0, 0}, nrows = 0;
   if (d >= 2) {
@@ -1631,75 +1686,59 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
       nrows *= op->ncls[k];
     }
   }
-  const int64_t hs_n = d == 3 ? int64_t(op->M[0]) * (4 * op->R[0] + 1) * 3 * op->M[1] * op->M[2] : 0;
   const int F = d + 1;
   // filtered curves: node-major for d = 1, in blocks of 16 nodes above
   const int64_t nblk16 = d == 1 ? 0 : (d == 3 ? op->M[0] : 1) * int64_t((op->M[d - 2] + 3) / 4) * ((op->M[d - 1] + 3) / 4);
   const size_t zn_n = d == 1 ? size_t(P) * F * n : size_t(nblk16) * F * size_t((n + 1) / 2) * 32;
-  const size_t bytes_main = carve_bytes(zn_n, 8) + 2 * carve_bytes(size_t(P) * n, 8) +
-                            2 * carve_bytes(P, 8) + carve_bytes(htab.size(), 8) +
-                            carve_bytes(size_t(op->lr_blocks) * (2 * n + 1) * 64, 8) +
-                            carve_bytes(size_t(2 * n + 1) * 64, 8) + carve_bytes(itab.size(), 4) +
-                            carve_bytes(size_t(nrows) * 8, 8) + carve_bytes(size_t(hs_n), 8);
+  const size_t lr_n = size_t(op->lr_blocks) * (2 * n + 1) * 64;
+  const size_t bytes_zn = carve_bytes(zn_n, 8), bytes_pfn = d == 1 ? 0 : carve_bytes(size_t(P) * F * n, 8);
+  const size_t bytes_main = 2 * carve_bytes(size_t(P) * n, 8) + 2 * carve_bytes(P, 8) + carve_bytes(htab.size(), 8) +
+                            carve_bytes(lr_n, 8) + carve_bytes(size_t(2 * n + 1) * 64, 8);
   const size_t bytes_band =
       mode == FPCA_COVOP_STORE_BAND ? carve_bytes(size_t(op->n_stiles) * op->nslot * 4096, 8) : 0;
+  const size_t bytes_rows = carve_bytes(size_t(nrows) * 8, 8), bytes_tables = carve_bytes(itab.size(), 4) + bytes_rows;
+  // k_hsum's sums of one s_0
+  const size_t bytes_plane = d == 3 ? size_t(4 * op->R[0] + 1) * 3 * op->M[1] * op->M[2] * 8 : 0;
+  double *pfn = nullptr;  // node-major filtered curves, until they are in blocks
   auto fail = [&](int rc) {
-    if (op->Zn) (void)hipFree(op->Zn);
-    if (op->band) (void)hipFree(op->band);
-    if (op->delta) (void)hipFree(op->delta);
-    delete op;
+    if (pfn) (void)hipFree(pfn);
+    free_op(op);
     return rc;
   };
   if (int rc = set_device(ctx)) return fail(rc);
   {
+    // the band's blocks follow once the node-major curves are gone
     size_t free_b = 0, total_b = 0;
-    FPCA_HIP(hipMemGetInfo(&free_b, &total_b));
-    const size_t temp = carve_bytes(size_t(P) * F * n, 8) * (d == 1 ? 1 : 2) + carve_bytes(size_t(P) * n, 8);
-    if (bytes_main + bytes_band + temp > free_b)
-      return fail(set_error(FPCA_ERR_WORKSPACE, "covariance operator needs %zu bytes, %zu free",
-                            bytes_main + bytes_band + temp, free_b));
+    const size_t need = bytes_main + bytes_zn + std::max(bytes_pfn, bytes_band + bytes_plane);
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return fail(set_error(FPCA_ERR_DEVICE, "hipMemGetInfo failed"));
+    if (need > free_b)
+      return fail(set_error(FPCA_ERR_WORKSPACE, "covariance operator needs %zu bytes, %zu free", need, free_b));
   }
-  void *mem = nullptr;
-  if (hipMalloc(&mem, bytes_main) != hipSuccess) return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
-  Carver cv{static_cast<char *>(mem), 0, bytes_main};
-  op->Zn = cv.take<double>(zn_n);
+  auto device_alloc = [&](auto **p, size_t bytes) {
+    if (hipMalloc(reinterpret_cast<void **>(p), bytes) == hipSuccess) return true;
+    *p = nullptr;
+    (void)hipGetLastError();
+    return false;
+  };
+  if (!device_alloc(&op->mem, bytes_main) || !device_alloc(&op->Zn, bytes_zn) || (d >= 2 && !device_alloc(&pfn, bytes_pfn)))
+    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
+  Carver cv{op->mem, 0, bytes_main};
   op->Ln = cv.take<double>(size_t(P) * n);
   op->Bn = cv.take<double>(size_t(P) * n);
   op->Y2 = cv.take<double>(P);
   op->mu = cv.take<double>(P);
   op->tab = cv.take<double>(htab.size());
-  op->lr_part = cv.take<double>(size_t(op->lr_blocks) * (2 * n + 1) * 64);
+  op->lr_part = cv.take<double>(lr_n);
   op->lr_tot = cv.take<double>(size_t(2 * n + 1) * 64);
-  int *ditab = nullptr;
-  double *rows_tab = nullptr;
-  if (d >= 2) {
-    ditab = cv.take<int>(itab.size());
-    rows_tab = cv.take<double>(size_t(nrows) * 8);
-    for (int k = 0; k < d; ++k) op->cls[k] = ditab + cls_off[k];
-    op->rows = rows_tab;
-    if (hs_n) op->hsum = cv.take<double>(size_t(hs_n));
-  }
-  if (bytes_band && hipMalloc(reinterpret_cast<void **>(&op->band), bytes_band) != hipSuccess)
-    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc of the band failed"));
   hipStream_t s = ctx->stream;
   if (hipMemcpyAsync(op->tab, htab.data(), htab.size() * 8, hipMemcpyHostToDevice, s) != hipSuccess ||
-      (ditab && hipMemcpyAsync(ditab, itab.data(), itab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess) ||
       hipMemcpyAsync(op->mu, mu, size_t(P) * 8, hipMemcpyDeviceToDevice, s) != hipSuccess)
     return fail(set_error(FPCA_ERR_DEVICE, "copy failed"));
-  // temporaries: the transposed curves and the family buffers
-  double *Yn = nullptr, *tmp = nullptr, *last = op->Zn;
-  if (hipMalloc(reinterpret_cast<void **>(&Yn), size_t(P) * n * 8) != hipSuccess)
-    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
-  if (hipMalloc(reinterpret_cast<void **>(&tmp), size_t(P) * F * n * 8) != hipSuccess) {
-    (void)hipFree(Yn);
-    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
-  }
-  if (d >= 2 && hipMalloc(reinterpret_cast<void **>(&last), size_t(P) * F * n * 8) != hipSuccess) {
-    (void)hipFree(Yn);
-    (void)hipFree(tmp);
-    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
-  }
-  const CovGeo g = make_geo(op);
+  // the transposed curves take the place of the products' partial sums (which are
+  // larger); the passes alternate between pfn and the operator's block, and the
+  // curves end in the latter
+  double *Yn = op->lr_part, *last = d == 1 ? op->Zn : pfn, *tmp = op->Zn;
+  CovGeo g = make_geo(op);
   int rc = FPCA_OK;
   do {
     hipLaunchKernelGGL(k_transpose, dim3(unsigned((P + 31) / 32), unsigned((n + 31) / 32)), dim3(32, 8), 0, s, n, P,
@@ -1728,36 +1767,63 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
     if (rc != FPCA_OK) break;
     hipLaunchKernelGGL(k_lr_prep, dim3(nb256(P * n)), dim3(256), 0, s, g, last, op->Ln, op->Bn);
     if (d >= 2) hipLaunchKernelGGL(k_retile, dim3(unsigned(nblk16), unsigned(F)), dim3(256), 0, s, g, last, op->Zn);
-    if (hipGetLastError() != hipSuccess) {
-      rc = set_error(FPCA_ERR_DEVICE, "prep launch failed");
-      break;
-    }
-    if (d >= 2) {
-      const int *rp[3] = {ditab + rep_off[0], ditab + rep_off[1], ditab + rep_off[2]};
-      if (hs_n)
-        hipLaunchKernelGGL(k_hsum, dim3(nb256(int64_t(op->M[1]) * op->M[2]) * unsigned(op->M[0] * (4 * op->R[0] + 1))),
-                           dim3(256), 0, s, g, op->Y2, op->hsum);
-      const dim3 wg(unsigned((nrows + 63) / 64));
-      if (d == 2)
-        hipLaunchKernelGGL(k_wtab<2>, wg, dim3(64), 0, s, g, nrows, rp[0], rp[1], rp[2], rows_tab);
-      else
-        hipLaunchKernelGGL(k_wtab<3>, wg, dim3(64), 0, s, g, nrows, rp[0], rp[1], rp[2], rows_tab);
-      if (hipGetLastError() != hipSuccess) {
-        rc = set_error(FPCA_ERR_DEVICE, "table launch failed");
-        break;
-      }
-    }
-    if (mode == FPCA_COVOP_STORE_BAND) rc = band_dispatch(op, true, nullptr, 0, nullptr);
+    if (hipGetLastError() != hipSuccess) rc = set_error(FPCA_ERR_DEVICE, "prep launch failed");
   } while (false);
-  // the temporaries are freed once the stream has used them
+  // pfn, the host's tables and the caller's Y are done with once the stream is
   const hipError_t e1 = hipStreamSynchronize(s);
-  (void)hipFree(Yn);
-  (void)hipFree(tmp);
-  if (last != op->Zn) (void)hipFree(last);
+  if (pfn) (void)hipFree(pfn);
+  pfn = nullptr;
   if (rc != FPCA_OK) return fail(rc);
   if (e1 != hipSuccess) return fail(hip_fail(e1, "covariance operator set-up"));
-  if (mode == FPCA_COVOP_RECOMPUTE && d == 2) reserve_delta<2>(op);
-  if (mode == FPCA_COVOP_RECOMPUTE && d == 3) reserve_delta<3>(op);
+  if (bytes_band && !device_alloc(&op->band, bytes_band))
+    return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc of the band failed"));
+  if (d >= 2) {
+    // The table of rows and k_hsum's sums of all s_0 are held where they fit; else
+    // the rows are solved for and the sums formed for fewer s_0 at a time.
+    if (d == 3) {
+      op->hs_planes = op->M[0];
+      while (op->hs_planes > 1 && scratch_malloc(ctx, reinterpret_cast<void **>(&op->hsum), bytes_plane * op->hs_planes) != hipSuccess)
+        op->hs_planes = (op->hs_planes + 1) / 2;
+      if (!op->hsum && !device_alloc(&op->hsum, bytes_plane))
+        return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
+      if (op->hs_planes == op->M[0]) rc = launch_hsum(op, g, 0, op->M[0]);
+    }
+    if (rc == FPCA_OK && scratch_malloc(ctx, reinterpret_cast<void **>(&op->tables), bytes_tables) == hipSuccess) {
+      double *rows = reinterpret_cast<double *>(op->tables);
+      const int *ditab = reinterpret_cast<const int *>(op->tables + bytes_rows);
+      if (hipMemcpyAsync(op->tables + bytes_rows, itab.data(), itab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess)
+        return fail(set_error(FPCA_ERR_DEVICE, "copy failed"));
+      for (int k = 0; k < d; ++k) op->cls[k] = ditab + cls_off[k];
+      op->rows = rows;
+      g = make_geo(op);
+      const int *rp[3] = {ditab + rep_off[0], ditab + rep_off[1], ditab + rep_off[2]};
+      const dim3 wg(unsigned((nrows + 63) / 64));
+      if (d == 2)
+        hipLaunchKernelGGL(k_wtab<2>, wg, dim3(64), 0, s, g, nrows, rp[0], rp[1], rp[2], rows);
+      else
+        hipLaunchKernelGGL(k_wtab<3>, wg, dim3(64), 0, s, g, nrows, rp[0], rp[1], rp[2], rows);
+      if (hipGetLastError() != hipSuccess) rc = set_error(FPCA_ERR_DEVICE, "table launch failed");
+    }
+  }
+  if (rc == FPCA_OK && mode == FPCA_COVOP_STORE_BAND) rc = band_dispatch(op, true, nullptr, 0, nullptr);
+  const hipError_t e2 = hipStreamSynchronize(s);
+  if (rc != FPCA_OK) return fail(rc);
+  if (e2 != hipSuccess) return fail(hip_fail(e2, "covariance operator set-up"));
+  if (mode == FPCA_COVOP_STORE_BAND) {
+    // products read the band and the low-rank part only
+    for (auto **p : {&op->Zn, &op->hsum}) {
+      if (*p) (void)hipFree(*p);
+      *p = nullptr;
+    }
+    if (op->tables) (void)hipFree(op->tables);
+    op->tables = nullptr;
+    op->rows = nullptr;
+    for (int k = 0; k < 3; ++k) op->cls[k] = nullptr;
+  } else if (d == 2) {
+    reserve_delta<2>(op);
+  } else if (d == 3) {
+    reserve_delta<3>(op);
+  }
   *op_out = op;
   return FPCA_OK;
 }
@@ -1775,9 +1841,6 @@ extern "C" int fpca_covop_destroy(fpca_covop op) {
   if (!op) return FPCA_OK;
   if (op->ctx) (void)hipSetDevice(op->ctx->device);
   if (op->ctx && op->ctx->stream) (void)hipStreamSynchronize(op->ctx->stream);
-  if (op->Zn) (void)hipFree(op->Zn);
-  if (op->band) (void)hipFree(op->band);
-  if (op->delta) (void)hipFree(op->delta);
-  delete op;
+  free_op(op);
   return FPCA_OK;
 }

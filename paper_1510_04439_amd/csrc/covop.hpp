@@ -12,7 +12,8 @@ struct fpca_covop_s {
   int64_t P = 0;
   int64_t n = 0;
   int mode = 0;
-  // device data, all FP64, owned by the operator
+  // device data, FP64 but for the tables, owned by the operator (mem: Ln .. tab and lr_*)
+  char *mem = nullptr;
   // curves filtered by K, K u_0, .., K u_{d-1}: P x (d+1) x n for d = 1, else in
   // blocks of 16 nodes (k_retile)
   double *Zn = nullptr;
@@ -24,11 +25,14 @@ struct fpca_covop_s {
   int64_t tab_K[3] = {0, 0, 0}, tab_U[3] = {0, 0, 0}, tab_W[3] = {0, 0, 0}, tab_E[3] = {0, 0, 0}, tab_nd[3] = {0, 0, 0};
   double *band = nullptr;  // stored band blocks (mode FPCA_COVOP_STORE_BAND)
   // d >= 2 (see CovGeo): pair classes and rows of the inverse weight-moment
-  // matrices, and (d = 3) Y2 summed over p_0
+  // matrices (in `tables`; null: no memory for them), and (d = 3) Y2 summed over p_0
+  // for hs_planes s_0
+  char *tables = nullptr;
   const int *cls[3] = {nullptr, nullptr, nullptr};
   int ncls[3] = {0, 0, 0};
   const double *rows = nullptr;
   double *hsum = nullptr;
+  int hs_planes = 0;
   double *delta = nullptr;  // blocks of Delta between a launch and their transposes (null: all pairs formed)
   int delta_units = 0, delta_dists = 0;  // units of s-nodes and distances that it holds
   double *lr_part = nullptr;  // partial products of the low-rank apply

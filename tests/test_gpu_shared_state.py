@@ -308,3 +308,46 @@ def test_operator_products_repeat(torch, F, h, monkeypatch, M, R, n, limit):
             op.close()
             hh.close()
     assert normwise_rel(res[0], res[1]) < 1e-13
+
+
+@pytest.mark.parametrize("M,R,n,limit", [((64, 30, 28), (6, 2, 2), 6, 12 << 20), ((12, 30, 28), (5, 2, 2), 9, 1 << 20),
+                                         ((70, 70), (28, 28), 5, 8 << 20)])
+def test_operator_memory(torch, F, monkeypatch, M, R, n, limit):
+    """The tables of an operator are held where they fit and dispensed with where they do not (a limit on one
+    allocation): for some s_0 at a time, or solved pair by pair, to the same products; a stored band keeps none."""
+    _say(f"operator memory M={M} limit={limit}")
+    rng = np.random.default_rng(sum(M))
+    d, P, r = len(M), int(np.prod(M)), 20
+    Y, X = dev(torch, 1.0 + rng.standard_normal((n, P))), dev(torch, rng.standard_normal((P, r)))
+    mu = Y.mean(0)
+    hb = [(k + 0.45) / (m - 1) for k, m in zip(R, M)]
+    # curves, their smooths and the low-rank sums, padded to blocks of four, and a block of each of the handle's
+    curves = 8 * P * ((d + 1) * 1.4 * (n + 1) + 2 * n + 2 * n + 4) + (4 << 20)
+    tb = {2: 8, 3: 4}[d]
+    band = 8.0 * P * 64 * np.prod([(2 * -(-2 * k // tb) + 1) * (-(-m // tb) * tb) / m for k, m in zip(R, M)])
+    res = []
+    for cap, mode in ((0, F.FPCA_COVOP_RECOMPUTE), (limit, F.FPCA_COVOP_RECOMPUTE), (0, F.FPCA_COVOP_STORE_BAND),
+                      (limit, F.FPCA_COVOP_STORE_BAND)):
+        if cap:
+            monkeypatch.setenv("FPCA_DEBUG_ALLOC_LIMIT", str(cap))
+        hh = F.Handle(0)
+        monkeypatch.delenv("FPCA_DEBUG_ALLOC_LIMIT", raising=False)
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        op = F.CovOp(hh, F.Grid(M), Y, mu, hb, mode)
+        try:
+            held = before - torch.cuda.mem_get_info()[0]
+            _say(f"mode {mode} cap {cap}: held {held >> 20} MB")
+            if mode == F.FPCA_COVOP_STORE_BAND:
+                assert held <= band + curves + (8 << 20)
+            elif cap:
+                assert held <= 3 * cap + curves + (8 << 20)
+            out = torch.full((P, r), float("nan"), dtype=torch.float64, device="cuda:0")
+            op.apply(X, out)
+            torch.cuda.synchronize()
+            res.append(out.cpu().numpy())
+        finally:
+            op.close()
+            hh.close()
+    for a in res[1:]:
+        assert normwise_rel(a, res[0]) < 1e-12
