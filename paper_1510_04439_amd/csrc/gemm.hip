@@ -812,15 +812,23 @@ int gram_mfma(fpca_context *ctx, int nm, const GramMats<T> &ms, int64_t K, int64
   return FPCA_OK;
 }
 
-// FP32 products of 1024 or more 128x128 tiles (P of about 5800 or more) and 1000
-// or more rows, with aligned rows, go to k_syrk_f32, which reads half the operand
-// bytes per product: P = 8100, 2000 rows 1306 us there, 1344 on the 64x64 tiles
-// (200 rows: 209, 197; P = 5820, 2000 rows: 777, 772; P = 8190, not aligned, which
-// k_syrk_f32 took element by element: 1729, 1547).
+// FP32 products of 1024 or more 128x128 tiles (256 CUs: from 5633 columns on) and
+// 1000 or more rows, with aligned rows, go to k_syrk_f32, which reads half the
+// operand bytes per product, where its whole rounds of the CUs take less time: a
+// round of 128x128 tiles takes as long as 3.42 of 64x64 ones, which need no whole
+// rounds (several workgroups share a CU). 5000 rows, 64x64 and 128x128 tiles: P =
+// 5636 (five rounds, the last nearly empty) 1670 and 1809 us, 5820 1773 and 1814, 6400
+// 2055 and 1804, 6912 2360 and 2097, 7040 2458 and 2516, 7200 2661 and 2524, 8192 3330
+// and 3090; 500 rows the same to 4 %. Fewer columns stay with the split rows, whose
+// FP32 sums are shorter.
 bool large_tiles(const fpca_context *ctx, const float *A, int64_t K, int64_t N) {
-  const int64_t nb = (N + TB - 1) / TB;
-  return nb * (nb + 1) / 2 >= 4 * ctx->num_cus && K >= 1000 && N % 4 == 0 &&
-         (reinterpret_cast<uintptr_t>(A) & 15) == 0;
+  auto tiles = [&](int64_t edge) {
+    const int64_t nb = (N + edge - 1) / edge;
+    return nb * (nb + 1) / 2;
+  };
+  const int64_t cus = ctx->num_cus;
+  return tiles(TB) >= 4 * cus && K >= 1000 && N % 4 == 0 && (reinterpret_cast<uintptr_t>(A) & 15) == 0 &&
+         3.42 * double((tiles(TB) + cus - 1) / cus * cus) < double(tiles(GT));
 }
 
 }  // namespace

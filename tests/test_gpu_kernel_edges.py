@@ -382,3 +382,22 @@ def test_paths_without_scratch(torch, F, h, monkeypatch):
         lim.close()
     for a, b, tol in zip(full, small, (1e-12, 1e-5, 1e-12, 1e-5, 1e-5)):
         assert normwise_rel(b, a) < tol
+
+
+@pytest.mark.parametrize("P", [5636, 6400])
+def test_gram_both_sides_of_the_large_tiles(torch, F, h, P):
+    """FP32 products of more than a thousand 128-column tiles: in whole rounds of the CUs (6400) and one tile past
+    (5636, which 64-column tiles take). Entry by entry within the rounding bound of a sum of 1000 terms."""
+    _say(f"gram large P={P}")
+    n = 1000
+    y = np.random.default_rng(P).standard_normal((n, P)).astype(np.float32)
+    S = torch.full((P, P), float("nan"), dtype=torch.float32, device="cuda:0")
+    F.fpca_bin(h, F.Grid((P,)), F.FPCA_BIN_COV, F.FPCA_COMMON_GRID, F.FPCA_F32, F.FPCA_PREC_F32, n, None, None,
+               dev(torch, y), None, 0, None, S)
+    h.sync()
+    assert torch.equal(S, S.T)
+    y64 = dev(torch, y).double()
+    w = 1.0 / (P * (P - 1.0))
+    ref, amp = w * (y64.T.contiguous() @ y64), w * (y64.abs().T.contiguous() @ y64.abs())
+    ref.fill_diagonal_(0.0)
+    assert bool(torch.all((S.double() - ref).abs() <= (n + 4) * np.finfo(np.float32).eps * amp))
