@@ -308,8 +308,9 @@ int fpca_eig_randomized(fpca_handle handle, int dtype, int prec, const fpca_grid
  *     product; the operator holds O(n P) memory and, for d >= 2 where they fit,
  *     tables that depend on the windows, not on n: up to 343 MB for d = 3 and
  *     687 MB for d = 2 at the widest windows, 3 (4 R + 1) P doubles for d = 3
- *     (R: the first coordinate's window in grid steps), and up to 512 MB (d = 2: 1 GB) in which a product keeps band blocks
- *     between launches; without them products take longer) or FPCA_COVOP_STORE_BAND (the
+ *     (R: the first coordinate's window in grid steps), and up to 512 MB
+ *     (d = 2: 1 GB) in which a product keeps band blocks between launches;
+ *     without them products take longer) or FPCA_COVOP_STORE_BAND (the
  *     band is formed once and kept in 64 x 64 FP64 blocks, about
  *     P x 64 x prod_k (2 ceil(2R_k / b_k) + 1) doubles with tile extents
  *     b = 64 / 8 / 4 for d = 1 / 2 / 3; products then stream it).
@@ -368,7 +369,7 @@ int fpca_noise_variance(fpca_handle handle, const fpca_grid *grid, int dtype, co
  * fpca_bin). Computed per curve as the k x k system
  *   (Phi_i^T Phi_i + sigma2 Lambda^{-1}) xi_i = Phi_i^T (Y_i - mu_i)
  * (the same result by the push-through identity), FP64 accumulation and
- * Cholesky solve. Components with evals[l] <= 0 are left out of Sigma_i and
+ * elimination (a pivot that is not positive gives NaN scores). Components with evals[l] <= 0 are left out of Sigma_i and
  * score 0. Observations with t outside [0,1]^d, or a non-finite y, are left
  * out; a curve with none scores 0.
  *   design, n, offsets, t, y: as in fpca_bin (common grid: y is n x P with

@@ -38,7 +38,10 @@ namespace {
 // 20 CV jobs: 43 ms; 8 columns 45; 128 MB 45, 256 MB 45, all of Y (3.6 GB) 49.
 constexpr int QBW = 16;
 constexpr int YCHUNK = 512;
-constexpr int SB_MAX = 8;    // jobs per launch (blockIdx.z)
+// Jobs per launch (blockIdx.z). 80 jobs, 1 / 4 / 8 / 16 per launch: 16^2 nodes 2.36,
+// 0.94, 0.69 and 0.56 ms, 24^2 3.78, 2.20, 1.92 and 1.93, 32^2 9.4, 8.6, 8.3 and 8.1 (16:
+// twice the kernel arguments).
+constexpr int SB_MAX = 8;
 constexpr int SC_TILE = 32;  // score tile
 constexpr int SC_WG = 2048;   // score workgroups per job, at most
 
@@ -653,6 +656,8 @@ int staged_scores(fpca_context *ctx, const fpca_grid *grid, const std::vector<St
   // score workgroups per job, by the grid: many jobs on a small one need little
   const int nt = (s.P + SC_TILE - 1) / SC_TILE, npairs = nt * (nt + 1) / 2, nsc = std::min(npairs, SC_WG);
   const size_t bytes_part = carve_bytes(J * nsc, 8);
+  // 1 GB of moments at most: 32^2 nodes eight jobs, 40^2 three (40 jobs 10.5 ms; 10.1 with
+  // eight), 16^3 one (20 jobs 43.5 ms; 42.1 with four)
   int nb_max = int(std::max<size_t>(1, std::min<size_t>({size_t(SB_MAX), J, (size_t(1) << 30) / per})));
   while (nb_max > 1 && !ws_room(ctx, bytes_part + nb_max * per)) --nb_max;  // a scratch limit: fewer jobs at a time
   if (int rc = ws_reserve(ctx, bytes_part + nb_max * per)) return rc;

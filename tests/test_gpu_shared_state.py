@@ -130,6 +130,21 @@ def test_many_cv_jobs_under_a_scratch_limit(torch, F, h, monkeypatch):
     assert np.array_equal(got, full)
 
 
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_cv_datasets_of_several_grids(torch, F, h, dt):
+    """Default engine, datasets of uneven size and one with a mask in one call: the scores of the separate calls."""
+    _say(f"cv several grids {dt}")
+    npdt, code = (np.float64, F.FPCA_F64) if dt == "f64" else (np.float32, F.FPCA_F32)
+    data = []
+    for i, M in enumerate([(9, 7), (16, 5), (9, 7), (17, 20), (4, 4)]):
+        mask = dev(torch, (np.arange(M[0] * M[1]) % 5 > 0).astype(np.uint8)) if i == 2 else None
+        data.append((F.Grid(M, mask), *(dev(torch, a) for a in cv_slabs(M, npdt, 20 + i))))
+    hs = [0.35, 0.5, 0.7]
+    got = F.fpca_cv_batched(h, code, data, 3, hs)
+    for i, one in enumerate(data):
+        assert np.array_equal(got[i], F.fpca_cv_batched(h, code, [one], 3, hs)[0]), i
+
+
 def test_optional_scratch_that_does_not_fit(torch, F, monkeypatch):
     """Scratch that a call can do without and cannot have (the allocation fails) costs the handle neither the block it
     holds nor the message of its last error, and the results are those of a handle that got it."""
