@@ -35,8 +35,8 @@
 // pair of blocks of 16 nodes:
 //   1. the 2d+1 response moments of the full pair sums as FP64 matrix
 //      products over the curves;
-//   2. the diagonal correction, coordinate by coordinate: summed over p_0 once
-//      per operator (k_hsum), over p_1 per workgroup and t-tile, over p_2 per
+//   2. the diagonal correction, coordinate by coordinate: summed over p_0 ahead
+//      of the products (k_hsum), over p_1 per workgroup and t-tile, over p_2 per
 //      lane;
 //   3. Delta from the first row of the inverse of the weight-moment matrix.
 //      That row depends on the two nodes' positions only, and coordinate by
@@ -44,7 +44,8 @@
 //      the operator tabulates it for every combination of the coordinates' pair
 //      classes (k_wtab);
 //   4. Delta times the t-rows of X added to the s-rows' outputs (or the block
-//      stored).
+//      stored). Of two mirrored blocks one is formed; k_band_turned applies the
+//      transposes.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
