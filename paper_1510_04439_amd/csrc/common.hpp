@@ -10,6 +10,13 @@
 
 #include "fpca.h"
 
+struct GramBlock {
+  hipStream_t stream;
+  void *p;
+  size_t size;
+  uint64_t used;
+};
+
 struct fpca_context {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -18,14 +25,9 @@ struct fpca_context {
   size_t ws_size = 0;
   size_t ws_limit = 0;  // 0 = unlimited
   size_t alloc_limit = 0;  // one scratch allocation larger than this fails as without memory (0 = none does)
-  // Gram products' block (gram_scratch), the stream that used it last, and what
-  // the next one must wait for first (1: gram_ev, 2: the device).
-  void *gram_ws = nullptr;
-  size_t gram_ws_size = 0;
-  bool gram_used = false;
-  hipStream_t gram_stream = nullptr;
-  int gram_wait = 0;
-  hipEvent_t gram_ev = nullptr;
+  // Gram products' blocks (gram_scratch) and the number of their uses.
+  std::vector<GramBlock> gram;
+  uint64_t gram_uses = 0;
   // Second arena for the split bf16 operands of the Gram product (its inputs
   // may live in the first arena).
   void *ws2 = nullptr;
@@ -107,8 +109,8 @@ int ws3_reserve(fpca_context *ctx, size_t bytes);
 // A block for the shares' sums of a Gram product, or null where there is none
 // (the conditions of ws_room). These products had no scratch of their own, so
 // they may be captured, replayed after the handle's blocks have moved, and
-// queued on several streams in turn: a captured product gets no block, and the
-// block passes from one stream to the next in order.
+// queued on several streams in turn: a captured product gets no block, and every
+// stream has its own.
 void *gram_scratch(fpca_context *ctx, size_t bytes);
 // Pinned host staging of at least `bytes` for table uploads; waits for the
 // previous upload from it first.

@@ -96,18 +96,29 @@ static int arena_reserve(fpca_context *ctx, void **arena, size_t *size, size_t b
   return FPCA_OK;
 }
 
+// Whether work may be queued on the stream eagerly now: not while it is being
+// captured, nor where the runtime cannot say (no error is left behind).
+static bool eager(hipStream_t stream) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs == hipStreamCaptureStatusNone;
+}
+
 // The same for work that has another way: false where the block cannot grow
 // (the scratch limit, a capture, no memory), and then the old block stays and
 // no error is set. The new block is there before the old one goes.
 static bool arena_room(fpca_context *ctx, void **arena, size_t *size, size_t bytes, size_t want) {
   if (bytes <= *size) return true;
   if (ctx->ws_limit && bytes > ctx->ws_limit) return false;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return false;
+  if (!eager(ctx->stream)) return false;
   void *p = nullptr;
   if (scratch_malloc(ctx, &p, want) != hipSuccess) return false;
   if (*arena && (hipStreamSynchronize(ctx->stream) != hipSuccess || hipFree(*arena) != hipSuccess)) {
     (void)hipFree(p);
+    (void)hipGetLastError();
     return false;
   }
   *arena = p;
@@ -128,42 +139,33 @@ bool ws_room(fpca_context *ctx, size_t bytes) {
   return arena_room(ctx, &ctx->ws, &ctx->ws_size, bytes, bytes + bytes / 8);
 }
 
-// The block belongs to the stream that used it last. When the handle goes on to
-// another one, fpca_set_stream marks the end of that stream's work with an event
-// (gram_ev), which the next stream waits for here; where it could not be marked
-// (the stream is gone or being captured), the whole device is waited for.
+// A block per stream, up to GRAM_STREAMS of them; one more stream takes over the
+// block unused for longest, once the device is idle. Streams are compared only: one
+// that had a block may have been destroyed since, and the runtime does not survive
+// being handed it again. (One block and an event after every product: 3 us more per
+// product.)
+constexpr size_t GRAM_STREAMS = 8;
 void *gram_scratch(fpca_context *ctx, size_t bytes) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
-  if (ctx->gram_wait) {
-    hipError_t e = ctx->gram_wait == 1 ? hipStreamWaitEvent(ctx->stream, ctx->gram_ev, 0) : hipErrorUnknown;
-    if (e != hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
+  if (!eager(ctx->stream)) return nullptr;
+  auto &blocks = ctx->gram;
+  GramBlock *b = nullptr;
+  for (GramBlock &e : blocks)
+    if (e.stream == ctx->stream) b = &e;
+  if (!b && blocks.size() < GRAM_STREAMS) {
+    blocks.push_back(GramBlock{ctx->stream, nullptr, 0, 0});
+    b = &blocks.back();
+  } else if (!b) {
+    if (hipDeviceSynchronize() != hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
     }
-    ctx->gram_wait = 0;
+    b = &blocks[0];
+    for (GramBlock &e : blocks)
+      if (e.used < b->used) b = &e;
+    b->stream = ctx->stream;
   }
-  if (!arena_room(ctx, &ctx->gram_ws, &ctx->gram_ws_size, bytes, bytes)) return nullptr;
-  ctx->gram_used = true;
-  ctx->gram_stream = ctx->stream;
-  return ctx->gram_ws;
-}
-
-// Before the handle's stream becomes `next`: see gram_scratch. A stream that is
-// being captured gets no block, so nothing is marked for it.
-static void gram_leave_stream(fpca_context *ctx, hipStream_t next) {
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(next, &cs);
-  if (e == hipSuccess && cs != hipStreamCaptureStatusNone) return;
-  e = hipSetDevice(ctx->device);
-  if (e == hipSuccess) e = hipStreamIsCapturing(ctx->gram_stream, &cs);
-  if (e == hipSuccess && cs != hipStreamCaptureStatusNone) e = hipErrorStreamCaptureUnsupported;
-  if (e == hipSuccess && !ctx->gram_ev) e = hipEventCreateWithFlags(&ctx->gram_ev, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventRecord(ctx->gram_ev, ctx->gram_stream);
-  if (e != hipSuccess) (void)hipGetLastError();
-  ctx->gram_wait = e == hipSuccess ? 1 : 2;
-  ctx->gram_used = false;
+  b->used = ++ctx->gram_uses;
+  return arena_room(ctx, &b->p, &b->size, bytes, bytes) ? b->p : nullptr;
 }
 
 int tables_stage(fpca_context *ctx, size_t bytes, char **out) {
@@ -258,8 +260,8 @@ int fpca_destroy(fpca_handle ctx) {
   if (ctx->ws) (void)hipFree(ctx->ws);
   if (ctx->ws2) (void)hipFree(ctx->ws2);
   if (ctx->ws3) (void)hipFree(ctx->ws3);
-  if (ctx->gram_ws) (void)hipFree(ctx->gram_ws);
-  if (ctx->gram_ev) (void)hipEventDestroy(ctx->gram_ev);
+  for (const GramBlock &b : ctx->gram)
+    if (b.p) (void)hipFree(b.p);
   if (ctx->cv_exec) (void)hipGraphExecDestroy(ctx->cv_exec);
   if (ctx->cap_stream) (void)hipStreamDestroy(ctx->cap_stream);
   if (ctx->ev_a) (void)hipEventDestroy(ctx->ev_a);
@@ -275,9 +277,7 @@ int fpca_destroy(fpca_handle ctx) {
 
 int fpca_set_stream(fpca_handle ctx, void *stream) {
   if (int rc = check_handle(ctx)) return rc;
-  const hipStream_t next = reinterpret_cast<hipStream_t>(stream);
-  if (ctx->gram_used && next != ctx->gram_stream) gram_leave_stream(ctx, next);
-  ctx->stream = next;
+  ctx->stream = reinterpret_cast<hipStream_t>(stream);
   return FPCA_OK;
 }
 

@@ -238,16 +238,18 @@ def test_captured_gram_after_the_scratch_moved(torch, F, h, npdt):
 
 
 @pytest.mark.parametrize("npdt", [np.float64, np.float32])
-def test_gram_on_two_streams_in_turn(torch, F, h, npdt):
-    """One handle, products of complete curves queued on two streams in turn with nothing waited for between them."""
-    _say(f"gram on two streams {npdt.__name__}")
+@pytest.mark.parametrize("nstreams", [2, 11])
+def test_gram_on_streams_in_turn(torch, F, h, npdt, nstreams):
+    """One handle, products of complete curves queued on its streams in turn with nothing waited for between them: two, and
+    more than it keeps blocks for."""
+    _say(f"gram on {nstreams} streams {npdt.__name__}")
     tol = 1e-13 if npdt == np.float64 else 1e-5
-    cases = [gram_case(torch, F, npdt, 3000 + 40 * i, 200 + 30 * (i % 3), 10 + i) for i in range(6)]
-    streams = [torch.cuda.Stream() for _ in range(2)]
+    cases = [gram_case(torch, F, npdt, 3000 + 40 * i, 200 + 30 * (i % 3), 10 + i) for i in range(12)]
+    streams = [torch.cuda.Stream() for _ in range(nstreams)]
     torch.cuda.synchronize()
     for _ in range(3):
         for i, (args, S, _) in enumerate(cases):
-            with torch.cuda.stream(streams[i % 2]):
+            with torch.cuda.stream(streams[i % nstreams]):
                 F.fpca_bin(h, *args, S)
     torch.cuda.synchronize()
     for args, S, ref in cases:
@@ -366,3 +368,22 @@ def test_operator_memory(torch, F, monkeypatch, M, R, n, limit):
             hh.close()
     for a in res[1:]:
         assert normwise_rel(a, res[0]) < 1e-12
+
+
+@pytest.mark.parametrize("npdt", [np.float64, np.float32])
+def test_gram_after_its_stream_is_gone(torch, F, h, npdt):
+    """A handle goes on to another stream after the one of its last product has been destroyed."""
+    _say(f"gram after its stream {npdt.__name__}")
+    tol = 1e-13 if npdt == np.float64 else 1e-5
+    args, S, ref = gram_case(torch, F, npdt, 900, 150, 4)
+    ncu = torch.cuda.get_device_properties(0).multi_processor_count
+    for _ in range(2):
+        raw = F.fpca_stream_create_cu_range(0, 0, ncu)
+        with torch.cuda.stream(torch.cuda.ExternalStream(raw)):
+            F.fpca_bin(h, *args, S)
+        torch.cuda.synchronize()
+        F.fpca_stream_destroy(raw)
+        S.fill_(float("nan"))
+        F.fpca_bin(h, *args, S)
+        h.sync()
+        assert normwise_rel(S.cpu().numpy().astype(np.float64), ref) < tol
