@@ -305,7 +305,8 @@ int fpca_eig_randomized(fpca_handle handle, int dtype, int prec, const fpca_grid
  *     grid steps (R_max = 2016, 28, 6 for d = 1, 2, 3) and be non-degenerate
  *     at every node, else FPCA_ERR_UNSUPPORTED.
  *   mode: FPCA_COVOP_RECOMPUTE (the band is recomputed tile by tile in every
- *     product; the operator holds O(n P) memory and, for d >= 2 where they fit,
+ *     product; the operator holds O(n P) memory and, for d >= 2 and each where it
+ *     takes at most half of what is free,
  *     tables that depend on the windows, not on n: up to 343 MB for d = 3 and
  *     687 MB for d = 2 at the widest windows, 3 (4 R + 1) P doubles for d = 3
  *     (R: the first coordinate's window in grid steps), and up to 512 MB

@@ -1316,6 +1316,18 @@ void free_op(fpca_covop_s *op) {
   delete op;
 }
 
+// Memory that an operator can do without: taken where it is at most half of what is
+// free, so that the calls which follow find theirs.
+bool optional_alloc(fpca_context *ctx, void **p, size_t bytes) {
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    free_b = 0;
+  }
+  *p = nullptr;
+  return bytes <= free_b / 2 && scratch_malloc(ctx, p, bytes) == hipSuccess;
+}
+
 unsigned nb256(int64_t n) { return unsigned((n + 255) / 256); }
 
 BandArgs band_args(const fpca_covop_s *op, const double *X, int r, double *out) {
@@ -1485,7 +1497,7 @@ void reserve_delta(fpca_covop_s *op) {
     else if (2 * u * wgs < cus)
       return;
     void *p = nullptr;
-    if (scratch_malloc(op->ctx, &p, unit * size_t(u * dists)) == hipSuccess) {
+    if (optional_alloc(op->ctx, &p, unit * size_t(u * dists))) {
       op->delta = static_cast<double *>(p);
       op->delta_units = int(u);
       op->delta_dists = int(dists);
@@ -1783,13 +1795,14 @@ extern "C" int fpca_covop_create(fpca_handle ctx, const fpca_grid *grid, int64_t
     // the rows are solved for and the sums formed for fewer s_0 at a time.
     if (d == 3) {
       op->hs_planes = op->M[0];
-      while (op->hs_planes > 1 && scratch_malloc(ctx, reinterpret_cast<void **>(&op->hsum), bytes_plane * op->hs_planes) != hipSuccess)
+      while (op->hs_planes > 1 &&
+             !optional_alloc(ctx, reinterpret_cast<void **>(&op->hsum), bytes_plane * op->hs_planes))
         op->hs_planes = (op->hs_planes + 1) / 2;
       if (!op->hsum && !device_alloc(&op->hsum, bytes_plane))
         return fail(set_error(FPCA_ERR_WORKSPACE, "hipMalloc failed"));
       if (op->hs_planes == op->M[0]) rc = launch_hsum(op, g, 0, op->M[0]);
     }
-    if (rc == FPCA_OK && scratch_malloc(ctx, reinterpret_cast<void **>(&op->tables), bytes_tables) == hipSuccess) {
+    if (rc == FPCA_OK && optional_alloc(ctx, reinterpret_cast<void **>(&op->tables), bytes_tables)) {
       double *rows = reinterpret_cast<double *>(op->tables);
       const int *ditab = reinterpret_cast<const int *>(op->tables + bytes_rows);
       if (hipMemcpyAsync(op->tables + bytes_rows, itab.data(), itab.size() * 4, hipMemcpyHostToDevice, s) != hipSuccess)

@@ -401,3 +401,30 @@ def test_gram_both_sides_of_the_large_tiles(torch, F, h, P):
     ref, amp = w * (y64.T.contiguous() @ y64), w * (y64.abs().T.contiguous() @ y64.abs())
     ref.fill_diagonal_(0.0)
     assert bool(torch.all((S.double() - ref).abs() <= (n + 4) * np.finfo(np.float32).eps * amp))
+
+
+@pytest.mark.parametrize("P,k,p", [(545, 5, 11), (1295, 20, 12), (2045, 36, 12), (1028, 50, 14)])
+@pytest.mark.parametrize("prec", ["f32", "bf16x3"])
+def test_eig_fp64_partials_of_fp32(torch, F, h, P, k, p, prec):
+    """FP32 products whose partial sums are FP64 (shares of the nodes longer than the FP32 sums): node counts that are
+    no multiple of four, of a tile or of a share, one to four blocks of 16 basis columns. Bars of the products at
+    ordinary sizes: 1e-5 for FP32, 1e-4 for BF16x3."""
+    _say(f"eig fp64 partials P={P} k={k} {prec}")
+    rng = np.random.default_rng(P)
+    V = np.linalg.qr(rng.standard_normal((P, P)))[0]
+    Gam = ((V * 0.9 ** np.arange(P)) @ V.T).astype(np.float32)
+    Gam = (Gam + Gam.T) / 2
+    om = np.full(P, 1.0 / P)
+    ef = torch.empty(k, P, dtype=torch.float32, device="cuda:0")
+    ev, fve = F.fpca_eig_randomized(h, F.FPCA_F32, F.FPCA_PREC_F32 if prec == "f32" else F.FPCA_PREC_BF16X3,
+                                    F.Grid((P,)), dev(torch, Gam), dev(torch, om), k, p, 2, 5, ef)
+    rev, rphi, rfve = oracle.eig_randomized(Gam.astype(np.float64), om, k, p, 2, 5)
+    tol = 1e-5 if prec == "f32" else 1e-4
+    assert np.abs(ev - rev).max() <= tol * np.abs(rev).max()
+    assert np.abs(fve - rfve).max() <= tol
+    phi = ef.cpu().numpy().astype(np.float64).T
+    for j in range(k):
+        gap = min(abs(rev[j] - rev[j - 1]) if j else np.inf, abs(rev[j] - rev[j + 1]) if j + 1 < k else np.inf)
+        scale = max(1.0, 0.1 * rev[0] / gap) if np.isfinite(gap) else 1.0
+        err = min(np.abs(phi[:, j] - rphi[:, j]).max(), np.abs(phi[:, j] + rphi[:, j]).max())
+        assert err <= 100 * tol * scale * np.abs(rphi[:, j]).max(), (j, err)

@@ -387,3 +387,35 @@ def test_gram_after_its_stream_is_gone(torch, F, h, npdt):
         F.fpca_bin(h, *args, S)
         h.sync()
         assert normwise_rel(S.cpu().numpy().astype(np.float64), ref) < tol
+
+
+def test_operator_on_a_full_card(torch, F, h):
+    """On a card with little memory left an operator does without a table that would take more than half of it, and
+    its products are those of one that had room."""
+    _say("operator on a full card")
+    rng = np.random.default_rng(12)
+    M, R, n, r = (70, 70), (28, 28), 5, 8  # a table of 602 MB, blocks of 220 MB
+    P = M[0] * M[1]
+    Y, X = dev(torch, 1.0 + rng.standard_normal((n, P))), dev(torch, rng.standard_normal((P, r)))
+    hb = [(k + 0.45) / (m - 1) for k, m in zip(R, M)]
+    res = []
+    for keep in (None, 400 << 20):
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        filler = torch.empty(free - keep, dtype=torch.uint8, device="cuda:0") if keep else None
+        before = torch.cuda.mem_get_info()[0]
+        op = F.CovOp(h, F.Grid(M), Y, Y.mean(0), hb, F.FPCA_COVOP_RECOMPUTE)
+        try:
+            left = torch.cuda.mem_get_info()[0]
+            _say(f"free {before >> 20} MB before, {left >> 20} after")
+            if keep:
+                assert left > before * 0.45
+            del filler
+            torch.cuda.empty_cache()
+            out = torch.full((P, r), float("nan"), dtype=torch.float64, device="cuda:0")
+            op.apply(X, out)
+            h.sync()
+            res.append(out.cpu().numpy())
+        finally:
+            op.close()
+    assert normwise_rel(res[1], res[0]) < 1e-12
