@@ -1360,7 +1360,7 @@ int launch_band_mfma(fpca_covop_s *op, const BandArgs &A) {
   const int64_t nwg = A.cnt * (d == 3 ? int64_t((op->M[1] + 3) / 4) : 1) * ((op->M[d - 1] + 7) / 8);
   if (nwg > 0x7fffffffLL) return set_error(FPCA_ERR_UNSUPPORTED, "covariance operator: too many nodes");
   FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(&k_band_mfma<d, NCB, STORE, HALF, TAB>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)));
+                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
   hipLaunchKernelGGL((k_band_mfma<d, NCB, STORE, HALF, TAB>), dim3(unsigned(nwg)), dim3(MT), lds, op->ctx->stream, A);
   FPCA_LAUNCH_CHECK("covop band");
   return FPCA_OK;

@@ -533,11 +533,13 @@ size_t job_bytes(const Shape &s, size_t elem, bool cv) {
          carve_bytes(9 * TAPW, 8);
 }
 
+// The attribute belongs to the process: always the same value, so that threads with
+// grids of different sizes do not lower it for each other.
 template <typename K>
 int want_lds(K kernel, size_t lds) {
   if (lds > 64 * 1024)
     FPCA_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                 int(lds)));
+                                 160 * 1024));
   return FPCA_OK;
 }
 

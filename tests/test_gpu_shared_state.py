@@ -419,3 +419,52 @@ def test_operator_on_a_full_card(torch, F, h):
         finally:
             op.close()
     assert normwise_rel(res[1], res[0]) < 1e-12
+
+
+def test_two_threads_with_two_grids(torch, F):
+    """Two host threads, a handle and a stream each, smooth covariances on grids whose kernels take different amounts
+    of LDS at the same time: every call succeeds, with the results of a thread by itself."""
+    _say("two threads")
+    import threading
+    jobs, want = [], []
+    for i, M in enumerate([(5, 40), (5, 37)]):
+        rng = np.random.default_rng(30 + i)
+        P = int(np.prod(M))
+        C = rng.random((P, P)) + 0.1
+        G = C * rng.standard_normal((P, P))
+        jobs.append((M, dev(torch, C + C.T), dev(torch, G + G.T)))
+
+    def smooth(hh, job, times):
+        M, C, G = job
+        P = int(np.prod(M))
+        gam = torch.empty(P, P, dtype=torch.float64, device="cuda:0")
+        for _ in range(times):
+            F.fpca_smooth_cov(hh, F.Grid(M), F.FPCA_F64, C, 0.0, G, None, F.FPCA_K_EPANECHNIKOV, 0.3, gam, None)
+        hh.sync()
+        return gam
+
+    hs = [F.Handle(0), F.Handle(0)]
+    try:
+        want = [smooth(hs[i], jobs[i], 1).clone() for i in range(2)]
+        torch.cuda.synchronize()
+        got, errors = [None, None], []
+
+        def work(i):
+            try:
+                with torch.cuda.stream(torch.cuda.Stream()):
+                    got[i] = smooth(hs[i], jobs[i], 400)
+            except Exception as e:  # reported by the main thread
+                errors.append(e)
+
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not errors, errors
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+    finally:
+        for hh in hs:
+            hh.close()
